@@ -85,7 +85,7 @@ __global__ void __launch_bounds__(256) maxpool2_chain_f32_kernel(const float *__
                                                                  uint8_t *__restrict__ tap, int H, int W, int Ho, int Wo,
                                                                  int d, int M, int nseg)
 {
-    const int xx = blockIdx.x * 256 + threadIdx.x;
+    const int xx = blockIdx.x * blockDim.x + threadIdx.x;
     const int phase = blockIdx.y / nseg, seg = blockIdx.y - phase * nseg;
     if (xx >= Wo || phase >= Ho) return;
     const int links = (Ho - phase + d - 1) / d;
@@ -134,11 +134,11 @@ hipError_t launch_maxpool_f32(const float *x, float *y, uint8_t *tap, int planes
 {
     if (Ho > 65535 || planes > 65535) return hipErrorInvalidValue;
     if (k == 2 && s == 1 && Ho == H - d && Wo == W - d) {
-        const int M = 32, links = (Ho + d - 1) / d, nseg = (links + M - 1) / M;
-        if ((long)d * nseg <= 65535) {
-            const dim3 grid((Wo + 255) / 256, (unsigned)(d * nseg), (unsigned)planes);
-            if (tap) hipLaunchKernelGGL(maxpool2_chain_f32_kernel<true>, grid, dim3(256), 0, stream, x, y, tap, H, W, Ho, Wo, d, M, nseg);
-            else hipLaunchKernelGGL(maxpool2_chain_f32_kernel<false>, grid, dim3(256), 0, stream, x, y, tap, H, W, Ho, Wo, d, M, nseg);
+        const PoolCut c = pool_cut(Ho, Wo, d, planes, 8);
+        if ((long)d * c.nseg <= 65535) {
+            const dim3 grid((Wo + c.threads - 1) / c.threads, (unsigned)(d * c.nseg), (unsigned)planes);
+            if (tap) hipLaunchKernelGGL(maxpool2_chain_f32_kernel<true>, grid, dim3(c.threads), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len, c.nseg);
+            else hipLaunchKernelGGL(maxpool2_chain_f32_kernel<false>, grid, dim3(c.threads), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len, c.nseg);
             return hipGetLastError();
         }
     }

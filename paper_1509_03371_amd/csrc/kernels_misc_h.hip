@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(256) maxpool2_chain_h_kernel(const uint4v *__r
                                                                uint2v *__restrict__ tap, int H, int W, int Ho, int Wo,
                                                                int d, int M, int nseg)
 {
-    const int xx = blockIdx.x * 256 + threadIdx.x;
+    const int xx = blockIdx.x * blockDim.x + threadIdx.x;
     const int phase = blockIdx.y / nseg, seg = blockIdx.y - phase * nseg;
     if (xx >= Wo || phase >= Ho) return;
     const int links = (Ho - phase + d - 1) / d;           // windows of this residue class
@@ -236,18 +236,18 @@ hipError_t launch_maxpool_h(const void *x, void *y, void *tap, int dtype, long p
 {
     if (Ho > 65535 || planes8 > 65535) return hipErrorInvalidValue;
     if (k == 2 && s == 1 && Ho == H - d && Wo == W - d) {
-        const int M = 32, links = (Ho + d - 1) / d, nseg = (links + M - 1) / M;
-        if ((long)d * nseg <= 65535) {
-            const dim3 grid((Wo + 255) / 256, (unsigned)(d * nseg), (unsigned)planes8);
+        const PoolCut c = pool_cut(Ho, Wo, d, planes8, 4);
+        if ((long)d * c.nseg <= 65535) {
+            const dim3 grid((Wo + c.threads - 1) / c.threads, (unsigned)(d * c.nseg), (unsigned)planes8);
             const uint4v *xi = static_cast<const uint4v *>(x);
             uint4v *yo = static_cast<uint4v *>(y);
             uint2v *tp = static_cast<uint2v *>(tap);
             if (dtype == 1) {
-                if (tap) hipLaunchKernelGGL((maxpool2_chain_h_kernel<1, true>), grid, dim3(256), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, M, nseg);
-                else hipLaunchKernelGGL((maxpool2_chain_h_kernel<1, false>), grid, dim3(256), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, M, nseg);
+                if (tap) hipLaunchKernelGGL((maxpool2_chain_h_kernel<1, true>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
+                else hipLaunchKernelGGL((maxpool2_chain_h_kernel<1, false>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
             } else {
-                if (tap) hipLaunchKernelGGL((maxpool2_chain_h_kernel<2, true>), grid, dim3(256), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, M, nseg);
-                else hipLaunchKernelGGL((maxpool2_chain_h_kernel<2, false>), grid, dim3(256), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, M, nseg);
+                if (tap) hipLaunchKernelGGL((maxpool2_chain_h_kernel<2, true>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
+                else hipLaunchKernelGGL((maxpool2_chain_h_kernel<2, false>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
             }
             return hipGetLastError();
         }
