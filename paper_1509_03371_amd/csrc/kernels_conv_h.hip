@@ -1143,8 +1143,9 @@ static hipError_t launch_conv_h_t(const ConvHArgs &a, hipStream_t stream)
         // chunk), so the shape that covers the output in the fewest rounds of one tile per CU wins: ragged maps waste
         // less of a squarer tile, which also stages less halo -- but a 32-column tile stages 72 short rows per chunk
         // where the 128-column one stages 24 long ones (twice the memory instructions; counted as a quarter more
-        // time), and maps too small to give every CU a tile keep the flat shape, which has the most tiles.  Measured on
-        // the U-Net's 64 -> 64 layer at 568^2: 48.2 -> 42.9 us (64 x 8); 128 -> 128 at 280^2: 49.1 -> 44.0 us (32 x 16).
+        // time), and maps too small to give every CU a tile keep the flat shape, which has the most tiles.  Measured (before
+        // such layers moved to kernels_conv_wide_h.hip) on 64 -> 64 at 568^2: 48.2 -> 42.9 us (64 x 8); 128 -> 128 at 280^2:
+        // 49.1 -> 44.0 us (32 x 16).
         auto fits = [&](int tx, int rt) {               // staged rows of at most 128 units, two stages within the LDS
             const int pw = tx + (KS - 1) * a.d;
             const size_t stage = (size_t)4 * (rt + KS - 1) * pw + (size_t)KS * KS * MT * 64;
@@ -1340,7 +1341,7 @@ int conv_h_pick_mode(int c_out, int c_in, int k, int d, int n, int Ho, int Wo)
         const int tiles = (c_out + 15) / 16;
         return ((tiles % 3 == 0 || tiles >= 8) ? 3 : 2) | CONV_H_TAPCOLS;
     }
-    return conv_h_pick_mt(c_out, k, n, Ho, Wo);
+    return conv_h_pick_mt(c_out, c_in, k, n, Ho, Wo);
 }
 
 // output-map tiles (16 maps each) per workgroup: as few padded tiles as possible; a 3x3 kernel's
@@ -1583,6 +1584,10 @@ hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream)
         if (a.dtype == 2) return b.mt == 2 ? launch_conv_h_k3_tapcols<2, 2>(b, stream) : (b.mt == 3 ? launch_conv_h_k3_tapcols<2, 3>(b, stream) : hipErrorInvalidValue);
         return hipErrorInvalidValue;
     }
+    if (a.mt <= 0 && conv_h_wide(a.c_out, a.c8_in, a.k)) {
+        if (!conv_h_supported(a.k, a.d, a.c_out) || a.img || a.vpool || a.hd) return hipErrorInvalidValue;
+        return launch_conv_wide_h(a, stream);
+    }
     // the packed weights were laid out for this many map tiles per group (0 = the default choice)
     const int mt = a.mt > 0 ? a.mt : conv_h_mt(a.c_out, a.k);
     if (a.img && (!conv_c1_h_applies(a, mt) || a.img_h < 1 || a.img_w < 1 || a.pad_top < 0 || a.pad_left < 0 || (a.pad_mode != 0 && a.pad_mode != 1)))
@@ -1710,11 +1715,12 @@ __global__ void __launch_bounds__(256) pack_weights_h_batch_kernel(PackHJobs b)
 }
 
 // size in 16-bit elements of the packing of a GEMM with gemm_m output maps and gemm_c8 input octets
-// Map tiles per workgroup for a forward layer with this output size.  Many maps on a small image (the
-// deep U-Net levels): with one persistent workgroup per CU a layer wants at least about 160 tiles, and
+// Map tiles per workgroup for a forward layer with this output size (0: the default packing, where
+// kernels_conv_wide_h.hip takes the layer).  Many maps on a small image: with one persistent workgroup per CU a layer wants at least about 160 tiles, and
 // fewer map tiles per workgroup give more of them (each then re-reads the input, so not more than needed).  The weights must be packed for the same value.
-int conv_h_pick_mt(int c_out, int k, int n, int Ho, int Wo)
+int conv_h_pick_mt(int c_out, int c_in, int k, int n, int Ho, int Wo)
 {
+    if (conv_h_wide(c_out, (c_in + 7) / 8, k)) return 0;
     int mt = conv_h_mt(c_out, k);
     const long sp = (long)((Wo + CH_TX - 1) / CH_TX) * ((Ho + 3) / 4) * n;   // tiles of 4 rows at least
     const int m_tiles = (c_out + 15) / 16;
@@ -1722,11 +1728,14 @@ int conv_h_pick_mt(int c_out, int k, int n, int Ho, int Wo)
     return mt;
 }
 
+// map tiles per group of a packing with the default layout
+static int packed_mt(int gemm_m, int gemm_c8, int k) { return conv_h_wide(gemm_m, gemm_c8, k) ? 4 : conv_h_mt(gemm_m, k); }
+
 long packed_h_elems(int gemm_m, int gemm_c8, int k, int mt)
 {
     const bool tapcols = mt > 0 && (mt & CONV_H_TAPCOLS) != 0;
     if (mt > 0) mt &= ~CONV_H_TAPCOLS;
-    if (mt <= 0) mt = conv_h_mt(gemm_m, k);
+    if (mt <= 0) mt = packed_mt(gemm_m, gemm_c8, k);
     const int m_tiles = (gemm_m + 15) / 16, mgroups = (m_tiles + mt - 1) / mt;
     const bool map4 = k >= 4 || tapcols;
     const int OC = map4 ? 1 : 4, CS = map4 ? (k + 3) / 4 : k;
@@ -1742,7 +1751,7 @@ hipError_t launch_pack_weights_h(const float *w_oihw, void *wp, int dtype, int c
     const int map4 = (k >= 4 || (mt > 0 && (mt & CONV_H_TAPCOLS))) ? 1 : 0;
     const long total = packed_h_elems(gemm_m, gemm_c8, k, mt);
     if (mt > 0) mt &= ~CONV_H_TAPCOLS;
-    if (mt <= 0) mt = conv_h_mt(gemm_m, k);
+    if (mt <= 0) mt = packed_mt(gemm_m, gemm_c8, k);
     const int blocks = (int)((total + 255) / 256 < 2048 ? (total + 255) / 256 : 2048);
     if (dtype == 1)
         hipLaunchKernelGGL(pack_weights_h_kernel<1>, dim3(blocks), dim3(256), 0, stream, w_oihw,
@@ -1769,7 +1778,7 @@ hipError_t launch_pack_weights_h_batch(const PackHJob *jobs, int n, int dtype, h
         o.map4 = (j.k >= 4 || (j.mt > 0 && (j.mt & CONV_H_TAPCOLS))) ? 1 : 0;
         o.total = packed_h_elems(o.gemm_m, o.gemm_c8, j.k, j.mt);
         o.mt = j.mt > 0 ? (j.mt & ~CONV_H_TAPCOLS) : 0;
-        if (o.mt <= 0) o.mt = conv_h_mt(o.gemm_m, j.k);
+        if (o.mt <= 0) o.mt = packed_mt(o.gemm_m, o.gemm_c8, j.k);
         const int OC = o.map4 ? 1 : 4, CS = o.map4 ? (j.k + 3) / 4 : j.k, nchunks = (o.gemm_c8 + OC - 1) / OC;
         const long tiles = o.total / ((long)CS * j.k * 512);                 // (map tiles of all groups) x chunks
         if (tiles % nchunks != 0) return hipErrorInvalidValue;

@@ -113,6 +113,9 @@ struct ConvHArgs {
     // image b - 1 (0: c8_in, images do not overlap); grp8 > 0: the c8_in input octets come in groups of grp8 with skip8 more
     // octet planes between two groups (the d - 1 slices between two depth taps)
     int xb8, grp8, skip8;
+    // scratch for launches that split their input maps over workgroups (kernels_conv_wide_h.hip); without it they don't
+    float *ws;
+    long ws_floats;
     // filled in by the launcher
     int m_tiles, mgroups, nchunks, xtiles, tiles_hi, tiles_lo, rem, ytiles_total, total_tiles, ypitch;
 };
@@ -124,10 +127,15 @@ bool conv_h_supported(int k, int d, int gemm_m);
 // does this launch (single_map set, img left null) run on the kernel that can read the fp32 image itself?
 bool conv_h_reads_image(const ConvHArgs &a);
 hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream);
+// 1x1 and 3x3 layers with many maps (kernels_conv_wide_h.hip): decided by what the weight packing knows too, so that weights
+// packed with mt = 0 are always packed for the kernel that reads them (four map tiles per group there)
+bool conv_h_wide(int gemm_m, int gemm_c8, int k);
+hipError_t launch_conv_wide_h(const ConvHArgs &a, hipStream_t stream);
+constexpr long CONV_H_WS_FLOATS = 8L << 20;       // ConvHArgs.ws: 32 MB hold the partial sums of 512 tiles of 64 maps x 256 pixels
 // 16-bit elements of the packed weights of a GEMM with gemm_m output maps and gemm_c8 input octets
 long packed_h_elems(int gemm_m, int gemm_c8, int k, int mt = 0);
 // map tiles per workgroup (mt) that suit a forward layer of this output size; pass it to the packing too
-int conv_h_pick_mt(int c_out, int k, int n, int Ho, int Wo);
+int conv_h_pick_mt(int c_out, int c_in, int k, int n, int Ho, int Wo);
 // ... or that value with CONV_H_TAPCOLS set: a 3x3 layer whose weights are packed (and whose launch runs) with the kernel
 // columns on the lane groups; pass the value to the packing and in ConvHArgs.mt as it is
 constexpr int CONV_H_TAPCOLS = 16;

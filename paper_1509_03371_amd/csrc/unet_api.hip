@@ -70,6 +70,7 @@ struct unet {
     std::vector<Stage> stages;
     float *logits = nullptr;                 // fp32 NCHW in every storage type
     float *zero_page = nullptr;              // 16-bit types: zeros the convolution reads for samples outside the image
+    float *conv_ws = nullptr;                // 16-bit types: partial sums of convolutions that split their input maps (CONV_H_WS_FLOATS)
     float *unpack_tmp = nullptr;             // 16-bit types: fp32 staging for unet_get_activation
     long unpack_tmp_floats = 0;
     Dims out_dims;
@@ -79,7 +80,7 @@ struct unet {
     {
         for (auto &p : buffers) free_dev(p);
         buffers.clear();
-        free_dev(unpack_tmp); free_dev(zero_page);
+        free_dev(unpack_tmp); free_dev(zero_page); free_dev(conv_ws);
         unpack_tmp_floats = 0;
         for (auto &kv : grad_of) { float *g = kv.second; free_dev(g); }
         grad_of.clear();
@@ -475,8 +476,8 @@ static sk_status plan_impl(unet_t *net, int32_t n, int32_t h_in, int32_t w_in, b
                 ConvParams &c = net->convs[op.param];
                 c.mt16 = sk::conv_h_pick_mode(c.c_out, c.c_in, c.k, op.d, n, op.out.h, op.out.w);
             } else if (op.kind == 2) {
-                for (auto &t : net->ups[op.param].tap) t.mt16 = sk::conv_h_pick_mt(net->ups[op.param].c_out, 1, n, op.in.h, op.in.w);
-                net->ups[op.param].cat.mt16 = sk::conv_h_pick_mt(4 * net->ups[op.param].c_out, 1, n, op.in.h, op.in.w);
+                for (auto &t : net->ups[op.param].tap) t.mt16 = sk::conv_h_pick_mt(net->ups[op.param].c_out, net->ups[op.param].c_in, 1, n, op.in.h, op.in.w);
+                net->ups[op.param].cat.mt16 = sk::conv_h_pick_mt(4 * net->ups[op.param].c_out, net->ups[op.param].c_in, 1, n, op.in.h, op.in.w);
             }
         }
     }
@@ -506,6 +507,7 @@ static sk_status plan_impl(unet_t *net, int32_t n, int32_t h_in, int32_t w_in, b
     }
     if (st == SK_OK && half) st = alloc_f(&net->unpack_tmp, net->unpack_tmp_floats);
     if (st == SK_OK && half) st = alloc_zero_page(&net->zero_page);
+    if (st == SK_OK && half) st = alloc_f(&net->conv_ws, sk::CONV_H_WS_FLOATS);
     if (st == SK_OK && training) {
         // a gradient buffer per activation buffer, winner codes per pool, scratch of the loss and the weight gradients
         for (float *bufp : net->buffers) {
@@ -598,6 +600,7 @@ sk_status unet_forward(unet_t *net, const float *image_dev, float *prob_dev, voi
                 const ConvParams &c = net->convs[op.param];
                 const bool to_logits = op.dst == net->logits;     // the last conv leaves fp32 NCHW
                 sk::ConvHArgs a = conv_h_args(c, dt, src, n, op.in, op.d, op.relu, op.dst, op.out, to_logits, net->zero_page);
+                a.ws = net->conv_ws; a.ws_floats = sk::CONV_H_WS_FLOATS;
                 SK_HIP(sk::launch_conv_h(a, stream));
             } else if (op.kind == 1) {
                 SK_HIP(sk::launch_maxpool_h(src, op.dst, net->training ? net->taps[opi] : nullptr, dt, (long)n * ((op.in.c + 7) / 8), op.in.h, op.in.w,
@@ -610,6 +613,7 @@ sk_status unet_forward(unet_t *net, const float *image_dev, float *prob_dev, voi
                     sk::ConvHArgs a = conv_h_args(u.cat, dt, src, n, op.in, 1, 0, op.dst, lowres, false, net->zero_page);
                     a.c8_out_total = (op.out.c + 7) / 8; a.o8_off = 0; a.OH = op.out.h; a.OW = op.out.w;
                     a.oy_mul = 2; a.oy_off = 0; a.ox_mul = 2; a.ox_off = 0; a.tap_maps = u.c_out;
+                    a.ws = net->conv_ws; a.ws_floats = sk::CONV_H_WS_FLOATS;
                     SK_HIP(sk::launch_conv_h(a, stream));
                 } else {
                     for (int t = 0; t < 4; ++t) {
@@ -617,6 +621,7 @@ sk_status unet_forward(unet_t *net, const float *image_dev, float *prob_dev, voi
                         sk::ConvHArgs a = conv_h_args(u.tap[t], dt, src, n, op.in, 1, 0, op.dst, lowres, false, net->zero_page);
                         a.c8_out_total = (op.out.c + 7) / 8; a.o8_off = 0; a.OH = op.out.h; a.OW = op.out.w;
                         a.oy_mul = 2; a.oy_off = t / 2; a.ox_mul = 2; a.ox_off = t % 2;
+                        a.ws = net->conv_ws; a.ws_floats = sk::CONV_H_WS_FLOATS;
                         SK_HIP(sk::launch_conv_h(a, stream));
                     }
                 }
@@ -697,6 +702,7 @@ static sk_status backward_h(unet_t *net, const int32_t *labels_dev, float *loss_
             a.k = c.k; a.d = op.d; a.in_off = (c.k - 1) * op.d; a.Ho = op.in.h; a.Wo = op.in.w; a.relu = 0; a.out_f32 = 0;
             a.c8_out_total = (op.in.c + 7) / 8; a.o8_off = 0; a.OH = op.in.h; a.OW = op.in.w;
             a.oy_mul = 1; a.oy_off = 0; a.ox_mul = 1; a.ox_off = 0;
+            a.ws = net->conv_ws; a.ws_floats = sk::CONV_H_WS_FLOATS;
             SK_HIP(sk::launch_conv_h(a, stream));
             written.insert(op.src);
         } else if (op.kind == 1) {
@@ -726,6 +732,7 @@ static sk_status backward_h(unet_t *net, const int32_t *labels_dev, float *loss_
             a.k = 1; a.d = 1; a.in_off = 0; a.Ho = op.in.h; a.Wo = op.in.w; a.relu = 0; a.out_f32 = 0;
             a.c8_out_total = (u.c_in + 7) / 8; a.o8_off = 0; a.OH = op.in.h; a.OW = op.in.w;
             a.oy_mul = 1; a.oy_off = 0; a.ox_mul = 1; a.ox_off = 0;
+            a.ws = net->conv_ws; a.ws_floats = sk::CONV_H_WS_FLOATS;
             SK_HIP(sk::launch_conv_h(a, stream));
             written.insert(op.src);
         } else if (op.kind == 3) {
