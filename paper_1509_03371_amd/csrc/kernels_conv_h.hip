@@ -1586,7 +1586,7 @@ hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream)
     }
     if (a.mt <= 0 && conv_h_wide(a.c_out, a.c8_in, a.k)) {
         if (!conv_h_supported(a.k, a.d, a.c_out) || a.img || a.vpool || a.hd) return hipErrorInvalidValue;
-        return launch_conv_wide_h(a, stream);
+        return a.k > 4 ? launch_conv_wide_big_h(a, stream) : launch_conv_wide_h(a, stream);
     }
     // the packed weights were laid out for this many map tiles per group (0 = the default choice)
     const int mt = a.mt > 0 ? a.mt : conv_h_mt(a.c_out, a.k);
@@ -1626,6 +1626,9 @@ hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream)
 // flip_transpose = 1 builds the data-gradient operator instead: the roles of input and output maps
 // are swapped and both taps are mirrored (element = W[c][o][k-1-i][k-1-j]).
 // Entries whose o or c lie beyond the real extents are zero.
+// kernel column, within its column step, that lane group g carries: g, or (map4 = 2, kernels_conv_wide_big_h.hip) 0, 2, 1, 3
+__device__ __forceinline__ int pack_col(int map4, int g) { return map4 == 2 ? (g >> 1) | ((g & 1) << 1) : g; }
+
 template <int DT>
 __device__ __forceinline__ void pack_weights_h_body(const float *w, unsigned short *wp, int c_out, int c_in, int k, int flip_transpose,
                                                     int mt_per_group, int map4, int gemm_m, int gemm_c8, long total)
@@ -1644,7 +1647,7 @@ __device__ __forceinline__ void pack_weights_h_body(const float *w, unsigned sho
         const int mg = (int)r;
         const int m = (mg * mt_per_group + mt) * 16 + l16;          // GEMM output map
         const int c = map4 ? ch * 8 + e : (ch * 4 + g) * 8 + e;     // GEMM input map
-        const int j = map4 ? 4 * cs + g : cs;
+        const int j = map4 ? 4 * cs + pack_col(map4, g) : cs;
         float v = 0.f;
         if (m < gemm_m && c < gemm_c8 * 8 && j < k) {
             if (!flip_transpose) {
@@ -1699,7 +1702,7 @@ __global__ void __launch_bounds__(256) pack_weights_h_batch_kernel(PackHJobs b)
     const long frag0 = (((long)(mtile / MT) * nchunks + ch) * CS * k) * MT + mtile % MT;
     for (int u = threadIdx.x; u < units; u += 256) {
         const int l16 = u & 15, g = (u >> 4) & 3, ci = u >> 6, cs = ci / k, i = ci - cs * k;
-        const int j = map4 ? 4 * cs + g : cs;
+        const int j = map4 ? 4 * cs + pack_col(map4, g) : cs;
         unsigned short h[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -1731,6 +1734,13 @@ int conv_h_pick_mt(int c_out, int c_in, int k, int n, int Ho, int Wo)
 // map tiles per group of a packing with the default layout
 static int packed_mt(int gemm_m, int gemm_c8, int k) { return conv_h_wide(gemm_m, gemm_c8, k) ? 4 : conv_h_mt(gemm_m, k); }
 
+// lane groups of a packed fragment: 0 = four input octets, 1 = four kernel columns, 2 = four kernel columns in the order of pack_col
+static int packed_map4(int gemm_m, int gemm_c8, int k, int mt)
+{
+    if (k > 4 && mt <= 0 && conv_h_wide(gemm_m, gemm_c8, k)) return 2;
+    return (k >= 4 || (mt > 0 && (mt & CONV_H_TAPCOLS))) ? 1 : 0;
+}
+
 long packed_h_elems(int gemm_m, int gemm_c8, int k, int mt)
 {
     const bool tapcols = mt > 0 && (mt & CONV_H_TAPCOLS) != 0;
@@ -1748,7 +1758,7 @@ hipError_t launch_pack_weights_h(const float *w_oihw, void *wp, int dtype, int c
 {
     const int gemm_m = flip_transpose ? c_in : c_out;
     const int gemm_c8 = ((flip_transpose ? c_out : c_in) + 7) / 8;
-    const int map4 = (k >= 4 || (mt > 0 && (mt & CONV_H_TAPCOLS))) ? 1 : 0;
+    const int map4 = packed_map4(gemm_m, gemm_c8, k, mt);
     const long total = packed_h_elems(gemm_m, gemm_c8, k, mt);
     if (mt > 0) mt &= ~CONV_H_TAPCOLS;
     if (mt <= 0) mt = packed_mt(gemm_m, gemm_c8, k);
@@ -1775,7 +1785,7 @@ hipError_t launch_pack_weights_h_batch(const PackHJob *jobs, int n, int dtype, h
         o.c_out = j.c_out; o.c_in = j.c_in; o.k = j.k; o.flip_transpose = j.flip_transpose;
         o.gemm_m = j.flip_transpose ? j.c_in : j.c_out;
         o.gemm_c8 = ((j.flip_transpose ? j.c_out : j.c_in) + 7) / 8;
-        o.map4 = (j.k >= 4 || (j.mt > 0 && (j.mt & CONV_H_TAPCOLS))) ? 1 : 0;
+        o.map4 = packed_map4(o.gemm_m, o.gemm_c8, j.k, j.mt);
         o.total = packed_h_elems(o.gemm_m, o.gemm_c8, j.k, j.mt);
         o.mt = j.mt > 0 ? (j.mt & ~CONV_H_TAPCOLS) : 0;
         if (o.mt <= 0) o.mt = packed_mt(o.gemm_m, o.gemm_c8, j.k);

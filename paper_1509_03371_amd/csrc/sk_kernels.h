@@ -127,10 +127,11 @@ bool conv_h_supported(int k, int d, int gemm_m);
 // does this launch (single_map set, img left null) run on the kernel that can read the fp32 image itself?
 bool conv_h_reads_image(const ConvHArgs &a);
 hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream);
-// 1x1 and 3x3 layers with many maps (kernels_conv_wide_h.hip): decided by what the weight packing knows too, so that weights
+// layers with many maps (1x1, 3x3: kernels_conv_wide_h.hip; 5x5, 6x6, 8x8, 10x10: kernels_conv_wide_big_h.hip): decided by what the weight packing knows too, so that weights
 // packed with mt = 0 are always packed for the kernel that reads them (four map tiles per group there)
 bool conv_h_wide(int gemm_m, int gemm_c8, int k);
 hipError_t launch_conv_wide_h(const ConvHArgs &a, hipStream_t stream);
+hipError_t launch_conv_wide_big_h(const ConvHArgs &a, hipStream_t stream);
 constexpr long CONV_H_WS_FLOATS = 8L << 20;       // ConvHArgs.ws: 32 MB hold the partial sums of 512 tiles of 64 maps x 256 pixels
 // 16-bit elements of the packed weights of a GEMM with gemm_m output maps and gemm_c8 input octets
 long packed_h_elems(int gemm_m, int gemm_c8, int k, int mt = 0);

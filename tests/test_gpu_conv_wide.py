@@ -1,9 +1,9 @@
-"""GPU parity of the 16-bit 1x1 / 3x3 convolution for many maps: every tile shape and dispatch branch at sizes that leave
+"""GPU parity of the 16-bit convolutions for many maps (1x1, 3x3, 5x5, 6x6, 8x8, 10x10): every tile shape and dispatch branch at sizes that leave
 remainders (pixels, rows, map groups, input maps off the chunk of 32), the widest kernel strides, fp32 output planes, and,
 through a U-Net small enough that its deep layers split their input maps, partial sums, masks and zero borders.
 
 The layer tests round image and weights to the storage type first, so that against fp64 only the sum's fp32 rounding (below
-K * 2^-24 of the sum of magnitudes, K <= 32*9*10: 2e-4) and the one rounding of the stored result (half a unit: 2^-8 bf16, 2^-11
+K * 2^-24 of the sum of magnitudes, K <= 64*100: 2e-4) and the one rounding of the stored result (half a unit: 2^-8 bf16, 2^-11
 fp16, relative) are left."""
 import numpy as np
 import pytest
@@ -32,6 +32,10 @@ def rounded(a, dtype):
     # 1x1: 128 x 128 pixels on eight waves; on four; 128 x 256; 64 x 256 (an odd number of 64-map groups in the first three)
     (1, 1, 40, 112, 2, 23, 60), (1, 1, 64, 320, 1, 17, 30), (1, 1, 33, 512, 2, 90, 101), (1, 1, 320, 448, 1, 150, 150), (1, 1, 64, 64, 2, 300, 300),
     (1, 1, 32, 64, 1, 1, 1),
+    # large kernels, 16 rows x 32 pixels: two, four and six input loads a wave; 8 rows x 64: strides too wide for the former
+    # (10x10 at 10, 8x8 at 18) and more tiles than CUs where that is fewer rounds
+    (5, 1, 40, 70, 2, 37, 41), (6, 1, 33, 112, 1, 22, 39), (6, 3, 64, 64, 1, 49, 50), (8, 8, 40, 64, 2, 93, 90), (10, 8, 64, 64, 1, 107, 130),
+    (10, 10, 32, 64, 1, 100, 122), (8, 18, 40, 64, 1, 130, 149), (5, 2, 32, 512, 1, 72, 136),
 ])
 def test_layer(dtype, k, d, c_in, c_out, n, h, w):
     from paper_1509_03371_amd import binding as B
@@ -68,6 +72,30 @@ def test_many_class_planes(k, c_in, c_out, h, w):
     net.plan(2, h, w, pad=False, keep=True)
     net.forward(torch.from_numpy(img).cuda())
     assert np.abs(net.get_activation(1) - OL.conv_sk(img, ws[1], bs[1], 1, relu=False)).max() <= 2e-4
+    net.close()
+
+
+def test_usknet_data_gradients():
+    # 64..512 maps: the data gradients of the 6x6, 4x4, 8x8 and 1x1 layers read zero borders around the error maps.  Tolerances as
+    # in the 16-bit training tests, which hold the nets of few maps to them
+    from paper_1509_03371_amd import binding as B
+    base, h, w, n = 64, 206, 214, 2
+    params = S.usknet_params(2, 2, 550, base=base, bias_scale=0.1)
+    net = B.USKNet(2, 2, base_ch=base, dtype="bf16")
+    for i, name in enumerate(S.USKNET_PARAM_NAMES):
+        net.set_weights(i, *params[name])
+    img = np.stack([np.stack([S.em_like_image(h, w, 551 + 7 * i + c) for c in range(2)]) for i in range(n)]).astype(np.float32)
+    net.plan(n, h, w, training=True)
+    ho, wo = net.output_size(h, w)
+    lab = np.random.default_rng(552).integers(0, 2, (n, ho, wo)).astype(np.int32)
+    net.forward(torch.from_numpy(img).cuda())
+    net.backward(torch.from_numpy(lab).cuda())
+    p64 = {k: (a.astype(np.float64), b.astype(np.float64)) for k, (a, b) in params.items()}
+    _, ref = ON.usknet_backward(img, p64, lab, base=base)
+    for i, name in enumerate(S.USKNET_PARAM_NAMES):
+        err = np.abs(net.get_grad(i)[0] - ref[name][0]).max() / np.abs(ref[name][0]).max()
+        print("%s %.2e" % (name, err), flush=True)
+        assert err <= 8e-2, name
     net.close()
 
 
