@@ -6,17 +6,23 @@
 // Section 4.2).  Run layer by layer, the backward pass of these three moves the hidden maps five times between the
 // GPU and its memory (200 maps per pixel against 48 of the input): written by the forward pass, read by the second
 // convolution, by its weight gradient and as the ReLU mask, and their gradient written and read twice more.
-// Here a workgroup takes 64 pixels at a time and keeps everything but x and dx on the chip:
-//   1. per wave, 16 pixels: h (recomputed from x, MFMA 16x16x32 with the W1 fragments in LDS), z, the softmax, the
-//      loss term, dz = (p - onehot) / P, dh = (W2^T dz) * [h > 0] on the accumulator layout of h, and
-//      dx = W1^T dh by a second MFMA whose K index runs over the hidden maps in the order the accumulators hold
-//      them (as the forward head does for z) -- stored to memory in the octet layout;
-//   2. h, dh, x and dz of the 64 pixels go to LDS in the octet layout (16-bit, rounded as the layer-by-layer path
-//      rounds them when it stores them);
-//   3. the weight gradients contract over pixels: dW1 = dh x^T, dW2 = dz h^T, db1 = dh 1, db2 = dz 1, MFMA operands
+// Here a workgroup of eight waves takes 64 pixels at a time and keeps everything but x and dx on the chip:
+//   1. a wave owns a pair of hidden tiles (nets with few of them: a share of the pixels too) and keeps its fragments of
+//      W1 and W2 in registers for the whole launch: h (recomputed from x, MFMA 16x16x32), rounded to LDS in the octet
+//      layout, and the pair's share of z, fp32, to LDS;
+//   2. every wave adds the shares and forms the softmax, one pixel per lane; dz = (p - onehot) / P; the loss term (one
+//      wave); dh = (W2^T dz) * [h > 0] on the accumulator layout of h, to LDS in the octet layout (16-bit, rounded as
+//      the layer-by-layer path rounds when it stores);
+//   3. dx = W1^T dh with W1^T fragments in registers: a wave owns 16 input maps of half of the pixel groups;
+//   4. the weight gradients contract over pixels: dW1 = dh x^T, dW2 = dz h^T, db1 = dh 1, db2 = dz 1, MFMA operands
 //      read from those tiles with the transposing LDS read (ds_read_b64_tr_b16: lane 4r + q of a group of 16 names
 //      maps 4q..4q+3 of pixel r and receives pixels 0..3 of map 4q + e); wave w owns the hidden-map tiles
-//      w, w + 4, ... of dW1 and dW2 and keeps them in accumulators for the whole launch.
+//      w, w + 8, ... of dW1 and dW2 and keeps them in accumulators for the whole launch.
+// The x of the next block is in flight during a block and lands in the second x tile, which holds the shares of z until then.
+// Bound by LDS and the three barriers a block: about 400 KB of LDS traffic per 64 pixels (3200 cycles of a CU; the
+// MFMAs take 1400).  With a wave per 16 pixels and all weights in LDS (four waves, one to a SIMD: 125 KB of LDS) nothing
+// hid a load, a barrier or the per-pixel 64-bit divisions.  48 -> 200 -> 2, bf16, 8 x 1024^2 pixels: 2.73 -> 1.91 ms; 512^2:
+// 101 -> 75 us.  128 pixels a block spill (82 registers).
 // Each workgroup writes its sums once; head_train_reduce_kernel adds the workgroups' copies in a fixed order,
 // scatters them to the two layers' dW / db and finishes the loss.
 #include "sk_kernels.h"
@@ -35,7 +41,10 @@ typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 
 namespace {
 
-constexpr int HB_THREADS = 256, HB_PIX = 64;
+constexpr int HB_WAVES = 8, HB_THREADS = 64 * HB_WAVES, HB_PIX = 64;
+
+// bytes a pixel takes in an x tile, which also holds up to 8 partial z of 16 bytes
+__host__ __device__ constexpr int x_row_bytes(int ksteps) { return ksteps * 64 + 16 > 128 ? ksteps * 64 + 16 : 128; }
 
 template <int DT> __device__ __forceinline__ floatx4 mfma32(uint4v a, uint4v b, floatx4 c)
 {
@@ -76,70 +85,81 @@ __global__ __launch_bounds__(HB_THREADS) void head_train_bwd_h_kernel(HeadTrainA
     extern __shared__ uint4v smem16[];
     constexpr int HP = (HT + 1) / 2;                             // pairs of hidden tiles = K steps of the products over hidden maps
     constexpr int PH = HT * 32 + 16;                             // bytes of a pixel's row in the h / dh tiles (16 of padding)
-    constexpr int PX = KSTEPS * 64 + 16;                         // ... in the x tile
-    constexpr int SLOTS = (HT + 3) / 4;                          // hidden tiles per wave
-    uint4v *w1 = smem16;                                         // [HT][KSTEPS][64]   A fragments of h = W1 x
-    uint4v *w2f = w1 + HT * KSTEPS * 64;                         // [HP][64]           A fragments of z = W2 h
-    uint4v *w1t = w2f + HP * 64;                                 // [NT1][HP][64]      A fragments of dx = W1^T dh
-    float *w2c = reinterpret_cast<float *>(w1t + NT1 * HP * 64); // [4][HT*16]         W2 rows, fp32
-    float *b1 = w2c + 4 * HT * 16;                               // [HT*16]
-    float *b2 = b1 + HT * 16;                                    // [4]
-    float *red = b2 + 4;                                         // [4 + 4]            block sums
-    char *hs = reinterpret_cast<char *>(red + 8);                // [64][PH]
-    char *dhs = hs + HB_PIX * PH;                                // [64][PH]
-    char *xs = dhs + HB_PIX * PH;                                // [64][PX]
-    char *dzs = xs + HB_PIX * PX;                                // [64][16]  classes 0..3 in the first 8 bytes, zeros behind
-    char *zero16 = dzs + HB_PIX * 16;                            // 16 bytes of zeros: the gradient's map quads 2 and 3
+    constexpr int PX = KSTEPS * 64 + 16;                         // ... in the x tiles
+    constexpr int XB = HB_PIX * x_row_bytes(KSTEPS);                // bytes of an x tile (or of the partial z that share its place)
+    constexpr int HSPLIT = HP > 4 ? 8 : HP > 2 ? 4 : 2;          // waves over the hidden pairs; the others split the pixels
+    constexpr int NPG = HB_PIX / 16 * HSPLIT / HB_WAVES;            // 16-pixel groups of a wave in the pixel phases
+    constexpr int SLOTS = (HT + HB_WAVES - 1) / HB_WAVES;        // hidden tiles of a wave in the weight gradients
+    constexpr int XLD = HB_PIX * KSTEPS * 4 / HB_THREADS > 0 ? HB_PIX * KSTEPS * 4 / HB_THREADS : 1;    // octets of x a thread stages
+    constexpr int NWG = HB_WAVES / NT1;                          // waves per 16 input maps of dx
+    float *w2c = reinterpret_cast<float *>(smem16);              // [4][HT*16]         W2 rows, fp32
+    float *b2 = w2c + 4 * HT * 16;                               // [4]
+    float *red = b2 + 4;                                         // [16]               block sums
+    char *hs = reinterpret_cast<char *>(red + 16);               // [HB_PIX][PH]
+    char *dhs = hs + HB_PIX * PH;                                   // [HB_PIX][PH]
+    char *xs0 = dhs + HB_PIX * PH;                                  // 2 x [HB_PIX][PX]; the next block's also holds [HP][HB_PIX][4] partial z
+    char *dzs = xs0 + 2 * XB;                                    // [HB_PIX][16]  classes 0..3 in the first 8 bytes, zeros behind
+    char *zero16 = dzs + HB_PIX * 16;                               // 16 bytes of zeros: the gradient's map quads 2 and 3
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hp = wave % HSPLIT, pg0 = wave / HSPLIT * NPG;     // this wave's hidden pair and first pixel group
+    const bool has0 = 2 * hp < HT, has1 = 2 * hp + 1 < HT;       // ... and which of the pair's tiles there are
 
-    // ---- weights into LDS --------------------------------------------------------------------------------------
-    for (int q = tid; q < HT * KSTEPS * 64; q += HB_THREADS) w1[q] = static_cast<const uint4v *>(a.w1p)[q];
-    for (int q = tid; q < HP * 64; q += HB_THREADS) {
-        const int pr = q >> 6, ln = q & 63, cls = ln & 15, gg = ln >> 4;
-        unsigned short v[8];
+    // ---- weights: this wave's fragments into registers, W2 into LDS ----------------------------------------------
+    uint4v w1[2][KSTEPS], w2f, w1t[HP];
+    floatx4 b1[2];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int h = 16 * (2 * pr + (e >> 2)) + 4 * gg + (e & 3);
-            v[e] = to16<DT>((cls < a.classes && h < a.hidden) ? a.w2[cls * a.hidden + h] : 0.f);
-        }
-        w2f[q] = uint4v{v[0] | ((unsigned)v[1] << 16), v[2] | ((unsigned)v[3] << 16), v[4] | ((unsigned)v[5] << 16), v[6] | ((unsigned)v[7] << 16)};
+    for (int i = 0; i < 2; ++i) {
+        const int t = 2 * hp + i;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) w1[i][ks] = t < HT ? static_cast<const uint4v *>(a.w1p)[(t * KSTEPS + ks) * 64 + lane] : uint4v{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b1[i][r] = 16 * t + 4 * g + r < a.hidden ? a.b1[16 * t + 4 * g + r] : 0.f;
     }
-    for (int q = tid; q < NT1 * HP * 64; q += HB_THREADS) {
-        // row m = input map 16 nt + (lane & 15); K value 8 gg + e = hidden map 16 (2 pr + e / 4) + 4 gg + e % 4
-        const int ln = q & 63, pr = (q >> 6) % HP, nt = (q >> 6) / HP, c = 16 * nt + (ln & 15), gg = ln >> 4;
+    {   // A fragment of z = W2 h: row = class, K value 8 g + e = hidden map 16 (2 hp + e / 4) + 4 g + e % 4 (the accumulators' order)
         unsigned short v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int h = 16 * (2 * pr + (e >> 2)) + 4 * gg + (e & 3);
+            const int h = 16 * (2 * hp + (e >> 2)) + 4 * g + (e & 3);
+            v[e] = to16<DT>((l16 < a.classes && h < a.hidden) ? a.w2[l16 * a.hidden + h] : 0.f);
+        }
+        w2f = uint4v{v[0] | ((unsigned)v[1] << 16), v[2] | ((unsigned)v[3] << 16), v[4] | ((unsigned)v[5] << 16), v[6] | ((unsigned)v[7] << 16)};
+    }
+    const int xt = wave % NT1, xg0 = wave / NT1;                 // dx: this wave's input map tile, its first pixel group
+#pragma unroll
+    for (int pr = 0; pr < HP; ++pr) {   // A fragments of dx = W1^T dh: row = input map, K value 8 g + e = hidden map 32 pr + 8 g + e
+        const int c = 16 * xt + l16;
+        unsigned short v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int h = 32 * pr + 8 * g + e;
             v[e] = to16<DT>((c < a.c_in && h < a.hidden) ? a.w1[(long)h * a.c_in + c] : 0.f);
         }
-        w1t[q] = uint4v{v[0] | ((unsigned)v[1] << 16), v[2] | ((unsigned)v[3] << 16), v[4] | ((unsigned)v[5] << 16), v[6] | ((unsigned)v[7] << 16)};
+        w1t[pr] = uint4v{v[0] | ((unsigned)v[1] << 16), v[2] | ((unsigned)v[3] << 16), v[4] | ((unsigned)v[5] << 16), v[6] | ((unsigned)v[7] << 16)};
     }
     for (int q = tid; q < 4 * HT * 16; q += HB_THREADS) {
         const int cls = q / (HT * 16), h = q - cls * (HT * 16);
         w2c[q] = (cls < a.classes && h < a.hidden) ? a.w2[cls * a.hidden + h] : 0.f;
     }
-    for (int q = tid; q < HT * 16; q += HB_THREADS) b1[q] = q < a.hidden ? a.b1[q] : 0.f;
     if (tid < 4) b2[tid] = tid < a.classes ? a.b2[tid] : 0.f;
-    for (int q = tid; q < HB_PIX * 4 + 4; q += HB_THREADS) reinterpret_cast<unsigned *>(dzs)[q] = 0u;    // dzs and zero16
+    for (int q = tid; q < HB_PIX * 4 + 4; q += HB_THREADS) reinterpret_cast<unsigned *>(dzs)[q] = 0u;       // dzs and zero16
     // labelled pixels P (exact: integers), the same sum in every thread
+    long *cs = reinterpret_cast<long *>(red);                    // HB_WAVES longs = the 16 floats
     {
         long local = 0;
         for (int q = tid; q < a.ncounts; q += HB_THREADS) local += a.counts[q];
         for (int off = 32; off > 0; off >>= 1) local += __shfl_down(local, off, 64);
-        long *cs = reinterpret_cast<long *>(red);                // 4 longs = the 8 floats
         if (lane == 0) cs[wave] = local;
     }
     __syncthreads();
     float invP;
     {
-        const long *cs = reinterpret_cast<const long *>(red);
-        const long kept = cs[0] + cs[1] + cs[2] + cs[3];
+        long kept = 0;
+#pragma unroll
+        for (int w = 0; w < HB_WAVES; ++w) kept += cs[w];
         invP = 1.f / (float)(kept > 0 ? kept : 1);
     }
-    __syncthreads();
 
     const int plane = a.plane;
     const long total = (long)a.n * plane;
@@ -147,12 +167,56 @@ __global__ __launch_bounds__(HB_THREADS) void head_train_bwd_h_kernel(HeadTrainA
     const uint4v *xin = static_cast<const uint4v *>(a.x);
     const long nblocks = (total + HB_PIX - 1) / HB_PIX;
 
+    // image and pixel of a block's first pixel, for the block at work and the one whose x is being loaded: a step of the
+    // grid is added to them, so that no block costs a division
+    const long step = (long)gridDim.x * HB_PIX, img_step = step / plane;
+    const int pix_step = (int)(step - img_step * plane);
+    auto advance = [&](long &img, int &pix) {
+        img += img_step;
+        const unsigned q = (unsigned)pix + (unsigned)pix_step;
+        const bool over = q >= (unsigned)plane;
+        pix = (int)(over ? q - (unsigned)plane : q);
+        img += over ? 1 : 0;
+    };
+    auto locate = [&](long &img, int &pix, int off) {            // pixel `off` behind (img, pix); past the last one: the last one
+        unsigned q = (unsigned)pix + (unsigned)off;
+        if (plane >= HB_PIX) {
+            const bool over = q >= (unsigned)plane;
+            q -= over ? (unsigned)plane : 0u;
+            img += over ? 1 : 0;
+        } else {
+            img += q / (unsigned)plane;
+            q %= (unsigned)plane;
+        }
+        pix = img < a.n ? (int)q : plane - 1;
+        img = img < a.n ? img : a.n - 1;
+    };
+    uint4v nx[XLD];
+    auto load_x = [&](long img, int pix) {
+#pragma unroll
+        for (int i = 0; i < XLD; ++i) {
+            const int q = tid + i * HB_THREADS, o = q / HB_PIX;
+            long im = img;
+            int px = pix;
+            locate(im, px, q % HB_PIX);
+            const uint4v v = xin[(im * c8 + (o < c8 ? o : c8 - 1)) * plane + px];
+            nx[i] = o < c8 ? v : uint4v{0u, 0u, 0u, 0u};
+        }
+    };
+    auto store_x = [&](char *xs) {
+#pragma unroll
+        for (int i = 0; i < XLD; ++i) {
+            const int q = tid + i * HB_THREADS, o = q / HB_PIX;
+            if (o < KSTEPS * 4) *reinterpret_cast<uint4v *>(xs + (q % HB_PIX) * PX + o * 16) = nx[i];
+        }
+    };
+
     // this lane's offsets into the tiles for the transposing reads (lane 4r + q of a 16-lane group: pixel r, map quad q)
     const int rr = l16 >> 2, q4 = l16 & 3;
     unsigned off_h[SLOTS], off_x[NT1], off_dz;
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
-        int t = wave + 4 * s;
+        int t = wave + HB_WAVES * s;
         t = t < HT ? t : HT - 1;
         off_h[s] = (unsigned)((8 * g + rr) * PH + (2 * t + (q4 >> 1)) * 16 + (q4 & 1) * 8);
     }
@@ -173,129 +237,151 @@ __global__ __launch_bounds__(HB_THREADS) void head_train_bwd_h_kernel(HeadTrainA
     const uint4v ones = uint4v{one2, one2, one2, one2};
     float loss_local = 0.f;
 
-    auto load_x = [&](long blk, uint4v (&bv)[KSTEPS]) {
-        long p = blk * HB_PIX + 16 * wave + l16;
-        p = p < total ? p : total - 1;
-        const long img = p / plane, pix = p - img * plane;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            const int o = ks * 4 + g;
-            const uint4v v = xin[(img * c8 + (o < c8 ? o : c8 - 1)) * plane + pix];
-            bv[ks] = o < c8 ? v : uint4v{0u, 0u, 0u, 0u};
-        }
-    };
-
-    uint4v bv[KSTEPS], nx[KSTEPS];
-    if ((long)blockIdx.x < nblocks) load_x(blockIdx.x, bv);
+    // the grid has no more workgroups than there are blocks
+    long bimg = (long)blockIdx.x * HB_PIX / plane, ximg = bimg;
+    int bpix = (int)((long)blockIdx.x * HB_PIX - bimg * plane), xpix = bpix;
+    load_x(ximg, xpix);
+    store_x(xs0);
+    advance(ximg, xpix);
+    load_x(ximg, xpix);                                         // past the last pixel: that pixel, never used
+    __syncthreads();
+    int cur = 0;
     for (long blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
-        const long nblk = blk + gridDim.x;
-        load_x(nblk < nblocks ? nblk : blk, nx);                // in flight during this block
-        const long p = blk * HB_PIX + 16 * wave + l16;          // this lane's pixel
-        const bool inside = p < total;
-        const long pc = inside ? p : total - 1;
-        const long img = pc / plane, pix = pc - img * plane;
-        const int lab = a.labels[pc];
-        const int px = 16 * wave + l16;                          // its row in the tiles
+        const char *xs = xs0 + cur * XB;
+        char *xnext = xs0 + (cur ^ 1) * XB;
+        const int lab = blk * HB_PIX + lane < total ? a.labels[blk * HB_PIX + lane] : -1;      // needed after the first barrier
 
-        // ---- 1. the wave's 16 pixels ---------------------------------------------------------------------------
+        // ---- 1. h of the wave's hidden pair on its pixel groups, and the pair's share of z -------------------------
+        floatx4 hacc[2][NPG];
+        if (has0) {
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) *reinterpret_cast<uint4v *>(xs + px * PX + (4 * ks + g) * 16) = bv[ks];
-        floatx4 hacc[HT];
+            for (int j = 0; j < NPG; ++j) {
+                const int px = 16 * (pg0 + j) + l16;
+                hacc[0][j] = b1[0];
+                hacc[1][j] = b1[1];
 #pragma unroll
-        for (int t = 0; t < HT; ++t) hacc[t] = *reinterpret_cast<const floatx4 *>(b1 + t * 16 + 4 * g);
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks)
-#pragma unroll
-            for (int t = 0; t < HT; ++t) hacc[t] = mfma32<DT>(w1[(t * KSTEPS + ks) * 64 + lane], bv[ks], hacc[t]);
-        // ReLU, rounding to the storage type (what the layer-by-layer path stores), z
-        unsigned hb[HT][2];
-#pragma unroll
-        for (int t = 0; t < HT; ++t) {
-            hb[t][0] = pack16x2<DT>(fmaxf(hacc[t][0], 0.f), fmaxf(hacc[t][1], 0.f));
-            hb[t][1] = pack16x2<DT>(fmaxf(hacc[t][2], 0.f), fmaxf(hacc[t][3], 0.f));
-            *reinterpret_cast<uint2v *>(hs + px * PH + (2 * t + (g >> 1)) * 16 + (g & 1) * 8) = uint2v{hb[t][0], hb[t][1]};
-        }
-        floatx4 z = g == 0 ? *reinterpret_cast<const floatx4 *>(b2) : floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int pr = 0; pr < HP; ++pr) {
-            const bool two = 2 * pr + 1 < HT;
-            const uint4v hv = uint4v{hb[2 * pr][0], hb[2 * pr][1], two ? hb[2 * pr + 1 < HT ? 2 * pr + 1 : 0][0] : 0u,
-                                     two ? hb[2 * pr + 1 < HT ? 2 * pr + 1 : 0][1] : 0u};
-            z = mfma32<DT>(w2f[pr * 64 + lane], hv, z);
-        }
-        // softmax, loss term and dz in the lanes of group 0 (classes 0..3 of pixel l16), then to the pixel's other lanes
-        float dz[4] = {0.f, 0.f, 0.f, 0.f};
-        if (g == 0 && inside && lab >= 0 && lab < a.classes) {
-            float m = z[0];
-#pragma unroll
-            for (int c = 1; c < 4; ++c)
-                if (c < a.classes) m = fmaxf(m, z[c]);
-            float e[4], sum = 0.f, zl = 0.f;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                e[c] = c < a.classes ? expf(z[c] - m) : 0.f;
-                sum += e[c];
-                zl = c == lab ? z[c] : zl;
+                for (int ks = 0; ks < KSTEPS; ++ks) {
+                    const uint4v bv = *reinterpret_cast<const uint4v *>(xs + px * PX + (4 * ks + g) * 16);
+                    hacc[0][j] = mfma32<DT>(w1[0][ks], bv, hacc[0][j]);
+                    hacc[1][j] = mfma32<DT>(w1[1][ks], bv, hacc[1][j]);
+                }
             }
-            loss_local -= zl - m - logf(sum);
-            const float inv = 1.f / sum;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) dz[c] = c < a.classes ? (e[c] * inv - (c == lab ? 1.f : 0.f)) * invP : 0.f;
+            for (int j = 0; j < NPG; ++j) {
+                // ReLU, rounding to the storage type (what the layer-by-layer path stores), z
+                const int px = 16 * (pg0 + j) + l16;
+                uint4v hv;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    hv[2 * i] = pack16x2<DT>(fmaxf(hacc[i][j][0], 0.f), fmaxf(hacc[i][j][1], 0.f));
+                    hv[2 * i + 1] = pack16x2<DT>(fmaxf(hacc[i][j][2], 0.f), fmaxf(hacc[i][j][3], 0.f));
+                }
+                char *row = hs + px * PH + (4 * hp + (g >> 1)) * 16 + (g & 1) * 8;
+                *reinterpret_cast<uint2v *>(row) = uint2v{hv[0], hv[1]};
+                if (has1) *reinterpret_cast<uint2v *>(row + 32) = uint2v{hv[2], hv[3]};
+                const floatx4 z = mfma32<DT>(w2f, hv, floatx4{0.f, 0.f, 0.f, 0.f});
+                if (g == 0) *reinterpret_cast<floatx4 *>(xnext + (hp * HB_PIX + px) * 16) = z;
+            }
         }
-        if (g == 0) *reinterpret_cast<uint2v *>(dzs + px * 16) = uint2v{pack16x2<DT>(dz[0], dz[1]), pack16x2<DT>(dz[2], dz[3])};
+        __syncthreads();                                        // all shares of z are in LDS
+
+        // ---- 2. softmax, loss term and dz = (p - onehot) / P, one pixel per lane, the same in every wave --------------
+        floatx4 z = *reinterpret_cast<const floatx4 *>(b2);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) dz[c] = __shfl(dz[c], l16, 64);
-        // dh = (W2^T dz) where h > 0, rounded to the storage type; dx = W1^T dh
-        unsigned dhb[HT][2];
+        for (int pr = 0; pr < HP; ++pr) z += *reinterpret_cast<const floatx4 *>(xnext + (pr * HB_PIX + lane) * 16);
+        const bool kept = lab >= 0 && lab < a.classes;
+        float m = z[0];
 #pragma unroll
-        for (int t = 0; t < HT; ++t) {
-            floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 1; c < 4; ++c)
+            if (c < a.classes) m = fmaxf(m, z[c]);
+        float e[4], dz[4], sum = 0.f, zl = 0.f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            e[c] = 0.f;
+            if (c < a.classes) e[c] = expf(z[c] - m);           // uniform
+            sum += e[c];
+            zl = c == lab ? z[c] : zl;
+        }
+        const float inv = 1.f / sum;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) dz[c] = kept && c < a.classes ? (e[c] * inv - (c == lab ? 1.f : 0.f)) * invP : 0.f;
+        if (wave == HB_WAVES - 1) {                             // (the wave with the least to do in phase 1)
+            if (kept) loss_local -= zl - m - logf(sum);
+            *reinterpret_cast<uint2v *>(dzs + lane * 16) = uint2v{pack16x2<DT>(dz[0], dz[1]), pack16x2<DT>(dz[2], dz[3])};
+        }
+        // dh = (W2^T dz) where h > 0, rounded to the storage type
+        if (has0) {
+            floatx4 v[2][NPG];
+#pragma unroll
+            for (int j = 0; j < NPG; ++j) v[0][j] = v[1][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 if (c >= a.classes) break;                      // uniform
-                const floatx4 w = *reinterpret_cast<const floatx4 *>(w2c + c * (HT * 16) + t * 16 + 4 * g);
-                v += w * dz[c];
+                const float *wp = w2c + c * (HT * 16) + 32 * hp + 4 * g;
+                const floatx4 wa = *reinterpret_cast<const floatx4 *>(wp), wb = has1 ? *reinterpret_cast<const floatx4 *>(wp + 16) : floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < NPG; ++j) {
+                    const float d = __shfl(dz[c], 16 * (pg0 + j) + l16, 64);
+                    v[0][j] += wa * d;
+                    v[1][j] += wb * d;
+                }
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = hacc[t][r] > 0.f ? v[r] : 0.f;
-            dhb[t][0] = pack16x2<DT>(v[0], v[1]);
-            dhb[t][1] = pack16x2<DT>(v[2], v[3]);
-            *reinterpret_cast<uint2v *>(dhs + px * PH + (2 * t + (g >> 1)) * 16 + (g & 1) * 8) = uint2v{dhb[t][0], dhb[t][1]};
+            for (int j = 0; j < NPG; ++j) {
+                char *row = dhs + (16 * (pg0 + j) + l16) * PH + (4 * hp + (g >> 1)) * 16 + (g & 1) * 8;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[i][j][r] = hacc[i][j][r] > 0.f ? v[i][j][r] : 0.f;
+                    if (i == 0 || has1) *reinterpret_cast<uint2v *>(row + 32 * i) = uint2v{pack16x2<DT>(v[i][j][0], v[i][j][1]), pack16x2<DT>(v[i][j][2], v[i][j][3])};
+                }
+            }
         }
-        if (a.dx != nullptr) {
-            floatx4 dxa[NT1];
-#pragma unroll
-            for (int nt = 0; nt < NT1; ++nt) dxa[nt] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int pr = 0; pr < HP; ++pr) {
-                const bool two = 2 * pr + 1 < HT;
-                const uint4v dv = uint4v{dhb[2 * pr][0], dhb[2 * pr][1], two ? dhb[2 * pr + 1 < HT ? 2 * pr + 1 : 0][0] : 0u,
-                                         two ? dhb[2 * pr + 1 < HT ? 2 * pr + 1 : 0][1] : 0u};
-#pragma unroll
-                for (int nt = 0; nt < NT1; ++nt) dxa[nt] = mfma32<DT>(w1t[(nt * HP + pr) * 64 + lane], dv, dxa[nt]);
-            }
-            // lane (g, l16) holds input maps 16 nt + 4g .. + 3 of its pixel: half an octet
+        __syncthreads();                                        // h, dh and dz of the block are in LDS, the shares of z are read
+
+        store_x(xnext);
+        advance(ximg, xpix);
+        load_x(ximg, xpix);                                     // in flight during the next block
+
+        // ---- 3. dx = W1^T dh -----------------------------------------------------------------------------------------
+        if (a.dx != nullptr && xg0 < NWG) {
             char *dxp = static_cast<char *>(a.dx);
+            const int o8 = 2 * xt + (g >> 1);                   // lane (g, l16) holds input maps 16 xt + 4g .. + 3 of its pixel: half an octet
 #pragma unroll
-            for (int nt = 0; nt < NT1; ++nt) {
-                const int o8 = 2 * nt + (g >> 1);
+            for (int j = 0; j < (HB_PIX / 16 + NWG - 1) / NWG; ++j) {
+                const int pg = xg0 + j * NWG;
+                if (pg >= HB_PIX / 16) break;                      // uniform
+                const char *row = dhs + (16 * pg + l16) * PH;
+                floatx4 dxa = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int pr = 0; pr < HP; ++pr) {
+                    const bool there = 4 * pr + 3 < 2 * HT || 4 * pr + g < 2 * HT;      // an odd number of tiles: no octets behind the last
+                    uint4v dv = *reinterpret_cast<const uint4v *>(row + (there ? 4 * pr + g : 0) * 16);
+                    if (!there) dv = uint4v{0u, 0u, 0u, 0u};
+                    dxa = mfma32<DT>(w1t[pr], dv, dxa);
+                }
+                long img = bimg;
+                int pix = bpix;
+                const bool inside = blk * HB_PIX + 16 * pg + l16 < total;
+                locate(img, pix, 16 * pg + l16);
                 if (inside && o8 < c8)
                     *reinterpret_cast<uint2v *>(dxp + ((img * c8 + o8) * plane + pix) * 16 + (g & 1) * 8) =
-                        uint2v{pack16x2<DT>(dxa[nt][0], dxa[nt][1]), pack16x2<DT>(dxa[nt][2], dxa[nt][3])};
+                        uint2v{pack16x2<DT>(dxa[0], dxa[1]), pack16x2<DT>(dxa[2], dxa[3])};
             }
         }
-        __syncthreads();                                        // the tiles of all 64 pixels are in LDS
 
-        // ---- 2. weight gradients: contraction over the 64 pixels (two K steps of 32) ------------------------------
+        // ---- 4. weight gradients: contraction over the block's pixels (K steps of 32) ----------------------------------
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
+        for (int ks = 0; ks < HB_PIX / 32; ++ks) {
+            const uint4v adz = read_frag(hs, off_dz + ks * 32 * dz_step, off_dz + (ks * 32 + 4) * dz_step);
+            if (wave == HB_WAVES - 1) accb2 = mfma32<DT>(adz, ones, accb2);
+            if (wave >= HT) continue;                           // uniform
             uint4v bx[NT1];
 #pragma unroll
             for (int nt = 0; nt < NT1; ++nt) bx[nt] = read_frag(xs, off_x[nt] + ks * 32 * PX, off_x[nt] + (ks * 32 + 4) * PX);
-            const uint4v adz = read_frag(hs, off_dz + ks * 32 * dz_step, off_dz + (ks * 32 + 4) * dz_step);
 #pragma unroll
             for (int s = 0; s < SLOTS; ++s) {
-                if (wave + 4 * s >= HT) break;                  // uniform
+                if (wave + HB_WAVES * s >= HT) break;           // uniform
                 const uint4v adh = read_frag(dhs, off_h[s] + ks * 32 * PH, off_h[s] + (ks * 32 + 4) * PH);
                 const uint4v bh = read_frag(hs, off_h[s] + ks * 32 * PH, off_h[s] + (ks * 32 + 4) * PH);
 #pragma unroll
@@ -303,29 +389,28 @@ __global__ __launch_bounds__(HB_THREADS) void head_train_bwd_h_kernel(HeadTrainA
                 accb1[s] = mfma32<DT>(adh, ones, accb1[s]);
                 acc2[s] = mfma32<DT>(adz, bh, acc2[s]);
             }
-            if (wave == 0) accb2 = mfma32<DT>(adz, ones, accb2);
         }
-        __syncthreads();                                        // ... and read: the next block may overwrite them
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) bv[ks] = nx[ks];
+        __syncthreads();                                        // the tiles are read and the next x is written
+        advance(bimg, bpix);
+        cur ^= 1;
     }
 
     // ---- this workgroup's sums -----------------------------------------------------------------------------------
     float *copy = a.scratch + (long)blockIdx.x * copy_floats_of(HT, NT1);
 #pragma unroll
     for (int s = 0; s < SLOTS; ++s) {
-        const int t = wave + 4 * s;
+        const int t = wave + HB_WAVES * s;
         if (t >= HT) break;
 #pragma unroll
         for (int nt = 0; nt < NT1; ++nt) *reinterpret_cast<floatx4 *>(copy + ((t * NT1 + nt) * 64 + lane) * 4) = acc1[s][nt];
         *reinterpret_cast<floatx4 *>(copy + HT * NT1 * 256 + (t * 64 + lane) * 4) = acc2[s];
         if (l16 == 0) *reinterpret_cast<floatx4 *>(copy + HT * NT1 * 256 + HT * 256 + t * 16 + 4 * g) = accb1[s];   // every column holds the same sums
     }
-    if (wave == 0 && l16 == 0) *reinterpret_cast<floatx4 *>(copy + HT * NT1 * 256 + HT * 256 + HT * 16 + 4 * g) = accb2;
-    for (int off = 32; off > 0; off >>= 1) loss_local += __shfl_down(loss_local, off, 64);
-    if (lane == 0) red[wave] = loss_local;
-    __syncthreads();
-    if (tid == 0) copy[HT * NT1 * 256 + HT * 256 + HT * 16 + 16] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (wave == HB_WAVES - 1) {
+        if (l16 == 0) *reinterpret_cast<floatx4 *>(copy + HT * NT1 * 256 + HT * 256 + HT * 16 + 4 * g) = accb2;
+        for (int off = 32; off > 0; off >>= 1) loss_local += __shfl_down(loss_local, off, 64);
+        if (lane == 0) copy[HT * NT1 * 256 + HT * 256 + HT * 16 + 16] = loss_local;
+    }
 }
 
 // Sums the workgroups' copies element by element (fixed order) and scatters: dW1[h][c], dW2[class][h], db1, db2, loss.
@@ -378,17 +463,16 @@ __global__ void __launch_bounds__(256) head_train_reduce_kernel(HeadTrainArgs a,
     }
 }
 
-size_t smem_bytes(int HT, int KSTEPS, int NT1)
+constexpr size_t smem_bytes(int HT, int KSTEPS)
 {
-    const int HP = (HT + 1) / 2;
-    return (size_t)(HT * KSTEPS * 64 + HP * 64 + NT1 * HP * 64) * 16 + (size_t)(4 * HT * 16 + HT * 16 + 4 + 8) * 4 +
-           (size_t)HB_PIX * (2 * (HT * 32 + 16) + (KSTEPS * 64 + 16) + 16) + 16;
+    return (size_t)(4 * HT * 16 + 4 + 16) * 4 + (size_t)HB_PIX * (2 * (HT * 32 + 16) + 2 * x_row_bytes(KSTEPS) + 16) + 16;
 }
 
 template <int DT, int HT, int KSTEPS, int NT1>
 hipError_t launch_t(const HeadTrainArgs &a, int blocks, hipStream_t stream)
 {
-    const size_t smem = smem_bytes(HT, KSTEPS, NT1);
+    constexpr size_t smem = smem_bytes(HT, KSTEPS);
+    static_assert(smem <= 160 * 1024, "LDS of a CU");
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&head_train_bwd_h_kernel<DT, HT, KSTEPS, NT1>),
@@ -409,6 +493,12 @@ hipError_t launch_ht(const HeadTrainArgs &a, int nt1, int blocks, hipStream_t st
     case 3: return launch_t<DT, HT, 2, 3>(a, blocks, stream);
     default: return hipErrorInvalidValue;
     }
+}
+
+template <int DT>
+hipError_t launch_dt(const HeadTrainArgs &a, int HT, int nt1, int blocks, hipStream_t stream)
+{
+    return HT == 4 ? launch_ht<DT, 4>(a, nt1, blocks, stream) : HT == 8 ? launch_ht<DT, 8>(a, nt1, blocks, stream) : launch_ht<DT, 13>(a, nt1, blocks, stream);
 }
 
 int tiles_of(int hidden)
@@ -440,14 +530,13 @@ hipError_t launch_head_train_bwd(HeadTrainArgs a, size_t scratch_floats, hipStre
     if ((a.c_in + 7) / 8 > (NT1 == 3 ? 8 : 4)) return hipErrorInvalidValue;
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-    const long nblocks = ((long)a.n * a.plane + HB_PIX - 1) / HB_PIX;
+    const long total = (long)a.n * a.plane;
+    const long nblocks = (total + HB_PIX - 1) / HB_PIX;
     long blocks = cus;
     if (blocks > nblocks) blocks = nblocks;
     if (blocks > (long)(scratch_floats / cf)) blocks = (long)(scratch_floats / cf);
     if (blocks < 1) return hipErrorInvalidValue;
-    hipError_t e = hipErrorInvalidValue;
-    if (a.dtype == 1) e = HT == 4 ? launch_ht<1, 4>(a, NT1, (int)blocks, stream) : HT == 8 ? launch_ht<1, 8>(a, NT1, (int)blocks, stream) : launch_ht<1, 13>(a, NT1, (int)blocks, stream);
-    else e = HT == 4 ? launch_ht<2, 4>(a, NT1, (int)blocks, stream) : HT == 8 ? launch_ht<2, 8>(a, NT1, (int)blocks, stream) : launch_ht<2, 13>(a, NT1, (int)blocks, stream);
+    const hipError_t e = a.dtype == 1 ? launch_dt<1>(a, HT, NT1, (int)blocks, stream) : launch_dt<2>(a, HT, NT1, (int)blocks, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(head_train_reduce_kernel, dim3((cf + 63) / 64), dim3(256), 0, stream, a, (int)blocks, HT, NT1, cf);
     return hipGetLastError();

@@ -97,6 +97,37 @@ def test_fused_head_training_matches_layer_by_layer():
         assert np.abs(db1 - db0).max() <= 3e-3 * max(np.abs(db0).max(), np.abs(dw0).max())
 
 
+@pytest.mark.parametrize("width,hidden,classes,n,h,w,kept", [
+    (8, 16, 2, 9, 5, 7, 0.8),              # one octet, one hidden tile; images smaller than a workgroup's 64 pixels
+    (16, 33, 3, 1, 7, 9, 0.8),             # 63 pixels; a pair with one tile
+    (17, 65, 1, 2, 8, 8, 0.8),             # exactly 64 pixels an image; 5 of 8 hidden tiles; one class
+    (32, 128, 4, 1, 5, 13, 0.8),           # 65 pixels, two full map tiles, 8 full hidden tiles
+    (48, 193, 2, 3, 91, 97, 0.1),          # 13 hidden tiles, one map in the last; two blocks in some workgroups, images not of whole blocks
+    (33, 208, 4, 7, 67, 71, 0.1),          # five octets, 13 full tiles
+])
+def test_fused_head_training_edges(width, hidden, classes, n, h, w, kept):
+    """Against the layer-by-layer plan, at edges of the kernel's hidden, map and pixel tiles.  The two differ where the
+    layer-by-layer path rounds dz and W2 to 16 bits before dh: 2 x 2^-11 of a term, 1e-3; three times that for terms
+    that cancel, the bound of the test above.  Few labels are kept where there are many pixels: 1 / P stays a normal fp16."""
+    layers = S.sknet_layers(width=width, hidden=hidden, classes=classes, stages=1)
+    ws, bs = S.he_normal_weights(layers, 1, 900 + hidden, bias_scale=0.05)
+    img = S.em_like_batch(n, h, w, 64)
+    labels = labels_for(n, h, w, classes, 65, False)
+    labels[np.random.default_rng(66).random(labels.shape) >= kept] = -1
+    out = []
+    for fused in (False, True):
+        net = make_net(layers, 1, ws, bs, "f16")
+        net.plan(n, h, w, pad=True, training=True, fused_head=fused)
+        net.forward(torch.from_numpy(img).cuda())
+        loss = net.backward(torch.from_numpy(labels).cuda()).item()
+        out.append((loss, [net.get_grad(i) for i in range(net.num_convs())]))
+        net.close()
+    assert abs(out[0][0] - out[1][0]) <= 1e-4 * max(abs(out[0][0]), 1e-2)
+    for (dw0, db0), (dw1, db1) in zip(out[0][1], out[1][1]):
+        assert relerr(dw1, dw0.astype(np.float64)) <= 3e-3
+        assert np.abs(db1 - db0).max() <= 3e-3 * max(np.abs(db0).max(), np.abs(dw0).max())
+
+
 def test_fused_head_training_refusals():
     from paper_1509_03371_amd import binding as B
     layers = S.sknet_layers(width=16, hidden=40, stages=1)
