@@ -25,6 +25,7 @@
 // 101 -> 75 us.  128 pixels a block spill (82 registers).
 // Each workgroup writes its sums once; head_train_reduce_kernel adds the workgroups' copies in a fixed order,
 // scatters them to the two layers' dW / db and finishes the loss.
+#include "reduce_copies.h"
 #include "sk_kernels.h"
 
 namespace sk {
@@ -416,32 +417,17 @@ __global__ __launch_bounds__(HB_THREADS) void head_train_bwd_h_kernel(HeadTrainA
 // Sums the workgroups' copies element by element (fixed order) and scatters: dW1[h][c], dW2[class][h], db1, db2, loss.
 __global__ void __launch_bounds__(256) head_train_reduce_kernel(HeadTrainArgs a, int copies, int HT, int NT1, int copy_floats)
 {
-    __shared__ float sh[4][64];
+    __shared__ __attribute__((aligned(16))) float sh[16][64];
     __shared__ long cnt[4];
-    const int e64 = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int e = (int)blockIdx.x * 64 + e64;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    if (e < copy_floats) {
-        const float *src = a.scratch + e;
-        int cp = w;
-        for (; cp + 12 < copies; cp += 16) {
-            s0 += src[(long)(cp + 0) * copy_floats];
-            s1 += src[(long)(cp + 4) * copy_floats];
-            s2 += src[(long)(cp + 8) * copy_floats];
-            s3 += src[(long)(cp + 12) * copy_floats];
-        }
-        for (; cp < copies; cp += 4) s0 += src[(long)cp * copy_floats];
-    }
-    sh[w][e64] = (s0 + s1) + (s2 + s3);
-    {
+    const int e = (int)blockIdx.x * 64 + (int)threadIdx.x;      // (threads 0 .. 63)
+    if ((int)blockIdx.x == (int)gridDim.x - 1) {                // the last workgroup finishes the loss
         long local = 0;
         for (int q = threadIdx.x; q < a.ncounts; q += blockDim.x) local += a.counts[q];
         for (int off = 32; off > 0; off >>= 1) local += __shfl_down(local, off, 64);
-        if (e64 == 0) cnt[w] = local;
+        if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = local;
     }
-    __syncthreads();
-    if (w != 0 || e >= copy_floats) return;
-    const float v = (sh[0][e64] + sh[1][e64]) + (sh[2][e64] + sh[3][e64]);
+    const float v = sum_copies64(a.scratch, copy_floats, (int)blockIdx.x * 64, copy_floats, copies, sh);     // (holds a barrier)
+    if (threadIdx.x >= 64 || e >= copy_floats) return;
     const int n1 = HT * NT1 * 256, n2 = n1 + HT * 256, n3 = n2 + HT * 16, n4 = n3 + 16;
     if (e < n1) {               // ((t * NT1 + nt) * 64 + lane) * 4 + r: hidden map 16 t + 4 g + r, input map 16 nt + l16
         const int r = e & 3, ln = (e >> 2) & 63, tn = e >> 8, nt = tn % NT1, t = tn / NT1;

@@ -32,6 +32,7 @@
 // scatters the 36864 sums to OIHW.
 #include <algorithm>
 
+#include "reduce_copies.h"
 #include "sk_kernels.h"
 
 namespace sk {
@@ -354,34 +355,16 @@ __global__ void __launch_bounds__(256) wgrad_rows_reduce_kernel(const float *__r
                                                                 int c_out, int c_in, int MT, int NCT, int dw_blocks,
                                                                 const float *__restrict__ bias_part, float *__restrict__ db)
 {
-    __shared__ float sh[4][64];
-    const int e64 = threadIdx.x & 63, w = threadIdx.x >> 6;
+    __shared__ __attribute__((aligned(16))) float sh[16][64];
     if ((int)blockIdx.x >= dw_blocks) {
-        const int o = ((int)blockIdx.x - dw_blocks) * 64 + e64;
-        float v = 0.f;
-        if (o < c_out)
-            for (int cp = w; cp < copies; cp += 4) v += bias_part[(long)cp * (MT * 16) + o];
-        sh[w][e64] = v;
-        __syncthreads();
-        if (w == 0 && o < c_out) db[o] = (sh[0][e64] + sh[1][e64]) + (sh[2][e64] + sh[3][e64]);
+        const int first = ((int)blockIdx.x - dw_blocks) * 64, o = first + (int)threadIdx.x;
+        const float v = sum_copies64(bias_part, MT * 16, first, MT * 16, copies, sh);
+        if (threadIdx.x < 64 && o < c_out) db[o] = v;
         return;
     }
-    const int e = (int)blockIdx.x * 64 + e64;                   // element of a copy
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    if (e < copy_floats) {
-        const float *src = scratch + e;
-        int cp = w;
-        for (; cp + 12 < copies; cp += 16) {
-            s0 += src[(long)(cp + 0) * copy_floats];
-            s1 += src[(long)(cp + 4) * copy_floats];
-            s2 += src[(long)(cp + 8) * copy_floats];
-            s3 += src[(long)(cp + 12) * copy_floats];
-        }
-        for (; cp < copies; cp += 4) s0 += src[(long)cp * copy_floats];
-    }
-    sh[w][e64] = (s0 + s1) + (s2 + s3);
-    __syncthreads();
-    if (w == 0 && e < copy_floats) {
+    const int e = (int)blockIdx.x * 64 + (int)threadIdx.x;      // element of a copy (threads 0 .. 63)
+    const float v = sum_copies64(scratch, copy_floats, (int)blockIdx.x * 64, copy_floats, copies, sh);
+    if (threadIdx.x < 64 && e < copy_floats) {
         // e = ((((j * NCT + ct) * 4 + i) * MT + m) * 64 + lane) * 4 + r4, lane = 16 g + l16: map o = 16 m + 4 g + r4, input map c = 16 ct + l16
         const int r4 = e & 3, ln = (e >> 2) & 63;
         int rest = e >> 8;
@@ -391,7 +374,7 @@ __global__ void __launch_bounds__(256) wgrad_rows_reduce_kernel(const float *__r
         rest >>= 2;
         const int ct = rest % NCT, j = rest / NCT;
         const int o = 16 * m + 4 * (ln >> 4) + r4, c = 16 * ct + (ln & 15);
-        if (o < c_out && c < c_in) dw[((long)o * c_in + c) * 16 + i * 4 + j] = (sh[0][e64] + sh[1][e64]) + (sh[2][e64] + sh[3][e64]);
+        if (o < c_out && c < c_in) dw[((long)o * c_in + c) * 16 + i * 4 + j] = v;
     }
 }
 

@@ -102,6 +102,9 @@ def test_fused_head_training_matches_layer_by_layer():
     (16, 33, 3, 1, 7, 9, 0.8),             # 63 pixels; a pair with one tile
     (17, 65, 1, 2, 8, 8, 0.8),             # exactly 64 pixels an image; 5 of 8 hidden tiles; one class
     (32, 128, 4, 1, 5, 13, 0.8),           # 65 pixels, two full map tiles, 8 full hidden tiles
+    (16, 40, 2, 1, 40, 33, 0.8),           # 21 private copies of the sums: 2 rounds of 16, some groups without a second
+    (16, 40, 2, 1, 80, 81, 0.4),           # 102: a batch of four, then single ones
+    (24, 40, 2, 1, 104, 104, 0.2),         # 169: a batch of eight, then single ones
     (48, 193, 2, 3, 91, 97, 0.1),          # 13 hidden tiles, one map in the last; two blocks in some workgroups, images not of whole blocks
     (33, 208, 4, 7, 67, 71, 0.1),          # five octets, 13 full tiles
 ])
