@@ -411,6 +411,10 @@ sk_status sknet_set_weights(sknet_t *net, int32_t conv_idx, const float *w_host,
     std::memcpy(c.w.data(), w_host, sizeof(float) * c.wcount());
     if (b_host) std::memcpy(c.b.data(), b_host, sizeof(float) * c.c_out);
     if (net->planned) {
+        if (!b_host) {   // keep the device's current biases (an SGD step may have changed them)
+            SK_HIP(hipStreamSynchronize(net->last_stream));
+            SK_HIP(hipMemcpy(c.b.data(), c.b_dev, sizeof(float) * c.c_out, hipMemcpyDeviceToHost));
+        }
         SK_TRY(upload_conv(c, net->training, net->last_stream, net->dtype));
         const int L = (int)net->layers.size();
         if (net->fuse_head && conv_idx == net->conv_of_layer[L - 2]) {

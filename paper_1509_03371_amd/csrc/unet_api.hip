@@ -310,20 +310,54 @@ sk_status unet_param_kind(const unet_t *net, int32_t idx, int32_t *kind)
     return SK_OK;
 }
 
+// a parameter's device master (after SGD steps the current one) -> host memory; the caller has waited for the last pass
+static sk_status read_conv(const ConvParams &c, float *w, float *b)
+{
+    if (w) SK_HIP(hipMemcpy(w, c.w_dev, sizeof(float) * c.wcount(), hipMemcpyDeviceToHost));
+    if (b) SK_HIP(hipMemcpy(b, c.b_dev, sizeof(float) * c.c_out, hipMemcpyDeviceToHost));
+    return SK_OK;
+}
+
+static sk_status read_up(const UpParams &u, float *w, float *b)
+{
+    if (w) {
+        std::vector<float> cat((size_t)4 * u.c_out * u.c_in);
+        SK_HIP(hipMemcpy(cat.data(), u.cat.w_dev, sizeof(float) * cat.size(), hipMemcpyDeviceToHost));
+        unstack_taps(cat.data(), u, w);
+    }
+    if (b) SK_HIP(hipMemcpy(b, u.tap[0].b_dev, sizeof(float) * u.c_out, hipMemcpyDeviceToHost));
+    return SK_OK;
+}
+
+// device masters -> host masters
+static sk_status sync_masters(unet_t *net)
+{
+    if (!net->planned || !net->training) return SK_OK;
+    if (net->last_stream) SK_HIP(hipStreamSynchronize(net->last_stream));
+    for (auto &c : net->convs) SK_TRY(read_conv(c, c.w.data(), c.b.data()));
+    for (auto &u : net->ups) SK_TRY(read_up(u, u.w.data(), u.b.data()));
+    return SK_OK;
+}
+
 sk_status unet_set_weights(unet_t *net, int32_t idx, const float *w_host, const float *b_host)
 {
     SK_TRY(check(net));
     if (!w_host || idx < 0 || idx >= (int)net->params.size()) return fail(SK_EINVAL, "unet_set_weights: bad arguments");
     const auto &p = net->params[idx];
+    // without new biases the current ones stay: on a training plan those of the device, which SGD steps have changed
+    const bool keep_b = !b_host && net->planned && net->training;
+    if (keep_b && net->last_stream) SK_HIP(hipStreamSynchronize(net->last_stream));
     if (p.kind == 0) {
         ConvParams &c = net->convs[p.idx];
         std::memcpy(c.w.data(), w_host, sizeof(float) * c.wcount());
         if (b_host) std::memcpy(c.b.data(), b_host, sizeof(float) * c.c_out);
+        if (keep_b) SK_TRY(read_conv(c, nullptr, c.b.data()));
         if (net->planned) SK_TRY(upload_conv(c, net->training, net->last_stream, net->dtype));
     } else {
         UpParams &u = net->ups[p.idx];
         std::memcpy(u.w.data(), w_host, sizeof(float) * u.w.size());
         if (b_host) std::memcpy(u.b.data(), b_host, sizeof(float) * u.c_out);
+        if (keep_b) SK_TRY(read_up(u, nullptr, u.b.data()));
         if (net->planned) SK_TRY(upload_up(u, net->dtype));
     }
     return SK_OK;
@@ -335,8 +369,6 @@ sk_status unet_output_size(const unet_t *net, int32_t h_in, int32_t w_in, int32_
     if (!h_out || !w_out) return fail(SK_EINVAL, "unet_output_size: null output");
     return walk_sizes(net, h_in, w_in, h_out, w_out);
 }
-
-static sk_status sync_masters(unet_t *net);
 
 static sk_status plan_impl(unet_t *net, int32_t n, int32_t h_in, int32_t w_in, bool training)
 {
@@ -861,35 +893,6 @@ sk_status unet_get_grad(unet_t *net, int32_t idx, float *dw_host, float *db_host
     if (db_host)
         for (int o2 = 0; o2 < u.c_out; ++o2)
             db_host[o2] = (db[o2] + db[u.c_out + o2]) + (db[2 * u.c_out + o2] + db[3 * u.c_out + o2]);
-    return SK_OK;
-}
-
-// a parameter's device master (after SGD steps the current one) -> host memory; the caller has waited for the last pass
-static sk_status read_conv(const ConvParams &c, float *w, float *b)
-{
-    if (w) SK_HIP(hipMemcpy(w, c.w_dev, sizeof(float) * c.wcount(), hipMemcpyDeviceToHost));
-    if (b) SK_HIP(hipMemcpy(b, c.b_dev, sizeof(float) * c.c_out, hipMemcpyDeviceToHost));
-    return SK_OK;
-}
-
-static sk_status read_up(const UpParams &u, float *w, float *b)
-{
-    if (w) {
-        std::vector<float> cat((size_t)4 * u.c_out * u.c_in);
-        SK_HIP(hipMemcpy(cat.data(), u.cat.w_dev, sizeof(float) * cat.size(), hipMemcpyDeviceToHost));
-        unstack_taps(cat.data(), u, w);
-    }
-    if (b) SK_HIP(hipMemcpy(b, u.tap[0].b_dev, sizeof(float) * u.c_out, hipMemcpyDeviceToHost));
-    return SK_OK;
-}
-
-// device masters -> host masters
-static sk_status sync_masters(unet_t *net)
-{
-    if (!net->planned || !net->training) return SK_OK;
-    if (net->last_stream) SK_HIP(hipStreamSynchronize(net->last_stream));
-    for (auto &c : net->convs) SK_TRY(read_conv(c, c.w.data(), c.b.data()));
-    for (auto &u : net->ups) SK_TRY(read_up(u, u.w.data(), u.b.data()));
     return SK_OK;
 }
 
