@@ -382,6 +382,13 @@ sk_status sknet3d_get_pool_argmax(sknet3d_t *net, int32_t pool_idx, int32_t *idx
 sk_status sk_probe_mfma(int32_t dtype, int32_t operands, int32_t iters, void *hip_stream, double *tflops);
 sk_status sk_probe_copy(const void *src_dev, void *dst_dev, uint64_t bytes, int32_t reps, void *hip_stream,
                         double *gb_per_s);
+/* sk_probe_conv_path: which kernel a 16-bit convolution of these sizes runs on; host arithmetic only, nothing is launched.
+ *   One image group of n images, h_out x w_out output samples a map.  flags: 1 = a data gradient (maps_in = the gradient's maps,
+ *   the samples around the map are zeros), 2 = fp32 output planes (a net's last layer), 4 = with the U-Net plans' scratch for
+ *   split input maps.  path4 (HOST) receives kernel, tile shape, split, loads: kernel 0 = the kernels for few maps, 1 = many maps
+ *   at 1x1 / 3x3, 2 = many maps at 5x5 to 10x10; the others are 0, 1, 0 for kernel 0.  SK_EUNSUPPORTED: no kernel takes it. */
+sk_status sk_probe_conv_path(int32_t k, int32_t d, int32_t maps_in, int32_t maps_out, int32_t n, int32_t h_out, int32_t w_out,
+                             int32_t flags, int32_t *path4);
 
 #ifdef __cplusplus
 }

@@ -95,6 +95,7 @@ _SIGS = {
     "sknet3d_get_pool_argmax": [_vp, _i32, _ip],
     "sk_probe_mfma": [_i32, _i32, _i32, _vp, C.POINTER(C.c_double)],
     "sk_probe_copy": [_vp, _vp, C.c_uint64, _i32, _vp, C.POINTER(C.c_double)],
+    "sk_probe_conv_path": [_i32] * 8 + [_ip],
 }
 for _name, _args in _SIGS.items():
     _f = getattr(lib, _name)
@@ -166,6 +167,14 @@ def sk_probe_copy(src, dst, reps=10, stream=None):
     out = C.c_double(0.0)
     _check(lib.sk_probe_copy(C.c_void_p(src.data_ptr()), C.c_void_p(dst.data_ptr()), nbytes, reps, _stream(stream), C.byref(out)))
     return out.value
+
+
+def sk_probe_conv_path(k, d, maps_in, maps_out, n, h_out, w_out, data_gradient=False, planes=False, scratch=False):
+    """(kernel, tile shape, split, loads) of a 16-bit convolution; host arithmetic, nothing runs."""
+    out = (C.c_int32 * 4)()
+    flags = (1 if data_gradient else 0) | (2 if planes else 0) | (4 if scratch else 0)
+    _check(lib.sk_probe_conv_path(k, d, maps_in, maps_out, n, h_out, w_out, flags, out))
+    return tuple(out)
 
 
 def sknet_conv_flops(f_in, f_out, k, w_out):

@@ -3,6 +3,7 @@
 // direct global -> LDS loads, waits, and the epilogue.
 #include "sk_kernels.h"
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 

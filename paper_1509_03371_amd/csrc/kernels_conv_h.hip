@@ -1383,7 +1383,9 @@ bool conv_h_supported(int k, int d)
 }
 
 // ... and the two-stage tile of the register-staged kernel (what every shape can fall back to) fits
-// the LDS for a GEMM with gemm_m output maps: a 3x3 kernel with 48 maps or more stops at d = 6
+// the LDS for a GEMM with gemm_m output maps: a 3x3 kernel with 48 maps or more stops at d = 6.
+// Weights packed for the kernels of many maps cannot fall back: conv_h_wide takes only layers whose
+// smallest tile there fits wherever this one does
 bool conv_h_supported(int k, int d, int gemm_m)
 {
     if (!conv_h_supported(k, d) || gemm_m < 1) return false;
@@ -1563,6 +1565,12 @@ bool conv_h_reads_image(const ConvHArgs &a)
 {
     if (a.img || (a.dtype != 1 && a.dtype != 2) || !conv_h_supported(a.k, a.d)) return false;
     return conv_c1_h_applies(a, a.mt > 0 ? a.mt : conv_h_mt(a.c_out, a.k));
+}
+
+ConvHPath conv_h_path(const ConvHArgs &a)
+{
+    if (a.mt <= 0 && conv_h_wide(a.c_out, a.c8_in, a.k)) return a.k > 4 ? conv_wide_big_path(a) : conv_wide_path(a);
+    return {0, 0, 1, 0};
 }
 
 hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream)

@@ -33,7 +33,6 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
     constexpr int KR = big_rows<KS>(), RP = KS / KR, CS = (KS + 3) / 4, NS = CS * RP;    // rows of a step, steps of a chunk
     constexpr int SLAB = KR * 4;                               // 1 KB weight fragments of a step
     constexpr int NW = (SLAB + 7) / 8;                         // weight loads of a wave per step
-    constexpr int XS = (NX + NS - 2) / (NS - 1);               // input loads of a wave per step but the last
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, g = lane >> 4;
     const int wm = wave / T::PWV, pwv = wave % T::PWV;
@@ -126,7 +125,7 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
     const uint4v *const wfrag = wbuf + wm * WM * 64 + lane;
     // One step; its N loads for later steps go between the MFMAs.
     auto step = [&](bool act, int buf, int s, int sl, auto loads, auto &&load) {
-        constexpr int N = decltype(loads)::value, GROUPS = KR * R, SPREAD = N > 0 ? GROUPS / N : 1;
+        constexpr int N = decltype(loads)::value, GROUPS = KR * R, SPREAD = N > 0 ? GROUPS / std::max(N, 1) : 1;
         static_assert(N <= GROUPS, "one load per group of MFMAs at most");
         if (!act) {
 #pragma unroll
@@ -276,6 +275,16 @@ size_t big_smem(const WideGeom &w)
     return (size_t)2 * w.oct_units * 16 + (size_t)3 * big_rows<KS>() * 4096 + (size_t)w.pgroups * 64 * sizeof(float);
 }
 
+// (the biases of all maps share the LDS with the tile: see conv_h_wide)
+template <int KS>
+bool big_fits(const WideGeom &w)
+{
+    return w.tiles >= 1 && w.oct_units / 64 <= 48 && big_smem<KS>(w) <= 160 * 1024;
+}
+
+// input loads of a wave per chunk
+int big_loads(const WideGeom &w) { return w.oct_units / 64 <= 16 ? 2 : w.oct_units / 64 <= 32 ? 4 : 6; }
+
 template <int DT, int KS, int XW, int NX, bool PAD, int OUT>
 hipError_t launch_big_n(const WideArgs &k, size_t smem, hipStream_t stream)
 {
@@ -299,25 +308,41 @@ hipError_t launch_big_x(const ConvHArgs &a, hipStream_t stream)
     k.a = a;
     k.w = big_geom<KS, XW>(a);
     const size_t smem = big_smem<KS>(k.w);
-    const int blks = k.w.oct_units / 64;
-    if (k.w.tiles < 1 || blks > 48 || smem > 160 * 1024 || !a.zeros) return hipErrorInvalidValue;
+    if (!big_fits<KS>(k.w) || !a.zeros) return hipErrorInvalidValue;
     if ((long)a.H * a.W * 16 >= 0xffffffffL || (long)(a.out_f32 ? a.c_out * 4L : a.c8_out_total * 16L) * a.OH * a.OW >= 0x7fffffffL) return hipErrorInvalidValue;
-    if (blks <= 16) return launch_big_n<DT, KS, XW, 2, PAD, OUT>(k, smem, stream);
-    if (blks <= 32) return launch_big_n<DT, KS, XW, 4, PAD, OUT>(k, smem, stream);
-    return launch_big_n<DT, KS, XW, 6, PAD, OUT>(k, smem, stream);
+    switch (big_loads(k.w)) {
+    case 2: return launch_big_n<DT, KS, XW, 2, PAD, OUT>(k, smem, stream);
+    case 4: return launch_big_n<DT, KS, XW, 4, PAD, OUT>(k, smem, stream);
+    default: return launch_big_n<DT, KS, XW, 6, PAD, OUT>(k, smem, stream);
+    }
+}
+
+// 16-column groups across a tile: 2 (32 x 16 output pixels) or 4 (64 x 8, which fits every kernel stride), the shape with fewer
+// rounds of one tile per CU
+template <int KS>
+int big_columns(const ConvHArgs &a)
+{
+    if (a.out_f32) return 4;
+    const WideGeom sq = big_geom<KS, 2>(a), flat = big_geom<KS, 4>(a);
+    const int cus = wide_cus();
+    return big_fits<KS>(sq) && (sq.tiles + cus - 1) / cus <= (flat.tiles + cus - 1) / cus ? 2 : 4;
 }
 
 template <int DT, int KS>
 hipError_t launch_big_k(const ConvHArgs &a, hipStream_t stream)
 {
     if (a.out_f32) return a.in_off ? hipErrorInvalidValue : launch_big_x<DT, KS, 4, false, WV_F32>(a, stream);
-    // 32 x 16 or 64 x 8 output pixels (the latter fits every kernel stride): the shape with fewer rounds of one tile per CU
-    const WideGeom sq = big_geom<KS, 2>(a), flat = big_geom<KS, 4>(a);
-    const int cus = wide_cus();
-    const bool sq_fits = sq.oct_units / 64 <= 48 && big_smem<KS>(sq) <= 160 * 1024;
-    if (sq_fits && (sq.tiles + cus - 1) / cus <= (flat.tiles + cus - 1) / cus)
+    if (big_columns<KS>(a) == 2)
         return a.in_off ? launch_big_x<DT, KS, 2, true, WV_OCT>(a, stream) : launch_big_x<DT, KS, 2, false, WV_OCT>(a, stream);
     return a.in_off ? launch_big_x<DT, KS, 4, true, WV_OCT>(a, stream) : launch_big_x<DT, KS, 4, false, WV_OCT>(a, stream);
+}
+
+template <int KS>
+ConvHPath big_path(const ConvHArgs &a)
+{
+    const int columns = big_columns<KS>(a);
+    const WideGeom w = columns == 2 ? big_geom<KS, 2>(a) : big_geom<KS, 4>(a);
+    return {big_fits<KS>(w) ? 2 : -1, columns, 1, big_loads(w)};
 }
 
 template <int DT>
@@ -333,6 +358,16 @@ hipError_t launch_big_dt(const ConvHArgs &a, hipStream_t stream)
 }
 
 }  // namespace
+
+ConvHPath conv_wide_big_path(const ConvHArgs &a)
+{
+    switch (a.k) {
+    case 5: return big_path<5>(a);
+    case 6: return big_path<6>(a);
+    case 8: return big_path<8>(a);
+    default: return big_path<10>(a);
+    }
+}
 
 hipError_t launch_conv_wide_big_h(const ConvHArgs &a, hipStream_t stream)
 {

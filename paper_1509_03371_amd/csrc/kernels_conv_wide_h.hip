@@ -170,7 +170,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
     const uint4v *const xfrag = xbuf + g * oct_units + l16 + xrow, *const wfrag = wbuf + wm * KS * 4 * 64 + lane;
     const int pitch = KS == 1 ? 16 : pw, dil = KS == 1 ? 0 : k.a.d, buf_units = 4 * oct_units;
     auto step = [&](bool act, int buf, int cs, int sl, auto loads, auto &&load) {
-        constexpr int N = decltype(loads)::value, GROUPS = KS * R, SPREAD = N > 0 && GROUPS > N ? GROUPS / N : 1;
+        constexpr int N = decltype(loads)::value, GROUPS = KS * R, SPREAD = N > 0 && GROUPS > N ? GROUPS / std::max(N, 1) : 1;
         if (!act) {                                            // a wave without pixels or maps in the tile only loads
 #pragma unroll
             for (int q = 0; q < N; ++q) load(q);
@@ -459,6 +459,23 @@ size_t wide_smem(const WideGeom &w)
     return x + wt + (w.split > 1 ? 0 : (size_t)w.pgroups * 64 * sizeof(float));
 }
 
+template <int NWV, int KS, int MG, int S>
+bool wide_fits(const WideGeom &w)
+{
+    return w.tiles >= 1 && w.oct_units <= 64 * (NWV / 4) * WV_XQ && wide_smem<KS, MG, S>(w) <= 160 * 1024;
+}
+
+// Input loads of a wave per chunk, 3x3: exact for the tile of kernel stride 1 (LEAST), one more up to about stride 4, the most for
+// wider ones
+template <class T, int LPO> struct WideLoads {
+    static constexpr int LEAST = (((T::RT + 2) * (T::TX + 2) + 63) / 64 + LPO - 1) / LPO, MORE = LEAST + 1 < WV_XQ ? LEAST + 1 : WV_XQ;
+    static int of(const WideGeom &w)
+    {
+        const int nx = ((w.oct_units + 63) / 64 + LPO - 1) / LPO;
+        return nx <= LEAST ? LEAST : nx <= MORE ? MORE : WV_XQ;
+    }
+};
+
 template <int DT, int NWV, int KS, int MG, int R, int XW, int NX, bool PAD, int OUT, int S>
 hipError_t launch_wide_n(const WideArgs &k, size_t smem, hipStream_t stream)
 {
@@ -493,7 +510,7 @@ hipError_t launch_wide_m(const ConvHArgs &a, int split, hipStream_t stream)
     w.split = split;
     w.ws = a.ws;
     const size_t smem = wide_smem<KS, MG, S>(w);
-    if (w.tiles < 1 || w.oct_units > 64 * LPO * WV_XQ || smem > 160 * 1024 || !a.zeros) return hipErrorInvalidValue;
+    if (!wide_fits<NWV, KS, MG, S>(w) || !a.zeros) return hipErrorInvalidValue;
     // (sample offsets inside an octet plane are 32-bit)
     if ((long)a.H * a.W * 16 >= 0xffffffffL || (long)(a.out_f32 ? a.c_out * 4L : a.c8_out_total * 16L) * a.OH * a.OW >= 0x7fffffffL) return hipErrorInvalidValue;
     if ((long)w.tiles * split > 0x3fffffffL) return hipErrorInvalidValue;
@@ -501,16 +518,15 @@ hipError_t launch_wide_m(const ConvHArgs &a, int split, hipStream_t stream)
     if constexpr (KS == 1) {
         return launch_wide_n<DT, NWV, 1, MG, R, XW, T::TX / (64 * LPO), false, OUT, S>(k, smem, stream);
     } else {
-        // loads of a wave per chunk: exact for the tile of kernel stride 1, one more up to about stride 4, the most for wider ones
-        constexpr int NX1 = (((T::RT + 2) * (T::TX + 2) + 63) / 64 + LPO - 1) / LPO, NX2 = NX1 + 1 < WV_XQ ? NX1 + 1 : WV_XQ;
-        const int nx = ((w.oct_units + 63) / 64 + LPO - 1) / LPO;
+        using L = WideLoads<T, LPO>;
+        const int nx = L::of(w);
         if (a.in_off) {
-            if (nx <= NX1) return launch_wide_n<DT, NWV, 3, MG, R, XW, NX1, true, OUT, S>(k, smem, stream);
-            if (nx <= NX2) return launch_wide_n<DT, NWV, 3, MG, R, XW, NX2, true, OUT, S>(k, smem, stream);
+            if (nx == L::LEAST) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::LEAST, true, OUT, S>(k, smem, stream);
+            if (nx == L::MORE) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::MORE, true, OUT, S>(k, smem, stream);
             return launch_wide_n<DT, NWV, 3, MG, R, XW, WV_XQ, true, OUT, S>(k, smem, stream);
         }
-        if (nx <= NX1) return launch_wide_n<DT, NWV, 3, MG, R, XW, NX1, false, OUT, S>(k, smem, stream);
-        if (nx <= NX2) return launch_wide_n<DT, NWV, 3, MG, R, XW, NX2, false, OUT, S>(k, smem, stream);
+        if (nx == L::LEAST) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::LEAST, false, OUT, S>(k, smem, stream);
+        if (nx == L::MORE) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::MORE, false, OUT, S>(k, smem, stream);
         return launch_wide_n<DT, NWV, 3, MG, R, XW, WV_XQ, false, OUT, S>(k, smem, stream);
     }
 }
@@ -533,7 +549,7 @@ double wide_cost(const ConvHArgs &a, int split, const WideFit &f)
     using T = WideTile<NWV, KS, MG, R, XW>;
     WideGeom w = wide_geom<NWV, KS, MG, R, XW>(a);
     w.split = split;
-    if (w.tiles < 1 || split > w.nchunks || w.oct_units > 64 * (NWV / 4) * WV_XQ || wide_smem<KS, MG, S>(w) > 160 * 1024) return 1e30;
+    if (split > w.nchunks || !wide_fits<NWV, KS, MG, S>(w)) return 1e30;
     const double items = (double)w.tiles * split;
     if (split > 1 && (!a.ws || items * T::FLOATS > (double)a.ws_floats)) return 1e30;
     const int cus = wide_cus(), steps = KS * ((w.nchunks + split - 1) / split);
@@ -542,24 +558,22 @@ double wide_cost(const ConvHArgs &a, int split, const WideFit &f)
     return t + (split > 1 ? 5 + items * T::FLOATS * 8 / 8e6 : 0);
 }
 
-template <int DT>
-hipError_t launch_wide_dt(const ConvHArgs &a, hipStream_t stream)
+struct WidePick {
+    int shape, split;
+};
+WidePick wide_pick(const ConvHArgs &a)
 {
-    if (a.out_f32) {                      // class planes: not where the time goes, one shape that fits every kernel stride
-        if (a.mask) return hipErrorInvalidValue;
-        return a.k == 3 ? launch_wide_m<DT, 8, 3, 1, 2, 2, WV_F32, 3>(a, 1, stream) : launch_wide_m<DT, 8, 1, 2, 2, 1, WV_F32, 4>(a, 1, stream);
-    }
+    if (a.out_f32) return {0, 1};         // class planes: not where the time goes, one shape that fits every kernel stride
     // The shape and split with the least estimated time.  Which one that is turns on how the tiles fill the CUs: measured (us,
     // with the launch's own 5 to 8), 3x3 with 64 x 8 rows x 32 / 16 x 32 / 12 x 64 pixels --  64 -> 64 at 570^2: 38.6 / 38.6 / 37.0;
     // 256 -> 256 at 138^2: 38.3 / 31.3 / 39.4; 512 -> 256 at 104^2: 36.0 / 51.8 / 67.7; 1024 -> 1024 at 30^2: 61.9 / 95.4 /
     // 122.3, split in four, eight, eight 32.4 / 35.2 / 40.
     double best = 1e30;
-    int shape = -1, split = 1;
+    WidePick pick{-1, 1};
     auto take = [&](int s, int sp, double cost) {
         if (cost < best) {
             best = cost;
-            shape = s;
-            split = sp;
+            pick = {s, sp};
         }
     };
     const int splits[] = {1, 2, 3, 4, 6, 8};
@@ -575,14 +589,26 @@ hipError_t launch_wide_dt(const ConvHArgs &a, hipStream_t stream)
             take(3, sp, wide_cost<4, 1, 1, 4, 1, 3>(a, sp, {0.45, 2.7, 0.50, 3.0}));
         }
     }
+    return pick;
+}
+
+template <int DT>
+hipError_t launch_wide_dt(const ConvHArgs &a, hipStream_t stream)
+{
+    if (a.out_f32) {
+        if (a.mask) return hipErrorInvalidValue;
+        return a.k == 3 ? launch_wide_m<DT, 8, 3, 1, 2, 2, WV_F32, 3>(a, 1, stream) : launch_wide_m<DT, 8, 1, 2, 2, 1, WV_F32, 4>(a, 1, stream);
+    }
+    const WidePick pick = wide_pick(a);
+    const int split = pick.split;
     if (a.k == 3) {
-        switch (shape) {
+        switch (pick.shape) {
         case 0: return launch_wide<DT, 8, 3, 1, 2, 2, 3>(a, split, stream);
         case 1: return launch_wide<DT, 8, 3, 1, 4, 2, 3>(a, split, stream);
         case 2: return launch_wide<DT, 8, 3, 1, 6, 4, 3>(a, split, stream);
         }
     } else {
-        switch (shape) {
+        switch (pick.shape) {
         case 0: return launch_wide<DT, 8, 1, 2, 2, 1, 4>(a, split, stream);
         case 1: return launch_wide<DT, 4, 1, 2, 4, 1, 4>(a, split, stream);
         case 2: return launch_wide<DT, 4, 1, 2, 8, 1, 3>(a, split, stream);
@@ -592,12 +618,43 @@ hipError_t launch_wide_dt(const ConvHArgs &a, hipStream_t stream)
     return hipErrorInvalidValue;
 }
 
+template <int NWV, int KS, int MG, int R, int XW, int S>
+ConvHPath wide_path(const ConvHArgs &a, const WidePick &p)
+{
+    using T = WideTile<NWV, KS, MG, R, XW>;
+    const WideGeom w = wide_geom<NWV, KS, MG, R, XW>(a);
+    const int loads = KS == 1 ? T::TX / (64 * (NWV / 4)) : WideLoads<T, NWV / 4>::of(w);
+    return {wide_fits<NWV, KS, MG, S>(w) ? 1 : -1, p.shape, p.split, loads};
+}
+
 }  // namespace
 
-// At least 64 output maps with at most a fifth of the packed ones empty, and 32 input maps
+ConvHPath conv_wide_path(const ConvHArgs &a)
+{
+    const WidePick p = wide_pick(a);
+    if (a.k == 3) {
+        switch (p.shape) {
+        case 0: return wide_path<8, 3, 1, 2, 2, 3>(a, p);
+        case 1: return wide_path<8, 3, 1, 4, 2, 3>(a, p);
+        case 2: return wide_path<8, 3, 1, 6, 4, 3>(a, p);
+        }
+    } else {
+        switch (p.shape) {
+        case 0: return wide_path<8, 1, 2, 2, 1, 4>(a, p);
+        case 1: return wide_path<4, 1, 2, 4, 1, 4>(a, p);
+        case 2: return wide_path<4, 1, 2, 8, 1, 3>(a, p);
+        case 3: return wide_path<4, 1, 1, 4, 1, 3>(a, p);
+        }
+    }
+    return {-1, 0, 1, 0};
+}
+
+// At least 64 output maps with at most a fifth of the packed ones empty, and 32 input maps.  The biases of all maps lie in the LDS
+// beside the tile: at 5x5, whose tile is the largest there, layers of more than 7168 maps stay on conv_h_kernel (at the widest
+// kernel stride it takes, 18, they would not fit; the other kernel sizes fit wherever conv_h_kernel does).
 bool conv_h_wide(int gemm_m, int gemm_c8, int k)
 {
-    if ((k != 1 && k != 3 && k != 5 && k != 6 && k != 8 && k != 10) || gemm_c8 < 4) return false;
+    if ((k != 1 && k != 3 && k != 5 && k != 6 && k != 8 && k != 10) || gemm_c8 < 4 || (k == 5 && gemm_m > 7168)) return false;
     const int m_tiles = (gemm_m + 15) / 16, pad = (m_tiles + 3) / 4 * 4 - m_tiles;
     return m_tiles >= 4 && 4 * pad <= m_tiles;
 }

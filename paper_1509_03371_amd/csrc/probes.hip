@@ -172,4 +172,25 @@ sk_status sk_probe_copy(const void *src_dev, void *dst_dev, uint64_t bytes, int3
     return SK_OK;
 }
 
+sk_status sk_probe_conv_path(int32_t k, int32_t d, int32_t maps_in, int32_t maps_out, int32_t n, int32_t h_out, int32_t w_out,
+                             int32_t flags, int32_t *path4)
+{
+    if (!path4 || k < 1 || d < 1 || maps_in < 1 || maps_out < 1 || n < 1 || h_out < 1 || w_out < 1 || (flags & ~7))
+        return fail(SK_EINVAL, "probe_conv_path: bad arguments");
+    if (!sk::conv_h_supported(k, d, maps_out))
+        return fail(SK_EUNSUPPORTED, "probe_conv_path: a 16-bit %dx%d convolution at d = %d to %d maps is not built", k, k, d, maps_out);
+    sk::ConvHArgs a{};
+    float scratch = 0.f;                       // stands for a plan's scratch: nothing reads it
+    const int halo = (k - 1) * d, grad = flags & 1;
+    a.n = n; a.k = k; a.d = d; a.c8_in = (maps_in + 7) / 8; a.c_out = maps_out; a.c8_out = a.c8_out_total = (maps_out + 7) / 8;
+    a.Ho = a.OH = h_out; a.Wo = a.OW = w_out;
+    a.in_off = grad ? halo : 0; a.H = grad ? h_out - halo : h_out + halo; a.W = grad ? w_out - halo : w_out + halo;
+    a.out_f32 = flags & 2 ? 1 : 0;
+    if (flags & 4) { a.ws = &scratch; a.ws_floats = sk::CONV_H_WS_FLOATS; }
+    const sk::ConvHPath p = sk::conv_h_path(a);
+    if (p.kernel < 0) return fail(SK_EUNSUPPORTED, "probe_conv_path: no kernel takes a %dx%d convolution at d = %d to %d maps", k, k, d, maps_out);
+    path4[0] = p.kernel; path4[1] = p.shape; path4[2] = p.split; path4[3] = p.loads;
+    return SK_OK;
+}
+
 }  // extern "C"

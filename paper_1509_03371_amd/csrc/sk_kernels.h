@@ -130,6 +130,15 @@ hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream);
 // layers with many maps (1x1, 3x3: kernels_conv_wide_h.hip; 5x5, 6x6, 8x8, 10x10: kernels_conv_wide_big_h.hip): decided by what the weight packing knows too, so that weights
 // packed with mt = 0 are always packed for the kernel that reads them (four map tiles per group there)
 bool conv_h_wide(int gemm_m, int gemm_c8, int k);
+// Which kernel a launch runs on: 1 = kernels_conv_wide_h.hip, 2 = kernels_conv_wide_big_h.hip, 0 = another one, -1 = none takes it;
+// for the first two the tile shape (1x1, 3x3: its number in the dispatch; larger: 16-column groups across a tile), over how many
+// workgroups the input maps are split, and the input loads of a wave per chunk
+struct ConvHPath {
+    int kernel, shape, split, loads;
+};
+ConvHPath conv_h_path(const ConvHArgs &a);
+ConvHPath conv_wide_path(const ConvHArgs &a);
+ConvHPath conv_wide_big_path(const ConvHArgs &a);
 hipError_t launch_conv_wide_h(const ConvHArgs &a, hipStream_t stream);
 hipError_t launch_conv_wide_big_h(const ConvHArgs &a, hipStream_t stream);
 constexpr long CONV_H_WS_FLOATS = 8L << 20;       // ConvHArgs.ws: 32 MB hold the partial sums of 512 tiles of 64 maps x 256 pixels

@@ -36,6 +36,8 @@ def rounded(a, dtype):
     # (10x10 at 10, 8x8 at 18) and more tiles than CUs where that is fewer rounds
     (5, 1, 40, 70, 2, 37, 41), (6, 1, 33, 112, 1, 22, 39), (6, 3, 64, 64, 1, 49, 50), (8, 8, 40, 64, 2, 93, 90), (10, 8, 64, 64, 1, 107, 130),
     (10, 10, 32, 64, 1, 100, 122), (8, 18, 40, 64, 1, 130, 149), (5, 2, 32, 512, 1, 72, 136),
+    # more maps than the LDS holds biases for at this kernel stride: conv_h_kernel
+    (5, 18, 32, 7184, 1, 75, 81),
 ])
 def test_layer(dtype, k, d, c_in, c_out, n, h, w):
     from paper_1509_03371_amd import binding as B

@@ -183,3 +183,21 @@ def test_sknet3d_handle_host_logic():
         down.context()
     assert e.value.status_name == "SK_ESHAPE"
     down.close()
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8, 10])
+def test_accepted_16_bit_layers_have_a_kernel(k):
+    # whatever a plan accepts ("not built" is what it refuses) some kernel takes: the tile with the biases of all maps fits the LDS
+    # at every kernel stride, in every form a plan launches (octets or fp32 planes, forward or data gradient, with or without scratch)
+    accepted = 0
+    for d in range(1, 72):
+        for maps in list(range(16, 513, 16)) + list(range(1024, 25000, 509)) + [7168, 7169, 7184, 12289, 13313]:
+            for form in ({}, {"planes": True}, {"data_gradient": True}, {"scratch": True}):
+                try:
+                    B.sk_probe_conv_path(k, d, 32, maps, 1, 300, 300, **form)
+                    accepted += 1
+                except B.SknetError as e:
+                    assert "is not built" in str(e), (d, maps, form)
+    assert accepted > 400
+    layer = S.conv(7184, 5, 18, relu=False)
+    B.SKNet([layer], 32, 7184, dtype="bf16").close()
