@@ -594,8 +594,9 @@ static hipError_t launch_conv_f32_nt(const ConvF32Args &a, hipStream_t stream)
         return launch_conv_f32_pf_t<NT, 1, 4, 4, 2>(a, stream);
     }
     // 5x5 (the tiny net's second layer, 8 -> 16 maps at d = 2 on 96x96: 33 us on the generic kernel, whose chunk waits for its
-    // loads; 4-row tiles because such layers are small)
-    if (a.k == 5 && halo <= 64) return launch_conv_f32_pf_t<NT, 1, 5, 4, 2>(a, stream);
+    // loads; 4-row tiles because such layers are small).  Maps and weight slabs beyond the 32-bit byte offsets of that kernel
+    // stay on the generic one.
+    if (a.k == 5 && halo <= 64 && (long)a.H * a.W < (1L << 29) && 100L * a.n_pad < (1L << 29)) return launch_conv_f32_pf_t<NT, 1, 5, 4, 2>(a, stream);
     // the large kernels of the USK-Net (6x6 at d = 1, 8x8 at d = 8) and of the paper's SK-Net (10x10 at
     // d = 8, a 73-pixel window: three column groups, forward only); one chunk of four maps holds
     // 4*k*k K values and its weight slab fills most of the LDS, so one workgroup per CU

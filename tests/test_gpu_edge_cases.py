@@ -67,3 +67,25 @@ def test_image_too_small_for_reflect_padding_is_rejected():
     with pytest.raises(B.SknetError):
         net.plan(1, 60, 60, pad=False)         # unpadded: the map vanishes
     net.close()
+
+
+def test_fp32_5x5_map_of_more_than_2_to_the_29_samples():
+    # byte offsets inside such a map leave 32 bits: the layer runs on the generic kernel.  fp32 sums of 25 products, softmax
+    # of two logits below 8: 1e-5
+    from paper_1509_03371_amd import binding as B
+    side = 23171
+    assert side * side >= 2 ** 29
+    rng = np.random.default_rng(46)
+    w, b = (rng.standard_normal((2, 1, 5, 5)) * 0.5).astype(np.float32), rng.standard_normal(2).astype(np.float32)
+    net = B.SKNet([S.conv(2, 5, 1, relu=False)], 1, 2)
+    net.set_weights(0, w, b)
+    net.plan(1, side, side, pad=False)
+    img = torch.rand((1, 1, side, side), generator=torch.Generator("cuda").manual_seed(47), device="cuda")
+    prob = net.forward(img)
+    out = side - 4
+    assert tuple(prob.shape) == (1, 2, out, out)
+    for y, x in ((0, 0), (0, out - 40), (out - 40, 0), (out - 40, out - 40), (out // 2, out // 3), (17000, 22001)):
+        ref = torch.nn.functional.conv2d(img[:, :, y:y + 44, x:x + 44].cpu().double(), torch.from_numpy(w).double(), torch.from_numpy(b).double())
+        got = prob[:, :, y:y + 40, x:x + 40].cpu().double()
+        assert (got - ref.softmax(1)).abs().max() <= 1e-5, (y, x)
+    net.close()
