@@ -1167,20 +1167,27 @@ static hipError_t launch_conv_h_t(const ConvHArgs &a, hipStream_t stream)
     return launch_conv_h_m<DT, KS, MT, MAP4, R, false, VU>(a, stream);
 }
 
+// does the 64 x 8 pixel tile of launch_conv_h_big exist for this kernel and fit the LDS?
+static bool conv_h_big_square(int k, int mt, int d, int c_out)
+{
+    if (k != 6 && k != 8 && k != 10) return false;
+    const int cs = (k + 3) / 4, pw = 64 + (4 * cs - 1) * d;
+    const size_t stage = (size_t)(8 + k - 1) * pw + (size_t)cs * k * mt * 64;
+    return pw <= 192 && 2 * stage * 16 + (size_t)(((c_out + 15) / 16 + mt - 1) / mt * mt) * 64 <= 160 * 1024;
+}
+
 // kernels larger than 4x4: the register-staged kernel with the lane groups on four consecutive kernel columns, four
 // output rows per tile, forward only; tiles wider than 192 units (10x10 at d = 8) stage a fourth column group per row
 template <int DT, int KS, int MT>
 static hipError_t launch_conv_h_big(const ConvHArgs &a, hipStream_t stream)
 {
     if (a.mask) return hipErrorInvalidValue;
-    constexpr int TAPW = 4 * ((KS + 3) / 4), CS = (KS + 3) / 4;
+    constexpr int TAPW = 4 * ((KS + 3) / 4);
     if constexpr (KS == 6 || KS == 8 || KS == 10) {
         // 64 x 8 pixel tiles where they cover the output in fewer rounds of one tile per CU (see launch_conv_h_t): the
         // k - 1 halo rows weigh less under eight output rows than under four, and ragged maps waste less
         const int pw = 64 + (TAPW - 1) * a.d, cus = device_cus();
-        const size_t stage = (size_t)(8 + KS - 1) * pw + (size_t)CS * KS * MT * 64;
-        const bool fits = pw <= 192 && 2 * stage * 16 + (size_t)(((a.c_out + 15) / 16 + MT - 1) / MT * MT) * 64 <= 160 * 1024;
-        if (fits && (conv_h_tile_count(a, MT, 64, 8) + cus - 1) / cus < (conv_h_tile_count(a, MT, 128, 4) + cus - 1) / cus) {
+        if (conv_h_big_square(KS, MT, a.d, a.c_out) && (conv_h_tile_count(a, MT, 64, 8) + cus - 1) / cus < (conv_h_tile_count(a, MT, 128, 4) + cus - 1) / cus) {
             if (pw <= 128) return launch_conv_h_m<DT, KS, MT, true, 4, false, 2, 4>(a, stream);
             return launch_conv_h_m<DT, KS, MT, true, 4, false, 3, 4>(a, stream);
         }
@@ -1341,7 +1348,7 @@ int conv_h_pick_mode(int c_out, int c_in, int k, int d, int n, int Ho, int Wo)
         const int tiles = (c_out + 15) / 16;
         return ((tiles % 3 == 0 || tiles >= 8) ? 3 : 2) | CONV_H_TAPCOLS;
     }
-    return conv_h_pick_mt(c_out, c_in, k, n, Ho, Wo);
+    return conv_h_pick_mt(c_out, c_in, k, d, n, Ho, Wo);
 }
 
 // output-map tiles (16 maps each) per workgroup: as few padded tiles as possible; a 3x3 kernel's
@@ -1725,13 +1732,41 @@ __global__ void __launch_bounds__(256) pack_weights_h_batch_kernel(PackHJobs b)
     }
 }
 
-// size in 16-bit elements of the packing of a GEMM with gemm_m output maps and gemm_c8 input octets
-// Map tiles per workgroup for a forward layer with this output size (0: the default packing, where
-// kernels_conv_wide_h.hip takes the layer).  Many maps on a small image: with one persistent workgroup per CU a layer wants at least about 160 tiles, and
-// fewer map tiles per workgroup give more of them (each then re-reads the input, so not more than needed).  The weights must be packed for the same value.
-int conv_h_pick_mt(int c_out, int c_in, int k, int n, int Ho, int Wo)
+// Map tiles per workgroup of a layer of this size: 0 = the default packing and kernel, or conv_h_mt() to keep a layer that
+// conv_h_wide would take on conv_h_kernel, whose tiles are smaller (a quarter to three quarters of the maps): one that has not
+// enough large tiles to fill the GPU runs longer on each of them.  The weights must be packed for the same value.
+//
+// k > 4: by rounds of tiles per CU, here and there.  A tile of the kernel for many maps costs 1.25 (5x5, 6x6), 1.6 (8x8) and
+// 2.5 (10x10) of conv_h_kernel's: over 928 layers (32 to 128 -> 64 to 1024 maps, 8^2 to 3 x 300^2, d = 1 to 8, bf16) the kernel
+// for many maps took 0.95 to 2.74 of the time below these lines (10x10 64 -> 64 at 32^2: 79 us of 37, 8x8 at 250^2: 66 of 55)
+// and 0.53 to 1.07 above (10x10 64 -> 256 at 250^2: 184 us of 259).
+// 3x3 to 64 maps from at most 64: up to 64^2 pixels the few large steps are as long as the launch (32 -> 64 at 64^2: 19.5 us
+// of 18.9, at 128^2 20.3 of 21.2), and from one chunk of 32 maps at wide kernel strides most of a 32-column tile is halo
+// (32 -> 64 at d = 12, 3 x 300^2: 65 us of 62; at d = 8 59.9 of 60.3).
+int conv_h_size_mt(int gemm_m, int gemm_c8, int k, int d, int n, int Ho, int Wo)
 {
-    if (conv_h_wide(c_out, (c_in + 7) / 8, k)) return 0;
+    if (!conv_h_wide(gemm_m, gemm_c8, k) || k == 1) return 0;
+    const int mt = conv_h_mt(gemm_m, k);
+    if (k == 3) {
+        const bool few = gemm_c8 <= 8 && (long)n * Ho * Wo <= 64L * 64, halo = gemm_c8 <= 4 && d > 10;
+        return gemm_m <= 64 && (few || halo) ? mt : 0;
+    }
+    ConvHArgs a{};
+    a.n = n; a.k = k; a.d = d; a.c8_in = gemm_c8; a.c_out = gemm_m; a.Ho = Ho; a.Wo = Wo;
+    const long cus = device_cus();
+    auto rounds = [&](int tiles, int tx, int rt) { return (conv_h_tile_count(a, tiles, tx, rt) + cus - 1) / cus; };
+    const long here = conv_h_big_square(k, mt, d, gemm_m) ? std::min(rounds(mt, 128, 4), rounds(mt, 64, 8)) : rounds(mt, 128, 4);
+    const long there = conv_wide_big_path(a).shape == 2 ? rounds(4, 32, 16) : rounds(4, 64, 8);
+    return 100 * here < (k == 10 ? 250 : k == 8 ? 160 : 125) * there ? mt : 0;
+}
+
+// ... for the forward layers of the U-Net and the USK-Net.  Many maps on a small image: with one persistent workgroup per CU
+// a layer of conv_h_kernel wants at least about 160 tiles, and fewer map tiles per workgroup give more of them (each then
+// re-reads the input, so not more than needed).
+int conv_h_pick_mt(int c_out, int c_in, int k, int d, int n, int Ho, int Wo)
+{
+    const int c8 = (c_in + 7) / 8;
+    if (conv_h_wide(c_out, c8, k) && conv_h_size_mt(c_out, c8, k, d, n, Ho, Wo) == 0) return 0;
     int mt = conv_h_mt(c_out, k);
     const long sp = (long)((Wo + CH_TX - 1) / CH_TX) * ((Ho + 3) / 4) * n;   // tiles of 4 rows at least
     const int m_tiles = (c_out + 15) / 16;
@@ -1749,6 +1784,7 @@ static int packed_map4(int gemm_m, int gemm_c8, int k, int mt)
     return (k >= 4 || (mt > 0 && (mt & CONV_H_TAPCOLS))) ? 1 : 0;
 }
 
+// size in 16-bit elements of the packing of a GEMM with gemm_m output maps and gemm_c8 input octets
 long packed_h_elems(int gemm_m, int gemm_c8, int k, int mt)
 {
     const bool tapcols = mt > 0 && (mt & CONV_H_TAPCOLS) != 0;

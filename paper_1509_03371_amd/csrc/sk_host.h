@@ -56,7 +56,7 @@ struct ConvParams {
     float *wp_fwd = nullptr, *wp_bwd = nullptr;       // fp32 packings
     float *wp16_fwd = nullptr, *wp16_bwd = nullptr;   // 16-bit packings (typed loosely; see kernels_conv_h.hip)
     float *dw = nullptr, *db = nullptr, *vw = nullptr, *vb = nullptr;
-    int mt16 = 0;                         // 16-bit forward packing: map tiles per workgroup (0 = default)
+    int mt16 = 0, mt16_bwd = 0;           // 16-bit packings (forward, data gradient): map tiles per workgroup (0 = default)
     int n_pad = 0, rows_fwd = 0;          // forward packing: [rows_fwd][n_pad]
     int n_pad_bwd = 0, rows_bwd = 0;      // data-gradient packing: [rows_bwd][n_pad_bwd]
     long wcount() const { return (long)c_out * c_in * k * k; }
@@ -93,7 +93,7 @@ inline sk_status repack_conv(ConvParams &c, bool training, int dtype, hipStream_
     } else {
         SK_HIP(sk::launch_pack_weights_h(c.w_dev, c.wp16_fwd, dtype, c.c_out, c.c_in, c.k, 0, c.mt16, stream));
         if (training && c.wp16_bwd)
-            SK_HIP(sk::launch_pack_weights_h(c.w_dev, c.wp16_bwd, dtype, c.c_out, c.c_in, c.k, 1, 0, stream));
+            SK_HIP(sk::launch_pack_weights_h(c.w_dev, c.wp16_bwd, dtype, c.c_out, c.c_in, c.k, 1, c.mt16_bwd, stream));
     }
     return SK_OK;
 }
@@ -124,7 +124,7 @@ inline sk_status alloc_conv(ConvParams &c, bool training, int dtype = SK_F32)
         if (training) SK_TRY(alloc_f(&c.wp_bwd, (long)c.rows_bwd * c.n_pad_bwd));
     } else {   // 16-bit elements, allocated in floats
         SK_TRY(alloc_f(&c.wp16_fwd, (sk::packed_h_elems(c.c_out, (c.c_in + 7) / 8, c.k, c.mt16) + 1) / 2));
-        if (training) SK_TRY(alloc_f(&c.wp16_bwd, (sk::packed_h_elems(c.c_in, (c.c_out + 7) / 8, c.k) + 1) / 2));
+        if (training) SK_TRY(alloc_f(&c.wp16_bwd, (sk::packed_h_elems(c.c_in, (c.c_out + 7) / 8, c.k, c.mt16_bwd) + 1) / 2));
     }
     if (training) {
         SK_TRY(alloc_f(&c.dw, c.wcount()));

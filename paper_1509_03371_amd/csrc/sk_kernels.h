@@ -127,8 +127,9 @@ bool conv_h_supported(int k, int d, int gemm_m);
 // does this launch (single_map set, img left null) run on the kernel that can read the fp32 image itself?
 bool conv_h_reads_image(const ConvHArgs &a);
 hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream);
-// layers with many maps (1x1, 3x3: kernels_conv_wide_h.hip; 5x5, 6x6, 8x8, 10x10: kernels_conv_wide_big_h.hip): decided by what the weight packing knows too, so that weights
-// packed with mt = 0 are always packed for the kernel that reads them (four map tiles per group there)
+// Layers with many maps (1x1, 3x3: kernels_conv_wide_h.hip; 5x5, 6x6, 8x8, 10x10: kernels_conv_wide_big_h.hip).  Decided by
+// what the weight packing knows too, so that weights packed with mt = 0 are always packed for the kernel that reads them
+// (four map tiles per group there); where the size of the maps speaks against it conv_h_size_mt gives another mt
 bool conv_h_wide(int gemm_m, int gemm_c8, int k);
 // Which kernel a launch runs on: 1 = kernels_conv_wide_h.hip, 2 = kernels_conv_wide_big_h.hip, 0 = another one, -1 = none takes it;
 // for the first two the tile shape (1x1, 3x3: its number in the dispatch; larger: 16-column groups across a tile), over how many
@@ -144,8 +145,10 @@ hipError_t launch_conv_wide_big_h(const ConvHArgs &a, hipStream_t stream);
 constexpr long CONV_H_WS_FLOATS = 8L << 20;       // ConvHArgs.ws: 32 MB hold the partial sums of 512 tiles of 64 maps x 256 pixels
 // 16-bit elements of the packed weights of a GEMM with gemm_m output maps and gemm_c8 input octets
 long packed_h_elems(int gemm_m, int gemm_c8, int k, int mt = 0);
-// map tiles per workgroup (mt) that suit a forward layer of this output size; pass it to the packing too
-int conv_h_pick_mt(int c_out, int c_in, int k, int n, int Ho, int Wo);
+// map tiles per workgroup (mt) that suit a layer of this output size; pass it to the packing too
+int conv_h_size_mt(int gemm_m, int gemm_c8, int k, int d, int n, int Ho, int Wo);
+// ... a forward layer of the U-Net or the USK-Net
+int conv_h_pick_mt(int c_out, int c_in, int k, int d, int n, int Ho, int Wo);
 // ... or that value with CONV_H_TAPCOLS set: a 3x3 layer whose weights are packed (and whose launch runs) with the kernel
 // columns on the lane groups; pass the value to the packing and in ConvHArgs.mt as it is
 constexpr int CONV_H_TAPCOLS = 16;

@@ -48,6 +48,7 @@ struct Conv3 {
     std::vector<TapRun> fwd, bwd;      // bwd: runs over the flipped taps, for the data gradient
     void *wp16 = nullptr;              // 16-bit nets: the kernel as a 2-D convolution over k * 8*ceil(c_in/8) input maps, packed MFMA fragments
     void *wp16_bwd = nullptr;          // ... and its data gradient: a 2-D convolution over k * 8*ceil(c_out/8) maps of the zero-padded gradient
+    int mt16 = 0, mt16_bwd = 0;        // map tiles per workgroup that wp16 and wp16_bwd are packed for (0 = default)
     float *exp2d = nullptr;            // fp32 staging of the two 2-D masters these are packed from
     float *dw = nullptr, *db = nullptr, *vw = nullptr, *vb = nullptr, *dw_tap = nullptr;
     // weight gradient of all depth taps in one launch: k > 1 and (d = 1, the tapped slices adjacent, or a power-of-two
@@ -113,13 +114,13 @@ sk_status repack_conv3_h(Conv3 &c, int dtype, bool with_bwd, hipStream_t stream)
     const int c8 = (c.c_in + 7) / 8, o8 = (c.c_out + 7) / 8, kk = c.k * c.k;
     const long fwd_floats = (long)c.c_out * c.k * c8 * 8 * kk, bwd_floats = (long)c.k * o8 * 8 * c.c_in * kk;
     if (!c.exp2d) SK_TRY(alloc_f(&c.exp2d, std::max(fwd_floats, bwd_floats)));
-    if (!c.wp16) SK_HIP(hipMalloc(&c.wp16, sizeof(unsigned short) * (size_t)sk::packed_h_elems(c.c_out, c.k * c8, c.k)));
+    if (!c.wp16) SK_HIP(hipMalloc(&c.wp16, sizeof(unsigned short) * (size_t)sk::packed_h_elems(c.c_out, c.k * c8, c.k, c.mt16)));
     SK_HIP(sk::launch_expand_taps3d(c.w_dev, c.exp2d, c.c_out, c.c_in, c.k, 0, stream));
-    SK_HIP(sk::launch_pack_weights_h(c.exp2d, c.wp16, dtype, c.c_out, c.k * c8 * 8, c.k, 0, 0, stream));
+    SK_HIP(sk::launch_pack_weights_h(c.exp2d, c.wp16, dtype, c.c_out, c.k * c8 * 8, c.k, 0, c.mt16, stream));
     if (with_bwd) {
-        if (!c.wp16_bwd) SK_HIP(hipMalloc(&c.wp16_bwd, sizeof(unsigned short) * (size_t)sk::packed_h_elems(c.c_in, c.k * o8, c.k)));
+        if (!c.wp16_bwd) SK_HIP(hipMalloc(&c.wp16_bwd, sizeof(unsigned short) * (size_t)sk::packed_h_elems(c.c_in, c.k * o8, c.k, c.mt16_bwd)));
         SK_HIP(sk::launch_expand_taps3d(c.w_dev, c.exp2d, c.c_out, c.c_in, c.k, 1, stream));
-        SK_HIP(sk::launch_pack_weights_h(c.exp2d, c.wp16_bwd, dtype, c.k * o8 * 8, c.c_in, c.k, 1, 0, stream));
+        SK_HIP(sk::launch_pack_weights_h(c.exp2d, c.wp16_bwd, dtype, c.k * o8 * 8, c.c_in, c.k, 1, c.mt16_bwd, stream));
     }
     return SK_OK;
 }
@@ -281,7 +282,7 @@ sk_status run_layer3(sknet3d *net, int li, hipStream_t stream)
         a.k = l.k; a.d = l.d; a.in_off = 0; a.Ho = out.h; a.Wo = out.w; a.relu = l.relu; a.out_f32 = last ? 1 : 0;
         a.c8_out_total = (out.c + 7) / 8; a.o8_off = 0; a.OH = out.h; a.OW = out.w;
         a.oy_mul = 1; a.oy_off = 0; a.ox_mul = 1; a.ox_off = 0;
-        a.mt = 0;
+        a.mt = cv.mt16;
         if (l.k > 1) a.xb8 = c8;
         if (l.k > 1 && l.d > 1) { a.grp8 = c8; a.skip8 = (l.d - 1) * c8; }
         SK_HIP(sk::launch_conv_h(a, stream));
@@ -503,6 +504,10 @@ sk_status sknet3d_plan(sknet3d_t *net, int32_t dz, int32_t h, int32_t w, int32_t
     for (int i = 0; i < L && st == SK_OK; ++i) {
         if (net->layers[i].kind != SK_CONV) continue;
         Conv3 &c = net->convs[net->conv_of_layer[i]];
+        if (half) {
+            c.mt16 = sk::conv_h_size_mt(c.c_out, c.k * ((c.c_in + 7) / 8), c.k, c.d, dims[i + 1].dz, dims[i + 1].h, dims[i + 1].w);
+            c.mt16_bwd = sk::conv_h_size_mt(c.c_in, c.k * ((c.c_out + 7) / 8), c.k, c.d, dims[i].dz, dims[i].h, dims[i].w);
+        }
         st = alloc_conv3(c, training, i > 0, half);
         if (st == SK_OK) st = upload_conv3(c, nullptr);
         if (st == SK_OK && half) st = upload_conv3_h(c, net->dtype, training && i > 0);
@@ -634,7 +639,7 @@ static sk_status backward3_h(sknet3d *net, const int32_t *labels_dev, float *los
             a.k = l.k; a.d = l.d; a.in_off = (l.k - 1) * l.d; a.Ho = in.h; a.Wo = in.w; a.relu = 0; a.out_f32 = 0;
             a.c8_out_total = (in.c + 7) / 8; a.o8_off = 0; a.OH = in.h; a.OW = in.w;
             a.oy_mul = 1; a.oy_off = 0; a.ox_mul = 1; a.ox_off = 0;
-            a.mt = 0;
+            a.mt = c.mt16_bwd;
             if (l.k > 1) a.xb8 = o8;
             if (l.k > 1 && l.d > 1) { a.grp8 = o8; a.skip8 = (l.d - 1) * o8; }
             SK_HIP(sk::launch_conv_h(a, stream));

@@ -556,6 +556,10 @@ sk_status sknet_plan(sknet_t *net, int32_t n, int32_t h, int32_t w, int32_t pad,
         }
         if (l.kind == SK_CONV) {
             ConvParams &c = net->convs[net->conv_of_layer[i]];
+            if (half) {
+                c.mt16 = sk::conv_h_size_mt(c.c_out, (c.c_in + 7) / 8, c.k, l.d, n, dims[i + 1].h, dims[i + 1].w);
+                c.mt16_bwd = sk::conv_h_size_mt(c.c_in, (c.c_out + 7) / 8, c.k, l.d, n, dims[i].h, dims[i].w);
+            }
             st = alloc_conv(c, training != 0, net->dtype);
             if (st == SK_OK) st = upload_conv(c, training != 0, nullptr, net->dtype);
             const size_t s = sk::wgrad_f32_scratch_floats(c.c_out, c.c_in, c.k);
@@ -651,6 +655,7 @@ static sk_status backward_layer(sknet_t *net, int li, float *gcur, float *gnext,
             a.k = c.k; a.d = l.d; a.in_off = (c.k - 1) * l.d; a.Ho = in.h; a.Wo = in.w; a.relu = 0; a.out_f32 = 0;
             a.c8_out_total = (in.c + 7) / 8; a.o8_off = 0; a.OH = in.h; a.OW = in.w;
             a.oy_mul = 1; a.oy_off = 0; a.ox_mul = 1; a.ox_off = 0;
+            a.mt = c.mt16_bwd;
             SK_HIP(sk::launch_conv_h(a, stream));
         } else {
             sk::ConvF32Args a{};
@@ -834,7 +839,7 @@ sk_status sknet_sgd_step(sknet_t *net, float lr, float momentum, float weight_de
             if (c.wp_bwd) pf[np++] = {c.w_dev, c.wp_bwd, c.c_out, c.c_in, c.k, 1, c.rows_bwd, c.n_pad_bwd};
         } else {
             ph[np++] = {c.w_dev, c.wp16_fwd, c.c_out, c.c_in, c.k, 0, c.mt16};
-            if (c.wp16_bwd) ph[np++] = {c.w_dev, c.wp16_bwd, c.c_out, c.c_in, c.k, 1, 0};
+            if (c.wp16_bwd) ph[np++] = {c.w_dev, c.wp16_bwd, c.c_out, c.c_in, c.k, 1, c.mt16_bwd};
         }
     }
     SK_HIP(sk::launch_sgd_batch_f32(sb, lr, momentum, weight_decay, stream));

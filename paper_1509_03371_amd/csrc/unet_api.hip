@@ -507,9 +507,10 @@ static sk_status plan_impl(unet_t *net, int32_t n, int32_t h_in, int32_t w_in, b
             if (op.kind == 0) {
                 ConvParams &c = net->convs[op.param];
                 c.mt16 = sk::conv_h_pick_mode(c.c_out, c.c_in, c.k, op.d, n, op.out.h, op.out.w);
+                c.mt16_bwd = sk::conv_h_size_mt(c.c_in, (c.c_out + 7) / 8, c.k, op.d, n, op.in.h, op.in.w);
             } else if (op.kind == 2) {
-                for (auto &t : net->ups[op.param].tap) t.mt16 = sk::conv_h_pick_mt(net->ups[op.param].c_out, net->ups[op.param].c_in, 1, n, op.in.h, op.in.w);
-                net->ups[op.param].cat.mt16 = sk::conv_h_pick_mt(4 * net->ups[op.param].c_out, net->ups[op.param].c_in, 1, n, op.in.h, op.in.w);
+                for (auto &t : net->ups[op.param].tap) t.mt16 = sk::conv_h_pick_mt(net->ups[op.param].c_out, net->ups[op.param].c_in, 1, 1, n, op.in.h, op.in.w);
+                net->ups[op.param].cat.mt16 = sk::conv_h_pick_mt(4 * net->ups[op.param].c_out, net->ups[op.param].c_in, 1, 1, n, op.in.h, op.in.w);
             }
         }
     }
@@ -735,6 +736,7 @@ static sk_status backward_h(unet_t *net, const int32_t *labels_dev, float *loss_
             a.c8_out_total = (op.in.c + 7) / 8; a.o8_off = 0; a.OH = op.in.h; a.OW = op.in.w;
             a.oy_mul = 1; a.oy_off = 0; a.ox_mul = 1; a.ox_off = 0;
             a.ws = net->conv_ws; a.ws_floats = sk::CONV_H_WS_FLOATS;
+            a.mt = c.mt16_bwd;
             SK_HIP(sk::launch_conv_h(a, stream));
             written.insert(op.src);
         } else if (op.kind == 1) {
@@ -949,7 +951,7 @@ sk_status unet_sgd_step(unet_t *net, float lr, float momentum, float weight_deca
         auto pack_h = [&](const ConvParams &c, bool bwd) -> sk_status {
             for (int f = 0; f < (bwd && c.wp16_bwd ? 2 : 1); ++f) {
                 hj[nh++] = f == 0 ? sk::PackHJob{c.w_dev, c.wp16_fwd, c.c_out, c.c_in, c.k, 0, c.mt16}
-                                  : sk::PackHJob{c.w_dev, c.wp16_bwd, c.c_out, c.c_in, c.k, 1, 0};
+                                  : sk::PackHJob{c.w_dev, c.wp16_bwd, c.c_out, c.c_in, c.k, 1, c.mt16_bwd};
                 if (nh == sk::BATCH_MAX) {
                     SK_HIP(sk::launch_pack_weights_h_batch(hj, nh, net->dtype, stream));
                     nh = 0;

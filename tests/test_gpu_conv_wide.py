@@ -21,26 +21,42 @@ def rounded(a, dtype):
     return torch.from_numpy(a).to(torch.bfloat16 if dtype == "bf16" else torch.float16).float().numpy()
 
 
+NARROW = (0, 0, 1, 0)                                  # conv_h_kernel: small images, or maps that would pack with too much waste
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("k,d,c_in,c_out,n,h,w", [
-    # 3x3, 64 x (8 rows x 32) tiles: remainders everywhere; the widest strides (one octet row of 68 units; d > rows)
-    (3, 1, 64, 64, 1, 36, 35), (3, 2, 40, 112, 2, 33, 64), (3, 18, 32, 64, 1, 56, 69), (3, 6, 96, 128, 1, 20, 50), (3, 1, 33, 64, 1, 3, 3),
-    # ... 16 rows x 32: more tiles than CUs; strides 1, 4 (five / six input loads a wave) and 6
-    (3, 1, 64, 128, 2, 262, 182), (3, 6, 96, 64, 2, 312, 302),
+@pytest.mark.parametrize("k,d,c_in,c_out,n,h,w,path", [
+    # 3x3, tiles of 8 rows x 32 pixels: remainders everywhere; strides 1, 2 and 6 (three and four input loads a wave)
+    (3, 1, 64, 64, 1, 36, 35, NARROW), (3, 2, 40, 112, 2, 33, 64, (1, 0, 1, 3)), (3, 18, 32, 64, 1, 56, 69, NARROW),
+    (3, 6, 96, 128, 1, 20, 50, (1, 0, 1, 4)), (3, 1, 33, 64, 1, 3, 3, NARROW), (3, 1, 72, 64, 1, 36, 35, (1, 0, 1, 3)),
+    # ... the widest stride (one octet row of 68 units; d > rows), and one pixel
+    (3, 18, 72, 64, 1, 56, 69, (1, 0, 1, 8)), (3, 1, 65, 64, 1, 3, 3, (1, 0, 1, 3)),
+    # ... 16 rows x 32: more tiles than CUs; strides 1 and 6 (five / eight input loads a wave)
+    (3, 1, 64, 128, 2, 262, 182, (1, 1, 1, 5)), (3, 6, 96, 64, 2, 312, 302, (1, 1, 1, 8)),
     # ... 12 rows x 64
-    (3, 1, 64, 64, 2, 402, 391),
+    (3, 1, 64, 64, 2, 402, 391, (1, 2, 1, 8)),
     # 1x1: 128 x 128 pixels on eight waves; on four; 128 x 256; 64 x 256 (an odd number of 64-map groups in the first three)
-    (1, 1, 40, 112, 2, 23, 60), (1, 1, 64, 320, 1, 17, 30), (1, 1, 33, 512, 2, 90, 101), (1, 1, 320, 448, 1, 150, 150), (1, 1, 64, 64, 2, 300, 300),
-    (1, 1, 32, 64, 1, 1, 1),
-    # large kernels, 16 rows x 32 pixels: two, four and six input loads a wave; 8 rows x 64: strides too wide for the former
-    # (10x10 at 10, 8x8 at 18) and more tiles than CUs where that is fewer rounds
-    (5, 1, 40, 70, 2, 37, 41), (6, 1, 33, 112, 1, 22, 39), (6, 3, 64, 64, 1, 49, 50), (8, 8, 40, 64, 2, 93, 90), (10, 8, 64, 64, 1, 107, 130),
-    (10, 10, 32, 64, 1, 100, 122), (8, 18, 40, 64, 1, 130, 149), (5, 2, 32, 512, 1, 72, 136),
-    # more maps than the LDS holds biases for at this kernel stride: conv_h_kernel
-    (5, 18, 32, 7184, 1, 75, 81),
+    (1, 1, 40, 112, 2, 23, 60, (1, 0, 1, 1)), (1, 1, 64, 320, 1, 17, 30, (1, 0, 1, 1)), (1, 1, 33, 512, 2, 90, 101, (1, 1, 1, 2)),
+    (1, 1, 320, 448, 1, 150, 150, (1, 2, 1, 4)), (1, 1, 64, 64, 2, 300, 300, (1, 3, 1, 4)), (1, 1, 32, 64, 1, 1, 1, (1, 0, 1, 1)),
+    # large kernels on images too small for large tiles, and 70 maps
+    (5, 1, 40, 70, 2, 37, 41, NARROW), (6, 1, 33, 112, 1, 22, 39, NARROW), (6, 3, 64, 64, 1, 49, 50, NARROW), (8, 8, 40, 64, 2, 93, 90, NARROW),
+    (10, 8, 64, 64, 1, 107, 130, NARROW), (10, 10, 32, 64, 1, 100, 122, NARROW), (8, 18, 40, 64, 1, 130, 149, NARROW), (5, 2, 32, 512, 1, 72, 136, NARROW),
+    # more maps than the LDS holds biases for at this kernel stride
+    (5, 18, 32, 7184, 1, 75, 81, NARROW),
+    # large kernels, 16 rows x 32 pixels: two, four and six input loads a wave; odd input maps, ragged map groups
+    (5, 1, 40, 64, 9, 61, 45, (2, 2, 1, 2)), (5, 9, 37, 64, 9, 82, 79, (2, 2, 1, 4)), (5, 16, 40, 64, 5, 138, 104, (2, 2, 1, 6)),
+    (6, 1, 33, 64, 9, 65, 76, (2, 2, 1, 2)), (6, 8, 40, 64, 9, 81, 106, (2, 2, 1, 4)), (6, 16, 40, 64, 5, 158, 145, (2, 2, 1, 6)),
+    (8, 1, 40, 112, 5, 56, 76, (2, 2, 1, 2)), (8, 8, 40, 112, 5, 93, 128, (2, 2, 1, 4)), (8, 12, 33, 112, 3, 145, 154, (2, 2, 1, 6)),
+    (10, 4, 40, 208, 5, 56, 109, (2, 2, 1, 4)), (10, 8, 40, 192, 3, 111, 139, (2, 2, 1, 6)), (10, 1, 40, 256, 9, 38, 10, (2, 2, 1, 4)),
+    # ... 8 rows x 64
+    (5, 1, 40, 208, 16, 9, 146, (2, 4, 1, 2)), (5, 10, 40, 112, 9, 71, 80, (2, 4, 1, 4)), (5, 18, 40, 64, 5, 154, 112, (2, 4, 1, 6)),
+    (6, 2, 40, 112, 16, 20, 155, (2, 4, 1, 2)), (6, 9, 40, 64, 16, 72, 90, (2, 4, 1, 4)), (6, 18, 40, 64, 9, 148, 131, (2, 4, 1, 6)),
+    (8, 10, 40, 208, 5, 100, 110, (2, 4, 1, 4)), (8, 16, 33, 112, 5, 161, 154, (2, 4, 1, 6)),
+    (10, 2, 40, 512, 9, 25, 58, (2, 4, 1, 4)), (10, 8, 40, 208, 5, 96, 118, (2, 4, 1, 6)), (10, 10, 40, 192, 5, 91, 92, (2, 4, 1, 6)),
 ])
-def test_layer(dtype, k, d, c_in, c_out, n, h, w):
+def test_layer(dtype, k, d, c_in, c_out, n, h, w, path):
     from paper_1509_03371_amd import binding as B
+    assert B.sk_probe_conv_path(k, d, c_in, c_out, n, h - (k - 1) * d, w - (k - 1) * d) == path
     layers = [S.conv(c_out, k, d, relu=True), S.conv(2, 1, 1, relu=False)]
     rng = np.random.default_rng(k * h + w)
     img = rounded(rng.standard_normal((n, c_in, h, w)).astype(np.float32), dtype)

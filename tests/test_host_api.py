@@ -201,3 +201,16 @@ def test_accepted_16_bit_layers_have_a_kernel(k):
     assert accepted > 400
     layer = S.conv(7184, 5, 18, relu=False)
     B.SKNet([layer], 32, 7184, dtype="bf16").close()
+
+
+@pytest.mark.parametrize("k,d,c_in,c_out,small,large", [
+    (5, 2, 64, 64, 100, 300), (6, 1, 64, 64, 100, 300), (8, 8, 64, 64, 250, 512), (10, 8, 64, 64, 250, 512), (10, 1, 128, 256, 96, 300),
+    (3, 1, 32, 64, 64, 128), (3, 12, 32, 64, 300, None), (1, 1, 32, 64, None, 8),
+])
+def test_small_images_keep_the_kernel_of_small_tiles(k, d, c_in, c_out, small, large):
+    # measured on both sides: the kernels for many maps take up to 2.7 times as long on images that do not fill the GPU with
+    # their larger tiles
+    for side, kernel in ((small, 0), (large, 1 if k < 4 else 2)):
+        if side is not None:
+            assert B.sk_probe_conv_path(k, d, c_in, c_out, 1, side, side)[0] == kernel
+            assert B.sk_probe_conv_path(k, d, c_in, c_out, 1, side, side, data_gradient=True)[0] == kernel
