@@ -690,8 +690,8 @@ static hipError_t launch_conv_c1_f32(const ConvF32Args &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// grp_maps is accepted for the kernel sizes with a prefetching specialisation when it is a multiple of the
-// largest K chunk (16 maps)
+// grp_maps is accepted where the prefetching kernel is sure to take the layer (5x5 layers may fall back to the generic one)
+// and it is a multiple of the largest K chunk (16 maps)
 bool conv_f32_groups_supported(int k, int d, int grp_maps)
 {
     const int halo = (k - 1) * d;

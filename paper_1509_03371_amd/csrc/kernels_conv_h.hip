@@ -1633,15 +1633,17 @@ hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Weight packing for conv_h_kernel.  The packed array is a sequence of 1 KB MFMA A fragments,
+// Weight packing for the 16-bit convolutions.  The packed array is a sequence of 1 KB MFMA A fragments,
 //   [mgroup][chunk][column step cs][kernel row i][m-tile mt][lane group g][l16][e = 0..7]
 // with element = W[o][c][i][j] (forward) where o = (mgroup*MT + mt)*16 + l16 and
-//   MAP4 (k >= 4): c = chunk*8 + e,           j = 4*cs + g (zero for j >= k)
-//   otherwise   : c = (chunk*4 + g)*8 + e,    j = cs
+//   map4 = 0: c = (chunk*4 + g)*8 + e,   j = cs
+//   map4 = 1: c = chunk*8 + e,           j = 4*cs + g (zero for j >= k): k >= 4, and 3x3 with CONV_H_TAPCOLS
+//   map4 = 2: c = chunk*8 + e,           j = 4*cs + (0, 2, 1, 3)[g]: kernels_conv_wide_big_h.hip, whose LDS reads serve
+//                                        groups 0 and 1 together and want their columns two kernel strides apart
 // flip_transpose = 1 builds the data-gradient operator instead: the roles of input and output maps
 // are swapped and both taps are mirrored (element = W[c][o][k-1-i][k-1-j]).
 // Entries whose o or c lie beyond the real extents are zero.
-// kernel column, within its column step, that lane group g carries: g, or (map4 = 2, kernels_conv_wide_big_h.hip) 0, 2, 1, 3
+// kernel column, within its column step, that lane group g carries
 __device__ __forceinline__ int pack_col(int map4, int g) { return map4 == 2 ? (g >> 1) | ((g & 1) << 1) : g; }
 
 template <int DT>

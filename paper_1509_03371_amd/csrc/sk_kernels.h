@@ -6,14 +6,6 @@
 
 namespace sk {
 
-// ---- implicit-GEMM SK convolution, fp32 activations, fp32 MFMA --------------------------------
-// Computes, for every image b, output map o and output position (y, x) in [0,Ho) x [0,Wo):
-//   acc = bias[o] + sum_{c,i,j} Wp[(c*k+i)*k+j][o] * X[b, c, y + i*d - in_off, x + j*d - in_off]
-// with X read as zero outside [0,H) x [0,W)  (in_off = 0: the forward "valid" SK convolution;
-// in_off = (k-1)*d with flipped, transposed weights: its data gradient),
-// then optional ReLU, then optional masking (acc = mask[...] > 0 ? acc : 0, same index as the
-// output), and stores it at
-//   Y[((b*out_maps + o + o_off)*OH + y*oy_mul + oy_off)*OW + x*ox_mul + ox_off].
 // How the k = 2, s = 1 pool kernels cut a map.  A thread walks a chain of `len` windows down one residue class of rows and
 // reads one row more than it has windows, so long chains (32) read least; but a chain is a serial row of memory latencies,
 // and a small map in chains of 32 fills a fraction of the GPU (96x96 with 8 or 16 maps: 32-64 workgroups, 11 us).  So row
@@ -38,6 +30,14 @@ inline PoolCut pool_cut(int Ho, int Wo, int d, long planes, int step)
     return c;
 }
 
+// ---- implicit-GEMM SK convolution, fp32 activations, fp32 MFMA --------------------------------
+// Computes, for every image b, output map o and output position (y, x) in [0,Ho) x [0,Wo):
+//   acc = bias[o] + sum_{c,i,j} Wp[(c*k+i)*k+j][o] * X[b, c, y + i*d - in_off, x + j*d - in_off]
+// with X read as zero outside [0,H) x [0,W)  (in_off = 0: the forward "valid" SK convolution;
+// in_off = (k-1)*d with flipped, transposed weights: its data gradient),
+// then optional ReLU, then optional masking (acc = mask[...] > 0 ? acc : 0, same index as the
+// output), and stores it at
+//   Y[((b*out_maps + o + o_off)*OH + y*oy_mul + oy_off)*OW + x*ox_mul + ox_off].
 struct ConvF32Args {
     const float *x;      // [n][c_in][H][W]
     const float *wp;     // packed weights [c_pad*k*k][n_pad], c_pad = roundup(c_in, 16), n_pad = roundup(c_out, 16)
