@@ -1742,21 +1742,37 @@ __global__ void __launch_bounds__(256) pack_weights_h_batch_kernel(PackHJobs b)
 // 2.5 (10x10) of conv_h_kernel's: over 928 layers (32 to 128 -> 64 to 1024 maps, 8^2 to 3 x 300^2, d = 1 to 8, bf16) the kernel
 // for many maps took 0.95 to 2.74 of the time below these lines (10x10 64 -> 64 at 32^2: 79 us of 37, 8x8 at 250^2: 66 of 55)
 // and 0.53 to 1.07 above (10x10 64 -> 256 at 250^2: 184 us of 259).
-// 3x3 to 64 maps from at most 64: up to 64^2 pixels the few large steps are as long as the launch (32 -> 64 at 64^2: 19.5 us
-// of 18.9, at 128^2 20.3 of 21.2), and from one chunk of 32 maps at wide kernel strides most of a 32-column tile is halo
-// (32 -> 64 at d = 12, 3 x 300^2: 65 us of 62; at d = 8 59.9 of 60.3).
-int conv_h_size_mt(int gemm_m, int gemm_c8, int k, int d, int n, int Ho, int Wo)
+// 3x3 to 64 maps, `once` = no CU has more than one of the smallest tiles there.  A launch then lasts as long as one tile: here
+// 4.9 us + 2.65 a chunk of 32 input maps (2.0 up to 64 columns, where half of the waves idle), there 5.3 + 1.65 forward and
+// 6.4 + 1.8 in a data gradient, which reads zeros around the image and a mask (982 and 990 layers of 32 to 256 maps, 12^2 to
+// 2 x 400^2, d = 1 to 16, bf16, of their own in a loop).  Forward: from at most 64 maps up to 64^2 pixels.  Data gradient: from
+// one chunk (32 -> 64 at 100^2, d = 4: 7.7 us here, 8.7 there; at 256^2, two tiles a CU, 15.2 and 13.7), and up to 64 columns from six
+// (96 -> 64 at 40^2: 10.8 and 11.6; 256 -> 64: equal).  From d = 10 on the loads of a chunk are padded to eight a wave there, so that
+// few chunks wait for them: data gradient from one (330^2: 21.8 and 25.7) or, once, two (64 -> 64 at 100^2: 10.4 and 11.8), forward
+// from one, once (100^2: 6.8 and 7.6) or at d > 10, where most of a 32-column tile is halo (d = 12 at 3 x 300^2: 62 and 65).
+// 3x3 to more maps at d = 6 (the widest stride there): data gradient from at most four chunks where the 32 x 16 tile with padded
+// loads would run and one round of tiles is enough here (32 / 64 / 128 -> 128 at 150^2: 10.9 / 14.8 / 22.1 and 13.7 / 17.0 / 23.6).
+int conv_h_size_mt(int gemm_m, int gemm_c8, int k, int d, int n, int Ho, int Wo, bool gradient)
 {
     if (!conv_h_wide(gemm_m, gemm_c8, k) || k == 1) return 0;
     const int mt = conv_h_mt(gemm_m, k);
-    if (k == 3) {
-        const bool few = gemm_c8 <= 8 && (long)n * Ho * Wo <= 64L * 64, halo = gemm_c8 <= 4 && d > 10;
-        return gemm_m <= 64 && (few || halo) ? mt : 0;
-    }
     ConvHArgs a{};
     a.n = n; a.k = k; a.d = d; a.c8_in = gemm_c8; a.c_out = gemm_m; a.Ho = Ho; a.Wo = Wo;
     const long cus = device_cus();
     auto rounds = [&](int tiles, int tx, int rt) { return (conv_h_tile_count(a, tiles, tx, rt) + cus - 1) / cus; };
+    if (k == 3) {
+        const int chunks = (gemm_c8 + 3) / 4;
+        if (gemm_m > 64) {
+            const ConvHPath p = conv_wide_path(a);
+            return gradient && chunks <= 4 && p.shape == 1 && p.loads == 8 && rounds(mt, 128, 4) == 1 ? mt : 0;
+        }
+        const bool once = rounds(4, 32, 8) == 1;
+        if (gradient) {
+            const bool short_tile = chunks == 1 || (Wo <= 64 && chunks <= 6) || (d >= 10 && chunks <= 2);
+            return (once && short_tile) || (chunks == 1 && d >= 10) ? mt : 0;
+        }
+        return (chunks <= 2 && (long)n * Ho * Wo <= 64L * 64) || (chunks == 1 && (d > 10 || (d == 10 && once))) ? mt : 0;
+    }
     const long here = conv_h_big_square(k, mt, d, gemm_m) ? std::min(rounds(mt, 128, 4), rounds(mt, 64, 8)) : rounds(mt, 128, 4);
     const long there = conv_wide_big_path(a).shape == 2 ? rounds(4, 32, 16) : rounds(4, 64, 8);
     return 100 * here < (k == 10 ? 250 : k == 8 ? 160 : 125) * there ? mt : 0;
@@ -1768,7 +1784,7 @@ int conv_h_size_mt(int gemm_m, int gemm_c8, int k, int d, int n, int Ho, int Wo)
 int conv_h_pick_mt(int c_out, int c_in, int k, int d, int n, int Ho, int Wo)
 {
     const int c8 = (c_in + 7) / 8;
-    if (conv_h_wide(c_out, c8, k) && conv_h_size_mt(c_out, c8, k, d, n, Ho, Wo) == 0) return 0;
+    if (conv_h_wide(c_out, c8, k) && conv_h_size_mt(c_out, c8, k, d, n, Ho, Wo, false) == 0) return 0;
     int mt = conv_h_mt(c_out, k);
     const long sp = (long)((Wo + CH_TX - 1) / CH_TX) * ((Ho + 3) / 4) * n;   // tiles of 4 rows at least
     const int m_tiles = (c_out + 15) / 16;

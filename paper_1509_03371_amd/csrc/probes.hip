@@ -186,7 +186,7 @@ sk_status sk_probe_conv_path(int32_t k, int32_t d, int32_t maps_in, int32_t maps
     a.Ho = a.OH = h_out; a.Wo = a.OW = w_out;
     a.in_off = grad ? halo : 0; a.H = grad ? h_out - halo : h_out + halo; a.W = grad ? w_out - halo : w_out + halo;
     a.out_f32 = flags & 2 ? 1 : 0;
-    a.mt = sk::conv_h_size_mt(maps_out, a.c8_in, k, d, n, h_out, w_out);
+    a.mt = sk::conv_h_size_mt(maps_out, a.c8_in, k, d, n, h_out, w_out, grad != 0);
     if (flags & 4) { a.ws = &scratch; a.ws_floats = sk::CONV_H_WS_FLOATS; }
     const sk::ConvHPath p = sk::conv_h_path(a);
     if (p.kernel < 0) return fail(SK_EUNSUPPORTED, "probe_conv_path: no kernel takes a %dx%d convolution at d = %d to %d maps", k, k, d, maps_out);

@@ -145,8 +145,8 @@ hipError_t launch_conv_wide_big_h(const ConvHArgs &a, hipStream_t stream);
 constexpr long CONV_H_WS_FLOATS = 8L << 20;       // ConvHArgs.ws: 32 MB hold the partial sums of 512 tiles of 64 maps x 256 pixels
 // 16-bit elements of the packed weights of a GEMM with gemm_m output maps and gemm_c8 input octets
 long packed_h_elems(int gemm_m, int gemm_c8, int k, int mt = 0);
-// map tiles per workgroup (mt) that suit a layer of this output size; pass it to the packing too
-int conv_h_size_mt(int gemm_m, int gemm_c8, int k, int d, int n, int Ho, int Wo);
+// map tiles per workgroup (mt) that suit a layer of this output size (forward or its data gradient); pass it to the packing too
+int conv_h_size_mt(int gemm_m, int gemm_c8, int k, int d, int n, int Ho, int Wo, bool gradient);
 // ... a forward layer of the U-Net or the USK-Net
 int conv_h_pick_mt(int c_out, int c_in, int k, int d, int n, int Ho, int Wo);
 // ... or that value with CONV_H_TAPCOLS set: a 3x3 layer whose weights are packed (and whose launch runs) with the kernel

@@ -505,8 +505,8 @@ sk_status sknet3d_plan(sknet3d_t *net, int32_t dz, int32_t h, int32_t w, int32_t
         if (net->layers[i].kind != SK_CONV) continue;
         Conv3 &c = net->convs[net->conv_of_layer[i]];
         if (half) {
-            c.mt16 = sk::conv_h_size_mt(c.c_out, c.k * ((c.c_in + 7) / 8), c.k, c.d, dims[i + 1].dz, dims[i + 1].h, dims[i + 1].w);
-            c.mt16_bwd = sk::conv_h_size_mt(c.c_in, c.k * ((c.c_out + 7) / 8), c.k, c.d, dims[i].dz, dims[i].h, dims[i].w);
+            c.mt16 = sk::conv_h_size_mt(c.c_out, c.k * ((c.c_in + 7) / 8), c.k, c.d, dims[i + 1].dz, dims[i + 1].h, dims[i + 1].w, false);
+            c.mt16_bwd = sk::conv_h_size_mt(c.c_in, c.k * ((c.c_out + 7) / 8), c.k, c.d, dims[i].dz, dims[i].h, dims[i].w, true);
         }
         st = alloc_conv3(c, training, i > 0, half);
         if (st == SK_OK) st = upload_conv3(c, nullptr);

@@ -557,8 +557,8 @@ sk_status sknet_plan(sknet_t *net, int32_t n, int32_t h, int32_t w, int32_t pad,
         if (l.kind == SK_CONV) {
             ConvParams &c = net->convs[net->conv_of_layer[i]];
             if (half) {
-                c.mt16 = sk::conv_h_size_mt(c.c_out, (c.c_in + 7) / 8, c.k, l.d, n, dims[i + 1].h, dims[i + 1].w);
-                c.mt16_bwd = sk::conv_h_size_mt(c.c_in, (c.c_out + 7) / 8, c.k, l.d, n, dims[i].h, dims[i].w);
+                c.mt16 = sk::conv_h_size_mt(c.c_out, (c.c_in + 7) / 8, c.k, l.d, n, dims[i + 1].h, dims[i + 1].w, false);
+                c.mt16_bwd = sk::conv_h_size_mt(c.c_in, (c.c_out + 7) / 8, c.k, l.d, n, dims[i].h, dims[i].w, true);
             }
             st = alloc_conv(c, training != 0, net->dtype);
             if (st == SK_OK) st = upload_conv(c, training != 0, nullptr, net->dtype);

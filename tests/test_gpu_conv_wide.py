@@ -190,7 +190,10 @@ def gradient_bound(ref, dz, w, dtype):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("k,d,maps,classes,n,h,w,path", [
     # the data gradient of a k x k layer to `classes` maps: zeros around the error map, ReLU mask of the layer below, ragged sizes
-    (3, 1, 112, 40, 2, 33, 37, (1, 0, 1, 3)), (3, 4, 64, 72, 1, 41, 66, (1, 0, 1, 4)), (3, 18, 64, 64, 1, 110, 71, (1, 0, 1, 8)),
+    (3, 1, 112, 40, 2, 33, 37, (1, 0, 1, 3)), (3, 4, 64, 72, 1, 41, 66, (1, 0, 1, 4)), (3, 18, 64, 64, 1, 333, 303, (1, 0, 1, 8)),
+    # sizes kept on conv_h_kernel: padded loads, one chunk, up to 64 columns, the 32 x 16 tile at stride 6
+    (3, 18, 64, 64, 1, 110, 71, (0, 0, 1, 0)), (3, 4, 64, 32, 1, 105, 110, (0, 0, 1, 0)), (3, 1, 64, 96, 1, 42, 64, (0, 0, 1, 0)),
+    (3, 6, 128, 40, 1, 162, 167, (0, 0, 1, 0)),
     (3, 1, 128, 40, 2, 262, 182, (1, 1, 1, 5)), (3, 6, 64, 40, 2, 310, 303, (1, 1, 1, 8)), (3, 1, 64, 40, 2, 402, 391, (1, 2, 1, 8)),
     (1, 1, 112, 40, 2, 23, 61, (1, 0, 1, 1)), (1, 1, 512, 33, 2, 90, 101, (1, 1, 1, 2)), (1, 1, 64, 40, 2, 301, 300, (1, 3, 1, 4)),
 ])
@@ -249,7 +252,8 @@ def test_volume_layer(dtype, k, d, c_in, c_out, size, path):
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 @pytest.mark.parametrize("k,d,maps,classes,size,relu,path", [
     (3, 1, 112, 12, (3, 19, 36), True, (1, 0, 1, 3)), (3, 2, 112, 20, (5, 20, 37), True, (1, 0, 1, 3)), (3, 2, 112, 20, (5, 20, 37), False, (1, 0, 1, 3)),
-    (3, 4, 64, 44, (9, 24, 39), True, (1, 0, 1, 4)), (5, 1, 64, 2, (16, 49, 45), False, (2, 2, 1, 2)), (5, 2, 64, 20, (16, 49, 47), False, (2, 2, 1, 2)),
+    (3, 4, 64, 44, (9, 24, 67), True, (1, 0, 1, 4)), (3, 4, 64, 44, (9, 24, 39), True, (0, 0, 1, 0)),
+    (5, 1, 64, 2, (16, 49, 45), False, (2, 2, 1, 2)), (5, 2, 64, 20, (16, 49, 47), False, (2, 2, 1, 2)),
     (5, 3, 112, 2, (13, 40, 62), False, (2, 2, 1, 4)), (5, 2, 64, 2, (9, 20, 20), False, (0, 0, 1, 0)),
 ])
 def test_volume_data_gradient(dtype, k, d, maps, classes, size, relu, path):

@@ -205,7 +205,7 @@ def test_accepted_16_bit_layers_have_a_kernel(k):
 
 @pytest.mark.parametrize("k,d,c_in,c_out,small,large", [
     (5, 2, 64, 64, 100, 300), (6, 1, 64, 64, 100, 300), (8, 8, 64, 64, 250, 512), (10, 8, 64, 64, 250, 512), (10, 1, 128, 256, 96, 300),
-    (3, 1, 32, 64, 64, 128), (3, 12, 32, 64, 300, None), (1, 1, 32, 64, None, 8),
+    (3, 1, 32, 64, 64, 300), (3, 12, 32, 64, 300, None), (1, 1, 32, 64, None, 8),
 ])
 def test_small_images_keep_the_kernel_of_small_tiles(k, d, c_in, c_out, small, large):
     # measured on both sides: the kernels for many maps take up to 2.7 times as long on images that do not fill the GPU with
@@ -214,3 +214,11 @@ def test_small_images_keep_the_kernel_of_small_tiles(k, d, c_in, c_out, small, l
         if side is not None:
             assert B.sk_probe_conv_path(k, d, c_in, c_out, 1, side, side)[0] == kernel
             assert B.sk_probe_conv_path(k, d, c_in, c_out, 1, side, side, data_gradient=True)[0] == kernel
+
+
+@pytest.mark.parametrize("d,c_in,c_out,small,large", [(4, 32, 64, 200, 300), (1, 96, 64, 64, 65), (10, 64, 64, 200, 400), (6, 64, 128, 162, 200)])
+def test_small_data_gradients_keep_the_kernel_of_small_tiles(d, c_in, c_out, small, large):
+    # 3x3: one chunk, up to 64 columns, padded loads, the 32 x 16 tile at stride 6; the forward layer of the small size does not
+    assert B.sk_probe_conv_path(3, d, c_in, c_out, 1, small, small)[0] == 1
+    assert B.sk_probe_conv_path(3, d, c_in, c_out, 1, small, small, data_gradient=True)[0] == 0
+    assert B.sk_probe_conv_path(3, d, c_in, c_out, 1, large, large, data_gradient=True)[0] == 1
