@@ -593,9 +593,10 @@ static hipError_t launch_conv_f32_nt(const ConvF32Args &a, hipStream_t stream)
         // at 512^2 (measured: 0.24 ms instead of 0.33 ms per 48->48 layer)
         return launch_conv_f32_pf_t<NT, 1, 4, 4, 2>(a, stream);
     }
-    // 5x5 (the tiny net's second layer, 8 -> 16 maps at d = 2 on 96x96: 33 us on the generic kernel, whose chunk waits for its
-    // loads; 4-row tiles because such layers are small).  Maps and weight slabs beyond the 32-bit byte offsets of that kernel
-    // stay on the generic one.
+    // 5x5: 4-row tiles, as for 4x4.  Faster than the generic kernel, whose chunk waits for its loads, on all 246 layers and data
+    // gradients measured (8 to 128 -> 16 to 256 maps, 48^2 to 2 x 768^2, d = 1 to 16): 8 -> 16 at 96^2 25 -> 8.5 us, 48 -> 128 at
+    // 512^2, d = 2 1540 -> 685 us (117 TFLOP/s), its data gradient 1804 -> 787 us.  Maps and weight slabs beyond the 32-bit byte
+    // offsets of the prefetching kernel stay on the generic one.
     if (a.k == 5 && halo <= 64 && (long)a.H * a.W < (1L << 29) && 100L * a.n_pad < (1L << 29)) return launch_conv_f32_pf_t<NT, 1, 5, 4, 2>(a, stream);
     // the large kernels of the USK-Net (6x6 at d = 1, 8x8 at d = 8) and of the paper's SK-Net (10x10 at
     // d = 8, a 73-pixel window: three column groups, forward only); one chunk of four maps holds

@@ -1738,6 +1738,8 @@ __global__ void __launch_bounds__(256) pack_weights_h_batch_kernel(PackHJobs b)
 // conv_h_wide would take on conv_h_kernel, whose tiles are smaller (a quarter to three quarters of the maps): one that has not
 // enough large tiles to fill the GPU runs longer on each of them.  The weights must be packed for the same value.
 //
+// 1x1: never.  Of 156 layers and data gradients (32 -> 64 to 1024 -> 512 maps, 48 -> 200 among them, 32^2 to 8 x 512^2, bf16) none is
+// faster here than there beyond half a percent.
 // k > 4: by rounds of tiles per CU, here and there.  A tile of the kernel for many maps costs 1.25 (5x5, 6x6), 1.6 (8x8) and
 // 2.5 (10x10) of conv_h_kernel's: over 928 layers (32 to 128 -> 64 to 1024 maps, 8^2 to 3 x 300^2, d = 1 to 8, bf16) the kernel
 // for many maps took 0.95 to 2.74 of the time below these lines (10x10 64 -> 64 at 32^2: 79 us of 37, 8x8 at 250^2: 66 of 55)
