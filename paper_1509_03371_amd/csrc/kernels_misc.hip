@@ -52,7 +52,10 @@ hipError_t launch_mirror_pad_f32(const float *in, float *out, int planes, int h,
 }
 
 // ---- max pooling with kernel stride d and layer stride s (Section 5.2.1) --------------------------
+// Winner codes: i * k + j in a byte; k = 2, s = 1 (the SK pools) adds POOL_POSITIVE where the maximum is positive: the
+// backward pass has the ReLU mask of the layer below in it, whose output at the winner IS the maximum.
 // grid: x = column blocks, y = output row, z = plane; no index division on the hot path
+constexpr int POOL_POSITIVE = 4;
 __global__ void maxpool_f32_kernel(const float *x, float *y, uint8_t *tap, int H, int W, int Ho, int Wo, int k, int d, int s)
 {
     const int xx = blockIdx.x * blockDim.x + threadIdx.x, yy = blockIdx.y;
@@ -71,55 +74,74 @@ __global__ void maxpool_f32_kernel(const float *x, float *y, uint8_t *tap, int H
         }
     const long q = (p * Ho + yy) * Wo + xx;
     y[q] = best;
-    if (tap) tap[q] = (uint8_t)code;
+    if (tap) tap[q] = (uint8_t)(code | (k == 2 && s == 1 && best > 0.f ? POOL_POSITIVE : 0));
 }
 
+// four consecutive columns of a row, at any column: rows of odd maps start at any multiple of four (codes: any) bytes, and
+// global memory takes such 16-byte (4-byte) accesses
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned uint1u __attribute__((aligned(1)));
+
 // k = 2, s = 1 (every SK pool of the paper): window (y, x) is {h[y], h[y + d]} where h[r] is the
-// first maximum of X[r][x], X[r][x + d].  A thread walks one column down the rows y0, y0 + d,
+// first maximum of X[r][x], X[r][x + d].  A thread walks four columns down the rows y0, y0 + d,
 // y0 + 2d, ... of one residue class mod d, so each h is formed once and serves both windows it
-// belongs to, and a block reads every input row it needs exactly once.  grid: x = column blocks,
-// y = residue class x segments of M chain links, z = plane.  Winner codes follow the row-major
+// belongs to, and each input row is read once.  Winner codes follow the row-major
 // scan (0,1 for row y; 2,3 for row y + d), strictly-greater replaces.
+// grid: x = (residue class, block of four columns) linearly, y = segments of M chain links, z = plane.
+// Bound by HBM, but only with four columns a thread: with one, the 32 memory instructions of eight windows of 64 threads
+// cost more than their bytes (48 maps at 527x527: 36.6 -> 26.4 us with codes = 4.5 TB/s, 32.3 -> 22.6 without).  The last
+// block of a row overlaps its neighbour.
 template <bool TAP>
-__global__ void __launch_bounds__(256) maxpool2_chain_f32_kernel(const float *__restrict__ x, float *__restrict__ y,
-                                                                 uint8_t *__restrict__ tap, int H, int W, int Ho, int Wo,
-                                                                 int d, int M, int nseg)
+__global__ void __launch_bounds__(64) maxpool2_chain_f32_kernel(const float *__restrict__ x, float *__restrict__ y,
+                                                                uint8_t *__restrict__ tap, int H, int W, int Ho, int Wo,
+                                                                int d, int M)
 {
-    const int xx = blockIdx.x * blockDim.x + threadIdx.x;
-    const int phase = blockIdx.y / nseg, seg = blockIdx.y - phase * nseg;
-    if (xx >= Wo || phase >= Ho) return;
-    const int links = (Ho - phase + d - 1) / d;
-    const int m0 = seg * M, m1 = min(links, m0 + M);
+    const int w4 = (Wo + 3) / 4, idx = blockIdx.x * 64 + threadIdx.x;
+    const int phase = idx / w4, xx = min(4 * (idx - phase * w4), Wo - 4), m0 = blockIdx.y * M;
+    if (phase >= d || phase >= Ho) return;
+    const int m1 = min((Ho - phase + d - 1) / d, m0 + M);
     if (m0 >= m1) return;
     const long p = blockIdx.z;
     const long rstep = (long)d * W, ostep = (long)d * Wo;
     const float *src = x + (p * H + phase + (long)m0 * d) * W + xx;
     float *dst = y + (p * Ho + phase + (long)m0 * d) * Wo + xx;
     uint8_t *tdst = TAP ? tap + (p * Ho + phase + (long)m0 * d) * Wo + xx : nullptr;
-    float h = src[0];
-    int hc = 0;
-    {
-        const float b = src[d];
-        if (b > h) { h = b; hc = 1; }
-    }
-    constexpr int U = 8;
+    // h: the row's maxima, hc: bit 8c is set where the right one of the pair is the greater
+    auto row = [](const float4u a, const float4u b, float4u &h, unsigned &hc) {
+        hc = 0u;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            h[c] = b[c] > a[c] ? b[c] : a[c];
+            if (TAP) hc |= b[c] > a[c] ? 1u << (8 * c) : 0u;
+        }
+    };
+    auto at = [](const float *q) { return *reinterpret_cast<const float4u *>(q); };
+    float4u h;
+    unsigned hc;
+    row(at(src), at(src + d), h, hc);
+    constexpr int U = 4;
     for (int m = m0; m < m1; m += U) {
-        float a[U], b[U];
+        float4u a[U], b[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {                     // all loads of the group first
             const float *r = src + (m + u < m1 ? (long)(u + 1) * rstep : 0);
-            a[u] = r[0];
-            b[u] = r[d];
+            a[u] = at(r);
+            b[u] = at(r + d);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (m + u >= m1) break;
-            float h2 = a[u];
-            int hc2 = 0;
-            if (b[u] > h2) { h2 = b[u]; hc2 = 1; }
-            const bool lower = h2 > h;
-            dst[(long)u * ostep] = lower ? h2 : h;
-            if (TAP) tdst[(long)u * ostep] = (uint8_t)(lower ? 2 + hc2 : hc);
+            float4u h2, best;
+            unsigned hc2, code = 0u;
+            row(a[u], b[u], h2, hc2);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const bool lower = h2[c] > h[c];
+                best[c] = lower ? h2[c] : h[c];
+                if (TAP) code |= (((lower ? hc2 : hc) >> (8 * c) & 1u) | (lower ? 2u : 0u) | (best[c] > 0.f ? POOL_POSITIVE : 0u)) << (8 * c);
+            }
+            *reinterpret_cast<float4u *>(dst + (long)u * ostep) = best;
+            if (TAP) *reinterpret_cast<uint1u *>(tdst + (long)u * ostep) = code;
             h = h2;
             hc = hc2;
         }
@@ -133,14 +155,12 @@ hipError_t launch_maxpool_f32(const float *x, float *y, uint8_t *tap, int planes
                               int Ho, int Wo, int k, int d, int s, hipStream_t stream)
 {
     if (Ho > 65535 || planes > 65535) return hipErrorInvalidValue;
-    if (k == 2 && s == 1 && Ho == H - d && Wo == W - d) {
-        const PoolCut c = pool_cut(Ho, Wo, d, planes, 8);
-        if ((long)d * c.nseg <= 65535) {
-            const dim3 grid((Wo + c.threads - 1) / c.threads, (unsigned)(d * c.nseg), (unsigned)planes);
-            if (tap) hipLaunchKernelGGL(maxpool2_chain_f32_kernel<true>, grid, dim3(c.threads), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len, c.nseg);
-            else hipLaunchKernelGGL(maxpool2_chain_f32_kernel<false>, grid, dim3(c.threads), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len, c.nseg);
-            return hipGetLastError();
-        }
+    if (k == 2 && s == 1 && Ho == H - d && Wo == W - d && Wo >= 4) {
+        const PoolCut c = pool_cut4(Ho, Wo, d, planes, 4);
+        const dim3 grid((unsigned)(((long)d * ((Wo + 3) / 4) + 63) / 64), (unsigned)c.nseg, (unsigned)planes);
+        if (tap) hipLaunchKernelGGL(maxpool2_chain_f32_kernel<true>, grid, dim3(64), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len);
+        else hipLaunchKernelGGL(maxpool2_chain_f32_kernel<false>, grid, dim3(64), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len);
+        return hipGetLastError();
     }
     hipLaunchKernelGGL(maxpool_f32_kernel, dim3((Wo + 255) / 256, Ho, planes), dim3(256), 0, stream, x, y, tap,
                        H, W, Ho, Wo, k, d, s);
@@ -398,9 +418,7 @@ hipError_t launch_place_tap_f32(const float *src, float *dst, long maps, int k, 
 // Gather form of the pool gradient: input sample (u, v) can only have won the windows whose
 // output sits at (u - i*d, v - j*d); it collects dY from those whose recorded tap is (i, j).
 // No atomics, so the result does not depend on scheduling.
-// K > 0: compile-time kernel size, the K*K codes and gradients fetched together (windows outside the output read
-// element 0 and are discarded); K = 0: any k
-template <int K>
+// Any k; k = 2 comes here only for maps narrower than the four columns of the chain form below.
 __global__ void maxpool_bwd_f32_kernel(const float *__restrict__ dy, const uint8_t *__restrict__ tap, const float *__restrict__ relu_src,
                                        float *__restrict__ dx, int H, int W, int Ho, int Wo, int k, int d)
 {
@@ -408,33 +426,14 @@ __global__ void maxpool_bwd_f32_kernel(const float *__restrict__ dy, const uint8
     if (v >= W) return;
     const long p = blockIdx.z;
     float acc = 0.f;
-    if constexpr (K > 0) {
-        long o[K * K];
-        bool ok[K * K];
-#pragma unroll
-        for (int t = 0; t < K * K; ++t) {
-            const int yy = u - (t / K) * d, xx = v - (t % K) * d;
-            ok[t] = yy >= 0 && yy < Ho && xx >= 0 && xx < Wo;
-            o[t] = ok[t] ? (p * Ho + yy) * Wo + xx : 0;
-        }
-        uint8_t code[K * K];
-        float g[K * K];
-#pragma unroll
-        for (int t = 0; t < K * K; ++t) code[t] = tap[o[t]];
-#pragma unroll
-        for (int t = 0; t < K * K; ++t) g[t] = dy[o[t]];
-#pragma unroll
-        for (int t = 0; t < K * K; ++t) acc += (ok[t] && code[t] == (uint8_t)t) ? g[t] : 0.f;
-    } else {
-        for (int i = 0; i < k; ++i) {
-            const int yy = u - i * d;
-            if (yy < 0 || yy >= Ho) continue;
-            for (int j = 0; j < k; ++j) {
-                const int xx = v - j * d;
-                if (xx < 0 || xx >= Wo) continue;
-                const long o = (p * Ho + yy) * Wo + xx;
-                if (tap[o] == i * k + j) acc += dy[o];
-            }
+    for (int i = 0; i < k; ++i) {
+        const int yy = u - i * d;
+        if (yy < 0 || yy >= Ho) continue;
+        for (int j = 0; j < k; ++j) {
+            const int xx = v - j * d;
+            if (xx < 0 || xx >= Wo) continue;
+            const long o = (p * Ho + yy) * Wo + xx;
+            if ((k == 2 ? tap[o] & 3 : tap[o]) == i * k + j) acc += dy[o];
         }
     }
     const long q = (p * H + u) * W + v;
@@ -442,14 +441,90 @@ __global__ void maxpool_bwd_f32_kernel(const float *__restrict__ dy, const uint8
     dx[q] = acc;
 }
 
+// k = 2: a thread walks four columns v .. v + 3 of dX down the rows u = y0, y0 + d, ... of one residue class, as the forward
+// kernel walks its windows.  Row u collects from the windows of rows u (codes 0 at column v, 1 at column v - d) and u - d
+// (codes 2, 3), so a window row is loaded once per walk and kept for the next step; and the codes carry the ReLU mask
+// (MASKED), so the layer's output is not read at all: 13 -> 9 bytes per sample.  Grid and four columns a thread as in the
+// forward kernel, for the same reason (48 maps at 527x527: 28.5 us; one column a thread in this form 44.2, one that fetches its
+// four windows and the mask 69.7).
+template <bool MASKED>
+__global__ void __launch_bounds__(64) maxpool2_bwd_chain_f32_kernel(const float *__restrict__ dy, const uint8_t *__restrict__ tap,
+                                                                    float *__restrict__ dx, int H, int W, int Ho, int Wo, int d, int M)
+{
+    const int w4 = (W + 3) / 4, idx = blockIdx.x * 64 + threadIdx.x;
+    const int phase = idx / w4, v = min(4 * (idx - phase * w4), W - 4), m0 = blockIdx.y * M;
+    if (phase >= d || phase >= H) return;
+    const int m1 = min((H - phase + d - 1) / d, m0 + M);
+    if (m0 >= m1) return;
+    const long p = blockIdx.z;
+    // windows at columns v .. v + 3 (a) and v - d .. (b).  Where some of the four lie outside the row the access is moved
+    // inside it and what it brought is moved back: by sa to lower, by sb to higher elements (4: none of them exists)
+    const int xa = min(v, Wo - 4), xb = max(v - d, 0), sa = min(v - xa, 4), sb = min(xb - (v - d), 4);
+    constexpr unsigned KEEP = MASKED ? 7u : 3u, WANT = MASKED ? POOL_POSITIVE : 0u;
+    constexpr unsigned NONE_A = 0x01010101u, NONE_B = 0u;            // codes that no element of a, b is asked for
+    struct Row {
+        float4u ga, gb;
+        unsigned ca, cb;
+    };
+    auto load = [&](int y) {                              // window row y, clamped into the map
+        const long base = (p * Ho + (y < 0 ? 0 : (y < Ho ? y : Ho - 1))) * Wo;
+        Row r;
+        r.ga = *reinterpret_cast<const float4u *>(dy + base + xa);
+        r.gb = *reinterpret_cast<const float4u *>(dy + base + xb);
+        r.ca = *reinterpret_cast<const uint1u *>(tap + base + xa);
+        r.cb = *reinterpret_cast<const uint1u *>(tap + base + xb);
+        return r;
+    };
+    auto settle = [&](Row &r, int y) {
+        const bool row = y >= 0 && y < Ho;
+        r.ca = row ? (unsigned)((((unsigned long)NONE_A << 32) | r.ca) >> (8 * sa)) : NONE_A;
+        r.cb = row ? (unsigned)((unsigned long)r.cb << (8 * sb)) : NONE_B;
+        if (sa & 1) r.ga = float4u{r.ga[1], r.ga[2], r.ga[3], 0.f};
+        if (sa & 2) r.ga = float4u{r.ga[2], r.ga[3], 0.f, 0.f};
+        if (sb & 1) r.gb = float4u{0.f, r.gb[0], r.gb[1], r.gb[2]};
+        if (sb & 2) r.gb = float4u{0.f, 0.f, r.gb[0], r.gb[1]};
+    };
+    int y = phase + m0 * d;
+    float *dst = dx + (p * H + y) * W + v;
+    const long ostep = (long)d * W;
+    Row above = load(y - d);
+    settle(above, y - d);
+    constexpr int U = 4;
+    for (int m = m0; m < m1; m += U) {
+        Row r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = load(y + u * d);          // all loads of the group first
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (m + u >= m1) break;
+            settle(r[u], y + u * d);
+            float4u g;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                auto pick = [&](unsigned codes, unsigned code, float val) { return (codes >> (8 * c) & KEEP) == (WANT | code) ? val : 0.f; };
+                g[c] = ((pick(r[u].ca, 0u, r[u].ga[c]) + pick(r[u].cb, 1u, r[u].gb[c])) + pick(above.ca, 2u, above.ga[c])) + pick(above.cb, 3u, above.gb[c]);
+            }
+            *reinterpret_cast<float4u *>(dst + (long)u * ostep) = g;
+            above = r[u];
+        }
+        y += U * d;
+        dst += (long)U * ostep;
+    }
+}
+
 hipError_t launch_maxpool_bwd_f32(const float *dy, const uint8_t *tap, const float *relu_src,
                                   float *dx, int planes, int H, int W, int Ho, int Wo, int k, int d,
                                   hipStream_t stream)
 {
     if (H > 65535 || planes > 65535) return hipErrorInvalidValue;
-    const dim3 grid((W + 255) / 256, H, planes);
-    if (k == 2) hipLaunchKernelGGL(maxpool_bwd_f32_kernel<2>, grid, dim3(256), 0, stream, dy, tap, relu_src, dx, H, W, Ho, Wo, k, d);
-    else hipLaunchKernelGGL(maxpool_bwd_f32_kernel<0>, grid, dim3(256), 0, stream, dy, tap, relu_src, dx, H, W, Ho, Wo, k, d);
+    if (k == 2 && Ho == H - d && Wo == W - d && Ho >= 1 && Wo >= 4) {
+        const PoolCut c = pool_cut4(H, W, d, planes, 4);
+        const dim3 grid((unsigned)(((long)d * ((W + 3) / 4) + 63) / 64), (unsigned)c.nseg, (unsigned)planes);
+        if (relu_src) hipLaunchKernelGGL(maxpool2_bwd_chain_f32_kernel<true>, grid, dim3(64), 0, stream, dy, tap, dx, H, W, Ho, Wo, d, c.len);
+        else hipLaunchKernelGGL(maxpool2_bwd_chain_f32_kernel<false>, grid, dim3(64), 0, stream, dy, tap, dx, H, W, Ho, Wo, d, c.len);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(maxpool_bwd_f32_kernel, dim3((W + 255) / 256, H, planes), dim3(256), 0, stream, dy, tap, relu_src, dx, H, W, Ho, Wo, k, d);
     return hipGetLastError();
 }
 
@@ -460,7 +535,7 @@ __global__ void tap_to_index_kernel(const uint8_t *tap, int32_t *idx, int planes
     for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < total; q += (long)gridDim.x * blockDim.x) {
         const int xx = (int)(q % Wo);
         const int yy = (int)((q / Wo) % Ho);
-        const int code = tap[q], i = code / k, j = code - i * k;
+        const int code = k == 2 && s == 1 ? tap[q] & 3 : tap[q], i = code / k, j = code - i * k;
         idx[q] = (s * yy + i * d) * W + s * xx + j * d;
     }
 }

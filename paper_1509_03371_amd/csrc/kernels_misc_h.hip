@@ -107,9 +107,23 @@ hipError_t launch_unpack_h(const void *in, float *out, int dtype, int n, int c, 
 }
 
 // ---- max pooling with kernel stride d and layer stride s (Section 5.2.1) on octets --------------------
+// winner code of element e of unit q (see maxpool_h_kernel)
+__device__ __forceinline__ unsigned pool_code_h(const void *tap, long q, int e, bool bits)
+{
+    if (bits) {
+        const unsigned w = static_cast<const unsigned *>(tap)[q];
+        return ((w >> e) & 1u) | (((w >> (8 + e)) & 1u) << 1);
+    }
+    return (static_cast<const uint2v *>(tap)[q][e >> 2] >> ((e & 3) * 8)) & 0xffu;
+}
+
+// Winner codes: one byte i * k + j per element, laid out like y -- except for k = 2, s = 1 (pool_bits_h), the SK pools,
+// whose codes are three bit planes of the octet in one 32-bit word per unit: bit e of byte 0 = j, of byte 1 = i of
+// element e's winner, of byte 2 = its value is positive.  Half the bytes, and the backward pass has the ReLU mask of the
+// layer below in them: that layer's output at the winner IS the window's maximum.
 // grid: x = column blocks, y = output row, z = plane (image x octet); no index division
 template <int DT>
-__global__ void maxpool_h_kernel(const uint4v *x, uint4v *y, uint2v *tap, int H, int W, int Ho, int Wo,
+__global__ void maxpool_h_kernel(const uint4v *x, uint4v *y, void *tap, int H, int W, int Ho, int Wo,
                                  int k, int d, int s)
 {
     const int xx = blockIdx.x * blockDim.x + threadIdx.x, yy = blockIdx.y;
@@ -141,9 +155,16 @@ __global__ void maxpool_h_kernel(const uint4v *x, uint4v *y, uint2v *tap, int H,
         }
     const long q = (p * Ho + yy) * Wo + xx;
     y[q] = uint4v{bits[0] | (bits[1] << 16), bits[2] | (bits[3] << 16), bits[4] | (bits[5] << 16), bits[6] | (bits[7] << 16)};
-    if (tap)
-        tap[q] = uint2v{code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24),
-                        code[4] | (code[5] << 8) | (code[6] << 16) | (code[7] << 24)};
+    if (!tap) return;
+    if (pool_bits_h(k, s)) {
+        unsigned word = 0u;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) word |= ((code[e] & 1u) << e) | ((code[e] >> 1) << (8 + e)) | ((best[e] > 0.f ? 1u : 0u) << (16 + e));
+        static_cast<unsigned *>(tap)[q] = word;
+    } else {
+        static_cast<uint2v *>(tap)[q] = uint2v{code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24),
+                                               code[4] | (code[5] << 8) | (code[6] << 16) | (code[7] << 24)};
+    }
 }
 
 // k = 2, s = 1 (every SK pool of the paper): window (y, x) is {h[y], h[y + d]} where h[r] is the
@@ -151,8 +172,8 @@ __global__ void maxpool_h_kernel(const uint4v *x, uint4v *y, uint2v *tap, int H,
 // y0 + 2d, ... of one residue class mod d, so each h is formed once and serves both windows it
 // belongs to, and a block reads every input row it needs exactly once (no second workgroup, on
 // another XCD with another L2, fetches the same rows again).  grid: x = column blocks,
-// y = residue class x segments of M chain links, z = plane.  Winner codes follow the row-major
-// scan: 0,1 for row y, 2,3 for row y + d, strictly-greater replaces.
+// y = residue class x segments of M chain links, z = plane.  The winner follows the row-major
+// scan: row y before row y + d, strictly-greater replaces.
 template <int DT>
 __device__ __forceinline__ void row_first_max(const uint4v a, const uint4v b, uint4v &h, unsigned &hc)
 {
@@ -168,7 +189,7 @@ __device__ __forceinline__ void row_first_max(const uint4v a, const uint4v b, ui
 
 template <int DT, bool TAP>
 __global__ void __launch_bounds__(256) maxpool2_chain_h_kernel(const uint4v *__restrict__ x, uint4v *__restrict__ y,
-                                                               uint2v *__restrict__ tap, int H, int W, int Ho, int Wo,
+                                                               unsigned *__restrict__ tap, int H, int W, int Ho, int Wo,
                                                                int d, int M, int nseg)
 {
     const int xx = blockIdx.x * blockDim.x + threadIdx.x;
@@ -181,7 +202,7 @@ __global__ void __launch_bounds__(256) maxpool2_chain_h_kernel(const uint4v *__r
     const long rstep = (long)d * W;
     const uint4v *src = x + (p * H + phase + (long)m0 * d) * W + xx;
     uint4v *dst = y + (p * Ho + phase + (long)m0 * d) * Wo + xx;
-    uint2v *tdst = TAP ? tap + (p * Ho + phase + (long)m0 * d) * Wo + xx : nullptr;
+    unsigned *tdst = TAP ? tap + (p * Ho + phase + (long)m0 * d) * Wo + xx : nullptr;
     const long ostep = (long)d * Wo;
     uint4v h;
     unsigned hc;
@@ -203,25 +224,15 @@ __global__ void __launch_bounds__(256) maxpool2_chain_h_kernel(const uint4v *__r
             unsigned hc2;
             row_first_max<DT>(a[u], b[u], h2, hc2);
             uint4v o;
-            unsigned c_lo = 0u, c_hi = 0u;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                unsigned msk = 0u;
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh) {
-                    const int e = 2 * w + hh;
-                    const unsigned v1 = hh ? (h[w] >> 16) : (h[w] & 0xffffu), v2 = hh ? (h2[w] >> 16) : (h2[w] & 0xffffu);
-                    const bool lower = up16<DT>(v2) > up16<DT>(v1);
-                    if (lower) msk |= hh ? 0xffff0000u : 0x0000ffffu;
-                    if (TAP) {
-                        const unsigned code = lower ? 2u + ((hc2 >> e) & 1u) : ((hc >> e) & 1u);
-                        if (e < 4) c_lo |= code << (8 * e); else c_hi |= code << (8 * (e - 4));
-                    }
-                }
-                o[w] = (h[w] & ~msk) | (h2[w] & msk);
-            }
+            unsigned lower;                               // bit e: the winner lies in row y + d
+            row_first_max<DT>(h, h2, o, lower);
             dst[(long)u * ostep] = o;
-            if (TAP) tdst[(long)u * ostep] = uint2v{c_lo, c_hi};
+            if (TAP) {
+                unsigned pos = 0u;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) pos |= up16<DT>(elem16(o, e)) > 0.f ? 1u << e : 0u;
+                tdst[(long)u * ostep] = (hc & ~lower) | (hc2 & lower) | (lower << 8) | (pos << 16);
+            }
             h = h2;
             hc = hc2;
         }
@@ -241,7 +252,7 @@ hipError_t launch_maxpool_h(const void *x, void *y, void *tap, int dtype, long p
             const dim3 grid((Wo + c.threads - 1) / c.threads, (unsigned)(d * c.nseg), (unsigned)planes8);
             const uint4v *xi = static_cast<const uint4v *>(x);
             uint4v *yo = static_cast<uint4v *>(y);
-            uint2v *tp = static_cast<uint2v *>(tap);
+            unsigned *tp = static_cast<unsigned *>(tap);
             if (dtype == 1) {
                 if (tap) hipLaunchKernelGGL((maxpool2_chain_h_kernel<1, true>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
                 else hipLaunchKernelGGL((maxpool2_chain_h_kernel<1, false>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
@@ -255,10 +266,10 @@ hipError_t launch_maxpool_h(const void *x, void *y, void *tap, int dtype, long p
     const dim3 grid((Wo + 255) / 256, Ho, (unsigned)planes8);
     if (dtype == 1)
         hipLaunchKernelGGL(maxpool_h_kernel<1>, grid, dim3(256), 0, stream, static_cast<const uint4v *>(x),
-                           static_cast<uint4v *>(y), static_cast<uint2v *>(tap), H, W, Ho, Wo, k, d, s);
+                           static_cast<uint4v *>(y), tap, H, W, Ho, Wo, k, d, s);
     else
         hipLaunchKernelGGL(maxpool_h_kernel<2>, grid, dim3(256), 0, stream, static_cast<const uint4v *>(x),
-                           static_cast<uint4v *>(y), static_cast<uint2v *>(tap), H, W, Ho, Wo, k, d, s);
+                           static_cast<uint4v *>(y), tap, H, W, Ho, Wo, k, d, s);
     return hipGetLastError();
 }
 
@@ -469,11 +480,10 @@ hipError_t launch_crop_copy_h(const void *src, void *dst, int n, int c8, int Hs,
 
 // Gather form of the pool gradient (s = 1): input unit (u, v) collects, per map, dY of the windows
 // whose recorded winner it is.  Sums are formed in fp32 and rounded once.  relu_src (optional,
-// same shape as dx) zeroes the result where the layer below produced a non-positive value.
-// K > 0: compile-time kernel size, the K*K code and gradient octets fetched together (windows outside the
-// output read unit 0 and are discarded); K = 0: any k.
-template <int DT, int K>
-__global__ void maxpool_bwd_h_kernel(const uint4v *__restrict__ dy, const uint2v *__restrict__ tap, const uint4v *__restrict__ relu_src,
+// same shape as dx) zeroes the result where the layer below produced a non-positive value (for k = 2 the codes say so).
+// Any k; k = 2 comes here only where the grid of the chain form below would be too large.
+template <int DT>
+__global__ void maxpool_bwd_h_kernel(const uint4v *__restrict__ dy, const void *__restrict__ tap, const uint4v *__restrict__ relu_src,
                                      uint4v *__restrict__ dx, int H, int W, int Ho, int Wo, int k, int d)
 {
     const int v = blockIdx.x * blockDim.x + threadIdx.x, u = blockIdx.y;
@@ -482,29 +492,6 @@ __global__ void maxpool_bwd_h_kernel(const uint4v *__restrict__ dy, const uint2v
     float acc[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    if constexpr (K > 0) {
-        long o[K * K];
-        bool ok[K * K];
-#pragma unroll
-        for (int t = 0; t < K * K; ++t) {
-            const int yy = u - (t / K) * d, xx = v - (t % K) * d;
-            ok[t] = yy >= 0 && yy < Ho && xx >= 0 && xx < Wo;
-            o[t] = ok[t] ? (p * Ho + yy) * Wo + xx : 0;
-        }
-        uint2v c[K * K];
-        uint4v g[K * K];
-#pragma unroll
-        for (int t = 0; t < K * K; ++t) c[t] = tap[o[t]];
-#pragma unroll
-        for (int t = 0; t < K * K; ++t) g[t] = dy[o[t]];
-#pragma unroll
-        for (int t = 0; t < K * K; ++t)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const unsigned code = (c[t][e >> 2] >> ((e & 3) * 8)) & 0xffu;
-                acc[e] += (ok[t] && code == (unsigned)t) ? up16<DT>(elem16(g[t], e)) : 0.f;
-            }
-    } else
     for (int i = 0; i < k; ++i) {
         const int yy = u - i * d;
         if (yy < 0 || yy >= Ho) continue;
@@ -512,14 +499,11 @@ __global__ void maxpool_bwd_h_kernel(const uint4v *__restrict__ dy, const uint2v
             const int xx = v - j * d;
             if (xx < 0 || xx >= Wo) continue;
             const long o = (p * Ho + yy) * Wo + xx;
-            const uint2v c = tap[o];
             const uint4v g = dy[o];
             const unsigned want = i * k + j;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const unsigned code = (c[e >> 2] >> ((e & 3) * 8)) & 0xffu;
-                if (code == want) acc[e] += up16<DT>(elem16(g, e));
-            }
+            for (int e = 0; e < 8; ++e)
+                if (pool_code_h(tap, o, e, pool_bits_h(k, 1)) == want) acc[e] += up16<DT>(elem16(g, e));
         }
     }
     const long q = (p * H + u) * W + v;
@@ -535,18 +519,108 @@ __global__ void maxpool_bwd_h_kernel(const uint4v *__restrict__ dy, const uint2v
     dx[q] = uint4v{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16), hv[4] | (hv[5] << 16), hv[6] | (hv[7] << 16)};
 }
 
+// k = 2: a thread walks column v of dX down the rows u = y0, y0 + d, ... of one residue class, as the forward kernel walks
+// its windows.  Row u collects from the windows of rows u (codes 0 at column v, 1 at column v - d) and u - d (codes 2, 3),
+// so every window row is loaded once per walk and kept for the next step: 36 bytes read and 16 written per unit against
+// 112 and 16 when each input unit fetched its four windows and the layer's output for the ReLU mask (MASKED takes that from
+// the codes).  Bound by HBM (6 B read, 2 written per element and direction would be the least without codes) and, close
+// behind, by the vector instructions that pick among 32 (element, window) pairs: with bit planes the codes of a unit are
+// eight bitwise operations and a pick is a sign-extended bit, an AND and the addition.  48 maps of 8 x 1066^2: 562 -> 410 us
+// (4.8 TB/s), the forward pass 447 -> 409; at 527x527 20.7 -> 15.8.
+template <int DT, bool MASKED>
+__global__ void __launch_bounds__(256) maxpool2_bwd_chain_h_kernel(const uint4v *__restrict__ dy, const unsigned *__restrict__ tap,
+                                                                   uint4v *__restrict__ dx, int H, int W, int Ho, int Wo, int d, int M, int nseg)
+{
+    const int v = blockIdx.x * blockDim.x + threadIdx.x;
+    const int phase = blockIdx.y / nseg, seg = blockIdx.y - phase * nseg;
+    if (v >= W || phase >= H) return;
+    const int links = (H - phase + d - 1) / d;
+    const int m0 = seg * M, m1 = min(links, m0 + M);
+    if (m0 >= m1) return;
+    const long p = blockIdx.z;
+    // windows at column v and at column v - d (clamped into the row; `in`: all ones where the window exists)
+    const unsigned xa = (unsigned)min(v, Wo - 1), xb = (unsigned)max(v - d, 0);
+    const unsigned ina = v < Wo ? 0xffu : 0u, inb = v >= d ? 0xffu : 0u;
+    struct Row {
+        uint4v ga, gb;
+        unsigned ca, cb;
+    };
+    auto load = [&](int y) {                              // window row y, clamped into the map
+        const long base = (p * Ho + (y < 0 ? 0 : (y < Ho ? y : Ho - 1))) * Wo;     // uniform
+        Row r;
+        r.ga = dy[base + xa];
+        r.gb = dy[base + xb];
+        r.ca = tap[base + xa];
+        r.cb = tap[base + xb];
+        return r;
+    };
+    // bit e of t[c]: element e of that window chose code c (c = 0, 2 at column v; 1, 3 at column v - d)
+    auto picks = [&](const Row &r, int y, unsigned (&t)[4]) {
+        const unsigned row = y >= 0 && y < Ho ? 0xffu : 0u;                        // uniform
+        const unsigned pa = (MASKED ? r.ca >> 16 : 0xffu) & ina & row, pb = (MASKED ? r.cb >> 16 : 0xffu) & inb & row;
+        const unsigned a0 = pa & ~r.ca, b1 = pb & r.cb, la = r.ca >> 8, lb = r.cb >> 8;
+        t[0] = a0 & ~la;
+        t[1] = b1 & ~lb;
+        t[2] = a0 & la;
+        t[3] = b1 & lb;
+    };
+    auto pick = [](uint4v g, unsigned t, int e) {         // the element, or +0
+        return __int_as_float(__float_as_int(up16<DT>(elem16(g, e))) & ((int)(t << (31 - e)) >> 31));
+    };
+    int y = phase + m0 * d;
+    uint4v *dst = dx + (p * H + y) * W + v;
+    const long ostep = (long)d * W;
+    Row above = load(y - d);
+    unsigned ta[4];
+    picks(above, y - d, ta);
+    constexpr int U = 4;
+    for (int m = m0; m < m1; m += U) {
+        Row r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = load(y + u * d);          // all loads of the group first
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (m + u >= m1) break;
+            unsigned t[4];
+            picks(r[u], y + u * d, t);
+            unsigned hv[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                hv[e] = down16<DT>(((pick(r[u].ga, t[0], e) + pick(r[u].gb, t[1], e)) + pick(above.ga, ta[2], e)) + pick(above.gb, ta[3], e));
+            dst[(long)u * ostep] = uint4v{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16), hv[4] | (hv[5] << 16), hv[6] | (hv[7] << 16)};
+            above = r[u];
+            ta[2] = t[2];
+            ta[3] = t[3];
+        }
+        y += U * d;
+        dst += (long)U * ostep;
+    }
+}
+
 hipError_t launch_maxpool_bwd_h(const void *dy, const void *tap, const void *relu_src, void *dx, int dtype,
                                 long planes8, int H, int W, int Ho, int Wo, int k, int d, hipStream_t stream)
 {
     if (H > 65535 || planes8 > 65535) return hipErrorInvalidValue;
-    const dim3 grid((W + 255) / 256, H, (unsigned)planes8);
     const uint4v *g = static_cast<const uint4v *>(dy), *rs = static_cast<const uint4v *>(relu_src);
-    const uint2v *tp = static_cast<const uint2v *>(tap);
     uint4v *out = static_cast<uint4v *>(dx);
-    if (dtype == 1 && k == 2) hipLaunchKernelGGL((maxpool_bwd_h_kernel<1, 2>), grid, dim3(256), 0, stream, g, tp, rs, out, H, W, Ho, Wo, k, d);
-    else if (dtype == 1) hipLaunchKernelGGL((maxpool_bwd_h_kernel<1, 0>), grid, dim3(256), 0, stream, g, tp, rs, out, H, W, Ho, Wo, k, d);
-    else if (k == 2) hipLaunchKernelGGL((maxpool_bwd_h_kernel<2, 2>), grid, dim3(256), 0, stream, g, tp, rs, out, H, W, Ho, Wo, k, d);
-    else hipLaunchKernelGGL((maxpool_bwd_h_kernel<2, 0>), grid, dim3(256), 0, stream, g, tp, rs, out, H, W, Ho, Wo, k, d);
+    if (k == 2 && Ho == H - d && Wo == W - d && Ho >= 1 && Wo >= 1) {
+        const PoolCut c = pool_cut(H, W, d, planes8, 4);
+        if ((long)d * c.nseg <= 65535) {
+            const dim3 grid((W + c.threads - 1) / c.threads, (unsigned)(d * c.nseg), (unsigned)planes8);
+            const unsigned *tp = static_cast<const unsigned *>(tap);
+            if (dtype == 1) {
+                if (rs) hipLaunchKernelGGL((maxpool2_bwd_chain_h_kernel<1, true>), grid, dim3(c.threads), 0, stream, g, tp, out, H, W, Ho, Wo, d, c.len, c.nseg);
+                else hipLaunchKernelGGL((maxpool2_bwd_chain_h_kernel<1, false>), grid, dim3(c.threads), 0, stream, g, tp, out, H, W, Ho, Wo, d, c.len, c.nseg);
+            } else {
+                if (rs) hipLaunchKernelGGL((maxpool2_bwd_chain_h_kernel<2, true>), grid, dim3(c.threads), 0, stream, g, tp, out, H, W, Ho, Wo, d, c.len, c.nseg);
+                else hipLaunchKernelGGL((maxpool2_bwd_chain_h_kernel<2, false>), grid, dim3(c.threads), 0, stream, g, tp, out, H, W, Ho, Wo, d, c.len, c.nseg);
+            }
+            return hipGetLastError();
+        }
+    }
+    const dim3 grid((W + 255) / 256, H, (unsigned)planes8);
+    if (dtype == 1) hipLaunchKernelGGL(maxpool_bwd_h_kernel<1>, grid, dim3(256), 0, stream, g, tap, rs, out, H, W, Ho, Wo, k, d);
+    else hipLaunchKernelGGL(maxpool_bwd_h_kernel<2>, grid, dim3(256), 0, stream, g, tap, rs, out, H, W, Ho, Wo, k, d);
     return hipGetLastError();
 }
 
@@ -659,7 +733,7 @@ hipError_t launch_place_h(const void *src, void *dst, int n, int c8, int Hd, int
 }
 
 // winner codes on the octet layout -> flat input offsets, int32 NCHW (for the parity accessor)
-__global__ void tap_to_index_h_kernel(const uint2v *tap, int32_t *idx, int n, int c, int Ho, int Wo, int W, int k, int d, int s)
+__global__ void tap_to_index_h_kernel(const void *tap, int32_t *idx, int n, int c, int Ho, int Wo, int W, int k, int d, int s)
 {
     const int c8 = (c + 7) / 8;
     const long plane = (long)Ho * Wo, total = (long)n * c8 * plane;
@@ -669,11 +743,10 @@ __global__ void tap_to_index_h_kernel(const uint2v *tap, int32_t *idx, int n, in
         const long t = q / plane;
         const int o = (int)(t % c8);
         const long b = t / c8;
-        const uint2v cd = tap[q];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             if (o * 8 + e >= c) continue;
-            const int code = (cd[e >> 2] >> ((e & 3) * 8)) & 0xff, i = code / k, j = code - i * k;
+            const int code = (int)pool_code_h(tap, q, e, pool_bits_h(k, s)), i = code / k, j = code - i * k;
             idx[(b * c + o * 8 + e) * plane + pix] = (s * yy + i * d) * W + s * xx + j * d;
         }
     }
@@ -683,7 +756,7 @@ hipError_t launch_tap_to_index_h(const void *tap, int32_t *idx, int n, int c, in
                                  hipStream_t stream)
 {
     const long total = (long)n * ((c + 7) / 8) * Ho * Wo;
-    hipLaunchKernelGGL(tap_to_index_h_kernel, dim3(grid_for(total)), dim3(256), 0, stream, static_cast<const uint2v *>(tap), idx, n, c, Ho, Wo, W, k, d, s);
+    hipLaunchKernelGGL(tap_to_index_h_kernel, dim3(grid_for(total)), dim3(256), 0, stream, tap, idx, n, c, Ho, Wo, W, k, d, s);
     return hipGetLastError();
 }
 

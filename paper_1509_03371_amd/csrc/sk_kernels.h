@@ -10,12 +10,13 @@ namespace sk {
 // reads one row more than it has windows, so long chains (32) read least; but a chain is a serial row of memory latencies,
 // and a small map in chains of 32 fills a fraction of the GPU (96x96 with 8 or 16 maps: 32-64 workgroups, 11 us).  So row
 // blocks are narrowed to the width and chains halved, down to `step` windows (whose loads a thread keeps in flight together),
-// until POOL_WAVES waves (eight per CU) are there: the forward pass with those two pools 68 -> 55 us, a bf16 training step
-// at 512x512 with four pools of 48 maps 0.80 -> 0.775 ms.  Maps that fill the GPU in chains of 32 keep them (fewest reads).
+// until POOL_WAVES waves (sixteen per CU) are there: the pools of 48 bf16 maps at 527x527, forward / backward in us, with
+// 1024, 2048, 4096, 8192 waves asked for: 26.6 / 29.2, 16.9 / 17.5, 16.2 / 15.7, 16.3 / 15.8.  Maps that fill the GPU in
+// chains of 32 keep them (fewest reads).
 struct PoolCut {
     int threads, len, nseg;
 };
-constexpr long POOL_WAVES = 2048;
+constexpr long POOL_WAVES = 4096;
 inline PoolCut pool_cut(int Ho, int Wo, int d, long planes, int step)
 {
     PoolCut c{256, 32, 1};
@@ -27,6 +28,16 @@ inline PoolCut pool_cut(int Ho, int Wo, int d, long planes, int step)
     while (c.threads > 64 && (Wo + c.threads / 2 - 1) / (c.threads / 2) * (c.threads / 2) < (Wo + c.threads - 1) / c.threads * c.threads)
         c.threads /= 2;
     while (c.len > step && waves() < POOL_WAVES) cut(c.len / 2);
+    return c;
+}
+// the same for the kernels whose threads take four columns of a chain and lie linearly over (residue class, column block)
+inline PoolCut pool_cut4(int Ho, int Wo, int d, long planes, int step)
+{
+    PoolCut c{64, 32, 1};
+    const int links = (Ho + d - 1) / d;
+    const long row_waves = ((long)d * ((Wo + 3) / 4) + 63) / 64 * planes;
+    auto cut = [&](int len) { c.len = len; c.nseg = (links + len - 1) / len; };
+    for (cut(32); c.len > step && row_waves * c.nseg < POOL_WAVES;) cut(c.len / 2);
     return c;
 }
 
@@ -166,11 +177,16 @@ hipError_t launch_pack_weights_h_batch(const PackHJob *jobs, int n, int dtype, h
 hipError_t launch_pad_pack_h(const float *in, void *out, int dtype, int n, int c, int h, int w, int top, int left,
                              int ho, int wo, int mode, hipStream_t stream);
 hipError_t launch_unpack_h(const void *in, float *out, int dtype, int n, int c, int h, int w, hipStream_t stream);
-// planes8 = n * ceil(C/8); tap (optional) holds one byte per element, laid out like y
+// winner codes of a 2-D pool on octets: pool_bits_h: three bit planes in a 32-bit word per unit, else a byte per element
+// (see maxpool_h_kernel); what the backward pass and the accessor read
+constexpr bool pool_bits_h(int k, int s) { return k == 2 && s == 1; }
+constexpr long pool_tap_bytes_h(int k, int s) { return pool_bits_h(k, s) ? 4 : 8; }     // per unit of the pool's output
+// planes8 = n * ceil(C/8); tap (optional) receives the winner codes, laid out like y
 hipError_t launch_maxpool_h(const void *x, void *y, void *tap, int dtype, long planes8, int H, int W, int Ho, int Wo,
                             int k, int d, int s, hipStream_t stream);
 hipError_t launch_crop_copy_h(const void *src, void *dst, int n, int c8, int Hs, int Ws, int c8_total, int o8_off,
                               int H, int W, int cy, int cx, hipStream_t stream);
+// s = 1; relu_src (optional, k = 2: only whether it is given counts) is the pool's input: the gradient is zero where it is not positive
 hipError_t launch_maxpool_bwd_h(const void *dy, const void *tap, const void *relu_src, void *dx, int dtype,
                                 long planes8, int H, int W, int Ho, int Wo, int k, int d, hipStream_t stream);
 // pool with layer stride s = k at d = 1: dx (H x W) from dy and the winner codes (Ho x Wo); acc != 0 adds to dx
@@ -260,11 +276,13 @@ hipError_t launch_wgrad_rows_h(const void *x, const void *dy, const void *zeros,
 // ---- HBM-bound layers ---------------------------------------------------------------------------
 hipError_t launch_mirror_pad_f32(const float *in, float *out, int planes, int h, int w, int top,
                                  int left, int ho, int wo, int mode, hipStream_t stream);
-// Y[p,y,x] = max_{i,j<k} X[p, s*y+i*d, s*x+j*d]; first maximum wins; tap (optional) = i*k+j.
+// Y[p,y,x] = max_{i,j<k} X[p, s*y+i*d, s*x+j*d]; first maximum wins; tap (optional) = i*k+j (k = 2, s = 1: + 4 where the
+// maximum is positive).
 hipError_t launch_maxpool_f32(const float *x, float *y, uint8_t *tap, int planes, int H, int W,
                               int Ho, int Wo, int k, int d, int s, hipStream_t stream);
 // dX[p,u,v] = sum over outputs whose recorded winner is (u,v) of dY; if relu_src != nullptr the
-// result is zeroed where relu_src[p,u,v] <= 0 (ReLU backward of the layer below, fused).  s = 1 only.
+// result is zeroed where relu_src[p,u,v] <= 0 (ReLU backward of the layer below, fused; relu_src is the pool's input, of
+// which the codes of k = 2 hold all that is needed).  s = 1 only.
 hipError_t launch_maxpool_bwd_f32(const float *dy, const uint8_t *tap, const float *relu_src,
                                   float *dx, int planes, int H, int W, int Ho, int Wo, int k, int d,
                                   hipStream_t stream);

@@ -549,7 +549,7 @@ sk_status sknet_plan(sknet_t *net, int32_t n, int32_t h, int32_t w, int32_t pad,
     for (int i = 0; i < L && st == SK_OK; ++i) {
         const sk_layer &l = net->layers[i];
         if (l.kind == SK_MAXPOOL && training) {
-            const size_t bytes = half ? (size_t)n * ((dims[i + 1].c + 7) / 8) * dims[i + 1].h * dims[i + 1].w * 8
+            const size_t bytes = half ? (size_t)n * ((dims[i + 1].c + 7) / 8) * dims[i + 1].h * dims[i + 1].w * sk::pool_tap_bytes_h(l.k, l.s)
                                       : (size_t)dims[i + 1].count(n);
             hipError_t e = hipMalloc(reinterpret_cast<void **>(&net->tap[i]), bytes);
             if (e != hipSuccess) st = fail(SK_ENOMEM, "plan: hipMalloc of a pool mask failed: %s", hipGetErrorString(e));

@@ -559,8 +559,8 @@ static sk_status plan_impl(unet_t *net, int32_t n, int32_t h_in, int32_t w_in, b
             const auto &op = net->ops[i];
             if (op.kind == 1) {
                 if (op.s != 1 && !(op.s == op.k && op.d == 1)) st = fail(SK_EUNSUPPORTED, "training: pool needs s = 1, or s = k with d = 1");
-                // one byte per element, in the layout of the pool's output
-                const size_t tap_bytes = half ? (size_t)octet_floats(n, op.out) * 2 : (size_t)op.out.count(n);
+                // in the layout of the pool's output
+                const size_t tap_bytes = half ? (size_t)octet_floats(n, op.out) / 4 * sk::pool_tap_bytes_h(op.k, op.s) : (size_t)op.out.count(n);
                 hipError_t e = st == SK_OK ? hipMalloc(reinterpret_cast<void **>(&net->taps[i]), tap_bytes) : hipSuccess;
                 if (e != hipSuccess) st = fail(SK_ENOMEM, "plan: hipMalloc of a pool mask failed: %s", hipGetErrorString(e));
             } else if (op.kind == 0) {
