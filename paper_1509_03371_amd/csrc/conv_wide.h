@@ -20,7 +20,7 @@ constexpr int WV_XQ = 8;        // input loads (64 units each) of a wave per chu
 
 struct WideGeom {
     int xtiles, ytiles, tiles_hi, tiles_lo, rem;      // 3x3: tiles of the output; 1x1: xtiles linear tiles, ytiles = 1
-    int mgroups, pgroups;                             // map groups of a workgroup / packed groups of four map tiles
+    int mgroups, pgroups;                             // map groups of a workgroup / packed groups of GT (four) map tiles
     int nchunks, split, tiles, total;                 // tiles: without the split; total: with it
     int pw, oct_units;                                // staged row pitch, staged units per octet (a multiple of 64)
     float *ws;                                        // split > 1: partial sums
@@ -74,11 +74,13 @@ __device__ __forceinline__ unsigned wide_mask2(unsigned v, unsigned m)
     return v;
 }
 
-template <int NWV, int KS, int MG, int R, int XW> struct WideTile {
-    static constexpr int PWV = NWV / MG;                              // pixel waves
+// MT: map tiles of a wave; GT: map tiles of a packed group (a workgroup takes MG groups)
+template <int NWV, int KS, int MG, int R, int XW, int MT = 4, int GT = 4> struct WideTile {
+    static constexpr int PWV = NWV / (MG * GT / MT);                  // pixel waves
     static constexpr int YW = KS == 1 ? 1 : PWV / XW, RT = R * YW;         // 3x3: wave rows, output rows of a tile
     static constexpr int TX = KS == 1 ? 16 * R * PWV : 16 * XW;            // output columns (1x1: linear pixels) of a tile
-    static constexpr long FLOATS = (long)NWV * R * 4 * 256;           // partial sums of a tile
+    static constexpr long FLOATS = (long)NWV * R * MT * 256;          // partial sums of a tile
+    static_assert(GT % MT == 0 && NWV % (MG * GT / MT) == 0, "map waves share out the tiles of a group");
     static_assert(KS == 1 || PWV % XW == 0, "pixel waves form a grid");
     static_assert(R % 2 == 0, "rows are stored in pairs");
 };

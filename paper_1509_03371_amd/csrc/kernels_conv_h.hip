@@ -1574,9 +1574,26 @@ bool conv_h_reads_image(const ConvHArgs &a)
     return conv_c1_h_applies(a, a.mt > 0 ? a.mt : conv_h_mt(a.c_out, a.k));
 }
 
+// 3x3 layers of 17 to 32 output maps: kernels_conv_wide_h.hip's tile of 32 maps x 64 x 12 pixels where fewer rounds of it, one tile
+// a CU, cover the output and these are the shorter.  A tile costs 2 + 0.9 a chunk of 32 input maps (data gradient 2 + 1.05) there
+// for 1 + 1 of a 512-pixel tile here (the 32 x 16 one a quarter more).  277 layers and data gradients of 32 to 384 -> 17 to 32 maps,
+// 24^2 to 32 x 460 x 110, d = 1 to 4, bf16, both kernels in turn: taken there 1.02 to 2.08 times as fast (384 -> 32 on 8 x 304 x 40:
+// 68.9 us here, 33.2 there; 32 -> 32 on 32 x 44 x 189: 16.9 and 15.6), kept here 0.64 to 1.05 but for two of 1.11 and 1.43 (32 -> 24
+// on 32 x 412 x 86: 59.1 and 53.2).
+static bool conv_h_wide32(const ConvHArgs &a)
+{
+    if (!conv_wide32_applies(a)) return false;
+    const long cus = device_cus(), chunks = (a.c8_in + 3) / 4;
+    auto rounds = [&](int tx, int rt) { return (double)((conv_h_tile_count(a, 2, tx, rt) + cus - 1) / cus); };
+    const double here = std::min(std::min(rounds(128, 4), rounds(64, 8)), 1.25 * rounds(32, 16));
+    const double there = rounds(64, 12);
+    return there < here && there * (2 + (a.in_off ? 1.05 : 0.9) * chunks) < here * (1 + chunks);
+}
+
 ConvHPath conv_h_path(const ConvHArgs &a)
 {
     if (a.mt <= 0 && conv_h_wide(a.c_out, a.c8_in, a.k)) return a.k > 4 ? conv_wide_big_path(a) : conv_wide_path(a);
+    if (conv_h_wide32(a)) return conv_wide32_path(a);
     return {0, 0, 1, 0};
 }
 
@@ -1603,6 +1620,7 @@ hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream)
         if (!conv_h_supported(a.k, a.d, a.c_out) || a.img || a.vpool || a.hd) return hipErrorInvalidValue;
         return a.k > 4 ? launch_conv_wide_big_h(a, stream) : launch_conv_wide_h(a, stream);
     }
+    if (conv_h_wide32(a)) return launch_conv_wide32_h(a, stream);
     // the packed weights were laid out for this many map tiles per group (0 = the default choice)
     const int mt = a.mt > 0 ? a.mt : conv_h_mt(a.c_out, a.k);
     if (a.img && (!conv_c1_h_applies(a, mt) || a.img_h < 1 || a.img_w < 1 || a.pad_top < 0 || a.pad_left < 0 || (a.pad_mode != 0 && a.pad_mode != 1)))

@@ -1,6 +1,6 @@
 // 16-bit convolution with many output maps (1x1 and 3x3, 64 maps and more): MFMA 16x16x32 with wide register tiles.
 //
-// What bounds conv_h_kernel on these layers is LDS and the instructions around the MFMAs: its waves multiply 48 maps x 64 pixels,
+// (3x3: 17 to 32 maps too.)  What bounds conv_h_kernel on these layers is LDS and the instructions around the MFMAs: its waves multiply 48 maps x 64 pixels,
 // 45 fragments (1 KB each) read per 108 MFMAs of a 3x3 chunk -- with the staging writes about 126 of the 128 bytes a CU's LDS
 // moves per cycle -- and every input sample passes through a register on its way to LDS.  Here a wave multiplies 64 maps x 32 to
 // 128 pixels, 20 fragments per 72 MFMAs of a kernel column in the largest shape, and input and weights go from global memory
@@ -22,7 +22,12 @@
 // 1024 -> 1024 at 30^2 77 -> 35 (input maps split in four), 192 -> 128 at 516^2 186 -> 127 (0.91), 96 -> 128 at stride 4 on 64 slices
 // of 136^2 325 -> 232 (1.0); 1x1 1024 -> 512 at 128^2 58 -> 37, 512 -> 256 at 202^2 103 -> 45, 1024 -> 2048 up-convolution at 28^2
 // 52 -> 24.
-// A step costs 0.52 / 0.93 / 1.20 us (32 / 64 / 96 pixels x 64 maps a wave) where its MFMAs are 0.32 / 0.64 / 0.96 at 2.4 GHz.
+// A step costs 0.52 / 0.93 / 1.20 us (tiles of 256 / 512 / 768 pixels x 64 maps) where its MFMAs are 0.32 / 0.64 / 0.96 at 2.4 GHz.
+// A wave of the smallest tile multiplies 32 maps x 64 pixels, half of a packed group of map tiles: 12 fragments read for 24 MFMAs, 16 at
+// 64 maps x 32 pixels (the U-Net's launches of it 28.5 -> 27.7 us, the 572^2 forward pass 668 -> 659).
+// 17 to 32 output maps (conv_wide32): 32 maps x 64 x 12 pixels a tile, 14 fragments read for 36 MFMAs of a wave; weights packed as for
+// conv_h_kernel.  128 -> 32 maps data gradient at stride 4 on 72 slices of 136^2 (295 GFLOP): 610 -> 384 us, 16 -> 32 at stride 2 on 74
+// slices of 138^2 120 -> 94; the 3-D training step 3.03 -> 2.77 ms.
 // Tried and dropped: 128 maps x 512 pixels a workgroup (1.63 us of 1.28; half as many tiles, and spills with masks), four waves
 // and two workgroups a CU for 3x3 (within 5 % either way), the loads of a step issued together behind its barrier (5 to 10 %).
 #include "conv_wide.h"
@@ -32,13 +37,13 @@ namespace sk {
 namespace {
 
 // NX: input loads of a wave per chunk; PAD: the launch reads zeros around the image (data gradient of a 3x3 layer)
-template <int DT, int NWV, int KS, int MG, int R, int XW, int NX, bool PAD, int OUT, int S>
+template <int DT, int NWV, int KS, int MG, int R, int XW, int NX, bool PAD, int OUT, int S, int MT, int GT>
 __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
 {
-    using T = WideTile<NWV, KS, MG, R, XW>;
+    using T = WideTile<NWV, KS, MG, R, XW, MT, GT>;
     extern __shared__ uint4v lds[];
     constexpr int RR = T::RT + KS - 1;
-    constexpr int SLAB = KS * 4 * MG;                          // 1 KB weight fragments of a step
+    constexpr int SLAB = KS * GT * MG;                         // 1 KB weight fragments of a step
     constexpr int NW = (SLAB + NWV - 1) / NWV;       // weight loads of a wave per step
     constexpr int NXB = KS == 3 ? 2 : S, NWB = KS == 3 ? 3 : S;   // input buffers, weight slots
 
@@ -54,7 +59,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
     const int pw = k.w.pw, oct_units = k.w.oct_units;
     uint4v *const xbuf = lds, *const wbuf = lds + NXB * 4 * oct_units;
     float *const bias_lds = reinterpret_cast<float *>(wbuf + NWB * SLAB * 64);
-    for (int q = tid; q < (k.w.split > 1 ? 0 : k.w.pgroups * 64); q += 64 * NWV) bias_lds[q] = (k.a.bias && q < (k.a.c_out + 15) / 16 * 16) ? k.a.bias[q] : 0.f;
+    for (int q = tid; q < (k.w.split > 1 ? 0 : k.w.pgroups * GT * 16); q += 64 * NWV) bias_lds[q] = (k.a.bias && q < (k.a.c_out + 15) / 16 * 16) ? k.a.bias[q] : 0.f;
 
     // this wave loads one octet of a chunk, every LPO-th 64 units of it
     constexpr int LPO = NWV / 4;
@@ -89,12 +94,12 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
         c.o_in = o - skips * q.a.grp8;
         c.have = o < q.a.c8_in;
         c.x = reinterpret_cast<const char *>(q.a.x) + ((long)c.p.b * (q.a.xb8 > 0 ? q.a.xb8 : q.a.c8_in) + o + (long)skips * q.a.skip8) * plane;
-        c.w = reinterpret_cast<const char *>(q.a.wp) + ((long)c.p.mg * MG * q.w.nchunks + c.ch) * (KS * KS * 4) * 1024;
+        c.w = reinterpret_cast<const char *>(q.a.wp) + ((long)c.p.mg * MG * q.w.nchunks + c.ch) * (KS * KS * GT) * 1024;
 #pragma unroll
         for (int u = 0; u < NW; ++u) {
-            const int h = wblk[u] / (KS * 4);
+            const int h = wblk[u] / (KS * GT);
             // (beyond the last packed group: any weights that exist, nothing reads them)
-            c.woff[u] = (wblk[u] - h * (KS * 4)) * 1024 + (c.p.mg * MG + h < q.w.pgroups ? h : 0) * ((long)q.w.nchunks * (KS * KS * 4) * 1024);
+            c.woff[u] = (wblk[u] - h * (KS * GT)) * 1024 + (c.p.mg * MG + h < q.w.pgroups ? h : 0) * ((long)q.w.nchunks * (KS * KS * GT) * 1024);
         }
     };
     const long plane4 = (long)k.a.H * k.a.W * 64;              // four octet planes
@@ -104,7 +109,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
     auto step_chunk = [&](Cursor &c) {
         if (++c.ch < c.end) {
             c.x += plane4;
-            c.w += KS * KS * 4 * 1024;
+            c.w += KS * KS * GT * 1024;
             c.have = c.ch * 4 + oct < c8_in;
             if (grp8 > 0) {
                 c.o_in += 4;
@@ -154,20 +159,20 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
         }
     };
     auto load_w = [&](const Cursor &c, int cs, int sl, int u) {
-        wide_load_lds(c.w + c.woff[u] + cs * (KS * 4 * 1024) + lane16, wbuf + (sl * SLAB + wblk[u]) * 64);
+        wide_load_lds(c.w + c.woff[u] + cs * (KS * GT * 1024) + lane16, wbuf + (sl * SLAB + wblk[u]) * 64);
     };
 
-    floatx4 acc[R][4];
+    floatx4 acc[R][MT];
 #pragma unroll
     for (int y = 0; y < R; ++y)
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) acc[y][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int mt = 0; mt < MT; ++mt) acc[y][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // One step: kernel column cs of the chunk in input buffer `buf` against the weights in slot sl.  load(q, n): the q-th of
     // the n loads the step issues for later ones; they go between the MFMAs, because eight waves that issue theirs together
     // behind the barrier stand in the memory pipeline's queue (16 cycles an instruction and more) while the matrix unit idles.
     const int xrow = KS == 1 ? pwv * 16 * R : (pwv / XW) * R * pw + (pwv % XW) * 16;
-    const uint4v *const xfrag = xbuf + g * oct_units + l16 + xrow, *const wfrag = wbuf + wm * KS * 4 * 64 + lane;
+    const uint4v *const xfrag = xbuf + g * oct_units + l16 + xrow, *const wfrag = wbuf + (wm * MT / GT * KS * GT + wm * MT % GT) * 64 + lane;
     const int pitch = KS == 1 ? 16 : pw, dil = KS == 1 ? 0 : k.a.d, buf_units = 4 * oct_units;
     auto step = [&](bool act, int buf, int cs, int sl, auto loads, auto &&load) {
         constexpr int N = decltype(loads)::value, GROUPS = KS * R, SPREAD = N > 0 && GROUPS > N ? GROUPS / std::max(N, 1) : 1;
@@ -178,16 +183,16 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
         }
         const uint4v *wl = wfrag + sl * SLAB * 64;
         const uint4v *xl = xfrag + buf * buf_units + cs * dil;
-        // fragments in the order the multiplication needs them: the four map tiles of kernel row 0 and the input rows, then
-        // four map tiles and one more input row per further kernel row
-        constexpr int NB = R + KS - 1, NREAD = KS * 4 + NB, HEAD = 4 + (R < 3 ? R : 3), PER = R == 2 ? 3 : 2;
-        uint4v af[KS][4], bf[NB];
+        // fragments in the order the multiplication needs them: the map tiles of kernel row 0 and the input rows, then
+        // the map tiles and one more input row per further kernel row
+        constexpr int NB = R + KS - 1, NREAD = KS * MT + NB, HEAD = MT + (R < 3 ? R : 3), PER = R == 2 ? 3 : 2;
+        uint4v af[KS][MT], bf[NB];
         auto read = [&](int q) {
-            if (q < 4) af[0][q] = wl[q * 64];
-            else if (q < 4 + R) bf[q - 4] = xl[(q - 4) * pitch];
+            if (q < MT) af[0][q] = wl[q * 64];
+            else if (q < MT + R) bf[q - MT] = xl[(q - MT) * pitch];
             else {
-                const int i = 1 + (q - 4 - R) / 5, m = (q - 4 - R) % 5;
-                if (m < 4) af[i][m] = wl[(i * 4 + m) * 64];
+                const int i = 1 + (q - MT - R) / (MT + 1), m = (q - MT - R) % (MT + 1);
+                if (m < MT) af[i][m] = wl[(i * GT + m) * 64];
                 else bf[R + i - 1] = xl[(R + i - 1) * pitch];
             }
         };
@@ -201,7 +206,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
             for (int r = 0; r < PER; ++r)
                 if (HEAD + q * PER + r < NREAD) read(HEAD + q * PER + r);
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) acc[y][mt] = wide_mfma<DT>(af[i][mt], bf[y + i], acc[y][mt]);
+            for (int mt = 0; mt < MT; ++mt) acc[y][mt] = wide_mfma<DT>(af[i][mt], bf[y + i], acc[y][mt]);
             if (q % SPREAD == SPREAD - 1 && q / SPREAD < N) load(q / SPREAD);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -211,20 +216,20 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
 
     auto epilogue = [&](const Cursor &c) {
         const WideArgs &q = *wide_args();
-        const int mt0 = (c.p.mg * MG + wm) * 4;
+        const int mt0 = c.p.mg * (MG * GT) + wm * MT;
         if (q.w.split > 1) {
-            floatx4 *dst = reinterpret_cast<floatx4 *>(q.w.ws + (long)c.t * T::FLOATS) + (long)wave * R * 4 * 64 + lane;
+            floatx4 *dst = reinterpret_cast<floatx4 *>(q.w.ws + (long)c.t * T::FLOATS) + (long)wave * R * MT * 64 + lane;
 #pragma unroll
             for (int y = 0; y < R; ++y)
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt) {
-                    dst[(y * 4 + mt) * 64] = acc[y][mt];
+                for (int mt = 0; mt < MT; ++mt) {
+                    dst[(y * MT + mt) * 64] = acc[y][mt];
                     acc[y][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
                 }
             return;
         }
         constexpr bool MASK = OUT == WV_OCT_MASK;
-        uint4v mk[MASK ? R / 2 : 1][MASK ? 4 : 1];
+        uint4v mk[MASK ? R / 2 : 1][MASK ? MT : 1];
         if constexpr (MASK) {
             // all masks in one batch: a load awaited between stores would wait for those stores too
             const long to_mask = reinterpret_cast<const char *>(q.a.mask) - reinterpret_cast<const char *>(q.a.y);     // laid out like y
@@ -232,23 +237,23 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
             for (int y = 0; y < R; y += 2) {
                 const WideDst<OUT> dst = wide_dst<OUT, KS, R, XW, T>(q.a, c.p, pwv, y, l16, g, mt0);
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt) {
+                for (int mt = 0; mt < MT; ++mt) {
                     mk[y / 2][mt] = uint4v{0u, 0u, 0u, 0u};
                     if (dst.ok[0] && (mt0 + mt) * 2 + (g >> 1) < q.a.c8_out)
                         mk[y / 2][mt] = *reinterpret_cast<const uint4v *>(dst.at[0] + to_mask + mt * 2 * ((long)q.a.OH * q.a.OW * 16));
                 }
             }
         }
-        float bia[4][4];
+        float bia[MT][4];
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) bia[mt][r] = bias_lds[(mt0 + mt) * 16 + 4 * g + r];
 #pragma unroll
         for (int y = 0; y < R; y += 2) {
             const WideDst<OUT> dst = wide_dst<OUT, KS, R, XW, T>(q.a, c.p, pwv, y, l16, g, mt0);
 #pragma unroll
-            for (int mt = 0; mt < 4; ++mt) {
+            for (int mt = 0; mt < MT; ++mt) {
                 wide_store<DT, OUT>(q.a, acc[y][mt], acc[y + 1][mt], bia[mt], dst, mt0, mt, g, mk[MASK ? y / 2 : 0][MASK ? mt : 0]);
                 acc[y][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
                 acc[y + 1][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -257,9 +262,9 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
     };
 
     // has this wave maps and pixels of the image in the tile?
-    const int Ho = k.a.Ho, Wo = k.a.Wo, pgroups = k.w.pgroups;
+    const int Ho = k.a.Ho, Wo = k.a.Wo, c_out = k.a.c_out;
     auto wave_active = [&](const WidePos &p) {
-        if ((p.mg * MG + wm) >= pgroups) return false;
+        if ((p.mg * (MG * GT) + wm * MT) * 16 >= c_out) return false;
         if (KS == 1) return p.x0 + pwv * R * 16 < Ho * Wo;
         return p.x0 + (pwv % XW) * 16 < Wo && p.py + dil * (p.ty * T::RT + (pwv / XW) * R) < Ho;
     };
@@ -375,12 +380,12 @@ __global__ __launch_bounds__(64 * NWV, 2) void conv_wide_h_kernel(WideArgs k)
 }
 
 // Sum of the partial sums of a split launch and its epilogue: a wave takes one pair of rows of one wave of one tile.
-template <int DT, int NWV, int KS, int MG, int R, int XW, int OUT>
+template <int DT, int NWV, int KS, int MG, int R, int XW, int OUT, int MT, int GT>
 __global__ __launch_bounds__(256) void conv_wide_reduce_h_kernel(WideArgs k)
 {
     const ConvHArgs &a = k.a;
     const WideGeom &w = k.w;
-    using T = WideTile<NWV, KS, MG, R, XW>;
+    using T = WideTile<NWV, KS, MG, R, XW, MT, GT>;
     const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
     const long unit = (long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = (int)(unit / (NWV * (R / 2))), rest = (int)(unit % (NWV * (R / 2)));
@@ -388,14 +393,14 @@ __global__ __launch_bounds__(256) void conv_wide_reduce_h_kernel(WideArgs k)
     if (tile >= w.tiles) return;
     const int wm = wave / T::PWV, pwv = wave % T::PWV;
     const WidePos p = wide_decode<KS, T>(w, a.n, tile);
-    const int mt0 = (p.mg * MG + wm) * 4;
-    if (mt0 >= w.pgroups * 4) return;
+    const int mt0 = p.mg * (MG * GT) + wm * MT;
+    if (mt0 * 16 >= a.c_out) return;
     if (KS == 1 ? p.x0 + pwv * R * 16 >= a.Ho * a.Wo : (p.x0 + (pwv % XW) * 16 >= a.Wo || p.py + a.d * (p.ty * T::RT + (pwv / XW) * R) >= a.Ho)) return;
     const WideDst<OUT> dst = wide_dst<OUT, KS, R, XW, T>(a, p, pwv, y, l16, g, mt0);
-    uint4v mk[4];
-    float bia[4][4];
+    uint4v mk[MT];
+    float bia[MT][4];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
+    for (int mt = 0; mt < MT; ++mt) {
         mk[mt] = uint4v{0u, 0u, 0u, 0u};
         if constexpr (OUT == WV_OCT_MASK) {
             const long to_mask = reinterpret_cast<const char *>(a.mask) - reinterpret_cast<const char *>(a.y);
@@ -408,26 +413,26 @@ __global__ __launch_bounds__(256) void conv_wide_reduce_h_kernel(WideArgs k)
             bia[mt][r] = a.bias && o < (a.c_out + 15) / 16 * 16 ? a.bias[o] : 0.f;
         }
     }
-    floatx4 v[8];
+    floatx4 v[2 * MT];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const floatx4 *src = reinterpret_cast<const floatx4 *>(w.ws + (long)tile * T::FLOATS) + ((long)wave * R + y) * 4 * 64 + lane;
+    for (int q = 0; q < 2 * MT; ++q) v[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const floatx4 *src = reinterpret_cast<const floatx4 *>(w.ws + (long)tile * T::FLOATS) + ((long)wave * R + y) * MT * 64 + lane;
 #pragma unroll 2
     for (int sp = 0; sp < w.split; ++sp) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] += src[q * 64];
+        for (int q = 0; q < 2 * MT; ++q) v[q] += src[q * 64];
         src += (long)w.tiles * (T::FLOATS / 4);
     }
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) wide_store<DT, OUT>(a, v[mt], v[4 + mt], bia[mt], dst, mt0, mt, g, mk[mt]);
+    for (int mt = 0; mt < MT; ++mt) wide_store<DT, OUT>(a, v[mt], v[MT + mt], bia[mt], dst, mt0, mt, g, mk[mt]);
 }
 
-template <int NWV, int KS, int MG, int R, int XW>
+template <int NWV, int KS, int MG, int R, int XW, int MT, int GT>
 WideGeom wide_geom(const ConvHArgs &a)
 {
-    using T = WideTile<NWV, KS, MG, R, XW>;
+    using T = WideTile<NWV, KS, MG, R, XW, MT, GT>;
     WideGeom w{};
-    w.pgroups = ((a.c_out + 15) / 16 + 3) / 4;
+    w.pgroups = ((a.c_out + 15) / 16 + GT - 1) / GT;
     w.mgroups = (w.pgroups + MG - 1) / MG;
     w.nchunks = (a.c8_in + 3) / 4;
     w.split = 1;
@@ -452,17 +457,17 @@ WideGeom wide_geom(const ConvHArgs &a)
     return w;
 }
 
-template <int KS, int MG, int S>
+template <int KS, int MG, int S, int GT>
 size_t wide_smem(const WideGeom &w)
 {
-    const size_t x = (size_t)(KS == 3 ? 2 : S) * 4 * w.oct_units * 16, wt = (size_t)(KS == 3 ? 3 : S) * KS * 4 * MG * 1024;
-    return x + wt + (w.split > 1 ? 0 : (size_t)w.pgroups * 64 * sizeof(float));
+    const size_t x = (size_t)(KS == 3 ? 2 : S) * 4 * w.oct_units * 16, wt = (size_t)(KS == 3 ? 3 : S) * KS * GT * MG * 1024;
+    return x + wt + (w.split > 1 ? 0 : (size_t)w.pgroups * GT * 16 * sizeof(float));
 }
 
-template <int NWV, int KS, int MG, int S>
+template <int NWV, int KS, int MG, int S, int GT>
 bool wide_fits(const WideGeom &w)
 {
-    return w.tiles >= 1 && w.oct_units <= 64 * (NWV / 4) * WV_XQ && wide_smem<KS, MG, S>(w) <= 160 * 1024;
+    return w.tiles >= 1 && w.oct_units <= 64 * (NWV / 4) * WV_XQ && wide_smem<KS, MG, S, GT>(w) <= 160 * 1024;
 }
 
 // Input loads of a wave per chunk, 3x3: exact for the tile of kernel stride 1 (LEAST), one more up to about stride 4, the most for
@@ -476,65 +481,66 @@ template <class T, int LPO> struct WideLoads {
     }
 };
 
-template <int DT, int NWV, int KS, int MG, int R, int XW, int NX, bool PAD, int OUT, int S>
+template <int DT, int NWV, int KS, int MG, int R, int XW, int NX, bool PAD, int OUT, int S, int MT, int GT>
 hipError_t launch_wide_n(const WideArgs &k, size_t smem, hipStream_t stream)
 {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_wide_h_kernel<DT, NWV, KS, MG, R, XW, NX, PAD, OUT, S>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_wide_h_kernel<DT, NWV, KS, MG, R, XW, NX, PAD, OUT, S, MT, GT>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     int blocks = wide_cus() / 8 * 8 * (NWV == 4 && smem <= 80 * 1024 ? 2 : 1);
     if (k.w.total < blocks) blocks = (k.w.total + 7) / 8 * 8;
-    hipLaunchKernelGGL((conv_wide_h_kernel<DT, NWV, KS, MG, R, XW, NX, PAD, OUT, S>), dim3(blocks), dim3(64 * NWV), smem, stream, k);
+    hipLaunchKernelGGL((conv_wide_h_kernel<DT, NWV, KS, MG, R, XW, NX, PAD, OUT, S, MT, GT>), dim3(blocks), dim3(64 * NWV), smem, stream, k);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || k.w.split == 1) return e;
     const long waves = (long)k.w.tiles * NWV * (R / 2);
-    hipLaunchKernelGGL((conv_wide_reduce_h_kernel<DT, NWV, KS, MG, R, XW, OUT>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream, k);
+    hipLaunchKernelGGL((conv_wide_reduce_h_kernel<DT, NWV, KS, MG, R, XW, OUT, MT, GT>), dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream, k);
     return hipGetLastError();
 }
 
-template <int DT, int NWV, int KS, int MG, int R, int XW, int OUT, int S>
+template <int DT, int NWV, int KS, int MG, int R, int XW, int OUT, int S, int MT = 4, int GT = 4>
 hipError_t launch_wide_m(const ConvHArgs &a, int split, hipStream_t stream)
 {
-    using T = WideTile<NWV, KS, MG, R, XW>;
+    using T = WideTile<NWV, KS, MG, R, XW, MT, GT>;
     constexpr int LPO = NWV / 4;
     WideArgs k;
     k.a = a;
-    k.w = wide_geom<NWV, KS, MG, R, XW>(a);
+    k.w = wide_geom<NWV, KS, MG, R, XW, MT, GT>(a);
     WideGeom &w = k.w;
     if (split > w.nchunks) split = w.nchunks;
     while (split > 1 && (!a.ws || (long)w.tiles * split * T::FLOATS > a.ws_floats)) --split;
     w.split = split;
     w.ws = a.ws;
-    const size_t smem = wide_smem<KS, MG, S>(w);
-    if (!wide_fits<NWV, KS, MG, S>(w) || !a.zeros) return hipErrorInvalidValue;
+    const size_t smem = wide_smem<KS, MG, S, GT>(w);
+    if (!wide_fits<NWV, KS, MG, S, GT>(w) || !a.zeros) return hipErrorInvalidValue;
     // (sample offsets inside an octet plane are 32-bit)
     if ((long)a.H * a.W * 16 >= 0xffffffffL || (long)(a.out_f32 ? a.c_out * 4L : a.c8_out_total * 16L) * a.OH * a.OW >= 0x7fffffffL) return hipErrorInvalidValue;
     if ((long)w.tiles * split > 0x3fffffffL) return hipErrorInvalidValue;
     w.total = w.tiles * split;
     if constexpr (KS == 1) {
-        return launch_wide_n<DT, NWV, 1, MG, R, XW, T::TX / (64 * LPO), false, OUT, S>(k, smem, stream);
+        return launch_wide_n<DT, NWV, 1, MG, R, XW, T::TX / (64 * LPO), false, OUT, S, MT, GT>(k, smem, stream);
     } else {
         using L = WideLoads<T, LPO>;
         const int nx = L::of(w);
         if (a.in_off) {
-            if (nx == L::LEAST) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::LEAST, true, OUT, S>(k, smem, stream);
-            if (nx == L::MORE) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::MORE, true, OUT, S>(k, smem, stream);
-            return launch_wide_n<DT, NWV, 3, MG, R, XW, WV_XQ, true, OUT, S>(k, smem, stream);
+            if (nx == L::LEAST) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::LEAST, true, OUT, S, MT, GT>(k, smem, stream);
+            if (nx == L::MORE) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::MORE, true, OUT, S, MT, GT>(k, smem, stream);
+            return launch_wide_n<DT, NWV, 3, MG, R, XW, WV_XQ, true, OUT, S, MT, GT>(k, smem, stream);
         }
-        if (nx == L::LEAST) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::LEAST, false, OUT, S>(k, smem, stream);
-        if (nx == L::MORE) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::MORE, false, OUT, S>(k, smem, stream);
-        return launch_wide_n<DT, NWV, 3, MG, R, XW, WV_XQ, false, OUT, S>(k, smem, stream);
+        if (nx == L::LEAST) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::LEAST, false, OUT, S, MT, GT>(k, smem, stream);
+        if (nx == L::MORE) return launch_wide_n<DT, NWV, 3, MG, R, XW, L::MORE, false, OUT, S, MT, GT>(k, smem, stream);
+        return launch_wide_n<DT, NWV, 3, MG, R, XW, WV_XQ, false, OUT, S, MT, GT>(k, smem, stream);
     }
 }
 
-template <int DT, int NWV, int KS, int MG, int R, int XW, int S>
+template <int DT, int NWV, int KS, int MG, int R, int XW, int S, int MT = 4, int GT = 4>
 hipError_t launch_wide(const ConvHArgs &a, int split, hipStream_t stream)
 {
-    return a.mask ? launch_wide_m<DT, NWV, KS, MG, R, XW, WV_OCT_MASK, S>(a, split, stream) : launch_wide_m<DT, NWV, KS, MG, R, XW, WV_OCT, S>(a, split, stream);
+    return a.mask ? launch_wide_m<DT, NWV, KS, MG, R, XW, WV_OCT_MASK, S, MT, GT>(a, split, stream)
+                  : launch_wide_m<DT, NWV, KS, MG, R, XW, WV_OCT, S, MT, GT>(a, split, stream);
 }
 
 // What a launch of one tile shape takes, roughly, in microseconds: `fit` the measured times of a step and of a tile's rest
@@ -543,13 +549,13 @@ hipError_t launch_wide(const ConvHArgs &a, int split, hipStream_t stream)
 struct WideFit {
     double step, rest, lone_step, lone_rest;
 };
-template <int NWV, int KS, int MG, int R, int XW, int S>
+template <int NWV, int KS, int MG, int R, int XW, int S, int MT = 4, int GT = 4>
 double wide_cost(const ConvHArgs &a, int split, const WideFit &f)
 {
-    using T = WideTile<NWV, KS, MG, R, XW>;
-    WideGeom w = wide_geom<NWV, KS, MG, R, XW>(a);
+    using T = WideTile<NWV, KS, MG, R, XW, MT, GT>;
+    WideGeom w = wide_geom<NWV, KS, MG, R, XW, MT, GT>(a);
     w.split = split;
-    if (split > w.nchunks || !wide_fits<NWV, KS, MG, S>(w)) return 1e30;
+    if (split > w.nchunks || !wide_fits<NWV, KS, MG, S, GT>(w)) return 1e30;
     const double items = (double)w.tiles * split;
     if (split > 1 && (!a.ws || items * T::FLOATS > (double)a.ws_floats)) return 1e30;
     const int cus = wide_cus(), steps = KS * ((w.nchunks + split - 1) / split);
@@ -579,7 +585,7 @@ WidePick wide_pick(const ConvHArgs &a)
     const int splits[] = {1, 2, 3, 4, 6, 8};
     for (int sp : splits) {
         if (a.k == 3) {
-            take(0, sp, wide_cost<8, 3, 1, 2, 2, 3>(a, sp, {0.52, 2.8, 0.52, 2.8}));
+            take(0, sp, wide_cost<8, 3, 1, 4, 2, 3, 2>(a, sp, {0.52, 2.8, 0.52, 2.8}));
             take(1, sp, wide_cost<8, 3, 1, 4, 2, 3>(a, sp, {0.93, 4.6, 0.93, 4.6}));
             take(2, sp, wide_cost<8, 3, 1, 6, 4, 3>(a, sp, {1.20, 6.5, 1.20, 6.5}));
         } else {
@@ -597,13 +603,13 @@ hipError_t launch_wide_dt(const ConvHArgs &a, hipStream_t stream)
 {
     if (a.out_f32) {
         if (a.mask) return hipErrorInvalidValue;
-        return a.k == 3 ? launch_wide_m<DT, 8, 3, 1, 2, 2, WV_F32, 3>(a, 1, stream) : launch_wide_m<DT, 8, 1, 2, 2, 1, WV_F32, 4>(a, 1, stream);
+        return a.k == 3 ? launch_wide_m<DT, 8, 3, 1, 4, 2, WV_F32, 3, 2>(a, 1, stream) : launch_wide_m<DT, 8, 1, 2, 2, 1, WV_F32, 4>(a, 1, stream);
     }
     const WidePick pick = wide_pick(a);
     const int split = pick.split;
     if (a.k == 3) {
         switch (pick.shape) {
-        case 0: return launch_wide<DT, 8, 3, 1, 2, 2, 3>(a, split, stream);
+        case 0: return launch_wide<DT, 8, 3, 1, 4, 2, 3, 2>(a, split, stream);
         case 1: return launch_wide<DT, 8, 3, 1, 4, 2, 3>(a, split, stream);
         case 2: return launch_wide<DT, 8, 3, 1, 6, 4, 3>(a, split, stream);
         }
@@ -618,13 +624,13 @@ hipError_t launch_wide_dt(const ConvHArgs &a, hipStream_t stream)
     return hipErrorInvalidValue;
 }
 
-template <int NWV, int KS, int MG, int R, int XW, int S>
+template <int NWV, int KS, int MG, int R, int XW, int S, int MT = 4, int GT = 4>
 ConvHPath wide_path(const ConvHArgs &a, const WidePick &p)
 {
-    using T = WideTile<NWV, KS, MG, R, XW>;
-    const WideGeom w = wide_geom<NWV, KS, MG, R, XW>(a);
+    using T = WideTile<NWV, KS, MG, R, XW, MT, GT>;
+    const WideGeom w = wide_geom<NWV, KS, MG, R, XW, MT, GT>(a);
     const int loads = KS == 1 ? T::TX / (64 * (NWV / 4)) : WideLoads<T, NWV / 4>::of(w);
-    return {wide_fits<NWV, KS, MG, S>(w) ? 1 : -1, p.shape, p.split, loads};
+    return {wide_fits<NWV, KS, MG, S, GT>(w) ? 1 : -1, p.shape, p.split, loads};
 }
 
 }  // namespace
@@ -634,7 +640,7 @@ ConvHPath conv_wide_path(const ConvHArgs &a)
     const WidePick p = wide_pick(a);
     if (a.k == 3) {
         switch (p.shape) {
-        case 0: return wide_path<8, 3, 1, 2, 2, 3>(a, p);
+        case 0: return wide_path<8, 3, 1, 4, 2, 3, 2>(a, p);
         case 1: return wide_path<8, 3, 1, 4, 2, 3>(a, p);
         case 2: return wide_path<8, 3, 1, 6, 4, 3>(a, p);
         }
@@ -647,6 +653,23 @@ ConvHPath conv_wide_path(const ConvHArgs &a)
         }
     }
     return {-1, 0, 1, 0};
+}
+
+// 3x3 layers of 17 to 32 output maps (two map tiles, packed as conv_h_kernel's)
+bool conv_wide32_applies(const ConvHArgs &a)
+{
+    if (a.k != 3 || a.c_out <= 16 || a.c_out > 32 || a.out_f32 || a.tap_maps || a.img || a.vpool || a.hd || (a.mt != 0 && a.mt != 2)) return false;
+    const WideGeom w = wide_geom<8, 3, 1, 6, 4, 2, 2>(a);
+    return a.c8_in >= 4 && wide_fits<8, 3, 1, 3, 2>(w);
+}
+
+ConvHPath conv_wide32_path(const ConvHArgs &a) { return wide_path<8, 3, 1, 6, 4, 3, 2, 2>(a, {3, 1}); }
+
+hipError_t launch_conv_wide32_h(const ConvHArgs &a, hipStream_t stream)
+{
+    if (a.dtype == 1) return launch_wide<1, 8, 3, 1, 6, 4, 3, 2, 2>(a, 1, stream);
+    if (a.dtype == 2) return launch_wide<2, 8, 3, 1, 6, 4, 3, 2, 2>(a, 1, stream);
+    return hipErrorInvalidValue;
 }
 
 // At least 64 output maps with at most a fifth of the packed ones empty, and 32 input maps.  The biases of all maps lie in the LDS

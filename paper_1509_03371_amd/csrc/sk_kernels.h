@@ -152,6 +152,10 @@ ConvHPath conv_h_path(const ConvHArgs &a);
 ConvHPath conv_wide_path(const ConvHArgs &a);
 ConvHPath conv_wide_big_path(const ConvHArgs &a);
 hipError_t launch_conv_wide_h(const ConvHArgs &a, hipStream_t stream);
+// ... and its form for 3x3 layers of 17 to 32 output maps, whose weights are packed as conv_h_kernel's
+bool conv_wide32_applies(const ConvHArgs &a);
+ConvHPath conv_wide32_path(const ConvHArgs &a);
+hipError_t launch_conv_wide32_h(const ConvHArgs &a, hipStream_t stream);
 hipError_t launch_conv_wide_big_h(const ConvHArgs &a, hipStream_t stream);
 constexpr long CONV_H_WS_FLOATS = 8L << 20;       // ConvHArgs.ws: 32 MB hold the partial sums of 512 tiles of 64 maps x 256 pixels
 // 16-bit elements of the packed weights of a GEMM with gemm_m output maps and gemm_c8 input octets
