@@ -1351,9 +1351,15 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     }
     long copies = (resident + groups - 1) / groups;
     if (copies > max_copies) copies = max_copies;
-    const int blocks = a.total_segs < copies ? a.total_segs : (int)copies;
+    int blocks = a.total_segs < copies ? a.total_segs : (int)copies;
     float *bias_part = scratch + (size_t)max_copies * a.MTo * 16 * a.NTk * 16;
-    const bool bias_in_kernel = db && h_path && MB <= 4;
+    // 4x4 layers of 8 to 48 maps: input rows kept from one output row to the next.  58 layers of 8 to 48 -> 8 to 48 maps (21 x 36 to
+    // 8 x 1050^2, d = 1 to 16), both kernels in turn: 1.10 to 2.28 times as fast there from 16 input maps on (48 -> 48 at 560^2: 424 and
+    // 211 us), with fewer -- one or two of its column tiles a wave -- 0.86 to 1.00 on short walks and small maps (12 -> 48 on 2 x 86 x 231
+    // at d = 16: 25.0 us here, 29.2 there) and 1.24 to 1.55 above this line
+    const bool rows_path = DT == 0 && x_bstride == 0 && grp_maps == 0 && wgrad_rows_f32_supported(c_in, c_out, k, d) &&
+                           (c_in >= 16 || (a.total_segs >= 256 && a.Ho >= 4 * d));
+    const bool bias_in_kernel = db && ((h_path && MB <= 4) || rows_path);
     if (bias_in_kernel) a.bias_part = bias_part;
     hipError_t e = hipErrorInvalidValue;
     if constexpr (DT != 0) {
@@ -1368,7 +1374,10 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
             else e = launch_wgrad_h_rb<DT, 2>(a, MB, NB, smem, blocks, stream);
         }
     }
-    if (!h_path) {
+    if (rows_path) {
+        e = launch_wgrad_rows_f32(static_cast<const float *>(x), static_cast<const float *>(dy), scratch, db ? bias_part : nullptr, n, c_in, H, W,
+                                  c_out, d, max_copies, &blocks, stream);
+    } else if (!h_path) {
 #define SK_WG_CASE(mb, nb) if (MB == mb && NB == nb) e = launch_wgrad_t<mb, nb, DT>(a, smem, blocks, stream);
         SK_WG_CASE(1, 1) SK_WG_CASE(1, 4) SK_WG_CASE(1, 12)
         SK_WG_CASE(3, 1) SK_WG_CASE(3, 4) SK_WG_CASE(3, 12)

@@ -254,6 +254,12 @@ hipError_t launch_wgrad_f32(const float *x, const float *dy, float *dw, float *d
                             int n, int c_in, int H, int W, int c_out, int k, int d,
                             hipStream_t stream, size_t scratch_cap = 0);
 
+// 4x4 kernels of 8 to 48 input and at most 48 output maps (kernels_wgrad_rows_f32.hip): at most max_copies private copies
+// [16 * ceil(c_out / 16)][16 * c_in] to scratch, *copies of them, and the sums of dY to bias_part[map * *copies + copy] (optional)
+bool wgrad_rows_f32_supported(int c_in, int c_out, int k, int d);
+hipError_t launch_wgrad_rows_f32(const float *x, const float *dy, float *scratch, float *bias_part, int n, int c_in, int H, int W, int c_out, int d,
+                                 int max_copies, int *copies, hipStream_t stream);
+
 // the same with the input addressed as launch_conv_f32 addresses it: images x_bstride floats apart (0 = c_in*H*W),
 // the c_in maps in groups of grp_maps (a power of two, or 0 = none) with grp_skip more floats between groups
 hipError_t launch_wgrad_f32_grouped(const float *x, const float *dy, float *dw, float *db, float *scratch, int n, int c_in, int H,
