@@ -1062,6 +1062,31 @@ hipError_t launch_place_f32(const float *in, float *out, int n, int in_maps, int
     return hipGetLastError();
 }
 
+// stacked up-convolution [t * c_out + o][c] -> [c][o][t], t < 4: a workgroup turns 32 maps o x 32 maps c x the four taps in LDS, rows of
+// 32 floats in, a float4 per (c, o) out
+__global__ void __launch_bounds__(256) unstack_taps_kernel(const float *__restrict__ cat, float *__restrict__ out, int c_out, int c_in)
+{
+    __shared__ float sh[4][32][33];
+    const int lane = threadIdx.x & 31, row = threadIdx.x >> 5, c0 = blockIdx.x * 32, o0 = blockIdx.y * 32;
+    for (int r = row; r < 4 * 32; r += 8) {
+        const int t = r >> 5, o = o0 + (r & 31), c = c0 + lane;
+        if (o < c_out && c < c_in) sh[t][r & 31][lane] = cat[((long)t * c_out + o) * c_in + c];
+    }
+    __syncthreads();
+    for (int r = row; r < 32; r += 8) {
+        const int c = c0 + r, o = o0 + lane;
+        if (c < c_in && o < c_out)
+            reinterpret_cast<float4 *>(out)[(long)c * c_out + o] = make_float4(sh[0][lane][r], sh[1][lane][r], sh[2][lane][r], sh[3][lane][r]);
+    }
+}
+
+hipError_t launch_unstack_taps(const float *cat, float *out, int c_out, int c_in, hipStream_t stream)
+{
+    if (c_out < 1 || c_in < 1 || (c_out + 31) / 32 > 65535) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(unstack_taps_kernel, dim3((c_in + 31) / 32, (c_out + 31) / 32), dim3(256), 0, stream, cat, out, c_out, c_in);
+    return hipGetLastError();
+}
+
 __global__ void fill_f32_kernel(float *p, float v, long count)
 {
     for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < count; q += (long)gridDim.x * blockDim.x) p[q] = v;

@@ -367,6 +367,8 @@ hipError_t launch_maxpool_stride_bwd_f32(const float *dy, const uint8_t *tap, fl
 hipError_t launch_space_to_depth2_f32(const float *in, float *out, int n, int in_maps, int maps, int h, int w, hipStream_t stream);
 hipError_t launch_place_f32(const float *in, float *out, int n, int in_maps, int c_off, int maps, int hi, int wi, int ho, int wo,
                             int oy, int ox, hipStream_t stream);
+// out[c][o][t] = cat[t*c_out + o][c], t < 4 (out 16-byte aligned)
+hipError_t launch_unstack_taps(const float *cat, float *out, int c_out, int c_in, hipStream_t stream);
 hipError_t launch_fill_f32(float *p, float v, long count, hipStream_t stream);
 
 }  // namespace sk

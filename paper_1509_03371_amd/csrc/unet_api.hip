@@ -9,6 +9,7 @@
 #include <new>
 #include <set>
 
+#include "host_reader.h"
 #include "sk_host.h"
 
 using namespace skh;
@@ -75,9 +76,11 @@ struct unet {
     long unpack_tmp_floats = 0;
     Dims out_dims;
     hipStream_t last_stream = nullptr;
+    sk::HostReader reader;                   // training: weights and gradients to the caller
 
     void release_plan()
     {
+        reader.close();
         for (auto &p : buffers) free_dev(p);
         buffers.clear();
         free_dev(unpack_tmp); free_dev(zero_page); free_dev(conv_ws);
@@ -148,17 +151,6 @@ sk_status walk_sizes(const unet *net, int h, int w, int *ho, int *wo)
     }
     *ho = h; *wo = w;
     return SK_OK;
-}
-
-// stacked 1x1 form [t*c_out + o][c] -> [c][o][t].  Sixteen input maps at a time, so that the rows being written stay in the
-// cache while the four tap planes are read in order (map by map the writes lie c_out*16 bytes apart).
-void unstack_taps(const float *cat, const UpParams &u, float *out)
-{
-    const size_t tap = (size_t)u.c_out * u.c_in;
-    for (int c0 = 0; c0 < u.c_in; c0 += 16)
-        for (int o = 0; o < u.c_out; ++o)
-            for (int c = c0; c < std::min(c0 + 16, u.c_in); ++c)
-                for (int t = 0; t < 4; ++t) out[((size_t)c * u.c_out + o) * 4 + t] = cat[t * tap + (size_t)o * u.c_in + c];
 }
 
 sk_status upload_up(UpParams &u, int dtype)
@@ -311,20 +303,26 @@ sk_status unet_param_kind(const unet_t *net, int32_t idx, int32_t *kind)
 }
 
 // a parameter's device master (after SGD steps the current one) -> host memory; the caller has waited for the last pass
-static sk_status read_conv(const ConvParams &c, float *w, float *b)
+static sk_status read_conv(const unet *net, const ConvParams &c, float *w, float *b)
 {
-    if (w) SK_HIP(hipMemcpy(w, c.w_dev, sizeof(float) * c.wcount(), hipMemcpyDeviceToHost));
+    if (w) SK_HIP(net->reader.read(w, c.w_dev, sizeof(float) * c.wcount()));
     if (b) SK_HIP(hipMemcpy(b, c.b_dev, sizeof(float) * c.c_out, hipMemcpyDeviceToHost));
     return SK_OK;
 }
 
-static sk_status read_up(const UpParams &u, float *w, float *b)
+// a stacked up-convolution tensor, put back in the order [c_in][c_out][2][2] on the device, in the plan's scratch (which holds at
+// least one copy of its gradient)
+static sk_status read_stacked(const unet *net, const UpParams &u, const float *cat, float *out)
 {
-    if (w) {
-        std::vector<float> cat((size_t)4 * u.c_out * u.c_in);
-        SK_HIP(hipMemcpy(cat.data(), u.cat.w_dev, sizeof(float) * cat.size(), hipMemcpyDeviceToHost));
-        unstack_taps(cat.data(), u, w);
-    }
+    SK_HIP(sk::launch_unstack_taps(cat, net->wgrad_scratch, u.c_out, u.c_in, net->last_stream));
+    SK_HIP(hipStreamSynchronize(net->last_stream));
+    SK_HIP(net->reader.read(out, net->wgrad_scratch, sizeof(float) * 4 * (size_t)u.c_out * u.c_in));
+    return SK_OK;
+}
+
+static sk_status read_up(const unet *net, const UpParams &u, float *w, float *b)
+{
+    if (w) SK_TRY(read_stacked(net, u, u.cat.w_dev, w));
     if (b) SK_HIP(hipMemcpy(b, u.tap[0].b_dev, sizeof(float) * u.c_out, hipMemcpyDeviceToHost));
     return SK_OK;
 }
@@ -333,9 +331,9 @@ static sk_status read_up(const UpParams &u, float *w, float *b)
 static sk_status sync_masters(unet_t *net)
 {
     if (!net->planned || !net->training) return SK_OK;
-    if (net->last_stream) SK_HIP(hipStreamSynchronize(net->last_stream));
-    for (auto &c : net->convs) SK_TRY(read_conv(c, c.w.data(), c.b.data()));
-    for (auto &u : net->ups) SK_TRY(read_up(u, u.w.data(), u.b.data()));
+    SK_HIP(hipStreamSynchronize(net->last_stream));
+    for (auto &c : net->convs) SK_TRY(read_conv(net, c, c.w.data(), c.b.data()));
+    for (auto &u : net->ups) SK_TRY(read_up(net, u, u.w.data(), u.b.data()));
     return SK_OK;
 }
 
@@ -351,13 +349,13 @@ sk_status unet_set_weights(unet_t *net, int32_t idx, const float *w_host, const 
         ConvParams &c = net->convs[p.idx];
         std::memcpy(c.w.data(), w_host, sizeof(float) * c.wcount());
         if (b_host) std::memcpy(c.b.data(), b_host, sizeof(float) * c.c_out);
-        if (keep_b) SK_TRY(read_conv(c, nullptr, c.b.data()));
+        if (keep_b) SK_TRY(read_conv(net, c, nullptr, c.b.data()));
         if (net->planned) SK_TRY(upload_conv(c, net->training, net->last_stream, net->dtype));
     } else {
         UpParams &u = net->ups[p.idx];
         std::memcpy(u.w.data(), w_host, sizeof(float) * u.w.size());
         if (b_host) std::memcpy(u.b.data(), b_host, sizeof(float) * u.c_out);
-        if (keep_b) SK_TRY(read_up(u, nullptr, u.b.data()));
+        if (keep_b) SK_TRY(read_up(net, u, nullptr, u.b.data()));
         if (net->planned) SK_TRY(upload_up(u, net->dtype));
     }
     return SK_OK;
@@ -578,6 +576,7 @@ static sk_status plan_impl(unet_t *net, int32_t n, int32_t h_in, int32_t w_in, b
         }
         if (st == SK_OK) st = alloc_f(&net->wgrad_scratch, (long)scratch);
         if (st == SK_OK) st = alloc_f(&net->s2d, s2d_floats);
+        if (st == SK_OK) net->reader.open();
         if (st == SK_OK) st = alloc_f(&net->image_copy, (long)n * net->c_in * h_in * w_in);
         if (st == SK_OK && half) st = alloc_f(&net->dz16, octet_floats(n, net->out_dims));
         if (st == SK_OK) st = alloc_f(&net->loss_partial, sk::softmax_loss_partials((long)n * net->out_dims.h * net->out_dims.w));
@@ -882,16 +881,15 @@ sk_status unet_get_grad(unet_t *net, int32_t idx, float *dw_host, float *db_host
     const auto &p = net->params[idx];
     if (p.kind == 0) {
         ConvParams &c = net->convs[p.idx];
-        if (dw_host) SK_HIP(hipMemcpy(dw_host, c.dw, sizeof(float) * c.wcount(), hipMemcpyDeviceToHost));
+        if (dw_host) SK_HIP(net->reader.read(dw_host, c.dw, sizeof(float) * c.wcount()));
         if (db_host) SK_HIP(hipMemcpy(db_host, c.db, sizeof(float) * c.c_out, hipMemcpyDeviceToHost));
         return SK_OK;
     }
     // up-convolution: the stacked 1x1 gradient [t*c_out + o][c] back to [c][o][a][b]; the bias is shared by the four taps
     UpParams &u = net->ups[p.idx];
-    std::vector<float> dw((size_t)4 * u.c_out * u.c_in), db((size_t)4 * u.c_out);
-    SK_HIP(hipMemcpy(dw.data(), u.cat.dw, sizeof(float) * dw.size(), hipMemcpyDeviceToHost));
+    std::vector<float> db((size_t)4 * u.c_out);
     SK_HIP(hipMemcpy(db.data(), u.cat.db, sizeof(float) * db.size(), hipMemcpyDeviceToHost));
-    if (dw_host) unstack_taps(dw.data(), u, dw_host);
+    if (dw_host) SK_TRY(read_stacked(net, u, u.cat.dw, dw_host));
     if (db_host)
         for (int o2 = 0; o2 < u.c_out; ++o2)
             db_host[o2] = (db[o2] + db[u.c_out + o2]) + (db[2 * u.c_out + o2] + db[3 * u.c_out + o2]);
@@ -986,8 +984,8 @@ sk_status unet_get_weights(unet_t *net, int32_t idx, float *w_host, float *b_hos
     if (net->planned && net->training) {
         // the device copy is the one SGD updates: this parameter only, straight to the caller (a net is read parameter by
         // parameter, and bringing all of them down for each -- 27 x 124 MB for the U-Net of 64 base maps -- took 440 ms)
-        if (net->last_stream) SK_HIP(hipStreamSynchronize(net->last_stream));
-        return p.kind == 0 ? read_conv(net->convs[p.idx], w_host, b_host) : read_up(net->ups[p.idx], w_host, b_host);
+        SK_HIP(hipStreamSynchronize(net->last_stream));
+        return p.kind == 0 ? read_conv(net, net->convs[p.idx], w_host, b_host) : read_up(net, net->ups[p.idx], w_host, b_host);
     }
     if (p.kind == 0) {
         const ConvParams &c = net->convs[p.idx];
