@@ -79,6 +79,10 @@ struct ConvF32Args {
 bool conv_f32_groups_supported(int k, int d, int grp_maps);
 hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t stream);
 
+// 1x1 layers of at most 48 maps on one side (kernels_1x1_f32.hip); launch_conv_f32 hands them over
+bool conv1x1_f32_supported(const ConvF32Args &a);
+hipError_t launch_conv1x1_f32(const ConvF32Args &a, hipStream_t stream);
+
 // Pack OIHW fp32 master weights [c_out][c_in][k][k] into the K-major layout launch_conv_f32 reads.
 // flip_transpose = 0: Wp[(c*k+i)*k+j][o] = W[o][c][i][j]                       (forward)
 // flip_transpose = 1: Wp[(o*k+i)*k+j][c] = W[o][c][k-1-i][k-1-j]               (data gradient)
@@ -224,6 +228,10 @@ long head_w1_packed_bytes(int dtype, int c_in, int hidden);
 hipError_t launch_pack_head_w1(const float *w1, void *out, int dtype, int hidden, int c_in, hipStream_t stream);
 hipError_t launch_head_fused(HeadArgs a, hipStream_t stream);
 
+// fp32, at most 48 input maps (kernels_1x1_f32.hip; a.ksteps filled in); launch_head_fused hands them over
+bool head1x1_f32_supported(const HeadArgs &a);
+hipError_t launch_head1x1_f32(const HeadArgs &a, hipStream_t stream);
+
 // Backward pass of the same head with the softmax loss in one kernel (16-bit storage): nothing but x is read and
 // nothing but dx, the two layers' weight / bias gradients and the loss is written.
 struct HeadTrainArgs {
@@ -259,6 +267,12 @@ hipError_t launch_wgrad_f32(const float *x, const float *dy, float *dw, float *d
 bool wgrad_rows_f32_supported(int c_in, int c_out, int k, int d);
 hipError_t launch_wgrad_rows_f32(const float *x, const float *dy, float *scratch, float *bias_part, int n, int c_in, int H, int W, int c_out, int d,
                                  int max_copies, int *copies, hipStream_t stream);
+
+// 1x1 kernels of at most 48 maps on one side and 208 on the other (kernels_1x1_f32.hip): private copies
+// [16 * ceil(c_out / 16)][16 * ceil(c_in / 16)], else as above
+bool wgrad1x1_f32_supported(int c_in, int c_out, long plane);
+hipError_t launch_wgrad1x1_f32(const float *x, const float *dy, float *scratch, float *bias_part, int n, int c_in, long plane, int c_out,
+                               int max_copies, int *copies, hipStream_t stream);
 
 // the same with the input addressed as launch_conv_f32 addresses it: images x_bstride floats apart (0 = c_in*H*W),
 // the c_in maps in groups of grp_maps (a power of two, or 0 = none) with grp_skip more floats between groups
