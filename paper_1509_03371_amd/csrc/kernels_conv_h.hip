@@ -444,9 +444,6 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
     const uint4v *wres = lds + S * stage_units;
     float *bias_lds = reinterpret_cast<float *>(lds + S * stage_units + wres_units);
     int *ypos = reinterpret_cast<int *>(bias_lds + a.mgroups * MT * 16);
-    // (NP > 0) arrivals at each stage: of producers (0 .. S - 1), of multiplying waves (S .. 2S - 1)
-    volatile int *const counters = ypos + a.ytiles_total;
-    if (NP > 0 && tid < 2 * S) counters[tid] = 0;
     if constexpr (RESW) {
         uint4v *wdst = lds + S * stage_units;
         const uint4v *wsrc_all = reinterpret_cast<const uint4v *>(a.wp);
@@ -599,8 +596,7 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[y][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    auto compute = [&](int buf, int chunk, int next_flag = 0) {
-        int flag = 0;
+    auto compute = [&](int buf, int chunk) {
         const uint4v *tile = lds + buf * stage_units;
         const uint4v *wl = RESW ? wres + chunk * WUNITS : tile + tile_units;
 #pragma unroll
@@ -617,7 +613,6 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
             for (int r = 0; r < RR; ++r) {
                 uint4v bnext = bcur;
                 if (r + 1 < RR) bnext = tile[off + (r + 1) * PW];
-                if (NP > 0 && r == RR - 2) flag = counters[next_flag];
                 if (r + 1 < KS) {
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) afr[r + 1][mt] = wl[((cs * KS + r + 1) * MT + mt) * 64 + lane];
@@ -634,8 +629,9 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
                 bcur = bnext;
             }
         }
-        return flag;
     };
+
+
 
     // Epilogue of one tile: bias, ReLU, optional ReLU mask of the layer below, conversion, store.
     // Everything it reads comes first (bias from LDS, the mask in one batch) and the stores follow
@@ -907,33 +903,16 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
     }
 
     if constexpr (NP > 0) {
-        // No barrier per chunk.  Each ring stage has two counters in LDS: `ready` counts the producer waves that have
-        // filled it, `done` the multiplying waves that have read it, chunk after chunk; a wave looks at the one it depends on (the
-        // multiplying waves half a chunk ahead) and adds itself to the other.  So the two multiplying waves of a SIMD drift apart:
-        // one converts and stores its tile, or waits for its first fragments, while the other has the matrix unit.  A wave's LDS
-        // operations execute in order, so its reads of a stage precede its arrival and its writes theirs.  Every wait ends: chunk c
-        // waits for chunk c - S to be read, which was ready before.
-        auto arrive = [&](int counter) {
-            asm volatile("" ::: "memory");
-            if (lane == 0) __hip_atomic_fetch_add(const_cast<int *>(counters + counter), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            asm volatile("" ::: "memory");
-        };
-        auto wait_for = [&](int counter, int want, int seen) {
-            asm volatile("" ::: "memory");
-            while (__builtin_amdgcn_readfirstlane(seen) < want) {
-                __builtin_amdgcn_s_sleep(1);
-                seen = counters[counter];
-            }
-            asm volatile("" ::: "memory");
-        };
-        auto wait_free = [&](int c) {                              // stage of chunk c: chunk c - S has been read by all
-            if (c >= S) wait_for(S + c % S, CH_WAVES * (c / S), counters[S + c % S]);
-        };
+        // Every wave meets the same barrier once per chunk.  A producer arrives when its loads of
+        // chunk q have landed and then refills the stage that was multiplied in the previous
+        // iteration; a multiplying wave arrives when it is done with chunk q - 1.
         if (wave >= CH_WAVES && hd > 0) {
             // The input lacks the horizontal half of its pool: unit x of the tile is max(X[x], X[x + hd]).  The producer
             // waves load both operands into registers (two chunks in flight, in two register sets), take the maximum
             // and write the result into the ring stage -- one LDS write per unit, where loading the raw row straight
-            // into LDS and pooling it in place cost the direct write, two reads and a write.  The values are ReLU outputs (>= +0): the unsigned 16-bit order of the
+            // into LDS and pooling it in place cost the direct write, two reads and a write.  Chunk c is loaded
+            // after barrier c - 3, written after barrier c - 1 (its stage was multiplied before barrier c - 2) and
+            // multiplied after barrier c.  The values are ReLU outputs (>= +0): the unsigned 16-bit order of the
             // bit patterns is their numerical order.
             const int my_rows = (ROWS - lw + LW - 1) / LW;         // tile rows this wave stages
             const int Lr = 2 * my_rows * VUE;                      // its loads per chunk
@@ -979,15 +958,13 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
                     }
                 }
             };
-            // chunk c (c >= 1): from its register set into its stage, then chunk c + 2 into the set
+            // chunk c (c >= 1), right after barrier c - 1: from its register set into its stage, then chunk c + 2 into the set
             auto step = [&](uint4v (&r)[RU][VUE][2], TilePos &p, int &ch, int c) {
                 if (c >= total_chunks) return;
                 __builtin_amdgcn_sched_barrier(0);
                 wait_vmcnt_at_most(c + 1 < total_chunks ? Lr : 0);   // the loads of chunk c + 1 are younger and may be in flight
                 __builtin_amdgcn_sched_barrier(0);
-                wait_free(c);
                 gstore(r, p, ch, c % S);
-                arrive(c % S);
                 if (c + 2 < total_chunks) {
                     take_next(p, ch);
                     gload(r, p, ch);
@@ -1003,30 +980,29 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
             wait_vmcnt_at_most(total_chunks > 1 ? Lr : 0);
             __builtin_amdgcn_sched_barrier(0);
             gstore(rA, pA, cA, 0);
-            arrive(0);
             if (total_chunks > 2) {
                 take_next(pA, cA);
                 gload(rA, pA, cA);                                   // chunk 2
             }
             for (int q = 0; q < total_chunks; q += 2) {
+                block_sync_lds();                                    // barrier q: chunk q is in LDS
                 step(rB, pB, cB, q + 1);
-                step(rA, pA, cA, q + 2);
+                if (q + 1 < total_chunks) {
+                    block_sync_lds();                                // barrier q + 1
+                    step(rA, pA, cA, q + 2);
+                }
             }
             return;
         }
         if (wave >= CH_WAVES) {
-            // (S - 1 chunks are under way already)
             for (int q = 0; q < total_chunks; ++q) {
                 int allow = (issued - q - 1) * L;          // loads of younger chunks may still be in flight
                 allow = allow < 63 ? allow : 63;
                 __builtin_amdgcn_sched_barrier(0);
                 wait_vmcnt_at_most(allow);
                 __builtin_amdgcn_sched_barrier(0);
-                arrive(q % S);
-                if (issued < total_chunks) {
-                    wait_free(issued);
-                    issue_next();
-                }
+                block_sync_lds();
+                if (issued < total_chunks) issue_next();
             }
             return;
         }
@@ -1034,31 +1010,23 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
         // columns lie right of the image (the ragged last x tile) then skips the tile's MFMAs and
         // stores as a whole and only keeps the barriers, and its SIMD is left to the other wave.
         TilePos cur = position(ccur);
-        int st = 0, want = NP, flag = 0;              // stage of the next chunk, the arrivals that make it ready, those last seen
-        auto advance_stage = [&]() {
-            arrive(S + st);
-            if (++st == S) {
-                st = 0;
-                want += NP;
-            }
-        };
+        int st = 0;
         for (int ctile = 0; ctile < my_tiles; ++ctile) {
             const bool idle = __builtin_amdgcn_readfirstlane((int)(cur.x0 + wave * 16 >= a.Wo)) != 0;
             if (idle) {
                 for (int ch = 0; ch < a.nchunks; ++ch) {
-                    wait_for(st, want, 0);               // (so that its arrivals count for the chunk they belong to)
-                    advance_stage();
+                    block_sync_lds();
+                    st = st + 1 == S ? 0 : st + 1;
                 }
-                flag = 0;
             } else {
 #pragma unroll
                 for (int y = 0; y < R; ++y)
 #pragma unroll
                     for (int mt = 0; mt < MT; ++mt) acc[y][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
                 for (int ch = 0; ch < a.nchunks; ++ch) {
-                    wait_for(st, want, flag);
-                    flag = compute(st, ch, st + 1 == S ? 0 : st + 1);
-                    advance_stage();
+                    block_sync_lds();
+                    compute(st, ch);
+                    st = st + 1 == S ? 0 : st + 1;
                 }
                 if constexpr (VPOOL) epilogue_vpool(cur, ypitch == R && cur.ty > 0 && ctile > 0, !(lead_in && ctile == 0));
                 else if (HAS_MASK || a.out_f32 || (R & 1)) epilogue(cur);
@@ -1239,7 +1207,7 @@ static int device_cus()
     return cus;
 }
 
-// LDS bytes of the ring kernel: S stages (+ resident weights) + bias + y-tile table (of tiles R - 1 rows apart at least) + counters
+// LDS bytes of the ring kernel: S stages (+ resident weights) + bias + y-tile table
 template <int KS, int MT, bool MAP4, int R, int S, bool RESW>
 static size_t ring_smem(int d, int c_out, int c8_in, int Ho, int hd = 0)
 {
@@ -1250,7 +1218,7 @@ static size_t ring_smem(int d, int c_out, int c8_in, int Ho, int hd = 0)
     const int nchunks = (c8_in + OC - 1) / OC;
     const int m_tiles_all = ((c_out + 15) / 16 + MT - 1) / MT * MT;
     const size_t units = RESW ? S * tile + nchunks * slab : S * (tile + slab);
-    return units * 16 + (size_t)m_tiles_all * 64 + (size_t)(Ho / (R - 1) + 2 * d + 2 + 2 * S) * 4;
+    return units * 16 + (size_t)m_tiles_all * 64 + (size_t)(Ho / R + 2 * d + 2) * 4;
 }
 
 template <int DT, int KS, int MT, bool MAP4, int R, bool HAS_MASK, int S, bool RESW, int NP = 0, bool VPOOL = false>
