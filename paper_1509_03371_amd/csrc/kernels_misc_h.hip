@@ -167,6 +167,16 @@ __global__ void maxpool_h_kernel(const uint4v *x, uint4v *y, void *tap, int H, i
     }
 }
 
+// ... of a 3-D pool (see maxpool3d_h_kernel)
+__device__ __forceinline__ unsigned pool3d_code_h(const void *tap, long q, int e, bool bits)
+{
+    if (bits) {
+        const unsigned w = static_cast<const unsigned *>(tap)[q];
+        return ((w >> e) & 1u) | (((w >> (8 + e)) & 1u) << 1) | (((w >> (16 + e)) & 1u) << 2);
+    }
+    return pool_code_h(tap, q, e, false);
+}
+
 // k = 2, s = 1 (every SK pool of the paper): window (y, x) is {h[y], h[y + d]} where h[r] is the
 // first maximum of X[r][x], X[r][x + d].  A thread walks one column down the rows y0, y0 + d,
 // y0 + 2d, ... of one residue class mod d, so each h is formed once and serves both windows it
@@ -275,10 +285,11 @@ hipError_t launch_maxpool_h(const void *x, void *y, void *tap, int dtype, long p
 
 // ---- 3-D max pooling on the slice-major octet layout [D][C8][H][W][8] (Section 5.2.2) -----------------------
 // Y[z][o8][y][x] = max over the k^3 taps X[s z + a d][o8][s y + i d][s x + j d]; tap (optional, laid out like y, one
-// byte per element): the winner's code (a k + i) k + j, the first maximum in that scan order.
+// byte per element): the winner's code (a k + i) k + j, the first maximum in that scan order.  k = 2, s = 1: four bit planes in a
+// 32-bit word per unit instead, as in the 2-D pools: j, i, a and whether the maximum is positive.
 // grid: x = column blocks, y = output row, z = (output slice, octet)
 template <int DT>
-__global__ void maxpool3d_h_kernel(const uint4v *x, uint4v *y, uint2v *tap, int C8, int H, int W, int Ho, int Wo, int k, int d, int s)
+__global__ void maxpool3d_h_kernel(const uint4v *x, uint4v *y, void *tap, int C8, int H, int W, int Ho, int Wo, int k, int d, int s)
 {
     const int xx = blockIdx.x * blockDim.x + threadIdx.x, yy = blockIdx.y;
     if (xx >= Wo) return;
@@ -311,16 +322,105 @@ __global__ void maxpool3d_h_kernel(const uint4v *x, uint4v *y, uint2v *tap, int 
             }
     const long q = ((long)blockIdx.z * Ho + yy) * Wo + xx;
     y[q] = uint4v{bits[0] | (bits[1] << 16), bits[2] | (bits[3] << 16), bits[4] | (bits[5] << 16), bits[6] | (bits[7] << 16)};
-    if (tap)
-        tap[q] = uint2v{code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24),
-                        code[4] | (code[5] << 8) | (code[6] << 16) | (code[7] << 24)};
+    if (!tap) return;
+    if (pool_bits_h(k, s)) {
+        unsigned word = 0u;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            word |= ((code[e] & 1u) << e) | ((code[e] >> 1 & 1u) << (8 + e)) | ((code[e] >> 2) << (16 + e)) | ((best[e] > 0.f ? 1u : 0u) << (24 + e));
+        static_cast<unsigned *>(tap)[q] = word;
+    } else {
+        static_cast<uint2v *>(tap)[q] = uint2v{code[0] | (code[1] << 8) | (code[2] << 16) | (code[3] << 24),
+                                               code[4] | (code[5] << 8) | (code[6] << 16) | (code[7] << 24)};
+    }
+}
+
+// k = 2, s = 1: a thread owns one position of an output octet plane and walks down the slices z0, z0 + d, ... of one residue class.
+// The first maximum of the 2x2 samples of slice z serves the windows of slices z - d and z, so each is formed once: four loads a window
+// instead of eight, three of which the neighbouring threads load too (the two pools of the 81x145x145 net, with codes: 160 -> 92 us).  grid: x = (residue class and chain segment, block of 256 positions), y = octet
+template <int DT, bool TAP>
+__global__ void __launch_bounds__(256) maxpool3d_k2_chain_h_kernel(const uint4v *__restrict__ x, uint4v *__restrict__ y, unsigned *__restrict__ tap,
+                                                                   int C8, int H, int W, int Do, int Ho, int Wo, int d, int M, int nseg, int pblocks)
+{
+    const int chain = blockIdx.x / pblocks, pb = blockIdx.x - chain * pblocks, phase = chain / nseg, seg = chain - phase * nseg;
+    const int pos = pb * 256 + threadIdx.x, o8 = blockIdx.y, m0 = seg * M;
+    if (pos >= Ho * Wo || phase >= Do) return;
+    const int m1 = min((Do - phase + d - 1) / d, m0 + M);
+    if (m0 >= m1) return;
+    const int yy = pos / Wo, xx = pos - yy * Wo;
+    const long zstep = (long)d * C8 * H * W, ostep = (long)d * C8 * Ho * Wo, below = (long)d * W;
+    const uint4v *src = x + (((long)(phase + m0 * d) * C8 + o8) * H + yy) * W + xx;
+    const long o0 = ((long)(phase + m0 * d) * C8 + o8) * Ho * Wo + pos;
+    uint4v *dst = y + o0;
+    unsigned *tdst = TAP ? tap + o0 : nullptr;
+    struct Quad {
+        uint4v v;
+        unsigned j, i;
+    };
+    auto quad = [](uint4v a, uint4v b, uint4v c, uint4v e) {
+        uint4v top, low;
+        unsigned jt, jl;
+        Quad q;
+        row_first_max<DT>(a, b, top, jt);
+        row_first_max<DT>(c, e, low, jl);
+        row_first_max<DT>(top, low, q.v, q.i);
+        q.j = (jt & ~q.i) | (jl & q.i);
+        return q;
+    };
+    Quad q = quad(src[0], src[d], src[below], src[below + d]);
+    constexpr int U = 2;
+    for (int m = m0; m < m1; m += U) {
+        uint4v s[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {                     // all loads of the group first
+            const uint4v *p = src + (m + u < m1 ? (u + 1) * zstep : 0);
+            s[u][0] = p[0];
+            s[u][1] = p[d];
+            s[u][2] = p[below];
+            s[u][3] = p[below + d];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (m + u >= m1) break;
+            const Quad q2 = quad(s[u][0], s[u][1], s[u][2], s[u][3]);
+            uint4v o;
+            unsigned far;                                 // bit e: the winner lies in slice z + d
+            row_first_max<DT>(q.v, q2.v, o, far);
+            dst[u * ostep] = o;
+            if (TAP) {
+                unsigned pos8 = 0u;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) pos8 |= up16<DT>(elem16(o, e)) > 0.f ? 1u << e : 0u;
+                tdst[u * ostep] = (q.j & ~far) | (q2.j & far) | (((q.i & ~far) | (q2.i & far)) << 8) | (far << 16) | (pos8 << 24);
+            }
+            q = q2;
+        }
+        src += U * zstep;
+        dst += U * ostep;
+        if (TAP) tdst += U * ostep;
+    }
+}
+
+// Chains of 16 slices, shorter where that leaves the GPU empty; false: a grid too large for this form
+static bool pool3d_cut(int C8, int D, long plane, int d, int &len, int &nseg, unsigned &gx, int &pblocks)
+{
+    const int links = (D + d - 1) / d;
+    const long pb = (plane + 255) / 256;
+    for (len = 16;; len /= 2) {
+        nseg = (links + len - 1) / len;
+        if (len == 4 || pb * 4 * d * nseg * C8 >= POOL_WAVES) break;
+    }
+    if (plane > 0x3fffffffL || (long)d * nseg * pb > 0x7fffffffL || C8 > 65535) return false;
+    gx = (unsigned)(d * nseg * pb);
+    pblocks = (int)pb;
+    return true;
 }
 
 // Gather form of the 3-D pool gradient (s = 1) on the slice-major octet layout: input unit (z, u, v) of octet o8 collects,
 // per map, dY of the windows whose recorded winner it is; fp32 sums, rounded once; relu_src as in the 2-D kernel.
 // grid: x = column blocks, y = input row, z = (input slice, octet)
 template <int DT>
-__global__ void maxpool3d_bwd_h_kernel(const uint4v *__restrict__ dy, const uint2v *__restrict__ tap, const uint4v *__restrict__ relu_src,
+__global__ void maxpool3d_bwd_h_kernel(const uint4v *__restrict__ dy, const void *__restrict__ tap, const uint4v *__restrict__ relu_src,
                                        uint4v *__restrict__ dx, int C8, int H, int W, int Do, int Ho, int Wo, int k, int d)
 {
     const int v = blockIdx.x * blockDim.x + threadIdx.x, u = blockIdx.y;
@@ -339,14 +439,11 @@ __global__ void maxpool3d_bwd_h_kernel(const uint4v *__restrict__ dy, const uint
                 const int xo = v - j * d;
                 if (xo < 0 || xo >= Wo) continue;
                 const long o = (((long)zo * C8 + o8) * Ho + yo) * Wo + xo;
-                const uint2v c = tap[o];
                 const uint4v g = dy[o];
                 const unsigned want = (unsigned)((a * k + i) * k + j);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const unsigned code = (c[e >> 2] >> ((e & 3) * 8)) & 0xffu;
-                    if (code == want) acc[e] += up16<DT>(elem16(g, e));
-                }
+                for (int e = 0; e < 8; ++e)
+                    if (pool3d_code_h(tap, o, e, pool_bits_h(k, 1)) == want) acc[e] += up16<DT>(elem16(g, e));
             }
         }
     }
@@ -363,6 +460,90 @@ __global__ void maxpool3d_bwd_h_kernel(const uint4v *__restrict__ dy, const uint
     dx[q] = uint4v{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16), hv[4] | (hv[5] << 16), hv[6] | (hv[7] << 16)};
 }
 
+// k = 2: a thread walks position (u, v) of dX down the slices z0, z0 + d, ... of one residue class, as the forward kernel walks its
+// windows.  Slice z collects from the windows of slices z (a = 0) and z - d (a = 1), so the four windows of a slice are loaded once
+// and what they give the next step is kept as a sum; MASKED takes the ReLU mask of the layer below from the codes.  (Eight windows with
+// byte codes a thread and the layer's output: 208 bytes loaded a unit, 80 here; the same two pools 196 -> 87 us.)
+template <int DT, bool MASKED>
+__global__ void __launch_bounds__(256) maxpool3d_k2_bwd_chain_h_kernel(const uint4v *__restrict__ dy, const unsigned *__restrict__ tap,
+                                                                       uint4v *__restrict__ dx, int C8, int H, int W, int D, int Do, int Ho, int Wo,
+                                                                       int d, int M, int nseg, int pblocks)
+{
+    const int chain = blockIdx.x / pblocks, pb = blockIdx.x - chain * pblocks, phase = chain / nseg, seg = chain - phase * nseg;
+    const int pos = pb * 256 + threadIdx.x, o8 = blockIdx.y, m0 = seg * M;
+    if (pos >= H * W || phase >= D) return;
+    const int m1 = min((D - phase + d - 1) / d, m0 + M);
+    if (m0 >= m1) return;
+    const int u = pos / W, v = pos - u * W;
+    // the four windows (i, j) of a slice that can have chosen this position, clamped into the plane; `in`: all ones where they exist
+    int at[4];
+    unsigned in[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int yy = u - (t >> 1) * d, xx = v - (t & 1) * d;
+        in[t] = yy >= 0 && yy < Ho && xx >= 0 && xx < Wo ? 0xffu : 0u;
+        at[t] = in[t] ? yy * Wo + xx : 0;
+    }
+    struct Slice {
+        uint4v g[4];
+        unsigned c[4];
+    };
+    auto load = [&](int z) {                              // windows of slice z, clamped into the volume
+        const long base = ((long)(z < 0 ? 0 : (z < Do ? z : Do - 1)) * C8 + o8) * Ho * Wo;
+        Slice s;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            s.g[t] = dy[base + at[t]];
+            s.c[t] = tap[base + at[t]];
+        }
+        return s;
+    };
+    auto pick = [](uint4v g, unsigned t, int e) {         // the element, or +0
+        return __int_as_float(__float_as_int(up16<DT>(elem16(g, e))) & ((int)(t << (31 - e)) >> 31));
+    };
+    // what the windows of slice z give slice z (near) and slice z + d (far)
+    auto split = [&](const Slice &s, int z, float (&near)[8], float (&far)[8]) {
+        const unsigned row = z >= 0 && z < Do ? 0xffu : 0u;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) near[e] = far[e] = 0.f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const unsigned c = s.c[t], j = t & 1 ? c : ~c, i = t & 2 ? c >> 8 : ~(c >> 8);
+            const unsigned mine = (MASKED ? c >> 24 : 0xffu) & in[t] & row & j & i, nm = mine & ~(c >> 16), fm = mine & (c >> 16);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                near[e] += pick(s.g[t], nm, e);
+                far[e] += pick(s.g[t], fm, e);
+            }
+        }
+    };
+    int z = phase + m0 * d;
+    uint4v *dst = dx + ((long)z * C8 + o8) * H * W + pos;
+    const long ostep = (long)d * C8 * H * W;
+    float kept[8], near[8], far[8];
+    split(load(z - d), z - d, near, kept);
+    constexpr int U = 2;
+    for (int m = m0; m < m1; m += U) {
+        Slice s[U];
+#pragma unroll
+        for (int w = 0; w < U; ++w) s[w] = load(z + w * d);          // all loads of the group first
+#pragma unroll
+        for (int w = 0; w < U; ++w) {
+            if (m + w >= m1) break;
+            split(s[w], z + w * d, near, far);
+            unsigned hv[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                hv[e] = down16<DT>(near[e] + kept[e]);
+                kept[e] = far[e];
+            }
+            dst[w * ostep] = uint4v{hv[0] | (hv[1] << 16), hv[2] | (hv[3] << 16), hv[4] | (hv[5] << 16), hv[6] | (hv[7] << 16)};
+        }
+        z += U * d;
+        dst += U * ostep;
+    }
+}
+
 hipError_t launch_maxpool3d_bwd_h(const void *dy, const void *tap, const void *relu_src, void *dx, int dtype, int C, int D, int H, int W,
                                   int Do, int Ho, int Wo, int k, int d, hipStream_t stream)
 {
@@ -371,8 +552,22 @@ hipError_t launch_maxpool3d_bwd_h(const void *dy, const void *tap, const void *r
     if (Do != D - (k - 1) * d || Ho != H - (k - 1) * d || Wo != W - (k - 1) * d || Do < 1 || Ho < 1 || Wo < 1) return hipErrorInvalidValue;
     const dim3 grid((W + 255) / 256, H, (unsigned)(D * C8));
     const uint4v *g = static_cast<const uint4v *>(dy), *rs = static_cast<const uint4v *>(relu_src);
-    const uint2v *tp = static_cast<const uint2v *>(tap);
     uint4v *out = static_cast<uint4v *>(dx);
+    int len, nseg, pblocks;
+    unsigned gx;
+    if (k == 2 && pool3d_cut(C8, D, (long)H * W, d, len, nseg, gx, pblocks)) {
+        const unsigned *tp = static_cast<const unsigned *>(tap);
+        const dim3 cgrid(gx, C8);
+        if (dtype == 1) {
+            if (rs) hipLaunchKernelGGL((maxpool3d_k2_bwd_chain_h_kernel<1, true>), cgrid, dim3(256), 0, stream, g, tp, out, C8, H, W, D, Do, Ho, Wo, d, len, nseg, pblocks);
+            else hipLaunchKernelGGL((maxpool3d_k2_bwd_chain_h_kernel<1, false>), cgrid, dim3(256), 0, stream, g, tp, out, C8, H, W, D, Do, Ho, Wo, d, len, nseg, pblocks);
+        } else {
+            if (rs) hipLaunchKernelGGL((maxpool3d_k2_bwd_chain_h_kernel<2, true>), cgrid, dim3(256), 0, stream, g, tp, out, C8, H, W, D, Do, Ho, Wo, d, len, nseg, pblocks);
+            else hipLaunchKernelGGL((maxpool3d_k2_bwd_chain_h_kernel<2, false>), cgrid, dim3(256), 0, stream, g, tp, out, C8, H, W, D, Do, Ho, Wo, d, len, nseg, pblocks);
+        }
+        return hipGetLastError();
+    }
+    const void *tp = tap;
     if (dtype == 1) hipLaunchKernelGGL(maxpool3d_bwd_h_kernel<1>, grid, dim3(256), 0, stream, g, tp, rs, out, C8, H, W, Do, Ho, Wo, k, d);
     else hipLaunchKernelGGL(maxpool3d_bwd_h_kernel<2>, grid, dim3(256), 0, stream, g, tp, rs, out, C8, H, W, Do, Ho, Wo, k, d);
     return hipGetLastError();
@@ -380,7 +575,7 @@ hipError_t launch_maxpool3d_bwd_h(const void *dy, const void *tap, const void *r
 
 // winner codes of a 3-D pool on the octet layout -> flat offsets ((z_in*H + y_in)*W + x_in) inside the map's input
 // volume, int32 [Do][C][Ho][Wo] (for the parity accessor)
-__global__ void tap3d_to_index_h_kernel(const uint2v *tap, int32_t *idx, int C, int Do, int Ho, int Wo, int H, int W, int k, int d, int s,
+__global__ void tap3d_to_index_h_kernel(const void *tap, int32_t *idx, int C, int Do, int Ho, int Wo, int H, int W, int k, int d, int s,
                                         long total)
 {
     const int C8 = (C + 7) / 8;
@@ -390,9 +585,7 @@ __global__ void tap3d_to_index_h_kernel(const uint2v *tap, int32_t *idx, int C, 
         const int yo = (int)(t % Ho);
         t /= Ho;
         const int c = (int)(t % C), zo = (int)(t / C);
-        const uint2v w = tap[(((long)zo * C8 + (c >> 3)) * Ho + yo) * Wo + xo];
-        const int e = c & 7;
-        const int code = (int)((w[e >> 2] >> ((e & 3) * 8)) & 0xffu);
+        const int code = (int)pool3d_code_h(tap, (((long)zo * C8 + (c >> 3)) * Ho + yo) * Wo + xo, c & 7, pool_bits_h(k, s));
         const int j = code % k, i = (code / k) % k, a = code / (k * k);
         idx[q] = (int32_t)((((long)s * zo + a * d) * H + s * yo + i * d) * W + s * xo + j * d);
     }
@@ -402,7 +595,7 @@ hipError_t launch_tap3d_to_index_h(const void *tap, int32_t *idx, int C, int Do,
                                    hipStream_t stream)
 {
     const long total = (long)C * Do * Ho * Wo;
-    hipLaunchKernelGGL(tap3d_to_index_h_kernel, dim3(grid_for(total)), dim3(256), 0, stream, static_cast<const uint2v *>(tap), idx, C, Do, Ho, Wo,
+    hipLaunchKernelGGL(tap3d_to_index_h_kernel, dim3(grid_for(total)), dim3(256), 0, stream, tap, idx, C, Do, Ho, Wo,
                        H, W, k, d, s, total);
     return hipGetLastError();
 }
@@ -444,13 +637,25 @@ hipError_t launch_maxpool3d_h(const void *x, void *y, void *tap, int dtype, int 
 {
     const int C8 = (C + 7) / 8;
     if (Ho > 65535 || (long)Do * C8 > 65535 || (dtype != 1 && dtype != 2) || D < 1) return hipErrorInvalidValue;
+    const uint4v *in = static_cast<const uint4v *>(x);
+    uint4v *out = static_cast<uint4v *>(y);
+    int len, nseg, pblocks;
+    unsigned gx;
+    if (pool_bits_h(k, s) && Do == D - d && Ho == H - d && Wo == W - d && pool3d_cut(C8, Do, (long)Ho * Wo, d, len, nseg, gx, pblocks)) {
+        unsigned *tp = static_cast<unsigned *>(tap);
+        const dim3 cgrid(gx, C8);
+        if (dtype == 1) {
+            if (tap) hipLaunchKernelGGL((maxpool3d_k2_chain_h_kernel<1, true>), cgrid, dim3(256), 0, stream, in, out, tp, C8, H, W, Do, Ho, Wo, d, len, nseg, pblocks);
+            else hipLaunchKernelGGL((maxpool3d_k2_chain_h_kernel<1, false>), cgrid, dim3(256), 0, stream, in, out, tp, C8, H, W, Do, Ho, Wo, d, len, nseg, pblocks);
+        } else {
+            if (tap) hipLaunchKernelGGL((maxpool3d_k2_chain_h_kernel<2, true>), cgrid, dim3(256), 0, stream, in, out, tp, C8, H, W, Do, Ho, Wo, d, len, nseg, pblocks);
+            else hipLaunchKernelGGL((maxpool3d_k2_chain_h_kernel<2, false>), cgrid, dim3(256), 0, stream, in, out, tp, C8, H, W, Do, Ho, Wo, d, len, nseg, pblocks);
+        }
+        return hipGetLastError();
+    }
     const dim3 grid((Wo + 255) / 256, Ho, (unsigned)(Do * C8));
-    if (dtype == 1)
-        hipLaunchKernelGGL(maxpool3d_h_kernel<1>, grid, dim3(256), 0, stream, static_cast<const uint4v *>(x), static_cast<uint4v *>(y),
-                           static_cast<uint2v *>(tap), C8, H, W, Ho, Wo, k, d, s);
-    else
-        hipLaunchKernelGGL(maxpool3d_h_kernel<2>, grid, dim3(256), 0, stream, static_cast<const uint4v *>(x), static_cast<uint4v *>(y),
-                           static_cast<uint2v *>(tap), C8, H, W, Ho, Wo, k, d, s);
+    if (dtype == 1) hipLaunchKernelGGL(maxpool3d_h_kernel<1>, grid, dim3(256), 0, stream, in, out, tap, C8, H, W, Ho, Wo, k, d, s);
+    else hipLaunchKernelGGL(maxpool3d_h_kernel<2>, grid, dim3(256), 0, stream, in, out, tap, C8, H, W, Ho, Wo, k, d, s);
     return hipGetLastError();
 }
 

@@ -185,8 +185,8 @@ hipError_t launch_pack_weights_h_batch(const PackHJob *jobs, int n, int dtype, h
 hipError_t launch_pad_pack_h(const float *in, void *out, int dtype, int n, int c, int h, int w, int top, int left,
                              int ho, int wo, int mode, hipStream_t stream);
 hipError_t launch_unpack_h(const void *in, float *out, int dtype, int n, int c, int h, int w, hipStream_t stream);
-// winner codes of a 2-D pool on octets: pool_bits_h: three bit planes in a 32-bit word per unit, else a byte per element
-// (see maxpool_h_kernel); what the backward pass and the accessor read
+// winner codes of a pool on octets: pool_bits_h: three bit planes (3-D: four) in a 32-bit word per unit, else a byte per element
+// (see maxpool_h_kernel, maxpool3d_h_kernel); what the backward pass and the accessor read
 constexpr bool pool_bits_h(int k, int s) { return k == 2 && s == 1; }
 constexpr long pool_tap_bytes_h(int k, int s) { return pool_bits_h(k, s) ? 4 : 8; }     // per unit of the pool's output
 // planes8 = n * ceil(C/8); tap (optional) receives the winner codes, laid out like y
@@ -313,7 +313,7 @@ hipError_t launch_maxpool_bwd_f32(const float *dy, const uint8_t *tap, const flo
 // 3-D pool on the slice-major layout X[D][C][H][W] -> Y[Do][C][Ho][Wo]; k, d, s act on the three axes alike;
 // tap (optional, k <= 6) receives the winner's code (a*k + i)*k + j, first maximum in (a, i, j) order
 // the same on the 16-bit slice-major octet layout [D][ceil(C/8)][H][W][8], forward only
-// tap (optional): one byte per element laid out like y, the winner's code (a k + i) k + j
+// tap (optional): the winner codes, laid out like y; relu_src of the gradient as in launch_maxpool_bwd_h
 hipError_t launch_maxpool3d_h(const void *x, void *y, void *tap, int dtype, int C, int D, int H, int W, int Do, int Ho, int Wo, int k, int d,
                               int s, hipStream_t stream);
 hipError_t launch_maxpool3d_bwd_h(const void *dy, const void *tap, const void *relu_src, void *dx, int dtype, int C, int D, int H, int W,

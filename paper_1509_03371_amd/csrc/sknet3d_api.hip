@@ -485,13 +485,14 @@ sk_status sknet3d_plan(sknet3d_t *net, int32_t dz, int32_t h, int32_t w, int32_t
     if (st == SK_OK && half) st = alloc_zero_page(&net->zero_page);
     for (int i = 0; i < L && st == SK_OK && training; ++i) {
         const sk_layer &l = net->layers[i];
-        // (16-bit storage: error maps in the slice-major octet layout, counted in floats; winner codes one byte per element of it)
+        // (16-bit storage: error maps in the slice-major octet layout, counted in floats)
         auto slice_floats = [&](const Dims3 &dm) { return half ? (long)((dm.c + 7) / 8) * dm.h * dm.w * 4 : dm.slice(); };
         const long padded = (dims[i + 1].dz + 2L * grad_pad(net, i)) * slice_floats(dims[i + 1]);
         if (padded > max_grad) max_grad = padded;
         if (dims[i].dz * slice_floats(dims[i]) > max_grad) max_grad = dims[i].dz * slice_floats(dims[i]);
         if (l.kind == SK_MAXPOOL) {
-            const size_t tap_bytes = half ? (size_t)dims[i + 1].dz * slice_floats(dims[i + 1]) * 2 : (size_t)dims[i + 1].count();
+            const size_t tap_bytes = half ? (size_t)dims[i + 1].dz * slice_floats(dims[i + 1]) / 4 * sk::pool_tap_bytes_h(l.k, l.s)
+                                          : (size_t)dims[i + 1].count();
             hipError_t e = hipMalloc(reinterpret_cast<void **>(&net->tap[i]), tap_bytes);
             if (e != hipSuccess) st = fail(SK_ENOMEM, "plan: winner codes: %s", hipGetErrorString(e));
         } else {
