@@ -505,7 +505,7 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
     };
     auto position = [&](const Cursor &c) {
         TilePos p;
-        const int yp = ypos[c.yt];
+        const int yp = __builtin_amdgcn_readfirstlane(ypos[c.yt]);
         p.py = yp >> 16;
         p.ty = yp & 0xffff;
         p.x0 = c.xt * CH_TX;
@@ -908,89 +908,90 @@ __global__ __launch_bounds__(CH_THREADS + 64 * NP) void conv_h_ring_kernel(ConvH
         // iteration; a multiplying wave arrives when it is done with chunk q - 1.
         if (wave >= CH_WAVES && hd > 0) {
             // The input lacks the horizontal half of its pool: unit x of the tile is max(X[x], X[x + hd]).  The producer
-            // waves load both operands into registers (two chunks in flight, in two register sets), take the maximum
-            // and write the result into the ring stage -- one LDS write per unit, where loading the raw row straight
-            // into LDS and pooling it in place cost the direct write, two reads and a write.  Chunk c is loaded
-            // after barrier c - 3, written after barrier c - 1 (its stage was multiplied before barrier c - 2) and
-            // multiplied after barrier c.  The values are ReLU outputs (>= +0): the unsigned 16-bit order of the
-            // bit patterns is their numerical order.
-            const int my_rows = (ROWS - lw + LW - 1) / LW;         // tile rows this wave stages
-            const int Lr = 2 * my_rows * VUE;                      // its loads per chunk
-            uint4v rA[RU][VUE][2], rB[RU][VUE][2];
-            TilePos pA = ipos, pB = ipos;
-            int cA = 0, cB = 0;
-            auto gload = [&](uint4v (&r)[RU][VUE][2], const TilePos &p, int ch) {
-                const int gy0 = p.py + d * (p.ty * ypitch), gx0 = p.x0 + lane;
+            // waves load both operands into registers, take the maximum and write the result into the ring stage -- one LDS
+            // write per unit, where loading the raw row straight into LDS and pooling it in place cost the direct write, two
+            // reads and a write.  Half of the waves take the even chunks, half the odd ones: chunk c is loaded behind barrier
+            // c - 3, written behind barrier c - 1 (its stage was multiplied before barrier c - 2) and multiplied behind barrier c,
+            // so that its loads have two chunks' time, and a wave has one chunk on the way and waits for all of its loads.
+            // (Every wave with two chunks on the way in two register sets: the compiler waited for both sets in front of the
+            // older one's use, which left one chunk's time.)  The values are ReLU outputs (>= +0): the unsigned 16-bit order
+            // of the bit patterns is their numerical order.
+            // What these waves execute, their SIMD does not multiply, so a chunk is straight-line code: rows by a scalar base and
+            // columns by a 32-bit offset, both computed once a tile.  Positions outside the image are clamped into it (they feed
+            // outputs that no one stores), a wave with a row fewer loads its last one twice.
+            static_assert(NP % 2 == 0 && CH_TX >= 128, "waves for even and odd chunks; the first two 64-unit groups of a row lie inside the tile");
+            constexpr int PR = NP / 2, PU = (ROWS + PR - 1) / PR;    // waves of a chunk, rows of a wave
+            const int parity = lw & 1, first_row = lw >> 1;
+            uint4v r[PU][VUE][2];
+            long row_at[PU];                                        // bytes from the chunk's octet plane to this wave's rows
+            unsigned col_at[VUE];                                   // ... from a row to this lane's units
+            const char *plane_at = nullptr, *const xbytes = reinterpret_cast<const char *>(a.x);
+            int tile_chunk = 0;                                     // the plane's chunk within its tile
+            auto open_tile = [&]() {
+                const TilePos p = position(icur);
 #pragma unroll
-                for (int u = 0; u < RU; ++u) {
-                    const int rid = lw + LW * u;
-                    if (rid >= ROWS) break;                          // uniform: this wave has no further row
-                    const int oc = rid / RR, rr = rid - oc * RR;
-                    int o = ch * OC + oc, gy = gy0 + rr * d;
-                    o = o < a.c8_in ? o : a.c8_in - 1;
-                    gy = gy < a.H ? gy : a.H - 1;
-                    const uint4v *row = reinterpret_cast<const uint4v *>(reinterpret_cast<const char *>(a.x) + in_plane(p.b, o) * plane_bytes_in +
-                                                                         (long)gy * Wmem * 16);
+                for (int u = 0; u < PU; ++u) {
+                    const int rid = first_row + PR * u < ROWS ? first_row + PR * u : ROWS - 1, gy = p.py + d * (p.ty * ypitch + rid);
+                    row_at[u] = (long)(gy < a.H ? gy : a.H - 1) * Wmem * 16;
+                }
+#pragma unroll
+                for (int v = 0; v < VUE; ++v) {
+                    const int gx = p.x0 + lane + 64 * v;
+                    col_at[v] = (unsigned)(gx < a.W ? gx : a.W - 1) * 16u;
+                }
+                plane_at = xbytes + (long)p.b * a.c8_in * plane_bytes_in;
+            };
+            auto skip = [&](int chunks) {                            // the load cursor moves on (the chunk that it reaches exists)
+                tile_chunk += chunks;
+                plane_at += chunks * plane_bytes_in;
+                if (tile_chunk >= a.nchunks) {
+                    do {
+                        tile_chunk -= a.nchunks;
+                        advance(icur);
+                    } while (tile_chunk >= a.nchunks);
+                    open_tile();
+                    plane_at += tile_chunk * plane_bytes_in;
+                }
+            };
+            auto gload = [&]() {
+#pragma unroll
+                for (int u = 0; u < PU; ++u) {
+                    const char *row = plane_at + row_at[u], *partner = row + hd * 16;
 #pragma unroll
                     for (int v = 0; v < VUE; ++v) {
-                        int gx = gx0 + 64 * v;
-                        gx = gx < a.W ? gx : a.W - 1;                // clamped: what lies outside is replaced by zero when it is stored
-                        r[u][v][0] = row[gx];
-                        r[u][v][1] = row[gx + hd];
+                        r[u][v][0] = *reinterpret_cast<const uint4v *>(row + col_at[v]);
+                        r[u][v][1] = *reinterpret_cast<const uint4v *>(partner + col_at[v]);
                     }
                 }
             };
-            auto gstore = [&](uint4v (&r)[RU][VUE][2], const TilePos &p, int ch, int st) {
-                uint4v *dst = lds + st * stage_units;
-                const int gy0 = p.py + d * (p.ty * ypitch), gx0 = p.x0 + lane;
+            auto gstore = [&](int st) {
+                uint4v *dst = lds + st * stage_units + first_row * PW + lane;
 #pragma unroll
-                for (int u = 0; u < RU; ++u) {
-                    const int rid = lw + LW * u;
-                    if (rid >= ROWS) break;
-                    const int oc = rid / RR, rr = rid - oc * RR;
-                    const bool rowok = ch * OC + oc < a.c8_in && gy0 + rr * d < a.H;
+                for (int u = 0; u < PU; ++u) {
+                    if (PR * (u + 1) > ROWS && first_row + PR * u >= ROWS) break;     // uniform: this wave has no further row
 #pragma unroll
                     for (int v = 0; v < VUE; ++v) {
-                        const int xc = lane + 64 * v;
-                        uint4v m = max_u16x8(r[u][v][0], r[u][v][1]);
-                        if (!(rowok && gx0 + 64 * v < a.W)) m = uint4v{0u, 0u, 0u, 0u};
-                        if (xc < PWL) dst[rid * PW + xc] = m;
+                        const uint4v m = max_u16x8(r[u][v][0], r[u][v][1]);
+                        if (v < 2 || lane + 64 * v < PWL) dst[u * (PR * PW) + 64 * v] = m;
                     }
                 }
             };
-            // chunk c (c >= 1), right after barrier c - 1: from its register set into its stage, then chunk c + 2 into the set
-            auto step = [&](uint4v (&r)[RU][VUE][2], TilePos &p, int &ch, int c) {
-                if (c >= total_chunks) return;
-                __builtin_amdgcn_sched_barrier(0);
-                wait_vmcnt_at_most(c + 1 < total_chunks ? Lr : 0);   // the loads of chunk c + 1 are younger and may be in flight
-                __builtin_amdgcn_sched_barrier(0);
-                gstore(r, p, ch, c % S);
+            int c = parity, st = parity % S;
+            if (c < total_chunks) {
+                open_tile();
+                if (parity) skip(1);
+                gload();
+            }
+            if (parity) block_sync_lds();                            // barrier 0
+            for (; c < total_chunks; c += 2) {
+                gstore(st);
+                st = st + 2 >= S ? st + 2 - S : st + 2;
                 if (c + 2 < total_chunks) {
-                    take_next(p, ch);
-                    gload(r, p, ch);
+                    skip(2);
+                    gload();
                 }
-            };
-            take_next(pA, cA);
-            gload(rA, pA, cA);                                       // chunk 0
-            if (total_chunks > 1) {
-                take_next(pB, cB);
-                gload(rB, pB, cB);                                   // chunk 1
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            wait_vmcnt_at_most(total_chunks > 1 ? Lr : 0);
-            __builtin_amdgcn_sched_barrier(0);
-            gstore(rA, pA, cA, 0);
-            if (total_chunks > 2) {
-                take_next(pA, cA);
-                gload(rA, pA, cA);                                   // chunk 2
-            }
-            for (int q = 0; q < total_chunks; q += 2) {
-                block_sync_lds();                                    // barrier q: chunk q is in LDS
-                step(rB, pB, cB, q + 1);
-                if (q + 1 < total_chunks) {
-                    block_sync_lds();                                // barrier q + 1
-                    step(rA, pA, cA, q + 2);
-                }
+                block_sync_lds();                                    // barrier c: chunk c is in LDS
+                if (c + 1 < total_chunks) block_sync_lds();          // barrier c + 1
             }
             return;
         }
@@ -1218,7 +1219,8 @@ static size_t ring_smem(int d, int c_out, int c8_in, int Ho, int hd = 0)
     const int nchunks = (c8_in + OC - 1) / OC;
     const int m_tiles_all = ((c_out + 15) / 16 + MT - 1) / MT * MT;
     const size_t units = RESW ? S * tile + nchunks * slab : S * (tile + slab);
-    return units * 16 + (size_t)m_tiles_all * 64 + (size_t)(Ho / R + 2 * d + 2) * 4;
+    // the table of y tiles: a pool of the output sets them R - 1 rows apart, which makes more of them
+    return units * 16 + (size_t)m_tiles_all * 64 + (size_t)(Ho / (R - 1) + 2 * d + 2) * 4;
 }
 
 template <int DT, int KS, int MT, bool MAP4, int R, bool HAS_MASK, int S, bool RESW, int NP = 0, bool VPOOL = false>
