@@ -2,6 +2,7 @@
 // kernel stride (forward with tap codes, gather-form backward), per-pixel softmax and softmax
 // loss, SGD, crop-and-place copy.  One element per thread, x fastest, so that a 64-lane
 // wavefront reads and writes consecutive addresses.
+#include "mirror_index.h"
 #include "sk_kernels.h"
 
 namespace sk {
@@ -14,21 +15,6 @@ static inline int grid_for(long total, int block = 256, int cap = 1 << 20)
 }
 
 // ---- mirror padding (Section 1.3) ---------------------------------------------------------------
-__device__ __forceinline__ int mirror_index(int t, int len, int mode)
-{
-    if (len == 1) return 0;
-    if (mode == 0) {                       // reflect: ... 2 1 | 0 1 2 ... L-1 | L-2 L-3 ...
-        const int period = 2 * (len - 1);
-        t %= period;
-        if (t < 0) t += period;
-        return t < len ? t : period - t;
-    }
-    const int period = 2 * len;            // symmetric: ... 1 0 | 0 1 ... L-1 | L-1 L-2 ...
-    t %= period;
-    if (t < 0) t += period;
-    return t < len ? t : period - 1 - t;
-}
-
 __global__ void mirror_pad_f32_kernel(const float *in, float *out, int planes, int h, int w, int top,
                                       int left, int ho, int wo, int mode)
 {

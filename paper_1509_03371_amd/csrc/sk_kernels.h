@@ -83,6 +83,20 @@ hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t stream);
 bool conv1x1_f32_supported(const ConvF32Args &a);
 hipError_t launch_conv1x1_f32(const ConvF32Args &a, hipStream_t stream);
 
+// First layer (one input map, d = 1) + mirror padding + pool k = 2, d = 1, s = 1 of an fp32 plan that does not keep the
+// layer's output (kernels_c1_pool_f32.hip)
+struct C1PoolF32Args {
+    const float *image;  // [n][h][w]
+    const float *wp;     // as in ConvF32Args
+    const float *bias;   // [n_pad]
+    float *padded;       // [n][h_pad][w_pad], written
+    float *y;            // [n][c_out][h_pad - k][w_pad - k]
+    int n, h, w, top, left, mode, h_pad, w_pad;
+    int k, c_out, n_pad, relu;
+};
+bool conv_c1_pool_f32_supported(int k, int n, int h_pad, int w_pad);
+hipError_t launch_conv_c1_pool_f32(const C1PoolF32Args &a, hipStream_t stream);
+
 // Pack OIHW fp32 master weights [c_out][c_in][k][k] into the K-major layout launch_conv_f32 reads.
 // flip_transpose = 0: Wp[(c*k+i)*k+j][o] = W[o][c][i][j]                       (forward)
 // flip_transpose = 1: Wp[(o*k+i)*k+j][c] = W[o][c][k-1-i][k-1-j]               (data gradient)
