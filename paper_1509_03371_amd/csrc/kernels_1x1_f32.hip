@@ -253,7 +253,12 @@ __global__ __launch_bounds__(P1_THREADS, 2) void conv1x1_out_kernel(Conv1Args a)
 // Fused head: h = ReLU(W1 x + b1), z = W2 h + b2, softmax.  A lane has hidden maps 4 g .. 4 g + 3 of every tile for its four pixels and adds
 // their share of the class sums; the four lane groups' shares meet in two shuffles, and group g writes class g (and g + 4).
 // 48 -> 200 -> 2 at 512^2: 73 -> 56 us; the matrix unit alone needs 35 and the staging of the weights five.
-template <int KS, int CL>
+// POOL: the input is that of an SK pool of kernel 2 and stride a.pool in front of the head, whose maps are not stored.  The waves then
+// walk the pixels with the pitch of the input rows, W + pool, so that the four samples of a window lie at fixed distances
+// for any lane (pixels x >= W are computed and dropped: 1.5 % at 512^2); maxima in the order of the pool kernel.
+// 48 maps at 512^2, d = 8: pool 22.7 + head 63.9 -> 79 us under the profiler, the forward pass 736 -> 726 us (the 96^2 net of 16 maps 22.6 -> 20.0,
+// 4 x 900 x 1000 9.55 -> 8.44 ms with the first layer's pool).
+template <int KS, int CL, bool POOL>
 __global__ __launch_bounds__(P1_THREADS, 2) void head1x1_kernel(HeadArgs a, int per_image)
 {
     extern __shared__ float smem[];
@@ -272,12 +277,25 @@ __global__ __launch_bounds__(P1_THREADS, 2) void head1x1_kernel(HeadArgs a, int 
         w2[q] = c < a.classes && m < a.hidden ? a.w2[c * a.hidden + m] : 0.f;
     }
     __syncthreads();
-    const Groups groups{0, 0, a.n * per_image, per_image, plane};
+    const int pitch = a.W + (POOL ? a.pool : 0), walk = POOL ? a.H * pitch - a.pool : plane;
+    const long in_plane = POOL ? (long)(a.H + a.pool) * pitch : plane;
+    const Groups groups{0, 0, a.n * per_image, per_image, walk};
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), stride = gridDim.x * P1_WAVES;
     auto load = [&](floatx4 (&x)[KS], int b, int px) {
-        const float *src = static_cast<const float *>(a.x) + (long)b * a.c_in * plane + px + 4 * l16;
+        const float *src = static_cast<const float *>(a.x) + (long)b * a.c_in * in_plane + px + 4 * l16;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) x[s] = load4(src + (long)(4 * s + g < a.c_in ? 4 * s + g : 0) * plane);
+        for (int s = 0; s < KS; ++s) {
+            const float *p = src + (4 * s + g < a.c_in ? 4 * s + g : 0) * in_plane;
+            x[s] = load4(p);
+            if constexpr (POOL) {
+                const floatx4 right = load4(p + a.pool), below = load4(p + (long)a.pool * pitch), corner = load4(p + (long)a.pool * pitch + a.pool);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float up = right[e] > x[s][e] ? right[e] : x[s][e], down = corner[e] > below[e] ? corner[e] : below[e];
+                    x[s][e] = down > up ? down : up;
+                }
+            }
+        }
 #pragma unroll
         for (int s = 0; s < KS; ++s)
             if (4 * s + g >= a.c_in) x[s] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -345,14 +363,24 @@ __global__ __launch_bounds__(P1_THREADS, 2) void head1x1_kernel(HeadArgs a, int 
                 z[c][e] = c < a.classes ? expf(z[c][e] - m[e]) : 0.f;
                 sum[e] = c == 0 ? z[c][e] : sum[e] + z[c][e];
             }
-        float *dst = a.prob + (long)b * a.classes * plane + px + 4 * l16;
+        const int q = px + 4 * l16, row = POOL ? (int)((unsigned)q / (unsigned)pitch) : 0, col = POOL ? q - row * pitch : 0;
+        float *dst = a.prob + (long)b * a.classes * plane + (POOL ? row * a.W + col : q);
 #pragma unroll
         for (int c = 0; c < CL; ++c)
             if (c < a.classes && (c & 3) == g) {
                 floatx4 p;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) p[e] = z[c][e] * (1.f / sum[e]);
-                store4(dst + (long)c * plane, p);
+                if (!POOL || col + 4 <= a.W) {
+                    store4(dst + (long)c * plane, p);
+                    continue;
+                }
+                // the end of a row: pixels up to W, then a gap of `pool`, then those of the next row (H*W of them in all)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (col + e < a.W) dst[(long)c * plane + e] = p[e];
+                    else if (col + e >= pitch) dst[(long)c * plane + e - a.pool] = p[e];
+                }
             }
         if (!more) return;
         grp += stride;
@@ -549,25 +577,25 @@ hipError_t launch_out(const Conv1Args &a, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <int KS>
-hipError_t launch_head_ks(const HeadArgs &a, int per_image, hipStream_t stream)
+template <int KS, int CL, bool POOL>
+hipError_t launch_head_cl(const HeadArgs &a, hipStream_t stream)
 {
-    const int tiles = (a.hidden + 15) / 16, cl = a.classes <= 2 ? 2 : (a.classes <= 4 ? 4 : 8);
-    const size_t smem = sizeof(float) * ((size_t)tiles * KS * 64 + (size_t)tiles * 16 * (1 + cl));
-    static bool set[3];
-    const int blocks = p1_blocks(a.n * per_image, smem);
-    hipError_t e = hipSuccess;
-    if (cl == 2) {
-        if ((e = allow_lds(&head1x1_kernel<KS, 2>, set[0])) == hipSuccess)
-            hipLaunchKernelGGL((head1x1_kernel<KS, 2>), dim3(blocks), dim3(P1_THREADS), smem, stream, a, per_image);
-    } else if (cl == 4) {
-        if ((e = allow_lds(&head1x1_kernel<KS, 4>, set[1])) == hipSuccess)
-            hipLaunchKernelGGL((head1x1_kernel<KS, 4>), dim3(blocks), dim3(P1_THREADS), smem, stream, a, per_image);
-    } else {
-        if ((e = allow_lds(&head1x1_kernel<KS, 8>, set[2])) == hipSuccess)
-            hipLaunchKernelGGL((head1x1_kernel<KS, 8>), dim3(blocks), dim3(P1_THREADS), smem, stream, a, per_image);
-    }
-    return e != hipSuccess ? e : hipGetLastError();
+    const int tiles = (a.hidden + 15) / 16, per_image = ((POOL ? a.H * (a.W + a.pool) - a.pool : a.H * a.W) + P1_PX - 1) / P1_PX;
+    const size_t smem = sizeof(float) * ((size_t)tiles * KS * 64 + (size_t)tiles * 16 * (1 + CL));
+    static bool set;
+    const hipError_t e = allow_lds(&head1x1_kernel<KS, CL, POOL>, set);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((head1x1_kernel<KS, CL, POOL>), dim3(p1_blocks(a.n * per_image, smem)), dim3(P1_THREADS), smem, stream, a, per_image);
+    return hipGetLastError();
+}
+
+template <int KS>
+hipError_t launch_head_ks(const HeadArgs &a, hipStream_t stream)
+{
+    if (a.pool) return a.classes <= 2 ? launch_head_cl<KS, 2, true>(a, stream) : launch_head_cl<KS, 4, true>(a, stream);
+    if (a.classes <= 2) return launch_head_cl<KS, 2, false>(a, stream);
+    if (a.classes <= 4) return launch_head_cl<KS, 4, false>(a, stream);
+    return launch_head_cl<KS, 8, false>(a, stream);
 }
 
 template <int RT, int CT, int RG>
@@ -623,6 +651,7 @@ hipError_t launch_conv1x1_f32(const ConvF32Args &c, hipStream_t stream)
 bool head1x1_f32_supported(const HeadArgs &a)
 {
     const long plane = (long)a.H * a.W, groups = a.n * ((plane + P1_PX - 1) / P1_PX);
+    if (a.pool < 0 || (a.pool > 0 && (a.classes > 4 || a.W < 4 || (plane + (long)a.H * a.pool) * a.n > 0x3fffffffL))) return false;
     return a.dtype == 0 && a.hd == 0 && a.c_in <= 48 && a.classes <= 8 && plane >= P1_PX && a.hidden <= 256 &&
            (a.hidden <= 64 || (groups >= 4L * device_cus() && a.c_in > 8));
 }
@@ -630,12 +659,11 @@ bool head1x1_f32_supported(const HeadArgs &a)
 hipError_t launch_head1x1_f32(const HeadArgs &a, hipStream_t stream)
 {
     if (!head1x1_f32_supported(a)) return hipErrorInvalidValue;
-    const int per_image = (a.H * a.W + P1_PX - 1) / P1_PX;
-    if (a.ksteps <= 2) return launch_head_ks<2>(a, per_image, stream);
-    if (a.ksteps <= 4) return launch_head_ks<4>(a, per_image, stream);
-    if (a.ksteps <= 6) return launch_head_ks<6>(a, per_image, stream);
-    if (a.ksteps <= 8) return launch_head_ks<8>(a, per_image, stream);
-    return launch_head_ks<12>(a, per_image, stream);
+    if (a.ksteps <= 2) return launch_head_ks<2>(a, stream);
+    if (a.ksteps <= 4) return launch_head_ks<4>(a, stream);
+    if (a.ksteps <= 6) return launch_head_ks<6>(a, stream);
+    if (a.ksteps <= 8) return launch_head_ks<8>(a, stream);
+    return launch_head_ks<12>(a, stream);
 }
 
 // one side at most 48 maps, the other at most 208, and few enough sums for the registers

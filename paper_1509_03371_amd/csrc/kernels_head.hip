@@ -552,6 +552,7 @@ hipError_t launch_head_fused(HeadArgs a, hipStream_t stream)
     if (a.hd < 0 || (a.hd > 0 && !head_takes_pending_pool(a.dtype, a.c_in, a.classes, a.hd))) return hipErrorInvalidValue;
     a.ksteps = head_ksteps(a.dtype, a.c_in);
     if (a.dtype == 0 && head1x1_f32_supported(a)) return launch_head1x1_f32(a, stream);
+    if (a.pool != 0) return hipErrorInvalidValue;
     if (a.dtype == 0) return launch_head_dt<0>(a, stream);
     if (a.dtype == 1) return launch_head_dt<1>(a, stream);
     return launch_head_dt<2>(a, stream);

@@ -235,6 +235,7 @@ struct HeadArgs {
     int dtype, n, c_in, H, W, hidden, classes;
     int hd;               // > 0: the input lacks the horizontal half of an SK pool at kernel stride hd (rows of W + hd samples)
     int ksteps;           // filled in by the launcher
+    int pool;             // > 0 (fp32, where head1x1_f32_supported): x is the input [n][c_in][H + pool][W + pool] of a pool of kernel 2, stride `pool`
 };
 bool head_supported(int dtype, int c_in, int hidden, int classes);
 bool head_takes_pending_pool(int dtype, int c_in, int classes, int hd);

@@ -67,6 +67,7 @@ struct sknet {
     int pending_head = 0;
     // fp32 inference plans: padding, first layer and its pool run as one launch (the layer's output is not stored)
     bool c1_pool = false;
+    int head_pool = 0;                // fp32 inference plans: the fused head takes the maxima of the pool in front of it (its d), whose maps are not stored
     bool kept(int layer) const        // is the output of `layer` in memory in the form the layer defines?
     {
         if (fuse_head && layer >= (int)layers.size() - 2) return false;
@@ -98,6 +99,7 @@ struct sknet {
         steps.clear();
         vpool.clear(); pending.clear(); pending_head = 0;
         fuse_head = c1_pool = false;
+        head_pool = 0;
         for (auto &c : convs) release_conv(c);
         planned = forward_done = backward_done = false;
     }
@@ -167,6 +169,10 @@ sk_status run_forward_step(sknet *net, int step_idx, hipStream_t stream)
         sk::HeadArgs a{};
         a.x = net->pending_head ? net->act[L - 3] : net->act[L - 2];    // a pending pool: the buffer of the convolution before it
         a.hd = net->pending_head;
+        if (net->head_pool) {
+            a.x = net->act[L - 3];
+            a.pool = net->head_pool;
+        }
         a.w1p = net->head_w1p; a.b1 = c1.b_dev; a.w2 = c2.w_dev; a.b2 = c2.b_dev;
         a.prob = net->last_prob; a.dtype = net->dtype; a.n = net->n; a.c_in = in.c; a.H = in.h; a.W = in.w;
         a.hidden = c1.c_out; a.classes = c2.c_out;
@@ -542,14 +548,23 @@ sk_status sknet_plan(sknet_t *net, int32_t n, int32_t h, int32_t w, int32_t pad,
     net->c1_pool = mode == 0 && !half && net->c_in == 1 && L >= 2 && net->layers[0].kind == SK_CONV && net->layers[0].d == 1 &&
                    net->layers[1].kind == SK_MAXPOOL && net->layers[1].k == 2 && net->layers[1].s == 1 && net->layers[1].d == 1 &&
                    sk::conv_c1_pool_f32_supported(net->layers[0].k, n, dims[0].h, dims[0].w);
+    net->head_pool = 0;
+    if (mode == 0 && !half && net->fuse_head && L >= 4 && !(L == 4 && net->c1_pool) && net->layers[L - 3].kind == SK_MAXPOOL && net->layers[L - 3].k == 2 &&
+        net->layers[L - 3].s == 1) {
+        sk::HeadArgs a{};
+        a.n = n; a.c_in = dims[L - 2].c; a.H = dims[L - 2].h; a.W = dims[L - 2].w;
+        a.hidden = net->layers[L - 2].c_out; a.classes = net->layers[L - 1].c_out; a.pool = net->layers[L - 3].d;
+        if (sk::head1x1_f32_supported(a)) net->head_pool = a.pool;
+    }
     net->steps.clear();
     net->steps.push_back({0, 0});
     for (int i = 0; i < (net->fuse_head ? L - 2 : L); ++i)
-        if (!(i > 0 && net->vpool[i - 1]) && !(i == 1 && net->c1_pool)) net->steps.push_back({1, i});
+        if (!(i > 0 && net->vpool[i - 1]) && !(i == 1 && net->c1_pool) && !(i == L - 3 && net->head_pool)) net->steps.push_back({1, i});
     net->steps.push_back({net->fuse_head ? 3 : 2, 0});
     for (int i = 0; i <= L && st == SK_OK; ++i) {
         if (net->fuse_head && i >= L - 1) continue;   // hidden maps and logits never leave the head kernel
         if (i == 1 && net->c1_pool) continue;         // goes from the convolution to its pool in registers
+        if (i == L - 2 && net->head_pool) continue;   // the head takes the maxima itself
         if (i >= 2 && net->vpool[i - 2]) continue;    // the output of a pool that runs inside its neighbours
         const bool f32 = (i == 0) ? !half : stored_f32(net, i - 1);
         const long count = f32 ? dims[i].count(n) : octet_floats(n, dims[i]);
@@ -888,12 +903,15 @@ sk_status sknet_get_activation(sknet_t *net, int32_t layer_idx, float *nchw_host
     const int i = layer_idx + 1;
     const Dims &dm = net->dims[i];
     const bool f32 = (i == 0) ? !net->half() : stored_f32(net, i - 1);
-    if (i == 1 && net->c1_pool) {   // not in memory: convolve the padded image once more
-        const ConvParams &c = net->convs[0];
+    // fp32 outputs that a fused launch leaves out: the layer runs once more on its input
+    if ((i == 1 && net->c1_pool) || (net->head_pool && i == (int)net->layers.size() - 2)) {
+        const sk_layer &l = net->layers[layer_idx];
+        const Dims &in = net->dims[layer_idx];
         float *tmp = nullptr;
         SK_TRY(alloc_f(&tmp, dm.count(net->n)));
-        hipError_t e = sk::launch_conv_f32(conv_args(c, net->act[0], net->n, net->dims[0], net->layers[0].d, net->layers[0].relu, tmp, dm),
-                                           net->last_stream);
+        hipError_t e = l.kind == SK_CONV ? sk::launch_conv_f32(conv_args(net->convs[0], net->act[0], net->n, in, l.d, l.relu, tmp, dm), net->last_stream)
+                                         : sk::launch_maxpool_f32(net->act[layer_idx], tmp, nullptr, net->n * in.c, in.h, in.w, dm.h, dm.w, l.k, l.d, l.s,
+                                                                  net->last_stream);
         if (e == hipSuccess) e = hipStreamSynchronize(net->last_stream);
         if (e == hipSuccess) e = hipMemcpy(nchw_host, tmp, sizeof(float) * dm.count(net->n), hipMemcpyDeviceToHost);
         (void)hipFree(tmp);
