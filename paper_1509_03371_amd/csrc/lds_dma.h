@@ -1,0 +1,19 @@
+// Global memory straight into LDS for kernels whose LDS reads are transposing ones.
+//
+// The compiler cannot tell which LDS addresses a transposing read (ds_read_b64_tr_b16) touches, and waits for EVERY
+// __builtin_amdgcn_global_load_lds under way ahead of it: rows that are loaded steps ahead of their use were waited for at once.  This load is
+// out of its sight, so the kernel waits for it alone: s_waitcnt vmcnt with the number of younger loads, then a barrier.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace sk {
+
+// lane l's sixteen bytes at src to dst + 16 l (dst: the same in every lane; inactive lanes move nothing)
+__device__ __forceinline__ void lds_dma16(const void *src, const void *dst)
+{
+    const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(const __attribute__((address_space(3))) void *)dst);
+    // m0 (nothing else in these kernels uses it) holds the LDS address, one instruction ahead of its use
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(at) : "memory");
+}
+
+}  // namespace sk
