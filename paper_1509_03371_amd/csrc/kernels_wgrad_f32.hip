@@ -927,29 +927,33 @@ __global__ __launch_bounds__(256, MB * NB > 36 ? 1 : 2) void wgrad_trr_h_kernel(
 
 // The same gradient with the staged input rows kept across steps (k >= 2), every load straight into LDS.
 // A workgroup walks a strip -- one image, one 64-column segment, the output rows of one residue class y = r, r + d,
-// r + 2d, ... -- so that consecutive steps share k - 1 of their k input rows: the rows sit in a ring of k + 2 LDS slots per
+// r + 2d, ... -- so that consecutive steps share k - 1 of their k input rows: the rows sit in a ring of LDS slots per
 // input octet (a tile group inside one map pair keeps only the kernel rows its taps use), and the column tiles' read
-// offsets rotate with the step.  The loads of a step (one new row per octet and a dY segment) are issued two steps ahead, into the slot and
-// the dY buffer that the step before the current one read, so a step has one barrier and waits for loads that had a whole step
-// to arrive.  The steps of all strips, in strip order, are dealt out to the workgroups in equal contiguous ranges.
+// offsets rotate with the step.  The steps of all strips, in strip order, are dealt out to the workgroups in equal contiguous ranges.
+// Four waves (one team) take a step a turn; two teams take two neighbouring steps of the strip in the same turn and add their sums through LDS
+// at the end (wgrad_strip_teams says where).  The loads of a turn -- one new row per octet and a dY segment for each step -- are
+// issued two turns ahead (two teams, whose turn takes twice as long: one), into the slots and the dY buffer that the turn before the
+// current one read, so a turn has one barrier and waits for loads that had a whole turn to arrive.
 // With rows staged through registers one step ahead (wgrad_trr_h_kernel, which keeps what this kernel's LDS does not hold) the
 // barriers of a step waited for memory.  A half of 32 columns that lies beyond the map is not multiplied.  3x3 layers of the U-Net at
-// 572^2: 42 -> 34.5 us on average (about 15 of them the private copies, 75 MB), 64 -> 64 at 568^2 69 -> 48; 3-D layers of 81 x 145 x 145: 369 -> 283,
-// 230 -> 131, 196 -> 113.
+// 572^2 42 + 14.2 (the reduction) -> 34.7 + 9.7 us on average, 64 -> 64 at 568^2 69 -> 48; 3-D layers of 81 x 145 x 145: 369 -> 296, 230 -> 131,
+// 196 -> 113.
 __device__ uint4v wg_zero16[1];                          // never written
 
-template <int MB, int NB, int DT>
-__global__ __launch_bounds__(256, MB * NB > 36 ? 1 : 2) void wgrad_strip_h_kernel(WgradArgs a)
+template <int MB, int NB, int DT, int TEAMS>
+__global__ __launch_bounds__(256 * TEAMS, MB * NB > 36 ? 1 : 2) void wgrad_strip_h_kernel(WgradArgs a)
 {
     constexpr int DYL = (2 * MB + 3) / 4, XU = 2;       // dY octets and input rows a wave loads for a step
     constexpr int NL = DYL + 2 * XU;                    // ... in loads (a row is 64 columns and the rest of the window)
     constexpr int DYB = 2 * MB * WG_TRP;                // a dY buffer
+    constexpr int LOOK = TEAMS > 1 ? 1 : 2;             // turns between a step's loads and the step
     extern __shared__ uint4v smem16[];
     const int k = a.k, d = a.d, kk = k * k;
     const int m_rows = a.MTo * 16;
-    uint4v *dys = smem16;                               // 3 x [2*MB octets][WG_TRP pixels]
-    uint4v *xs = dys + 3 * DYB;                         // [octets of the group][ni + 2 slots][xpitch pixels]
-    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    uint4v *dys = smem16;                               // (LOOK + 1) x TEAMS x [2*MB octets][WG_TRP pixels]
+    uint4v *xs = dys + (LOOK + 1) * TEAMS * DYB;        // [octets of the group][slots][xpitch pixels]
+    const int team = TEAMS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+    const int tid = threadIdx.x & 255, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rr = l16 >> 2, qq = l16 & 3;
     const int tail = (k - 1) * d;                       // window columns beyond the first 64: 1 .. 64 (checked by the launcher)
@@ -969,7 +973,7 @@ __global__ __launch_bounds__(256, MB * NB > 36 ? 1 : 2) void wgrad_strip_h_kerne
         i_lo = (nk_lo % kk) / k;
         ni = (nk_hi % kk) / k - i_lo + 1;
     }
-    const int slots = ni + 2;
+    const int slots = ni + TEAMS - 1 + LOOK * TEAMS;
     const unsigned slot_bytes = (unsigned)a.xpitch * 16;
     unsigned xoff[NB], aoff[MB];
     int iq[NB];                                         // kernel row of column tile q within the ring (wave-uniform)
@@ -1043,33 +1047,41 @@ __global__ __launch_bounds__(256, MB * NB > 36 ? 1 : 2) void wgrad_strip_h_kerne
     for (int gs = g0; gs < g1;) {
         const int b = bx / a.xsegs, x0 = (bx - b * a.xsegs) * WG_SEG;
         const int len = min(g1 - gs, class_len(r) - t);          // this workgroup's steps of the strip
-        int y = r + t * d;
+        const int y = r + t * d;
         wide_barrier();                                          // the strip before has been read
-        for (int rid = wave; rid < noct * ni; rid += 4) {
-            const int ocr = rid / ni, i = rid - ocr * ni;
+        // the first turn's window rows and dY segments
+        const int rows = ni - 1 + min(TEAMS, len);
+        for (int rid = wave + 4 * team; rid < noct * rows; rid += 4 * TEAMS) {
+            const int ocr = rid / rows, i = rid - ocr * rows;
             load_row(b, y + (i_lo + i) * d, x0, ocr, i);
         }
-        load_dy(b, y, x0, 0);
-        if (len > 1) load_step(b, y + d, x0, 1, ni);
+        if (team < len) load_dy(b, y + team * d, x0, team);
+        if (LOOK > 1 && len > 1) load_step(b, y + d, x0, 1, ni);
         const bool wide = x0 + 32 < a.Wo;
-        int rot = 0, buf = 0;                                    // slot of the window's first row; dY buffer
-        for (int st = 0; st < len; ++st) {
-            // the step's loads have landed; younger: those of the next one
-            if (st + 1 < len) wide_wait<NL>();
+        int rot = team, buf = 0;                                 // slot of the first row of the team's window; dY buffers
+        for (int st = 0; st < len; st += TEAMS) {
+            // the turn's loads have landed; younger: those of the next one
+            if (LOOK > 1 && st + 1 < len) wide_wait<NL>();
             else wide_wait<0>();
             wide_barrier();
-            if (st + 2 < len) {                                  // into what the step before this one read
-                const int to = rot == 0 ? slots - 1 : rot - 1;
-                load_step(b, y + 2 * d, x0, buf == 0 ? 2 : buf - 1, to);
+            const int mine = st + team;
+            if (mine + LOOK * TEAMS < len) {                     // into what the turn before this one read
+                int to = rot - TEAMS;
+                to = to < 0 ? to + slots : to;
+                load_step(b, y + (mine + LOOK * TEAMS) * d, x0, (buf == 0 ? LOOK : buf - 1) * TEAMS + team, to);
             }
+            const int rot_now = rot, buf_now = buf * TEAMS + team;
+            rot = rot + TEAMS >= slots ? rot + TEAMS - slots : rot + TEAMS;
+            buf = buf == LOOK ? 0 : buf + 1;
+            if (mine >= len) continue;                           // the odd end of a strip
             unsigned xo[NB];
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
-                int slot = iq[q] + rot;
+                int slot = iq[q] + rot_now;
                 slot = slot >= slots ? slot - slots : slot;
                 xo[q] = xoff[q] + (unsigned)slot * slot_bytes;
             }
-            const unsigned dyo = (unsigned)buf * (DYB * 16);
+            const unsigned dyo = (unsigned)buf_now * (DYB * 16);
 #pragma unroll
             for (int p = 0; p < WG_SEG; p += 32) {
                 if (p > 0 && !wide) break;                       // uniform: the rest of the segment lies beyond the map
@@ -1089,14 +1101,25 @@ __global__ __launch_bounds__(256, MB * NB > 36 ? 1 : 2) void wgrad_strip_h_kerne
                     bacc = mfma32<DT>(aw, ones, bacc);
                 }
             }
-            y += d;
-            rot = rot + 1 == slots ? 0 : rot + 1;
-            buf = buf == 2 ? 0 : buf + 1;
         }
         gs += len;
         t = 0;
         ++r;
         if (r >= d || class_len(r) == 0) { r = 0; ++bx; }
+    }
+    floatx4 *const sums = reinterpret_cast<floatx4 *>(smem16) + wave * ((MB * NB + 1) * 64) + lane;
+    if constexpr (TEAMS > 1) {                                  // the second team's sums to LDS, the first goes on and adds them
+        __syncthreads();
+        if (team == 1) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+#pragma unroll
+                for (int q = 0; q < NB; ++q) sums[(m * NB + q) * 64] = acc[m][q];
+            sums[MB * NB * 64] = bacc;
+        }
+        __syncthreads();
+        if (team == 1) return;
+        bacc += sums[MB * NB * 64];
     }
     if (sum_dy && l16 == 0) {                                   // every column of bacc holds the same sums
 #pragma unroll
@@ -1114,9 +1137,13 @@ __global__ __launch_bounds__(256, MB * NB > 36 ? 1 : 2) void wgrad_strip_h_kerne
         for (int q = 0; q < NB; ++q) {
             const int nk = (ngroup * NB + q) * 4 + wave;
             if (nk >= a.NTk) continue;
+            floatx4 v = acc[m][q];
+            if constexpr (TEAMS > 1) {
+                v += sums[(m * NB + q) * 64];
+                __builtin_amdgcn_sched_barrier(0);              // (all of them read ahead do not fit the registers)
+            }
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-                dst[((long)(mo0 + m) * 16 + 4 * g + r4) * ncols + nk * 16 + l16] = acc[m][q][r4];
+            for (int r4 = 0; r4 < 4; ++r4) dst[((long)(mo0 + m) * 16 + 4 * g + r4) * ncols + nk * 16 + l16] = v[r4];
         }
     }
 }
@@ -1444,18 +1471,35 @@ static hipError_t launch_wgrad_trr_t(const WgradArgs &a, size_t smem, int blocks
     return hipGetLastError();
 }
 
+// Teams of four waves in a workgroup of wgrad_strip_h_kernel.  The private copies of a gradient are as large as all accumulators of the GPU, and with
+// many a wave (3x3 layers of 48 and more input maps: 36 tiles, 75 MB) two workgroups a CU spend a third of the time on them: two teams
+// that add their sums first write and read half (16 U-Net steps 51.8 -> 50.5 ms; the reductions 14.2 -> 9.7 us).  With few a wave
+// (16 tiles and less: 33 MB and less) what counts is that the barriers of two workgroups do not fall together (3-D 48 -> 64 on 130 x 141 x 141: 131 us,
+// 161 with two teams; 113 and 125 for 16 output maps).  More than 36 tiles leave room for one wave a SIMD.
+static constexpr int wgrad_strip_teams(int MB, int NB) { return MB * NB >= 24 && MB * NB <= 36 ? 2 : 1; }
+
+// LDS of wgrad_strip_h_kernel (two teams: also the sums that they exchange), 0 where it does not fit as often as the registers do
+static size_t wgrad_strip_smem(int MB, int NB, int goct, int k, int xpitch)
+{
+    const int teams = wgrad_strip_teams(MB, NB), look = teams > 1 ? 1 : 2;
+    size_t smem = 16 * ((size_t)(look + 1) * teams * 2 * MB * WG_TRP + (size_t)goct * (k + teams - 1 + look * teams) * xpitch);
+    if (teams > 1) smem = std::max(smem, (size_t)(MB * NB + 1) * 4 * 1024);
+    return goct <= 8 && smem <= (MB * NB < 24 ? 80 : 160) * 1024u ? smem : 0;
+}
+
 template <int MB, int NB, int DT>
 static hipError_t launch_wgrad_strip_t(const WgradArgs &a, size_t smem, int blocks, hipStream_t stream)
 {
+    constexpr int TEAMS = wgrad_strip_teams(MB, NB);
     static bool attr_set = false;
     if (smem > 48 * 1024 && !attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&wgrad_strip_h_kernel<MB, NB, DT>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&wgrad_strip_h_kernel<MB, NB, DT, TEAMS>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const int mgroups = (a.MTo + MB - 1) / MB, ngroups = (a.NTk + 4 * NB - 1) / (4 * NB);
-    hipLaunchKernelGGL((wgrad_strip_h_kernel<MB, NB, DT>), dim3(blocks, mgroups * ngroups), dim3(256), smem, stream, a);
+    hipLaunchKernelGGL((wgrad_strip_h_kernel<MB, NB, DT, TEAMS>), dim3(blocks, mgroups * ngroups), dim3(256 * TEAMS), smem, stream, a);
     return hipGetLastError();
 }
 
@@ -1562,6 +1606,10 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
     const long per_cu = (long)(160 * 1024) / (long)(smem > 1 ? smem : 1);
     long resident = (long)cus * (per_cu < 1 ? 1 : (per_cu > 2 ? 2 : per_cu));
+    // input rows kept across steps: kernels of two rows or more
+    const bool ring = tr_path && k >= 2 && goct <= 12;
+    const size_t strip_smem = ring ? wgrad_strip_smem(MB, NB, goct, k, a.xpitch) : 0;
+    if (strip_smem && wgrad_strip_teams(MB, NB) > 1) resident = cus;
     // 16-bit path, few segments per workgroup (one 512^2 image): the private copies -- written once per workgroup, read
     // once by the reduction -- cost more than a second workgroup per CU hides (measured 96 + 12 -> 87 + 7 us per layer)
     if (h_path && wgrad_tile_groups(a.MTo, a.NTk, MB, NB) == 1 && a.NTk >= 48 && a.total_segs < 24L * 2 * cus && resident > cus) resident = cus;
@@ -1592,12 +1640,7 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     hipError_t e = hipErrorInvalidValue;
     if constexpr (DT != 0) {
         if (tr_path) {
-            // input rows kept across steps: kernels of two rows or more
-            const bool ring = k >= 2 && goct <= 12;
-            // where two workgroups a CU have the LDS for two more slots and dY buffers (one, where their registers allow no second)
-            const size_t strip = 16 * ((size_t)6 * MB * WG_TRP + (size_t)goct * (k + 2) * a.xpitch);
-            const bool fits = ring && goct <= 8 && strip <= (MB * NB > 36 ? 160 : 80) * 1024u;
-            e = launch_wgrad_tr<DT>(a, MB, NB, smem, fits ? strip : 0, blocks, stream, ring);
+            e = launch_wgrad_tr<DT>(a, MB, NB, smem, strip_smem, blocks, stream, ring);
         } else if (h_path) {
             if (k == 1 || d % 8 == 0) e = launch_wgrad_h_rb<DT, 16>(a, MB, NB, smem, blocks, stream);
             else if (d % 4 == 0) e = launch_wgrad_h_rb<DT, 8>(a, MB, NB, smem, blocks, stream);
