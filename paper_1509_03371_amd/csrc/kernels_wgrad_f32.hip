@@ -1351,10 +1351,11 @@ static int wgrad_tr_goct(int ntk, int nb, int kk)
 // Column tiles per wave.  The kernel prefetches ONE batch of 24 (octet, kernel row) input rows while it multiplies; a
 // group that needs more loads the rest in place and waits for it every segment.  So, for a gradient with many column
 // tiles: the largest count whose groups stay within one batch (3x3: 9 = four map pairs exactly, 8x8: 8 = half a pair,
-// 4x4: 12 = three pairs); 1x1 kernels touch a new octet pair with every tile and keep 12.
+// 4x4: 12 = three pairs); 1x1 kernels touch a new octet pair with every tile and take 4, which leaves the LDS of a CU to two
+// workgroups (1024 -> 4 x 512 maps of an up-convolution at 28^2, 64 tiles: 72 us with 12 a wave, of which a third were empty, 40 with 4).
 static int wgrad_tr_nb(int ntk, int k)
 {
-    if (ntk < 48) return ntk > 4 ? 4 : 1;
+    if (k == 1 || ntk < 48) return ntk > 4 ? 4 : 1;
     for (int nb : {12, 9, 8, 6})
         if (wgrad_tr_goct(ntk, nb, k * k) * k <= 24) return nb;
     return 12;
