@@ -44,11 +44,14 @@ struct HostReader {
         }
     }
 
-    // the caller has waited for what writes src; returns when dst holds it
+    // hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost), also in what it waits for: what was issued to the null stream, a graph's replay
+    // among it, which the lanes' own streams do not wait for
     hipError_t read(void *dst, const void *src, size_t bytes) const
     {
         const size_t pieces = (bytes + PIECE - 1) / PIECE;
         if (pieces < 2 || !stream[LANES - 1]) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+        const hipError_t waited = hipStreamSynchronize(nullptr);
+        if (waited != hipSuccess) return waited;
         std::atomic<size_t> next{0};
         std::atomic<int> error{hipSuccess};
         auto lane = [&](int i) {
