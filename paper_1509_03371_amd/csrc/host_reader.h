@@ -10,6 +10,25 @@
 
 namespace sk {
 
+// a device as the calling thread's current one, for as long as this lives
+struct DeviceScope {
+    int old = 0;
+    bool moved = false;
+    hipError_t status;
+    explicit DeviceScope(int device) : status(hipGetDevice(&old))
+    {
+        if (status != hipSuccess || old == device) return;
+        status = hipSetDevice(device);
+        moved = status == hipSuccess;
+    }
+    ~DeviceScope()
+    {
+        if (moved) (void)hipSetDevice(old);
+    }
+    DeviceScope(const DeviceScope &) = delete;
+    DeviceScope &operator=(const DeviceScope &) = delete;
+};
+
 // hipMemcpy into pageable memory runs at 10 to 18 GB/s: one thread copies out of the runtime's staging buffer and takes the page
 // faults of memory that was never touched, while the link (56 GB/s into pinned memory) waits.  Here LANES threads, the caller among them,
 // each take the next piece: link -> own pinned piece -> destination.  An epoch of sixteen U-Net
@@ -50,6 +69,8 @@ struct HostReader {
     {
         const size_t pieces = (bytes + PIECE - 1) / PIECE;
         if (pieces < 2 || !stream[LANES - 1]) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+        const DeviceScope on(device);
+        if (on.status != hipSuccess) return on.status;
         const hipError_t waited = hipStreamSynchronize(nullptr);
         if (waited != hipSuccess) return waited;
         std::atomic<size_t> next{0};
@@ -65,8 +86,6 @@ struct HostReader {
             if (e != hipSuccess) error = e;
         };
         std::thread helper[LANES];
-        int old = 0;
-        if (hipGetDevice(&old) != hipSuccess) old = device;
         for (int i = 1; i < LANES && (size_t)i < pieces; ++i) {
             try {
                 helper[i] = std::thread(lane, i);
@@ -77,8 +96,16 @@ struct HostReader {
         lane(0);
         for (auto &h : helper)
             if (h.joinable()) h.join();
-        if (old != device) (void)hipSetDevice(old);
         return static_cast<hipError_t>(error.load());
+    }
+
+    // what launch(stream) makes at src, from a kernel on the plan's device, whichever device the caller is on
+    template <class Launch> hipError_t read_made(void *dst, const void *src, size_t bytes, Launch &&launch) const
+    {
+        const DeviceScope on(device);
+        if (on.status != hipSuccess) return on.status;
+        const hipError_t made = launch(static_cast<hipStream_t>(nullptr));      // (the null stream: what read waits for)
+        return made == hipSuccess ? read(dst, src, bytes) : made;
     }
 };
 

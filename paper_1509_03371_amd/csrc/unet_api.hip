@@ -314,8 +314,8 @@ static sk_status read_conv(const unet *net, const ConvParams &c, float *w, float
 // least one copy of its gradient)
 static sk_status read_stacked(const unet *net, const UpParams &u, const float *cat, float *out)
 {
-    SK_HIP(sk::launch_unstack_taps(cat, net->wgrad_scratch, u.c_out, u.c_in, nullptr));      // (the null stream: as the copies, see HostReader::read)
-    SK_HIP(net->reader.read(out, net->wgrad_scratch, sizeof(float) * 4 * (size_t)u.c_out * u.c_in));
+    SK_HIP(net->reader.read_made(out, net->wgrad_scratch, sizeof(float) * 4 * (size_t)u.c_out * u.c_in,
+                                 [&](hipStream_t s) { return sk::launch_unstack_taps(cat, net->wgrad_scratch, u.c_out, u.c_in, s); }));
     return SK_OK;
 }
 
