@@ -5,7 +5,6 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
-#include <system_error>
 #include <thread>
 
 namespace sk {
@@ -89,7 +88,7 @@ struct HostReader {
         for (int i = 1; i < LANES && (size_t)i < pieces; ++i) {
             try {
                 helper[i] = std::thread(lane, i);
-            } catch (const std::system_error &) {
+            } catch (...) {                         // no thread, or no memory for one (nothing may leave through the C entry points)
                 break;                              // the lanes that run take every piece
             }
         }

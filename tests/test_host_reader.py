@@ -37,6 +37,16 @@ PROGRAM = r"""
 #include <new>
 #include <vector>
 #include "host_reader.h"
+static thread_local int failing_new = 0;                // the failing_new-th allocation of this thread from now on finds no memory
+void *operator new(size_t n)
+{
+    if (failing_new > 0 && --failing_new == 0) throw std::bad_alloc();
+    void *p = malloc(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 int main(int argc, char **argv)
 {
     const size_t bytes = (argc > 1 ? atol(argv[1]) : 0);
@@ -47,9 +57,11 @@ int main(int argc, char **argv)
     current_device = 0;                                 // ... is not the caller's when it reads
     int made_on = -1;
     null_stream = [&] { for (size_t i = 0; i < bytes; ++i) src[i] = (unsigned char)(i * 7 + (i >> 20)); };
-    const bool made = argc > 2;                         // by a kernel, which must run on the plan's device
+    const bool made = argc > 2 && argv[2][0] == 'm';                         // by a kernel, which must run on the plan's device
+    if (argc > 2 && !made) failing_new = atoi(argv[2]);
     const hipError_t e = made ? reader.read_made(dst.data(), src.data(), bytes, [&](hipStream_t s) { made_on = s ? -2 : current_device; return hipSuccess; })
                               : reader.read(dst.data(), src.data(), bytes);
+    failing_new = 0;
     if (current_device != 0 || (made && made_on != 1) || wrong_device) return 2;
     size_t wrong = e == hipSuccess ? 0 : bytes;
     for (size_t i = 0; i < bytes; ++i) wrong += dst[i] != (unsigned char)(i * 7 + (i >> 20));
@@ -81,4 +93,11 @@ def test_reads_behind_the_null_stream(program, size):
 @pytest.mark.parametrize("size", [1000, (7 << 20) + 3])
 def test_makes_and_reads_on_the_device_of_the_plan(program, size):
     r = subprocess.run([program, str(size), "made"], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
+
+
+# the first, second and third thread's allocation fails: with none, one and two helpers running
+@pytest.mark.parametrize("failing", [1, 2, 3])
+def test_reads_all_without_memory_for_threads(program, failing):
+    r = subprocess.run([program, str((23 << 20) + 3), str(failing)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
