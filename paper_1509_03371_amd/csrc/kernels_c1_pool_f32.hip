@@ -10,7 +10,8 @@
 // map, one float4 store a row.  The edge rows and columns are computed twice (1.56 times the multiplications
 // at R = 4): with 64 operations a sample that stays below the time of the stores.  The sums and maxima are taken in the order of
 // conv_c1_f32_kernel and maxpool2_chain_f32_kernel, so the results are theirs bit for bit.
-// The padded image goes to memory on the way (sknet_get_activation hands it out), by the threads of the first map group.
+// The padded image goes to memory on the way (sknet_get_activation hands it out), by the threads of the first map group, and so do
+// the weights and biases of the pass, by a workgroup beside the others: the layer's output, which is not stored, is made from these three.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -30,6 +31,13 @@ __global__ __launch_bounds__(64) void conv_c1_pool_f32_kernel(C1PoolF32Args a, i
     const int H = a.h_pad, W = a.w_pad, Ho = H - KS, Wo = W - KS;
     const int w4 = (Wo + 3) / 4, rows = (Ho + R - 1) / R;
     const int idx = blockIdx.x * 64 + threadIdx.x;
+    if (blockIdx.x == gridDim.x - 1) {                   // no samples
+        if (blockIdx.y == 0 && blockIdx.z == 0) {
+            for (int q = threadIdx.x; q < KS * KS * a.n_pad; q += 64) a.used_w[q] = a.wp[q];
+            for (int q = threadIdx.x; q < a.n_pad; q += 64) a.used_b[q] = a.bias[q];
+        }
+        return;
+    }
     if (idx >= rows * w4) return;
     const int rg = idx / w4;
     // the last group of a row or column is moved back inside the map: its samples are written twice, with the same values
@@ -128,7 +136,7 @@ hipError_t launch_t(const C1PoolF32Args &a, long waves, hipStream_t stream)
     // maps a thread walks over: as many as still leave two waves a SIMD (every further group reads the windows again)
     int per = (a.c_out + 1) & ~1;
     while (per > 2 && waves * ((a.c_out + per - 1) / per) < 2048) per = std::max(2, per / 2 & ~1);
-    hipLaunchKernelGGL((conv_c1_pool_f32_kernel<KS, R>), dim3((unsigned)waves, (a.c_out + per - 1) / per, a.n), dim3(64), 0, stream, a, per);
+    hipLaunchKernelGGL((conv_c1_pool_f32_kernel<KS, R>), dim3((unsigned)waves + 1, (a.c_out + per - 1) / per, a.n), dim3(64), 0, stream, a, per);
     return hipGetLastError();
 }
 

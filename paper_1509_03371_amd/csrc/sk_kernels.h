@@ -91,6 +91,7 @@ struct C1PoolF32Args {
     const float *bias;   // [n_pad]
     float *padded;       // [n][h_pad][w_pad], written
     float *y;            // [n][c_out][h_pad - k][w_pad - k]
+    float *used_w, *used_b;   // written: the weights [k*k][n_pad] and biases [n_pad] of this pass (the layer's own output is made from them later)
     int n, h, w, top, left, mode, h_pad, w_pad;
     int k, c_out, n_pad, relu;
 };

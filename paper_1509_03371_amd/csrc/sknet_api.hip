@@ -67,6 +67,7 @@ struct sknet {
     int pending_head = 0;
     // fp32 inference plans: padding, first layer and its pool run as one launch (the layer's output is not stored)
     bool c1_pool = false;
+    float *c1_used = nullptr;         // ... and leaves its packed weights here, then its biases: get_activation runs the layer on those of the pass
     int head_pool = 0;                // fp32 inference plans: the fused head takes the maxima of the pool in front of it (its d), whose maps are not stored
     bool kept(int layer) const        // is the output of `layer` in memory in the form the layer defines?
     {
@@ -95,7 +96,7 @@ struct sknet {
         }
         tap.clear();
         free_dev(gbuf[0]); free_dev(gbuf[1]); free_dev(loss_partial); free_dev(wgrad_scratch);
-        free_dev(logits_f32); free_dev(dz_f32); free_dev(head_w1p); free_dev(zero_page);
+        free_dev(logits_f32); free_dev(dz_f32); free_dev(head_w1p); free_dev(zero_page); free_dev(c1_used);
         steps.clear();
         vpool.clear(); pending.clear(); pending_head = 0;
         fuse_head = c1_pool = false;
@@ -219,6 +220,7 @@ sk_status run_forward_step(sknet *net, int step_idx, hipStream_t stream)
             } else if (li == 0 && net->c1_pool) {
                 sk::C1PoolF32Args a{};
                 a.image = net->last_image; a.wp = c.wp_fwd; a.bias = c.b_dev; a.padded = net->act[0]; a.y = net->act[2];
+                a.used_w = net->c1_used; a.used_b = net->c1_used + (long)c.rows_fwd * c.n_pad;
                 a.n = net->n; a.h = net->h; a.w = net->w; a.top = net->pad ? net->pad_top : 0; a.left = net->pad ? net->pad_left : 0;
                 a.mode = net->pad_mode; a.h_pad = in.h; a.w_pad = in.w; a.k = l.k; a.c_out = c.c_out; a.n_pad = c.n_pad; a.relu = l.relu;
                 SK_HIP(sk::launch_conv_c1_pool_f32(a, stream));
@@ -604,6 +606,15 @@ sk_status sknet_plan(sknet_t *net, int32_t n, int32_t h, int32_t w, int32_t pad,
             if (e != hipSuccess) st = fail(SK_EDEVICE, "plan: packing the head weights failed: %s", hipGetErrorString(e));
         }
     }
+    if (st == SK_OK && net->c1_pool) {
+        const ConvParams &c = net->convs[0];
+        const long floats = (long)(c.rows_fwd + 1) * c.n_pad;       // (the rows of the maps that pad the one map stay zero)
+        st = alloc_f(&net->c1_used, floats);
+        if (st == SK_OK) {
+            hipError_t e = hipMemset(net->c1_used, 0, sizeof(float) * (size_t)floats);
+            if (e != hipSuccess) st = fail(SK_EDEVICE, "plan: clearing a buffer failed: %s", hipGetErrorString(e));
+        }
+    }
     if (st == SK_OK && training) {
         float *unused = nullptr;
         st = static_scratch(&unused);        // sknet_backward_noalloc's scratch: its address on this device is looked up here
@@ -903,13 +914,16 @@ sk_status sknet_get_activation(sknet_t *net, int32_t layer_idx, float *nchw_host
     const int i = layer_idx + 1;
     const Dims &dm = net->dims[i];
     const bool f32 = (i == 0) ? !net->half() : stored_f32(net, i - 1);
-    // fp32 outputs that a fused launch leaves out: the layer runs once more on its input
+    // fp32 outputs that a fused launch leaves out: the layer runs once more on its input, a convolution with the weights of the pass
     if ((i == 1 && net->c1_pool) || (net->head_pool && i == (int)net->layers.size() - 2)) {
         const sk_layer &l = net->layers[layer_idx];
         const Dims &in = net->dims[layer_idx];
         float *tmp = nullptr;
         SK_TRY(alloc_f(&tmp, dm.count(net->n)));
-        hipError_t e = l.kind == SK_CONV ? sk::launch_conv_f32(conv_args(net->convs[0], net->act[0], net->n, in, l.d, l.relu, tmp, dm), net->last_stream)
+        sk::ConvF32Args a = conv_args(net->convs[0], net->act[0], net->n, in, l.d, l.relu, tmp, dm);
+        a.wp = net->c1_used;
+        a.bias = net->c1_used + (long)net->convs[0].rows_fwd * net->convs[0].n_pad;
+        hipError_t e = l.kind == SK_CONV ? sk::launch_conv_f32(a, net->last_stream)
                                          : sk::launch_maxpool_f32(net->act[layer_idx], tmp, nullptr, net->n * in.c, in.h, in.w, dm.h, dm.w, l.k, l.d, l.s,
                                                                   net->last_stream);
         if (e == hipSuccess) e = hipStreamSynchronize(net->last_stream);

@@ -1,0 +1,72 @@
+"""sknet_get_activation hands out the maps of the last forward pass, also of layers that a fused launch of an fp32 inference plan does not
+store: weights set, or other streams used, since then change nothing."""
+import numpy as np
+import pytest
+import torch
+
+import sk_synth as S
+from paper_1509_03371_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+# first layer with its pool (16 and 3 x 200 maps, n_pad beyond the first layer's own kernel); head with the pool in front of it
+NETS = [[S.conv(16, 4, 1), S.pool(2, 1), S.conv(8, 3, 1), S.pool(2, 2), S.conv(24, 1, 1), S.conv(2, 1, 1, relu=False)],
+        [S.conv(600, 3, 1, relu=False), S.pool(2, 1), S.conv(2, 1, 1, relu=False)]]
+
+
+def planned(layers, h, w, seed):
+    net = B.SKNet(layers, 1, 2)
+    ws, bs = S.he_normal_weights(layers, 1, seed, bias_scale=0.2)
+    for i, (wt, b) in enumerate(zip(ws, bs)):
+        net.set_weights(i, wt, b)
+    net.plan(1, h, w, pad=True)
+    return net
+
+
+@pytest.mark.parametrize("layers", NETS)
+def test_weights_set_after_the_pass(layers):
+    h, w = 70, 93
+    net = planned(layers, h, w, 1)
+    assert any(net.step_name(i).startswith("conv0") and net.step_name(i).endswith("_pool") for i in range(net.num_steps()))
+    ws, bs = S.he_normal_weights(layers, 1, 2, bias_scale=0.2)
+    read = [i for i in (-1, 0, 1, 2, 3) if i < len(layers) - 2]
+    img = torch.from_numpy(S.uniform_image(1, 1, h, w, 3)).cuda()
+    net.forward(img)
+    first = [net.get_activation(i) for i in read]
+    for i, (wt, b) in enumerate(zip(ws, bs)):
+        net.set_weights(i, wt, b)
+    for a, i in zip(first, read):
+        assert np.array_equal(a, net.get_activation(i)), i
+    net.forward(img)
+    second = [net.get_activation(i) for i in read]
+    net.close()
+    other = planned(layers, h, w, 2)
+    other.forward(img)
+    for a, b, i in zip(second, first, read):
+        assert np.array_equal(a, other.get_activation(i)), i
+        assert i < 0 or not np.array_equal(a, b), i
+    other.close()
+
+
+def test_weights_set_between_replays():
+    layers, h, w = NETS[0], 70, 93
+    net = planned(layers, h, w, 1)
+    img = torch.from_numpy(S.uniform_image(1, 1, h, w, 3)).cuda()
+    prob = torch.empty(net.out_shape(), device="cuda")
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            net.forward(img, prob, torch.cuda.current_stream())
+    for seed in (4, 5, 6):
+        ws, bs = S.he_normal_weights(layers, 1, seed, bias_scale=0.2)
+        for i, (wt, b) in enumerate(zip(ws, bs)):
+            net.set_weights(i, wt, b)
+        graph.replay()
+        torch.cuda.synchronize()
+        other = planned(layers, h, w, seed)
+        other.forward(img)
+        for i in (0, 1, 2, 3):
+            assert np.array_equal(net.get_activation(i), other.get_activation(i)), (seed, i)
+        other.close()
+    net.close()
