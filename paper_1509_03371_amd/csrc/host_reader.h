@@ -7,26 +7,9 @@
 #include <cstring>
 #include <thread>
 
-namespace sk {
+#include "device_scope.h"
 
-// a device as the calling thread's current one, for as long as this lives
-struct DeviceScope {
-    int old = 0;
-    bool moved = false;
-    hipError_t status;
-    explicit DeviceScope(int device) : status(hipGetDevice(&old))
-    {
-        if (status != hipSuccess || old == device) return;
-        status = hipSetDevice(device);
-        moved = status == hipSuccess;
-    }
-    ~DeviceScope()
-    {
-        if (moved) (void)hipSetDevice(old);
-    }
-    DeviceScope(const DeviceScope &) = delete;
-    DeviceScope &operator=(const DeviceScope &) = delete;
-};
+namespace sk {
 
 // hipMemcpy into pageable memory runs at 10 to 18 GB/s: one thread copies out of the runtime's staging buffer and takes the page
 // faults of memory that was never touched, while the link (56 GB/s into pinned memory) waits.  Here LANES threads, the caller among them,

@@ -5,6 +5,7 @@
 #include <mutex>
 #include <new>
 
+#include "device_scope.h"
 #include "sk_host.h"
 
 using namespace skh;
@@ -68,6 +69,7 @@ struct sknet {
     // fp32 inference plans: padding, first layer and its pool run as one launch (the layer's output is not stored)
     bool c1_pool = false;
     float *c1_used = nullptr;         // ... and leaves its packed weights here, then its biases: get_activation runs the layer on those of the pass
+    int device = 0;                   // of the plan
     int head_pool = 0;                // fp32 inference plans: the fused head takes the maxima of the pool in front of it (its d), whose maps are not stored
     bool kept(int layer) const        // is the output of `layer` in memory in the form the layer defines?
     {
@@ -486,6 +488,7 @@ sk_status sknet_plan(sknet_t *net, int32_t n, int32_t h, int32_t w, int32_t pad,
     if (net->planned)
         for (int i = 0; i < (int)net->convs.size(); ++i) SK_TRY(sknet_get_weights(net, i, nullptr, nullptr));
     net->release_plan();
+    SK_HIP(hipGetDevice(&net->device));
     net->n = n; net->h = h; net->w = w; net->pad = pad ? 1 : 0; net->training = training ? 1 : 0;
     net->pad_top = pt; net->pad_left = pl;
     net->dims = dims;
@@ -918,15 +921,18 @@ sk_status sknet_get_activation(sknet_t *net, int32_t layer_idx, float *nchw_host
     if ((i == 1 && net->c1_pool) || (net->head_pool && i == (int)net->layers.size() - 2)) {
         const sk_layer &l = net->layers[layer_idx];
         const Dims &in = net->dims[layer_idx];
+        // on the plan's device, whichever is the caller's, and on the null stream: a copy would wait for that one too, and a recorded
+        // pass may have been replayed there
+        const sk::DeviceScope on(net->device);
+        SK_HIP(on.status);
         float *tmp = nullptr;
         SK_TRY(alloc_f(&tmp, dm.count(net->n)));
         sk::ConvF32Args a = conv_args(net->convs[0], net->act[0], net->n, in, l.d, l.relu, tmp, dm);
         a.wp = net->c1_used;
         a.bias = net->c1_used + (long)net->convs[0].rows_fwd * net->convs[0].n_pad;
-        hipError_t e = l.kind == SK_CONV ? sk::launch_conv_f32(a, net->last_stream)
+        hipError_t e = l.kind == SK_CONV ? sk::launch_conv_f32(a, nullptr)
                                          : sk::launch_maxpool_f32(net->act[layer_idx], tmp, nullptr, net->n * in.c, in.h, in.w, dm.h, dm.w, l.k, l.d, l.s,
-                                                                  net->last_stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(net->last_stream);
+                                                                  nullptr);
         if (e == hipSuccess) e = hipMemcpy(nchw_host, tmp, sizeof(float) * dm.count(net->n), hipMemcpyDeviceToHost);
         (void)hipFree(tmp);
         if (e != hipSuccess) return fail(SK_EDEVICE, "get_activation: %s", hipGetErrorString(e));

@@ -70,3 +70,40 @@ def test_weights_set_between_replays():
             assert np.array_equal(net.get_activation(i), other.get_activation(i)), (seed, i)
         other.close()
     net.close()
+
+
+def test_reads_wait_for_a_replay_on_the_default_stream():
+    # large maps: the pass is still running when the accessor is called
+    layers = S.sknet_layers()
+    n, h, w = 2, 1000, 1000
+    net = B.SKNet(layers, 1, 2)
+    ws, bs = S.he_normal_weights(layers, 1, 8, bias_scale=0.2)
+    for i, (wt, b) in enumerate(zip(ws, bs)):
+        net.set_weights(i, wt, b)
+    net.plan(n, h, w, pad=True)
+    names = [net.step_name(i) for i in range(net.num_steps())]
+    last_pool = len(layers) - 3
+    assert any(s.endswith("_pool") for s in names) and not any(s.startswith("pool%d" % last_pool) for s in names), names
+    images = [torch.from_numpy(S.uniform_image(n, 1, h, w, 20 + i)).cuda() for i in range(2)]
+    img, prob = images[0].clone(), torch.empty(net.out_shape(), device="cuda")
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            net.forward(img, prob, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    want = []
+    for image in images:
+        img.copy_(image)
+        net.forward(img, prob)
+        torch.cuda.synchronize()
+        want.append([net.get_activation(i)[:, ::7].copy() for i in (0, last_pool)])
+    for rep in range(4):
+        for i, layer in enumerate((0, last_pool)):
+            img.copy_(images[rep % 2])
+            graph.replay()
+            assert np.array_equal(net.get_activation(layer)[:, ::7], want[rep % 2][i]), (rep, layer)
+            img.copy_(images[1 - rep % 2])             # the other image's maps in memory for the next replay
+            graph.replay()
+            torch.cuda.synchronize()
+    net.close()
