@@ -1348,14 +1348,26 @@ static int wgrad_tr_goct(int ntk, int nb, int kk)
     }
     return goct;
 }
+// 1x1 layers: share of the GPU that a launch with nb column tiles a wave keeps at work, from the places (two workgroups a CU with four tiles, one with
+// twelve, on 256 CUs), whole rounds of them and the tiles of a group that exist
+static double wgrad_1x1_fill(int ntk, int mgroups, int nb)
+{
+    const int places = nb > 4 ? WG_MAX_BLOCKS / 2 : WG_MAX_BLOCKS, ngroups = (ntk + 4 * nb - 1) / (4 * nb), groups = mgroups * ngroups;
+    const int copies = std::max(1, places / groups), rounds = (groups * copies + places - 1) / places;
+    return (double)ntk / (4 * nb * ngroups) * groups * copies / ((double)places * rounds);
+}
+
 // Column tiles per wave.  The kernel prefetches ONE batch of 24 (octet, kernel row) input rows while it multiplies; a
 // group that needs more loads the rest in place and waits for it every segment.  So, for a gradient with many column
 // tiles: the largest count whose groups stay within one batch (3x3: 9 = four map pairs exactly, 8x8: 8 = half a pair,
-// 4x4: 12 = three pairs); 1x1 kernels touch a new octet pair with every tile and take 4, which leaves the LDS of a CU to two
-// workgroups (1024 -> 4 x 512 maps of an up-convolution at 28^2, 64 tiles: 72 us with 12 a wave, of which a third were empty, 40 with 4).
-static int wgrad_tr_nb(int ntk, int k)
+// 4x4: 12 = three pairs).  1x1 kernels touch a new octet pair with every tile and take 4, which leaves the LDS of a CU to two
+// workgroups, or 12 where 4 leave a quarter of the GPU idle and 12 do not.  68 layers of 128 to 3072 -> 16 to 1536 maps on 28^2 to
+// 4 x 180 x 170: with 4 0.45 to 1.01 of the time that 12 take, but for 3072 -> 768 at 60^2 (137 us, 127 with 12) and 3072 -> 1536 at 30^2
+// (139 and 131), where 4 fill three quarters.
+static int wgrad_tr_nb(int ntk, int k, int mgroups)
 {
-    if (k == 1 || ntk < 48) return ntk > 4 ? 4 : 1;
+    if (ntk < 48) return ntk > 4 ? 4 : 1;
+    if (k == 1) return wgrad_1x1_fill(ntk, mgroups, 12) > 1.25 * wgrad_1x1_fill(ntk, mgroups, 4) ? 12 : 4;
     for (int nb : {12, 9, 8, 6})
         if (wgrad_tr_goct(ntk, nb, k * k) * k <= 24) return nb;
     return 12;
@@ -1392,7 +1404,7 @@ size_t wgrad_f32_scratch_floats(int c_out, int c_in, int k)
         int MT2, NT2, MB2, NB2;
         wgrad_tiling(c_out, c_in, k, false, MT2, NT2, MB2, NB2);
         NT2 = wgrad_tr_ntk(c_in, k);
-        NB2 = wgrad_tr_nb(NT2, k);
+        NB2 = wgrad_tr_nb(NT2, k, (MT2 + MB2 - 1) / MB2);
         copies = std::max(copies, wgrad_max_copies(wgrad_tile_groups(MT2, NT2, MB2, NB2)));
         NTk = std::max(NTk, NT2);
     }
@@ -1581,7 +1593,7 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     if (grouped_h && !tr_path) return hipErrorInvalidValue;
     if (tr_path) {
         a.NTk = wgrad_tr_ntk(c_in, k);
-        NB = wgrad_tr_nb(a.NTk, k);
+        NB = wgrad_tr_nb(a.NTk, k, (a.MTo + MB - 1) / MB);
     }
     a.xpitch = tr_path ? (PW + 7) / 8 * 8 + 4 : (h_path ? (PW + 7) / 8 * 8 + 8 : (PW + 31) / 32 * 32 + 4);
     // 16-bit matrix path: a tile group stages the input octets its columns touch (the most any group has)
@@ -1625,6 +1637,9 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
         if (fit < (size_t)max_copies) max_copies = (int)fit;
     }
     long copies = (resident + groups - 1) / groups;
+    // 16-bit 1x1 layers: no workgroup more than run at once, or the last ones take a round of their own (768 -> 19 maps on 4 x 180 x 170, three
+    // groups of 171 copies on 512 places: 102 us, of 170: 80)
+    if (tr_path && k == 1 && copies > 1 && copies * groups > resident) --copies;
     if (copies > max_copies) copies = max_copies;
     int blocks = a.total_segs < copies ? a.total_segs : (int)copies;
     float *bias_part = scratch + (size_t)max_copies * a.MTo * 16 * a.NTk * 16;
@@ -1726,7 +1741,7 @@ bool wgrad_h_grouped_supported(int c_in, int c_out, int k, int d)
     int MTo, NTk, MB, NB;
     wgrad_tiling(c_out, c_in, k, false, MTo, NTk, MB, NB);
     NTk = wgrad_tr_ntk(c_in, k);
-    NB = wgrad_tr_nb(NTk, k);
+    NB = wgrad_tr_nb(NTk, k, (MTo + MB - 1) / MB);
     const int PW = WG_SEG + (k - 1) * d, xpitch = (PW + 7) / 8 * 8 + 4;
     return 16 * ((size_t)2 * MB * WG_TRP + (size_t)wgrad_tr_goct(NTk, NB, k * k) * k * xpitch) <= 150 * 1024;
 }
