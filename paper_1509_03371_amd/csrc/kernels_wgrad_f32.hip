@@ -931,7 +931,7 @@ __global__ __launch_bounds__(256, MB * NB > 36 ? 1 : 2) void wgrad_trr_h_kernel(
 // input octet (a tile group inside one map pair keeps only the kernel rows its taps use), and the column tiles' read
 // offsets rotate with the step.  The steps of all strips, in strip order, are dealt out to the workgroups in equal contiguous ranges.
 // Four waves (one team) take a step a turn; two teams take two neighbouring steps of the strip in the same turn and add their sums through LDS
-// at the end (wgrad_strip_teams says where).  The loads of a turn -- one new row per octet and a dY segment for each step -- are
+// at the end (wgrad_strip_pairs says where).  The loads of a turn -- one new row per octet and a dY segment for each step -- are
 // issued two turns ahead (two teams, whose turn takes twice as long: one), into the slots and the dY buffer that the turn before the
 // current one read, so a turn has one barrier and waits for loads that had a whole turn to arrive.
 // With rows staged through registers one step ahead (wgrad_trr_h_kernel, which keeps what this kernel's LDS does not hold) the
@@ -1489,21 +1489,20 @@ static hipError_t launch_wgrad_trr_t(const WgradArgs &a, size_t smem, int blocks
 // that add their sums first write and read half (16 U-Net steps 51.8 -> 50.5 ms; the reductions 14.2 -> 9.7 us).  With few a wave
 // (16 tiles and less: 33 MB and less) what counts is that the barriers of two workgroups do not fall together (3-D 48 -> 64 on 130 x 141 x 141: 131 us,
 // 161 with two teams; 113 and 125 for 16 output maps).  More than 36 tiles leave room for one wave a SIMD.
-static constexpr int wgrad_strip_teams(int MB, int NB) { return MB * NB >= 24 && MB * NB <= 36 ? 2 : 1; }
+static constexpr bool wgrad_strip_pairs(int MB, int NB) { return MB * NB >= 24 && MB * NB <= 36; }
 
 // LDS of wgrad_strip_h_kernel (two teams: also the sums that they exchange), 0 where it does not fit as often as the registers do
-static size_t wgrad_strip_smem(int MB, int NB, int goct, int k, int xpitch)
+static size_t wgrad_strip_smem(int MB, int NB, int goct, int k, int xpitch, int teams)
 {
-    const int teams = wgrad_strip_teams(MB, NB), look = teams > 1 ? 1 : 2;
+    const int look = teams > 1 ? 1 : 2;
     size_t smem = 16 * ((size_t)(look + 1) * teams * 2 * MB * WG_TRP + (size_t)goct * (k + teams - 1 + look * teams) * xpitch);
     if (teams > 1) smem = std::max(smem, (size_t)(MB * NB + 1) * 4 * 1024);
     return goct <= 8 && smem <= (MB * NB < 24 ? 80 : 160) * 1024u ? smem : 0;
 }
 
-template <int MB, int NB, int DT>
+template <int MB, int NB, int DT, int TEAMS>
 static hipError_t launch_wgrad_strip_t(const WgradArgs &a, size_t smem, int blocks, hipStream_t stream)
 {
-    constexpr int TEAMS = wgrad_strip_teams(MB, NB);
     static bool attr_set = false;
     if (smem > 48 * 1024 && !attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&wgrad_strip_h_kernel<MB, NB, DT, TEAMS>),
@@ -1516,13 +1515,23 @@ static hipError_t launch_wgrad_strip_t(const WgradArgs &a, size_t smem, int bloc
     return hipGetLastError();
 }
 
+template <int MB, int NB, int DT>
+static hipError_t launch_wgrad_tr_mb(const WgradArgs &a, size_t smem, size_t strip_smem, int teams, int blocks, hipStream_t stream, bool ring)
+{
+    if (strip_smem) {
+        if constexpr (wgrad_strip_pairs(MB, NB))
+            if (teams > 1) return launch_wgrad_strip_t<MB, NB, DT, 2>(a, strip_smem, blocks, stream);
+        return launch_wgrad_strip_t<MB, NB, DT, 1>(a, strip_smem, blocks, stream);
+    }
+    return ring ? launch_wgrad_trr_t<MB, NB, DT>(a, smem, blocks, stream) : launch_wgrad_tr_t<MB, NB, DT>(a, smem, blocks, stream);
+}
+
 // ring = the strip-walking kernels that keep the staged input rows across steps; strip_smem != 0: the one that loads straight into LDS
 template <int DT>
-static hipError_t launch_wgrad_tr(const WgradArgs &a, int MB, int NB, size_t smem, size_t strip_smem, int blocks, hipStream_t stream, bool ring)
+static hipError_t launch_wgrad_tr(const WgradArgs &a, int MB, int NB, size_t smem, size_t strip_smem, int teams, int blocks, hipStream_t stream, bool ring)
 {
     hipError_t e = hipErrorInvalidValue;
-#define SK_WG_CASE(mb, nb) \
-    if (MB == mb && NB == nb) e = strip_smem ? launch_wgrad_strip_t<mb, nb, DT>(a, strip_smem, blocks, stream) : ring ? launch_wgrad_trr_t<mb, nb, DT>(a, smem, blocks, stream) : launch_wgrad_tr_t<mb, nb, DT>(a, smem, blocks, stream);
+#define SK_WG_CASE(mb, nb) if (MB == mb && NB == nb) e = launch_wgrad_tr_mb<mb, nb, DT>(a, smem, strip_smem, teams, blocks, stream, ring);
     SK_WG_CASE(1, 1) SK_WG_CASE(1, 4) SK_WG_CASE(1, 12) SK_WG_CASE(1, 6) SK_WG_CASE(1, 8) SK_WG_CASE(1, 9)
     SK_WG_CASE(3, 1) SK_WG_CASE(3, 4) SK_WG_CASE(3, 12) SK_WG_CASE(3, 6) SK_WG_CASE(3, 8) SK_WG_CASE(3, 9)
     SK_WG_CASE(4, 1) SK_WG_CASE(4, 4) SK_WG_CASE(4, 12) SK_WG_CASE(4, 6) SK_WG_CASE(4, 8) SK_WG_CASE(4, 9)
@@ -1621,13 +1630,17 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     long resident = (long)cus * (per_cu < 1 ? 1 : (per_cu > 2 ? 2 : per_cu));
     // input rows kept across steps: kernels of two rows or more
     const bool ring = tr_path && k >= 2 && goct <= 12;
-    const size_t strip_smem = ring ? wgrad_strip_smem(MB, NB, goct, k, a.xpitch) : 0;
-    if (strip_smem && wgrad_strip_teams(MB, NB) > 1) resident = cus;
+    const int groups = wgrad_tile_groups(a.MTo, a.NTk, MB, NB);
+    // two teams need more than one step for a workgroup: with one each they were 1.07 to 1.21 times as slow as one team (20 layers of 96 to 512 -> 32 to
+    // 256 maps), with 1.1 and more 0.73 to 1.05 (47)
+    int teams = ring && wgrad_strip_pairs(MB, NB) && a.total_segs > std::max(1, cus / groups) ? 2 : 1;
+    const size_t strip_smem = ring ? wgrad_strip_smem(MB, NB, goct, k, a.xpitch, teams) : 0;
+    if (teams > 1 && strip_smem) resident = cus;
+    else teams = 1;
     // 16-bit path, few segments per workgroup (one 512^2 image): the private copies -- written once per workgroup, read
     // once by the reduction -- cost more than a second workgroup per CU hides (measured 96 + 12 -> 87 + 7 us per layer)
     if (h_path && wgrad_tile_groups(a.MTo, a.NTk, MB, NB) == 1 && a.NTk >= 48 && a.total_segs < 24L * 2 * cus && resident > cus) resident = cus;
     if (resident > WG_MAX_BLOCKS) resident = WG_MAX_BLOCKS;
-    const int groups = wgrad_tile_groups(a.MTo, a.NTk, MB, NB);
     int max_copies = wgrad_max_copies(groups);
     if (scratch_cap > 0) {
         // a scratch buffer of a given size: as many private copies as it holds (fewer workgroups, same sums)
@@ -1637,9 +1650,10 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
         if (fit < (size_t)max_copies) max_copies = (int)fit;
     }
     long copies = (resident + groups - 1) / groups;
-    // 16-bit 1x1 layers: no workgroup more than run at once, or the last ones take a round of their own (768 -> 19 maps on 4 x 180 x 170, three
-    // groups of 171 copies on 512 places: 102 us, of 170: 80)
-    if (tr_path && k == 1 && copies > 1 && copies * groups > resident) --copies;
+    // 16-bit 1x1 layers and two teams: no workgroup more than run at once, or the last ones take a round of their own (1x1 768 -> 19 maps on
+    // 4 x 180 x 170, three groups of 171 copies on 512 places: 102 us, of 170: 80; 3x3 706 -> 96 on 2 x 343 x 304, 24 of 11 on 256: 525, of
+    // 10: 328)
+    if (tr_path && (k == 1 || teams > 1) && copies > 1 && copies * groups > resident) --copies;
     if (copies > max_copies) copies = max_copies;
     int blocks = a.total_segs < copies ? a.total_segs : (int)copies;
     float *bias_part = scratch + (size_t)max_copies * a.MTo * 16 * a.NTk * 16;
@@ -1656,7 +1670,7 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     hipError_t e = hipErrorInvalidValue;
     if constexpr (DT != 0) {
         if (tr_path) {
-            e = launch_wgrad_tr<DT>(a, MB, NB, smem, strip_smem, blocks, stream, ring);
+            e = launch_wgrad_tr<DT>(a, MB, NB, smem, strip_smem, teams, blocks, stream, ring);
         } else if (h_path) {
             if (k == 1 || d % 8 == 0) e = launch_wgrad_h_rb<DT, 16>(a, MB, NB, smem, blocks, stream);
             else if (d % 4 == 0) e = launch_wgrad_h_rb<DT, 8>(a, MB, NB, smem, blocks, stream);
