@@ -1,12 +1,13 @@
 """GPU check of the fp32 4x4 weight gradient that keeps input rows in LDS: against fp64 sums over the very tensors the GPU holds (the
 layer's input and the gradient of its output).  Ragged rows and columns, maps off the tiles of 8 and 16, one to six input maps
-a wave, walks shorter than the ring of rows, kernel strides with either slot pitch up to the widest that fits, several
-walks a workgroup, and sizes next to the dispatch's lines.  An element's sum is a chain of at most pixels / 4 + copies fp32 additions, so
+a wave, walks shorter than the ring of rows, kernel strides with either slot pitch up to the widest that fits, and sizes next to the
+dispatch's lines; in test_walks many steps and several walks a workgroup.  An element's sum is a chain of at most pixels / 4 + copies fp32 additions, so
 its error stays below (pixels / 4 + 512) * 2^-24 of the sum of magnitudes."""
 import numpy as np
 import pytest
 import torch
 
+import exact_wgrad
 import sk_synth as S
 
 pytestmark = pytest.mark.gpu
@@ -43,3 +44,13 @@ def test_gradient(c_in, c_out, d, n, h, w):
             assert bool(((torch.from_numpy(dw[:, :, i, j]).double() - ref).abs() <= bound * mag).all()), (i, j)
     ref, mag = dy.sum(dim=(0, 2, 3)), dy.abs().sum(dim=(0, 2, 3))
     assert bool(((torch.from_numpy(db).double() - ref).abs() <= bound * mag).all())
+
+
+# A workgroup (one a CU, 256) walks at least twice round its ring of five rows, over ends of strips, residue classes and images; nothing rounds,
+# so a row, column or buffer taken wrongly shows in the last bit.
+@pytest.mark.parametrize("c_in,c_out,d,n,h,w", [
+    (48, 48, 1, 3, 310, 205), (16, 16, 3, 4, 369, 140), (33, 20, 2, 5, 287, 137), (48, 33, 8, 2, 699, 150), (8, 24, 1, 7, 409, 66), (21, 48, 16, 3, 500, 177),
+])
+def test_walks(c_in, c_out, d, n, h, w):
+    assert -(-(w - 3 * d) // 64) * (h - 3 * d) * n >= 2 * 5 * 256
+    exact_wgrad.check(c_in, c_out, 4, d, n, h, w, "f32")

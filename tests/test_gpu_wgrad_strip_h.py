@@ -1,12 +1,14 @@
 """GPU check of the 16-bit weight gradient that loads input rows straight into LDS: against fp64 sums over the very tensors the GPU holds (the
 layer's input and the gradient of its output, both in the 16-bit type, whose products are exact in fp32).  Segments of one column to
-two segments and an odd rest (half a segment skipped at 32 and below), strips of one, two and more steps, residue classes of unequal
-length and empty ones, maps off the tiles, kernels of two to four rows with one tile group and several, windows up to the widest.
+two segments and an odd rest (half a segment skipped at 32 and below), residue classes of unequal length and empty ones, maps off the
+tiles, kernels of two to four rows with one tile group and several, windows up to the widest; in test_gradient a workgroup has one step, or
+two, in test_walks many.
 An element's sum takes at most pixels + 512 fp32 additions, so its error stays below (pixels + 512) * 2^-24 of the sum of magnitudes."""
 import numpy as np
 import pytest
 import torch
 
+import exact_wgrad
 import sk_synth as S
 
 pytestmark = pytest.mark.gpu
@@ -46,3 +48,19 @@ def test_gradient(c_in, c_out, k, d, n, h, w, dtype):
             assert bool(((torch.from_numpy(dw[:, :, i, j]).double() - ref).abs() <= bound * mag).all()), (i, j)
     ref, mag = dy.sum(dim=(0, 2, 3)), dy.abs().sum(dim=(0, 2, 3))
     assert bool(((torch.from_numpy(db).double() - ref).abs() <= bound * mag).all())
+
+
+# A workgroup walks at least twice round its ring of k + 2 (one team) or k + 3 (two) rows, over ends of strips, residue classes and images: the
+# gradient's tile groups share at most 512 workgroups, two teams at most 256, so steps (64-column segments of output rows) / that is the
+# least a workgroup gets.  Nothing rounds, so a row, column or buffer taken wrongly shows in the last bit.
+@pytest.mark.parametrize("c_in,c_out,k,d,n,h,w,workgroups,ring", [
+    (16, 16, 3, 1, 5, 522, 131, 512, 5), (24, 48, 3, 2, 9, 611, 94, 512, 5), (16, 64, 2, 3, 6, 700, 66, 512, 4), (64, 16, 3, 4, 3, 905, 70, 171, 5),
+    (64, 64, 4, 3, 3, 500, 100, 128, 6),                                      # one team (the last one: more than 36 tiles a wave)
+    (96, 64, 3, 1, 3, 301, 141, 128, 6), (128, 48, 3, 3, 5, 203, 97, 128, 6), (64, 48, 4, 2, 3, 379, 135, 128, 7), (200, 32, 3, 1, 2, 701, 66, 64, 6),
+])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_walks(c_in, c_out, k, d, n, h, w, workgroups, ring, dtype):
+    ho, wo = h - (k - 1) * d, w - (k - 1) * d
+    assert -(-wo // 64) * ho * n >= 2 * ring * workgroups
+    # (fp16: loss gradients of 1 / (4 * 4096) are still normal numbers)
+    exact_wgrad.check(c_in, c_out, k, d, n, h, w, dtype, None if dtype == "bf16" else 4096)
