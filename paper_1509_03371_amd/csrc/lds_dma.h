@@ -12,8 +12,12 @@ namespace sk {
 __device__ __forceinline__ void lds_dma16(const void *src, const void *dst)
 {
     const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(const __attribute__((address_space(3))) void *)dst);
-    // m0 (nothing else in these kernels uses it) holds the LDS address, one instruction ahead of its use
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(at) : "memory");
+    // m0 holds the LDS address, one instruction ahead of its use.  The compiler keeps operands of its own there: it has to know that they are
+    // lost, also where it warns that the register is not its to allocate
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(at) : "memory", "m0");
+#pragma clang diagnostic pop
 }
 
 }  // namespace sk
