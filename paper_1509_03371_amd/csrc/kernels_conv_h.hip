@@ -1208,9 +1208,10 @@ static int device_cus()
     return cus;
 }
 
-// LDS bytes of the ring kernel: S stages (+ resident weights) + bias + y-tile table
+// LDS bytes of the ring kernel: S stages (+ resident weights) + bias + table of the y tiles, which are `pitch` rows apart (R, or R - 1 where
+// the tiles of a pooled output overlap by a row)
 template <int KS, int MT, bool MAP4, int R, int S, bool RESW>
-static size_t ring_smem(int d, int c_out, int c8_in, int Ho, int hd = 0)
+static size_t ring_smem(int d, int c_out, int c8_in, int Ho, int hd = 0, int pitch = R)
 {
     constexpr int RR = R + KS - 1, OC = MAP4 ? 1 : 4, CS = MAP4 ? 1 : KS;
     const int PW = CH_TX + (MAP4 ? 3 : KS - 1) * d;            // (a pending pool of the input is finished before the tile is staged)
@@ -1219,8 +1220,7 @@ static size_t ring_smem(int d, int c_out, int c8_in, int Ho, int hd = 0)
     const int nchunks = (c8_in + OC - 1) / OC;
     const int m_tiles_all = ((c_out + 15) / 16 + MT - 1) / MT * MT;
     const size_t units = RESW ? S * tile + nchunks * slab : S * (tile + slab);
-    // the table of y tiles: a pool of the output sets them R - 1 rows apart, which makes more of them
-    return units * 16 + (size_t)m_tiles_all * 64 + (size_t)(Ho / (R - 1) + 2 * d + 2) * 4;
+    return units * 16 + (size_t)m_tiles_all * 64 + (size_t)(Ho / pitch + 2 * d + 2) * 4;
 }
 
 template <int DT, int KS, int MT, bool MAP4, int R, bool HAS_MASK, int S, bool RESW, int NP = 0, bool VPOOL = false>
@@ -1232,7 +1232,7 @@ static hipError_t launch_conv_h_ring_m(ConvHArgs a, hipStream_t stream)
     if (VPOOL && (!a.relu || a.out_f32 || a.tap_maps != 0 || a.oy_mul != 1 || a.ox_mul != 1 || a.oy_off != 0 || a.ox_off != 0 ||
                   a.OH != a.Ho - a.d || a.OW != a.Wo || a.Ho <= a.d))
         return hipErrorInvalidValue;
-    const size_t smem = ring_smem<KS, MT, MAP4, R, S, RESW>(a.d, a.c_out, a.c8_in, a.Ho, a.hd);
+    size_t smem = ring_smem<KS, MT, MAP4, R, S, RESW>(a.d, a.c_out, a.c8_in, a.Ho, a.hd);
     if (smem > 160 * 1024) return hipErrorInvalidValue;            // callers check the size first
     static bool attr_set = false;
     if (!attr_set) {
@@ -1253,9 +1253,11 @@ static hipError_t launch_conv_h_ring_m(ConvHArgs a, hipStream_t stream)
     a.tiles_lo = (q + R - 1) / R;
     if (VPOOL) {
         // carried rows pay one extra tile per workgroup (the tile above its run): worth it from about eight tiles per
-        // workgroup; below that, tiles that overlap by one row (R - 1 pooled rows each) cost less
+        // workgroup; below that, tiles that overlap by one row (R - 1 pooled rows each) cost less, where the LDS holds the table of so many
         const long per_wg = (long)a.xtiles * (a.rem * a.tiles_hi + (a.d - a.rem) * a.tiles_lo) * a.n / (device_cus() / 8 * 8);
-        if (per_wg < 8) {
+        const size_t overlapping = ring_smem<KS, MT, MAP4, R, S, RESW>(a.d, a.c_out, a.c8_in, a.Ho, a.hd, R - 1);
+        if (per_wg < 8 && overlapping <= 160 * 1024) {
+            smem = overlapping;
             a.ypitch = R - 1;
             a.tiles_hi = q >= 1 ? (q + R - 2) / (R - 1) : 1;         // q + 1 rows: q pooled rows
             a.tiles_lo = q >= 2 ? (q - 1 + R - 2) / (R - 1) : 1;     // q rows: q - 1 pooled rows
