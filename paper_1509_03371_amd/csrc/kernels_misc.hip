@@ -73,19 +73,19 @@ typedef unsigned uint1u __attribute__((aligned(1)));
 // y0 + 2d, ... of one residue class mod d, so each h is formed once and serves both windows it
 // belongs to, and each input row is read once.  Winner codes follow the row-major
 // scan (0,1 for row y; 2,3 for row y + d), strictly-greater replaces.
-// grid: x = (residue class, block of four columns) linearly, y = segments of M chain links, z = plane.
+// grid and workgroup: see pool_cut, with blocks of four columns for its columns; segments are M windows long, z = plane.
 // Bound by HBM, but only with four columns a thread: with one, the 32 memory instructions of eight windows of 64 threads
 // cost more than their bytes (48 maps at 527x527: 36.6 -> 26.4 us with codes = 4.5 TB/s, 32.3 -> 22.6 without).  The last
 // block of a row overlaps its neighbour.
-template <bool TAP>
-__global__ void __launch_bounds__(64) maxpool2_chain_f32_kernel(const float *__restrict__ x, float *__restrict__ y,
-                                                                uint8_t *__restrict__ tap, int H, int W, int Ho, int Wo,
-                                                                int d, int M)
+template <bool TAP, int U>
+__global__ void __launch_bounds__(256) maxpool2_chain_f32_kernel(const float *__restrict__ x, float *__restrict__ y,
+                                                                 uint8_t *__restrict__ tap, int H, int W, int Ho, int Wo,
+                                                                 int d, int M, int nseg, int pblocks)
 {
-    const int w4 = (Wo + 3) / 4, idx = blockIdx.x * 64 + threadIdx.x;
-    const int phase = idx / w4, xx = min(4 * (idx - phase * w4), Wo - 4), m0 = blockIdx.y * M;
-    if (phase >= d || phase >= Ho) return;
-    const int m1 = min((Ho - phase + d - 1) / d, m0 + M);
+    const int quad = blockIdx.x * blockDim.x + threadIdx.x, xx = min(4 * quad, Wo - 4);
+    const int sblock = blockIdx.y / pblocks, phase = (blockIdx.y - sblock * pblocks) * blockDim.y + threadIdx.y, seg = sblock * blockDim.z + threadIdx.z;
+    if (4 * quad >= Wo || phase >= d || phase >= Ho || seg >= nseg) return;
+    const int m0 = seg * M, m1 = min((Ho - phase + d - 1) / d, m0 + M);
     if (m0 >= m1) return;
     const long p = blockIdx.z;
     const long rstep = (long)d * W, ostep = (long)d * Wo;
@@ -102,18 +102,21 @@ __global__ void __launch_bounds__(64) maxpool2_chain_f32_kernel(const float *__r
         }
     };
     auto at = [](const float *q) { return *reinterpret_cast<const float4u *>(q); };
-    float4u h;
-    unsigned hc;
-    row(at(src), at(src + d), h, hc);
-    constexpr int U = 4;
-    for (int m = m0; m < m1; m += U) {
-        float4u a[U], b[U];
+    float4u a[U], b[U];
+    auto load = [&](int m) {                              // the lower rows of windows m .. m + U - 1
 #pragma unroll
-        for (int u = 0; u < U; ++u) {                     // all loads of the group first
+        for (int u = 0; u < U; ++u) {
             const float *r = src + (m + u < m1 ? (long)(u + 1) * rstep : 0);
             a[u] = at(r);
             b[u] = at(r + d);
         }
+    };
+    const float4u first = at(src), right = at(src + d);
+    load(m0);                                             // in flight together with the first row
+    float4u h;
+    unsigned hc;
+    row(first, right, h, hc);
+    for (int m = m0;;) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (m + u >= m1) break;
@@ -131,10 +134,23 @@ __global__ void __launch_bounds__(64) maxpool2_chain_f32_kernel(const float *__r
             h = h2;
             hc = hc2;
         }
+        m += U;
+        if (m >= m1) return;
         src += (long)U * rstep;
         dst += (long)U * ostep;
         if (TAP) tdst += (long)U * ostep;
+        load(m);
     }
+}
+
+template <bool TAP>
+static void launch_maxpool2_chain_f32(const PoolCut &c, dim3 grid, hipStream_t stream, const float *x, float *y, uint8_t *tap, int H, int W, int Ho, int Wo,
+                                      int d)
+{
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, c.block(), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len, c.nseg, c.pblocks); };
+    if (c.len >= 4) go(&maxpool2_chain_f32_kernel<TAP, 4>);
+    else if (c.len >= 2) go(&maxpool2_chain_f32_kernel<TAP, 2>);
+    else go(&maxpool2_chain_f32_kernel<TAP, 1>);
 }
 
 hipError_t launch_maxpool_f32(const float *x, float *y, uint8_t *tap, int planes, int H, int W,
@@ -142,11 +158,13 @@ hipError_t launch_maxpool_f32(const float *x, float *y, uint8_t *tap, int planes
 {
     if (Ho > 65535 || planes > 65535) return hipErrorInvalidValue;
     if (k == 2 && s == 1 && Ho == H - d && Wo == W - d && Wo >= 4) {
-        const PoolCut c = pool_cut4(Ho, Wo, d, planes, 4);
-        const dim3 grid((unsigned)(((long)d * ((Wo + 3) / 4) + 63) / 64), (unsigned)c.nseg, (unsigned)planes);
-        if (tap) hipLaunchKernelGGL(maxpool2_chain_f32_kernel<true>, grid, dim3(64), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len);
-        else hipLaunchKernelGGL(maxpool2_chain_f32_kernel<false>, grid, dim3(64), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len);
-        return hipGetLastError();
+        const PoolCut c = pool_cut(Ho, (Wo + 3) / 4, d, planes, tap ? POOL_WAVES : POOL_WAVES / 4);
+        if (c.gy <= 65535) {
+            const dim3 grid = c.grid((Wo + 3) / 4, planes);
+            if (tap) launch_maxpool2_chain_f32<true>(c, grid, stream, x, y, tap, H, W, Ho, Wo, d);
+            else launch_maxpool2_chain_f32<false>(c, grid, stream, x, y, tap, H, W, Ho, Wo, d);
+            return hipGetLastError();
+        }
     }
     hipLaunchKernelGGL(maxpool_f32_kernel, dim3((Wo + 255) / 256, Ho, planes), dim3(256), 0, stream, x, y, tap,
                        H, W, Ho, Wo, k, d, s);
@@ -433,14 +451,16 @@ __global__ void maxpool_bwd_f32_kernel(const float *__restrict__ dy, const uint8
 // (MASKED), so the layer's output is not read at all: 13 -> 9 bytes per sample.  Grid and four columns a thread as in the
 // forward kernel, for the same reason (48 maps at 527x527: 28.5 us; one column a thread in this form 44.2, one that fetches its
 // four windows and the mask 69.7).
-template <bool MASKED>
-__global__ void __launch_bounds__(64) maxpool2_bwd_chain_f32_kernel(const float *__restrict__ dy, const uint8_t *__restrict__ tap,
-                                                                    float *__restrict__ dx, int H, int W, int Ho, int Wo, int d, int M)
+template <bool MASKED, int U>
+__global__ void __launch_bounds__(256) maxpool2_bwd_chain_f32_kernel(const float *__restrict__ dy, const uint8_t *__restrict__ tap,
+                                                                     float *__restrict__ dx, int H, int W, int Ho, int Wo, int d, int M, int nseg,
+                                                                     int pblocks)
 {
-    const int w4 = (W + 3) / 4, idx = blockIdx.x * 64 + threadIdx.x;
-    const int phase = idx / w4, v = min(4 * (idx - phase * w4), W - 4), m0 = blockIdx.y * M;
-    if (phase >= d || phase >= H) return;
-    const int m1 = min((H - phase + d - 1) / d, m0 + M);
+    const int quad = blockIdx.x * blockDim.x + threadIdx.x, v = min(4 * quad, W - 4);
+    const int sblock = blockIdx.y / pblocks, phase = (blockIdx.y - sblock * pblocks) * blockDim.y + threadIdx.y, seg = sblock * blockDim.z + threadIdx.z;
+    if (4 * quad >= W || phase >= d || phase >= H || seg >= nseg) return;
+    const int links = (H - phase + d - 1) / d, windows = links - 1;      // rows of this residue class, and of windows
+    const int m0 = seg * M, m1 = min(links, m0 + M);
     if (m0 >= m1) return;
     const long p = blockIdx.z;
     // windows at columns v .. v + 3 (a) and v - d .. (b).  Where some of the four lie outside the row the access is moved
@@ -452,8 +472,9 @@ __global__ void __launch_bounds__(64) maxpool2_bwd_chain_f32_kernel(const float 
         float4u ga, gb;
         unsigned ca, cb;
     };
-    auto load = [&](int y) {                              // window row y, clamped into the map
-        const long base = (p * Ho + (y < 0 ? 0 : (y < Ho ? y : Ho - 1))) * Wo;
+    const int row0 = windows > 0 ? phase : 0;             // (a class without windows reads row 0)
+    auto load = [&](int l) {                              // window row l of the class, clamped into the map
+        const long base = (p * Ho + row0 + (long)max(0, min(l, windows - 1)) * d) * Wo;
         Row r;
         r.ga = *reinterpret_cast<const float4u *>(dy + base + xa);
         r.gb = *reinterpret_cast<const float4u *>(dy + base + xb);
@@ -461,8 +482,8 @@ __global__ void __launch_bounds__(64) maxpool2_bwd_chain_f32_kernel(const float 
         r.cb = *reinterpret_cast<const uint1u *>(tap + base + xb);
         return r;
     };
-    auto settle = [&](Row &r, int y) {
-        const bool row = y >= 0 && y < Ho;
+    auto settle = [&](Row &r, int l) {
+        const bool row = l >= 0 && l < windows;
         r.ca = row ? (unsigned)((((unsigned long)NONE_A << 32) | r.ca) >> (8 * sa)) : NONE_A;
         r.cb = row ? (unsigned)((unsigned long)r.cb << (8 * sb)) : NONE_B;
         if (sa & 1) r.ga = float4u{r.ga[1], r.ga[2], r.ga[3], 0.f};
@@ -470,20 +491,17 @@ __global__ void __launch_bounds__(64) maxpool2_bwd_chain_f32_kernel(const float 
         if (sb & 1) r.gb = float4u{0.f, r.gb[0], r.gb[1], r.gb[2]};
         if (sb & 2) r.gb = float4u{0.f, 0.f, r.gb[0], r.gb[1]};
     };
-    int y = phase + m0 * d;
-    float *dst = dx + (p * H + y) * W + v;
+    float *dst = dx + (p * H + phase + (long)m0 * d) * W + v;
     const long ostep = (long)d * W;
-    Row above = load(y - d);
-    settle(above, y - d);
-    constexpr int U = 4;
-    for (int m = m0; m < m1; m += U) {
-        Row r[U];
+    Row above = load(m0 - 1), r[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) r[u] = load(y + u * d);          // all loads of the group first
+    for (int u = 0; u < U; ++u) r[u] = load(m0 + u);      // all in flight together
+    settle(above, m0 - 1);
+    for (int m = m0;;) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (m + u >= m1) break;
-            settle(r[u], y + u * d);
+            settle(r[u], m + u);
             float4u g;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -493,9 +511,22 @@ __global__ void __launch_bounds__(64) maxpool2_bwd_chain_f32_kernel(const float 
             *reinterpret_cast<float4u *>(dst + (long)u * ostep) = g;
             above = r[u];
         }
-        y += U * d;
+        m += U;
+        if (m >= m1) return;
         dst += (long)U * ostep;
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = load(m + u);
     }
+}
+
+template <bool MASKED>
+static void launch_maxpool2_bwd_chain_f32(const PoolCut &c, dim3 grid, hipStream_t stream, const float *dy, const uint8_t *tap, float *dx, int H, int W,
+                                          int Ho, int Wo, int d)
+{
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, c.block(), 0, stream, dy, tap, dx, H, W, Ho, Wo, d, c.len, c.nseg, c.pblocks); };
+    if (c.len >= 4) go(&maxpool2_bwd_chain_f32_kernel<MASKED, 4>);
+    else if (c.len >= 2) go(&maxpool2_bwd_chain_f32_kernel<MASKED, 2>);
+    else go(&maxpool2_bwd_chain_f32_kernel<MASKED, 1>);
 }
 
 hipError_t launch_maxpool_bwd_f32(const float *dy, const uint8_t *tap, const float *relu_src,
@@ -504,11 +535,13 @@ hipError_t launch_maxpool_bwd_f32(const float *dy, const uint8_t *tap, const flo
 {
     if (H > 65535 || planes > 65535) return hipErrorInvalidValue;
     if (k == 2 && Ho == H - d && Wo == W - d && Ho >= 1 && Wo >= 4) {
-        const PoolCut c = pool_cut4(H, W, d, planes, 4);
-        const dim3 grid((unsigned)(((long)d * ((W + 3) / 4) + 63) / 64), (unsigned)c.nseg, (unsigned)planes);
-        if (relu_src) hipLaunchKernelGGL(maxpool2_bwd_chain_f32_kernel<true>, grid, dim3(64), 0, stream, dy, tap, dx, H, W, Ho, Wo, d, c.len);
-        else hipLaunchKernelGGL(maxpool2_bwd_chain_f32_kernel<false>, grid, dim3(64), 0, stream, dy, tap, dx, H, W, Ho, Wo, d, c.len);
-        return hipGetLastError();
+        const PoolCut c = pool_cut(H, (W + 3) / 4, d, planes, POOL_WAVES);
+        if (c.gy <= 65535) {
+            const dim3 grid = c.grid((W + 3) / 4, planes);
+            if (relu_src) launch_maxpool2_bwd_chain_f32<true>(c, grid, stream, dy, tap, dx, H, W, Ho, Wo, d);
+            else launch_maxpool2_bwd_chain_f32<false>(c, grid, stream, dy, tap, dx, H, W, Ho, Wo, d);
+            return hipGetLastError();
+        }
     }
     hipLaunchKernelGGL(maxpool_bwd_f32_kernel, dim3((W + 255) / 256, H, planes), dim3(256), 0, stream, dy, tap, relu_src, dx, H, W, Ho, Wo, k, d);
     return hipGetLastError();

@@ -181,30 +181,55 @@ __device__ __forceinline__ unsigned pool3d_code_h(const void *tap, long q, int e
 // first maximum of X[r][x], X[r][x + d].  A thread walks one column down the rows y0, y0 + d,
 // y0 + 2d, ... of one residue class mod d, so each h is formed once and serves both windows it
 // belongs to, and a block reads every input row it needs exactly once (no second workgroup, on
-// another XCD with another L2, fetches the same rows again).  grid: x = column blocks,
-// y = residue class x segments of M chain links, z = plane.  The winner follows the row-major
-// scan: row y before row y + d, strictly-greater replaces.
+// another XCD with another L2, fetches the same rows again).  Grid and workgroup: see pool_cut; segments are M windows long,
+// z = plane.  The winner follows the row-major scan: row y before row y + d, strictly-greater replaces.
+// Sets of elements come in split form: element 2 w in bit 2 w, element 2 w + 1 in bit 16 + 2 w, as a word's two halves give them.
 template <int DT>
 __device__ __forceinline__ void row_first_max(const uint4v a, const uint4v b, uint4v &h, unsigned &hc)
 {
     hc = 0u;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        unsigned m = 0u;
-        if (up16<DT>(b[w] & 0xffffu) > up16<DT>(a[w] & 0xffffu)) { m |= 0x0000ffffu; hc |= 1u << (2 * w); }
-        if (up16<DT>(b[w] >> 16) > up16<DT>(a[w] >> 16)) { m |= 0xffff0000u; hc |= 1u << (2 * w + 1); }
+        const unsigned lo = up16<DT>(b[w] & 0xffffu) > up16<DT>(a[w] & 0xffffu) ? 0x0000ffffu : 0u;
+        const unsigned m = lo | (up16<DT>(b[w] >> 16) > up16<DT>(a[w] >> 16) ? 0xffff0000u : 0u);
+        hc |= (m & 0x00010001u) << (2 * w);
         h[w] = (a[w] & ~m) | (b[w] & m);
     }
 }
 
-template <int DT, bool TAP>
+// the positive elements (not zero, no NaN).  Packed 16-bit integers: u - 1 of 1 .. infinity, and of nothing else, stays below the top bit
+// when the rest of the range is added with saturation.
+template <int DT>
+__device__ __forceinline__ unsigned positive_h(const uint4v o)
+{
+    typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+    constexpr unsigned short REST = DT == 1 ? 0x8000 - 0x7f80 : 0x8000 - 0x7c00;
+    unsigned not_pos = 0u;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const unsigned word = o[w];
+        const ushort2v v = __builtin_elementwise_add_sat((ushort2v)(__builtin_bit_cast(ushort2v, word) - (unsigned short)1), ushort2v{REST, REST});
+        not_pos |= (__builtin_bit_cast(unsigned, v) >> 15 & 0x00010001u) << (2 * w);
+    }
+    return not_pos ^ 0x00550055u;
+}
+
+// two sets in split form as two bit planes: bit e of byte 0, of byte 1
+__device__ __forceinline__ unsigned bit_planes_h(unsigned a, unsigned b)
+{
+    const unsigned both = a | (b << 8);
+    return (both | (both >> 15)) & 0xffffu;
+}
+
+// U: windows whose loads are in flight together
+template <int DT, bool TAP, int U>
 __global__ void __launch_bounds__(256) maxpool2_chain_h_kernel(const uint4v *__restrict__ x, uint4v *__restrict__ y,
                                                                unsigned *__restrict__ tap, int H, int W, int Ho, int Wo,
-                                                               int d, int M, int nseg)
+                                                               int d, int M, int nseg, int pblocks)
 {
     const int xx = blockIdx.x * blockDim.x + threadIdx.x;
-    const int phase = blockIdx.y / nseg, seg = blockIdx.y - phase * nseg;
-    if (xx >= Wo || phase >= Ho) return;
+    const int sblock = blockIdx.y / pblocks, phase = (blockIdx.y - sblock * pblocks) * blockDim.y + threadIdx.y, seg = sblock * blockDim.z + threadIdx.z;
+    if (xx >= Wo || phase >= d || phase >= Ho || seg >= nseg) return;
     const int links = (Ho - phase + d - 1) / d;           // windows of this residue class
     const int m0 = seg * M, m1 = min(links, m0 + M);
     if (m0 >= m1) return;
@@ -214,19 +239,21 @@ __global__ void __launch_bounds__(256) maxpool2_chain_h_kernel(const uint4v *__r
     uint4v *dst = y + (p * Ho + phase + (long)m0 * d) * Wo + xx;
     unsigned *tdst = TAP ? tap + (p * Ho + phase + (long)m0 * d) * Wo + xx : nullptr;
     const long ostep = (long)d * Wo;
-    uint4v h;
-    unsigned hc;
-    row_first_max<DT>(src[0], src[d], h, hc);
-    constexpr int U = 4;
-    for (int m = m0; m < m1; m += U) {
-        uint4v a[U], b[U];
+    uint4v a[U], b[U];
+    auto load = [&](int m) {                              // the lower rows of windows m .. m + U - 1
 #pragma unroll
-        for (int u = 0; u < U; ++u) {                     // all loads of the group first
-            const bool live = m + u < m1;
-            const uint4v *r = src + (live ? (long)(u + 1) * rstep : 0);
+        for (int u = 0; u < U; ++u) {
+            const uint4v *r = src + (m + u < m1 ? (long)(u + 1) * rstep : 0);
             a[u] = r[0];
             b[u] = r[d];
         }
+    };
+    const uint4v first = src[0], right = src[d];
+    load(m0);                                             // in flight together with the first row
+    uint4v h;
+    unsigned hc;
+    row_first_max<DT>(first, right, h, hc);
+    for (int m = m0;;) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (m + u >= m1) break;
@@ -234,22 +261,32 @@ __global__ void __launch_bounds__(256) maxpool2_chain_h_kernel(const uint4v *__r
             unsigned hc2;
             row_first_max<DT>(a[u], b[u], h2, hc2);
             uint4v o;
-            unsigned lower;                               // bit e: the winner lies in row y + d
+            unsigned lower;                               // whose winner lies in row y + d
             row_first_max<DT>(h, h2, o, lower);
             dst[(long)u * ostep] = o;
-            if (TAP) {
-                unsigned pos = 0u;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) pos |= up16<DT>(elem16(o, e)) > 0.f ? 1u << e : 0u;
-                tdst[(long)u * ostep] = (hc & ~lower) | (hc2 & lower) | (lower << 8) | (pos << 16);
-            }
+            if (TAP) tdst[(long)u * ostep] = bit_planes_h((hc & ~lower) | (hc2 & lower), lower) | (bit_planes_h(positive_h<DT>(o), 0u) << 16);
             h = h2;
             hc = hc2;
         }
+        m += U;
+        if (m >= m1) return;
         src += (long)U * rstep;
         dst += (long)U * ostep;
         if (TAP) tdst += (long)U * ostep;
+        load(m);
     }
+}
+
+template <int DT, bool TAP>
+static void launch_maxpool2_chain_h(const PoolCut &c, dim3 grid, hipStream_t stream, const void *x, void *y, void *tap, int H, int W, int Ho, int Wo, int d)
+{
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, c.block(), 0, stream, static_cast<const uint4v *>(x), static_cast<uint4v *>(y),
+                           static_cast<unsigned *>(tap), H, W, Ho, Wo, d, c.len, c.nseg, c.pblocks);
+    };
+    if (c.len >= 4) go(&maxpool2_chain_h_kernel<DT, TAP, 4>);
+    else if (c.len >= 2) go(&maxpool2_chain_h_kernel<DT, TAP, 2>);
+    else go(&maxpool2_chain_h_kernel<DT, TAP, 1>);
 }
 
 hipError_t launch_maxpool_h(const void *x, void *y, void *tap, int dtype, long planes8, int H, int W, int Ho, int Wo,
@@ -257,19 +294,13 @@ hipError_t launch_maxpool_h(const void *x, void *y, void *tap, int dtype, long p
 {
     if (Ho > 65535 || planes8 > 65535) return hipErrorInvalidValue;
     if (k == 2 && s == 1 && Ho == H - d && Wo == W - d) {
-        const PoolCut c = pool_cut(Ho, Wo, d, planes8, 4);
-        if ((long)d * c.nseg <= 65535) {
-            const dim3 grid((Wo + c.threads - 1) / c.threads, (unsigned)(d * c.nseg), (unsigned)planes8);
-            const uint4v *xi = static_cast<const uint4v *>(x);
-            uint4v *yo = static_cast<uint4v *>(y);
-            unsigned *tp = static_cast<unsigned *>(tap);
-            if (dtype == 1) {
-                if (tap) hipLaunchKernelGGL((maxpool2_chain_h_kernel<1, true>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
-                else hipLaunchKernelGGL((maxpool2_chain_h_kernel<1, false>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
-            } else {
-                if (tap) hipLaunchKernelGGL((maxpool2_chain_h_kernel<2, true>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
-                else hipLaunchKernelGGL((maxpool2_chain_h_kernel<2, false>), grid, dim3(c.threads), 0, stream, xi, yo, tp, H, W, Ho, Wo, d, c.len, c.nseg);
-            }
+        const PoolCut c = pool_cut(Ho, Wo, d, planes8, tap ? POOL_WAVES : POOL_WAVES / 4);
+        if (c.gy <= 65535) {
+            const dim3 grid = c.grid(Wo, planes8);
+            if (dtype == 1 && tap) launch_maxpool2_chain_h<1, true>(c, grid, stream, x, y, tap, H, W, Ho, Wo, d);
+            else if (dtype == 1) launch_maxpool2_chain_h<1, false>(c, grid, stream, x, y, tap, H, W, Ho, Wo, d);
+            else if (tap) launch_maxpool2_chain_h<2, true>(c, grid, stream, x, y, tap, H, W, Ho, Wo, d);
+            else launch_maxpool2_chain_h<2, false>(c, grid, stream, x, y, tap, H, W, Ho, Wo, d);
             return hipGetLastError();
         }
     }
@@ -384,15 +415,11 @@ __global__ void __launch_bounds__(256) maxpool3d_k2_chain_h_kernel(const uint4v 
             if (m + u >= m1) break;
             const Quad q2 = quad(s[u][0], s[u][1], s[u][2], s[u][3]);
             uint4v o;
-            unsigned far;                                 // bit e: the winner lies in slice z + d
+            unsigned far;                                 // whose winner lies in slice z + d
             row_first_max<DT>(q.v, q2.v, o, far);
             dst[u * ostep] = o;
-            if (TAP) {
-                unsigned pos8 = 0u;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) pos8 |= up16<DT>(elem16(o, e)) > 0.f ? 1u << e : 0u;
-                tdst[u * ostep] = (q.j & ~far) | (q2.j & far) | (((q.i & ~far) | (q2.i & far)) << 8) | (far << 16) | (pos8 << 24);
-            }
+            if (TAP)
+                tdst[u * ostep] = bit_planes_h((q.j & ~far) | (q2.j & far), (q.i & ~far) | (q2.i & far)) | (bit_planes_h(far, positive_h<DT>(o)) << 16);
             q = q2;
         }
         src += U * zstep;
@@ -732,14 +759,15 @@ __global__ void maxpool_bwd_h_kernel(const uint4v *__restrict__ dy, const void *
 // behind, by the vector instructions that pick among 32 (element, window) pairs: with bit planes the codes of a unit are
 // eight bitwise operations and a pick is a sign-extended bit, an AND and the addition.  48 maps of 8 x 1066^2: 562 -> 410 us
 // (4.8 TB/s), the forward pass 447 -> 409; at 527x527 20.7 -> 15.8.
-template <int DT, bool MASKED>
+template <int DT, bool MASKED, int U>
 __global__ void __launch_bounds__(256) maxpool2_bwd_chain_h_kernel(const uint4v *__restrict__ dy, const unsigned *__restrict__ tap,
-                                                                   uint4v *__restrict__ dx, int H, int W, int Ho, int Wo, int d, int M, int nseg)
+                                                                   uint4v *__restrict__ dx, int H, int W, int Ho, int Wo, int d, int M, int nseg,
+                                                                   int pblocks)
 {
     const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    const int phase = blockIdx.y / nseg, seg = blockIdx.y - phase * nseg;
-    if (v >= W || phase >= H) return;
-    const int links = (H - phase + d - 1) / d;
+    const int sblock = blockIdx.y / pblocks, phase = (blockIdx.y - sblock * pblocks) * blockDim.y + threadIdx.y, seg = sblock * blockDim.z + threadIdx.z;
+    if (v >= W || phase >= d || phase >= H || seg >= nseg) return;
+    const int links = (H - phase + d - 1) / d, windows = links - 1;      // rows of this residue class, and of windows
     const int m0 = seg * M, m1 = min(links, m0 + M);
     if (m0 >= m1) return;
     const long p = blockIdx.z;
@@ -750,8 +778,9 @@ __global__ void __launch_bounds__(256) maxpool2_bwd_chain_h_kernel(const uint4v 
         uint4v ga, gb;
         unsigned ca, cb;
     };
-    auto load = [&](int y) {                              // window row y, clamped into the map
-        const long base = (p * Ho + (y < 0 ? 0 : (y < Ho ? y : Ho - 1))) * Wo;     // uniform
+    const int row0 = windows > 0 ? phase : 0;             // (a class without windows reads row 0)
+    auto load = [&](int l) {                              // window row l of the class, clamped into the map
+        const long base = (p * Ho + row0 + (long)max(0, min(l, windows - 1)) * d) * Wo;
         Row r;
         r.ga = dy[base + xa];
         r.gb = dy[base + xb];
@@ -760,8 +789,8 @@ __global__ void __launch_bounds__(256) maxpool2_bwd_chain_h_kernel(const uint4v 
         return r;
     };
     // bit e of t[c]: element e of that window chose code c (c = 0, 2 at column v; 1, 3 at column v - d)
-    auto picks = [&](const Row &r, int y, unsigned (&t)[4]) {
-        const unsigned row = y >= 0 && y < Ho ? 0xffu : 0u;                        // uniform
+    auto picks = [&](const Row &r, int l, unsigned (&t)[4]) {
+        const unsigned row = l >= 0 && l < windows ? 0xffu : 0u;
         const unsigned pa = (MASKED ? r.ca >> 16 : 0xffu) & ina & row, pb = (MASKED ? r.cb >> 16 : 0xffu) & inb & row;
         const unsigned a0 = pa & ~r.ca, b1 = pb & r.cb, la = r.ca >> 8, lb = r.cb >> 8;
         t[0] = a0 & ~la;
@@ -772,22 +801,19 @@ __global__ void __launch_bounds__(256) maxpool2_bwd_chain_h_kernel(const uint4v 
     auto pick = [](uint4v g, unsigned t, int e) {         // the element, or +0
         return __int_as_float(__float_as_int(up16<DT>(elem16(g, e))) & ((int)(t << (31 - e)) >> 31));
     };
-    int y = phase + m0 * d;
-    uint4v *dst = dx + (p * H + y) * W + v;
+    uint4v *dst = dx + (p * H + phase + (long)m0 * d) * W + v;
     const long ostep = (long)d * W;
-    Row above = load(y - d);
-    unsigned ta[4];
-    picks(above, y - d, ta);
-    constexpr int U = 4;
-    for (int m = m0; m < m1; m += U) {
-        Row r[U];
+    Row above = load(m0 - 1), r[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) r[u] = load(y + u * d);          // all loads of the group first
+    for (int u = 0; u < U; ++u) r[u] = load(m0 + u);      // all in flight together
+    unsigned ta[4];
+    picks(above, m0 - 1, ta);
+    for (int m = m0;;) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (m + u >= m1) break;
             unsigned t[4];
-            picks(r[u], y + u * d, t);
+            picks(r[u], m + u, t);
             unsigned hv[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e)
@@ -797,9 +823,25 @@ __global__ void __launch_bounds__(256) maxpool2_bwd_chain_h_kernel(const uint4v 
             ta[2] = t[2];
             ta[3] = t[3];
         }
-        y += U * d;
+        m += U;
+        if (m >= m1) return;
         dst += (long)U * ostep;
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = load(m + u);
     }
+}
+
+template <int DT, bool MASKED>
+static void launch_maxpool2_bwd_chain_h(const PoolCut &c, dim3 grid, hipStream_t stream, const void *dy, const void *tap, void *dx, int H, int W, int Ho,
+                                        int Wo, int d)
+{
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, c.block(), 0, stream, static_cast<const uint4v *>(dy), static_cast<const unsigned *>(tap),
+                           static_cast<uint4v *>(dx), H, W, Ho, Wo, d, c.len, c.nseg, c.pblocks);
+    };
+    if (c.len >= 4) go(&maxpool2_bwd_chain_h_kernel<DT, MASKED, 4>);
+    else if (c.len >= 2) go(&maxpool2_bwd_chain_h_kernel<DT, MASKED, 2>);
+    else go(&maxpool2_bwd_chain_h_kernel<DT, MASKED, 1>);
 }
 
 hipError_t launch_maxpool_bwd_h(const void *dy, const void *tap, const void *relu_src, void *dx, int dtype,
@@ -809,17 +851,13 @@ hipError_t launch_maxpool_bwd_h(const void *dy, const void *tap, const void *rel
     const uint4v *g = static_cast<const uint4v *>(dy), *rs = static_cast<const uint4v *>(relu_src);
     uint4v *out = static_cast<uint4v *>(dx);
     if (k == 2 && Ho == H - d && Wo == W - d && Ho >= 1 && Wo >= 1) {
-        const PoolCut c = pool_cut(H, W, d, planes8, 4);
-        if ((long)d * c.nseg <= 65535) {
-            const dim3 grid((W + c.threads - 1) / c.threads, (unsigned)(d * c.nseg), (unsigned)planes8);
-            const unsigned *tp = static_cast<const unsigned *>(tap);
-            if (dtype == 1) {
-                if (rs) hipLaunchKernelGGL((maxpool2_bwd_chain_h_kernel<1, true>), grid, dim3(c.threads), 0, stream, g, tp, out, H, W, Ho, Wo, d, c.len, c.nseg);
-                else hipLaunchKernelGGL((maxpool2_bwd_chain_h_kernel<1, false>), grid, dim3(c.threads), 0, stream, g, tp, out, H, W, Ho, Wo, d, c.len, c.nseg);
-            } else {
-                if (rs) hipLaunchKernelGGL((maxpool2_bwd_chain_h_kernel<2, true>), grid, dim3(c.threads), 0, stream, g, tp, out, H, W, Ho, Wo, d, c.len, c.nseg);
-                else hipLaunchKernelGGL((maxpool2_bwd_chain_h_kernel<2, false>), grid, dim3(c.threads), 0, stream, g, tp, out, H, W, Ho, Wo, d, c.len, c.nseg);
-            }
+        const PoolCut c = pool_cut(H, W, d, planes8, POOL_WAVES);
+        if (c.gy <= 65535) {
+            const dim3 grid = c.grid(W, planes8);
+            if (dtype == 1 && rs) launch_maxpool2_bwd_chain_h<1, true>(c, grid, stream, dy, tap, dx, H, W, Ho, Wo, d);
+            else if (dtype == 1) launch_maxpool2_bwd_chain_h<1, false>(c, grid, stream, dy, tap, dx, H, W, Ho, Wo, d);
+            else if (rs) launch_maxpool2_bwd_chain_h<2, true>(c, grid, stream, dy, tap, dx, H, W, Ho, Wo, d);
+            else launch_maxpool2_bwd_chain_h<2, false>(c, grid, stream, dy, tap, dx, H, W, Ho, Wo, d);
             return hipGetLastError();
         }
     }

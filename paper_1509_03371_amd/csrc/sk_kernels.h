@@ -4,40 +4,55 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace sk {
 
-// How the k = 2, s = 1 pool kernels cut a map.  A thread walks a chain of `len` windows down one residue class of rows and
-// reads one row more than it has windows, so long chains (32) read least; but a chain is a serial row of memory latencies,
-// and a small map in chains of 32 fills a fraction of the GPU (96x96 with 8 or 16 maps: 32-64 workgroups, 11 us).  So row
-// blocks are narrowed to the width and chains halved, down to `step` windows (whose loads a thread keeps in flight together),
-// until POOL_WAVES waves (sixteen per CU) are there: the pools of 48 bf16 maps at 527x527, forward / backward in us, with
-// 1024, 2048, 4096, 8192 waves asked for: 26.6 / 29.2, 16.9 / 17.5, 16.2 / 15.7, 16.3 / 15.8.  Maps that fill the GPU in
-// chains of 32 keep them (fewest reads).
+// How the k = 2, s = 1 pool kernels cut a map.  A thread walks a chain of `len` windows (four columns of it in fp32) down one residue
+// class of rows and reads one row more than it has windows, so long chains (32) read least; but a chain is a serial row of
+// memory latencies, and a small map in chains of 32 fills a fraction of the GPU.  So chains are halved until POOL_WAVES waves (sixteen per CU)
+// are there: the pools of 48 bf16 maps at 527x527, forward / backward in us, with 1024, 2048, 4096, 8192 waves asked for: 26.6 / 29.2, 16.9 /
+// 17.5, 16.2 / 15.7, 16.3 / 15.8.  Below four windows for fewer waves (short_waves): with winner codes and backward, where a window is some
+// hundred instructions, POOL_WAVES too, without codes a quarter.  A workgroup holds several classes or segments of rows that do not fill it.
+// 128 pools (8 to 128 maps of 24x24 to 1066x1066, 1 to 8 images, d = 1 to 8, fp32 and bf16) against one window, or input sample, a thread:
+// without codes 0.39 to 1.06 of the time, with codes 0.42 to 1.08, backward 0.14 to 1.08; geometric means 0.79, 0.74, 0.76 (chains of
+// four windows and more in workgroups of one segment: backward up to 1.49 on small maps, whose 2.4 us became 3.3).
 struct PoolCut {
-    int threads, len, nseg;
+    int bx, bp, bs;              // workgroup: columns x residue classes x segments
+    int len, nseg, pblocks;      // grid: columns, (blocks of classes, fastest) x (blocks of segments), planes
+    long gy;
+    dim3 grid(int cols, long planes) const { return dim3((unsigned)((cols + bx - 1) / bx), (unsigned)gy, (unsigned)planes); }
+    dim3 block() const { return dim3(bx, bp, bs); }
 };
 constexpr long POOL_WAVES = 4096;
-inline PoolCut pool_cut(int Ho, int Wo, int d, long planes, int step)
+inline PoolCut pool_cut(int Ho, int cols, int d, long planes, long short_waves)
 {
-    PoolCut c{256, 32, 1};
+    PoolCut c{};
     const int links = (Ho + d - 1) / d;
-    auto waves = [&]() { return (long)((Wo + c.threads - 1) / c.threads) * (c.threads / 64) * d * c.nseg * planes; };
-    auto cut = [&](int len) { c.len = len; c.nseg = (links + len - 1) / len; };
-    cut(32);
-    if (waves() >= POOL_WAVES) return c;
-    while (c.threads > 64 && (Wo + c.threads / 2 - 1) / (c.threads / 2) * (c.threads / 2) < (Wo + c.threads - 1) / c.threads * c.threads)
-        c.threads /= 2;
-    while (c.len > step && waves() < POOL_WAVES) cut(c.len / 2);
-    return c;
-}
-// the same for the kernels whose threads take four columns of a chain and lie linearly over (residue class, column block)
-inline PoolCut pool_cut4(int Ho, int Wo, int d, long planes, int step)
-{
-    PoolCut c{64, 32, 1};
-    const int links = (Ho + d - 1) / d;
-    const long row_waves = ((long)d * ((Wo + 3) / 4) + 63) / 64 * planes;
-    auto cut = [&](int len) { c.len = len; c.nseg = (links + len - 1) / len; };
-    for (cut(32); c.len > step && row_waves * c.nseg < POOL_WAVES;) cut(c.len / 2);
+    auto threads = [&]() { return (long)cols * d * c.nseg * planes; };
+    for (c.len = 32;; c.len /= 2) {
+        c.nseg = (links + c.len - 1) / c.len;
+        if (c.len == 1 || threads() >= 64 * (c.len > 4 ? POOL_WAVES : short_waves)) break;
+    }
+    // the workgroup whose waves have the fewest idle lanes: whole rows or parts of them, several classes or segments of narrow ones
+    const int wg = threads() >= 32 * POOL_WAVES ? 256 : 64;
+    auto up = [](int v, int m) { return (v + m - 1) / m; };
+    double best = 0.;
+    for (int most = wg; most >= 64; most /= 2) {
+        const int parts = up(cols, most), bx = up(cols, parts);
+        for (int classes : {wg / bx, 1}) {
+            const int bp = up(d, up(d, std::max(1, std::min(d, classes)))), bs = std::min(c.nseg, std::max(1, wg / (bx * bp))), n = bx * bp * bs;
+            const double fill = (double)cols / (parts * bx) * d / (up(d, bp) * bp) * c.nseg / (up(c.nseg, bs) * bs) * n / (up(n, 64) * 64);
+            if (fill > best * (most == wg ? 1.02 : 1.25)) {      // (wide rows in narrow parts: 48 maps of 8 x 1066^2 10 % slower)
+                best = fill;
+                c.bx = bx;
+                c.bp = bp;
+                c.bs = bs;
+            }
+        }
+    }
+    c.pblocks = (d + c.bp - 1) / c.bp;
+    c.gy = (long)c.pblocks * ((c.nseg + c.bs - 1) / c.bs);
     return c;
 }
 

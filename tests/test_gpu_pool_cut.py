@@ -16,6 +16,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("maps,d,n,h,w", [
     (8, 1, 1, 6, 64), (8, 1, 1, 10, 66), (16, 1, 2, 18, 130), (8, 2, 1, 36, 259), (24, 4, 1, 133, 131), (48, 2, 1, 67, 258),
     (48, 4, 2, 140, 300), (8, 1, 1, 7, 7),
+    # narrow rows: several residue classes and segments a workgroup, some of them empty; chains of one, two and more windows
+    (8, 1, 1, 40, 21), (16, 3, 2, 61, 36), (64, 5, 4, 97, 33), (48, 1, 4, 300, 47), (128, 2, 8, 180, 66), (16, 7, 1, 20, 300), (48, 8, 1, 45, 1030),
 ])
 def test_pool_chains(dtype, training, maps, d, n, h, w):
     from paper_1509_03371_amd import binding as B

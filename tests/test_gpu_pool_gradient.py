@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("maps,d,n,h,w", [
     (8, 1, 1, 2, 2), (8, 1, 2, 9, 4), (16, 3, 1, 5, 6), (8, 1, 1, 6, 5), (8, 2, 1, 11, 8), (12, 5, 2, 7, 12), (16, 9, 1, 12, 13),
     (8, 4, 1, 75, 67), (24, 1, 1, 38, 261), (48, 8, 1, 140, 130), (48, 2, 2, 300, 301),
+    (64, 5, 4, 97, 33), (48, 1, 4, 300, 47), (16, 7, 1, 20, 300), (128, 1, 1, 12, 90),
 ])
 def test_pool_gradient(dtype, relu, maps, d, n, h, w):
     from paper_1509_03371_amd import binding as B
