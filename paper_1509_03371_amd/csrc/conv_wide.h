@@ -1,6 +1,7 @@
 #pragma once
 // What the 16-bit convolutions for many maps share (kernels_conv_wide_h.hip, kernels_conv_wide_big_h.hip): tile geometry,
 // direct global -> LDS loads, waits, and the epilogue.
+#include "lds_dma.h"
 #include "sk_kernels.h"
 
 #include <algorithm>
@@ -39,17 +40,6 @@ template <int DT> __device__ __forceinline__ unsigned wide_cvt(float f)
 {
     if constexpr (DT == 1) return __builtin_bit_cast(unsigned short, static_cast<__bf16>(f));
     else return __builtin_bit_cast(unsigned short, static_cast<_Float16>(f));
-}
-
-__device__ __forceinline__ void wide_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// wait until at most N of this wave's memory operations are outstanding
-template <int N> __device__ __forceinline__ void wide_wait()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is six bits");
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-    __builtin_amdgcn_sched_barrier(0);
 }
 
 // f(integral_constant 0), ..., f(integral_constant N - 1)

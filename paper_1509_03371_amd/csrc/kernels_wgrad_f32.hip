@@ -510,17 +510,6 @@ __device__ __forceinline__ uint4v read_frag_tr(const char *lds_base, unsigned of
 
 constexpr int WG_TRP = WG_SEG + 4;      // LDS pitch (16-byte units) of a dY octet row: row starts alternate between the two halves of the banks
 
-__device__ __forceinline__ void wide_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// wait until at most N of this wave's memory operations are outstanding
-template <int N> __device__ __forceinline__ void wide_wait()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is six bits");
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 template <int MB, int NB, int DT>
 __global__ __launch_bounds__(256) void wgrad_tr_h_kernel(WgradArgs a)
 {
@@ -1225,7 +1214,7 @@ __global__ void __launch_bounds__(256) wgrad_tr_reduce_kernel(const float *__res
     __shared__ __attribute__((aligned(16))) float sh[TRR_SPAN];
     const int t = threadIdx.x;
     if ((int)blockIdx.x >= dw_blocks) {
-        // bias: 64 maps per workgroup, wave w adds slices w, w+4, ... in four running sums; then the waves in order
+        // bias: 64 maps per workgroup, wave w adds slices w, w+4, ...; then the waves in order
         const int e = t & 63, w = t >> 6;
         const int o = ((int)blockIdx.x - dw_blocks) * 64 + e;
         float v = 0.f;

@@ -20,4 +20,16 @@ __device__ __forceinline__ void lds_dma16(const void *src, const void *dst)
 #pragma clang diagnostic pop
 }
 
+// meet the workgroup with this wave's LDS operations done (loads to LDS stay under way)
+__device__ __forceinline__ void wide_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// wait until at most N of this wave's memory operations are outstanding
+template <int N> __device__ __forceinline__ void wide_wait()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt is six bits");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 }  // namespace sk
