@@ -1504,6 +1504,9 @@ static hipError_t launch_wgrad_strip_t(const WgradArgs &a, size_t smem, int bloc
     return hipGetLastError();
 }
 
+// Which kernel has which tiles (map tiles x column tiles a wave): 1x1 kernels, the only ones without a ring, take 1, 4 or 12 column tiles; the strip
+// kernel's LDS does not hold six of 2x2 kernels (twelve octets a group) and, at wide kernel strides, where two workgroups share a CU,
+// 4 column tiles or one map tile with 9 or 12.
 template <int MB, int NB, int DT>
 static hipError_t launch_wgrad_tr_mb(const WgradArgs &a, size_t smem, size_t strip_smem, int teams, int blocks, hipStream_t stream, bool ring)
 {
@@ -1511,8 +1514,12 @@ static hipError_t launch_wgrad_tr_mb(const WgradArgs &a, size_t smem, size_t str
         if constexpr (wgrad_strip_pairs(MB, NB))
             if (teams > 1) return launch_wgrad_strip_t<MB, NB, DT, 2>(a, strip_smem, blocks, stream);
         return launch_wgrad_strip_t<MB, NB, DT, 1>(a, strip_smem, blocks, stream);
+    } else if (ring) {
+        if constexpr (NB == 6 || (MB == 1 && NB >= 9) || (MB > 1 && NB == 4)) return launch_wgrad_trr_t<MB, NB, DT>(a, smem, blocks, stream);
+    } else {
+        if constexpr (NB == 1 || NB == 4 || NB == 12) return launch_wgrad_tr_t<MB, NB, DT>(a, smem, blocks, stream);
     }
-    return ring ? launch_wgrad_trr_t<MB, NB, DT>(a, smem, blocks, stream) : launch_wgrad_tr_t<MB, NB, DT>(a, smem, blocks, stream);
+    return hipErrorInvalidValue;
 }
 
 // ring = the strip-walking kernels that keep the staged input rows across steps; strip_smem != 0: the one that loads straight into LDS
