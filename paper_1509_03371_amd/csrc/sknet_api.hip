@@ -160,8 +160,8 @@ sk_status check_net(const sknet_t *net)
     return SK_OK;
 }
 
-// forward step `step`: 0 = pad/copy, 1..L = layers, L+1 = softmax
-sk_status run_forward_step(sknet *net, int step_idx, hipStream_t stream)
+// forward step `step`: 0 = pad/copy, 1..L = layers, L+1 = softmax; again: on what the last pass left behind
+sk_status run_forward_step(sknet *net, int step_idx, hipStream_t stream, bool again = false)
 {
     const int L = (int)net->layers.size();
     const bool half = net->half();
@@ -225,6 +225,10 @@ sk_status run_forward_step(sknet *net, int step_idx, hipStream_t stream)
                 a.used_w = net->c1_used; a.used_b = net->c1_used + (long)c.rows_fwd * c.n_pad;
                 a.n = net->n; a.h = net->h; a.w = net->w; a.top = net->pad ? net->pad_top : 0; a.left = net->pad ? net->pad_left : 0;
                 a.mode = net->pad_mode; a.h_pad = in.h; a.w_pad = in.w; a.k = l.k; a.c_out = c.c_out; a.n_pad = c.n_pad; a.relu = l.relu;
+                if (again) {             // the padded image of the pass is there, the caller's image may be another or gone
+                    a.image = net->act[0];
+                    a.h = in.h; a.w = in.w; a.top = a.left = 0;
+                }
                 SK_HIP(sk::launch_conv_c1_pool_f32(a, stream));
             } else {
                 sk::ConvF32Args a = conv_args(c, net->act[li], net->n, in, l.d, l.relu, net->act[li + 1], out);
@@ -1013,9 +1017,9 @@ sk_status sknet_time_step(sknet_t *net, int32_t step, int32_t iters, void *hip_s
     hipEvent_t e0, e1;
     SK_HIP(hipEventCreate(&e0));
     SK_HIP(hipEventCreate(&e1));
-    sk_status st = run_forward_step(net, step, stream);   // warm-up
+    sk_status st = run_forward_step(net, step, stream, true);   // warm-up
     hipError_t e = hipEventRecord(e0, stream);
-    for (int i = 0; i < iters && st == SK_OK; ++i) st = run_forward_step(net, step, stream);
+    for (int i = 0; i < iters && st == SK_OK; ++i) st = run_forward_step(net, step, stream, true);
     if (e == hipSuccess) e = hipEventRecord(e1, stream);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     float ms = 0.f;

@@ -107,3 +107,20 @@ def test_reads_wait_for_a_replay_on_the_default_stream():
             graph.replay()
             torch.cuda.synchronize()
     net.close()
+
+
+def test_timing_a_step_reads_what_the_pass_left():
+    # the launch that pads, convolves and pools takes the padded image of the pass, not the buffer the caller's image was in
+    layers, h, w = NETS[0], 70, 93
+    net = planned(layers, h, w, 1)
+    img = torch.from_numpy(S.uniform_image(1, 1, h, w, 3)).cuda()
+    net.forward(img)
+    want = [net.get_activation(i) for i in (-1, 0, 1, 2)]
+    img.fill_(7.0)
+    names = [net.step_name(i) for i in range(net.num_steps())]
+    for i, name in enumerate(names):
+        if name.startswith("conv") or name.startswith("pool"):
+            net.time_step(i, 3)
+    for a, i in zip(want, (-1, 0, 1, 2)):
+        assert np.array_equal(a, net.get_activation(i)), i
+    net.close()
