@@ -201,6 +201,7 @@ def measure_train(torch, B, S, dtype, n, H, W, steps, warmup, first_seed, kernel
         net.forward(timg, prob, stream)
         parts, wg_ms, wg_flops, wg_bytes, wg_n = {}, 0.0, 0.0, 0.0, 0
         pool_bwd_bytes, pool_bwd_ms, pool_fwd_bytes, pool_fwd_ms = 0.0, 0.0, 0.0, 0.0
+        code = 1.0 if dtype == "f32" else 0.5                            # bytes of a winner code: 16-bit pools keep bit planes, a word for eight maps
         for step in range(net.num_steps()):
             name = net.step_name(step)
             m = re.match(r"pool(\d+)_", name)
@@ -209,7 +210,8 @@ def measure_train(torch, B, S, dtype, n, H, W, steps, warmup, first_seed, kernel
                 c, ho, wo = shapes[li + 1]
                 ms = net.time_step(step, kernel_iters, stream)
                 pool_fwd_ms += ms
-                pool_fwd_bytes += n * c * ho * wo * (2.0 * esize + 1)          # element in, element out, one winner code
+                hi, wi = shapes[li][1:]
+                pool_fwd_bytes += n * c * (hi * wi * esize + ho * wo * (esize + code))      # every input in, every output and its winner code out
         parts["loss_ms"] = round(net.time_backward_step(labels, 0, 2, kernel_iters, stream), 5)
         head_fused = dtype != "f32"                                      # its two layers have no steps of their own
         if head_fused:
@@ -234,8 +236,8 @@ def measure_train(torch, B, S, dtype, n, H, W, steps, warmup, first_seed, kernel
                 parts["poolbwd%d_ms" % li] = round(ms, 5)
                 hi, wi = shapes[li][1:]
                 pool_bwd_ms += ms
-                # gradient and winner code of every output in, gradient of every input out (+ its ReLU mask source in)
-                pool_bwd_bytes += n * c * (ho * wo * (esize + 1.0) + hi * wi * 2.0 * esize)
+                # gradient and winner code (which holds the ReLU mask) of every output in, gradient of every input out
+                pool_bwd_bytes += n * c * (ho * wo * (esize + code) + hi * wi * esize)
         ho, wo = shapes[-1][1:]
         # labels in (count pass), logits + labels in and fp32 gradient out (2 classes); 16-bit storage: the gradient is
         # read once more and written as one 16-byte octet per pixel for the layers below
