@@ -135,9 +135,11 @@ sk_status sknet_get_weights(sknet_t *net, int32_t conv_idx, float *w_host, float
  * HIP device (hipMalloc).  pad != 0: the library mirror-pads the image by v so that the output
  * is h x w; pad = 0: the caller's image already contains its context and the output is
  * (h - v) x (w - v).
- * mode 0 = inference: layers may be fused (at present: a trailing "1x1 conv + ReLU, 1x1 conv,
- *          softmax" runs as one kernel whose hidden maps and logits never reach memory; then
- *          sknet_get_activation reports SK_ESTATE for those two layers);
+ * mode 0 = inference: layers may be fused, and the maps between them are then not stored (at present: a trailing
+ *          "1x1 conv + ReLU, 1x1 conv, softmax" runs as one kernel; 16-bit storage: SK pools of kernel 2 run inside
+ *          the layers around them; fp32: the padding, a first 3x3 or 4x4 layer on one map and its SK pool of kernel 2 run as
+ *          one launch, and the pool in front of the head inside it).  sknet_get_activation reports SK_ESTATE for
+ *          layers it cannot hand out; the first layer's and the last pool's maps of fp32 plans it makes again (see there);
  * mode 1 = training: every activation and the pool winners are kept, gradient buffers allocated;
  * mode 2 = inference with every layer's output kept in memory (for parity checks);
  * mode 3 = training as mode 1, but a trailing "1x1 conv + ReLU, 1x1 conv" and the softmax loss (Sections 4.2, 4.3)
@@ -186,7 +188,9 @@ sk_status sknet_sgd_step(sknet_t *net, float lr, float momentum, float weight_de
 /* Debug / parity accessors; each synchronises the stream of the last call first.
  * get_grad: gradients of conv conv_idx as fp32 [f_out][f_in][k][k] and [f_out] (HOST).
  * get_activation: output of layer layer_idx (-1 = the padded image) as fp32 NCHW (HOST), sized
- *   as sknet_infer_shapes reports.
+ *   as sknet_infer_shapes reports, of the last forward pass: weights set since then change nothing.  Where an fp32
+ *   inference plan does not store a layer's maps the layer is run again on its input, with the weights of the pass, into a
+ *   temporary that the call allocates and frees (as it does to widen 16-bit maps).
  * get_pool_argmax: for max-pool number pool_idx (0-based among pools), per output element the
  *   flat offset (y*W_in + x) of the winning input sample inside its input plane, int32 NCHW
  *   (HOST).  Taps are scanned row-major and only a strictly greater value replaces the
@@ -206,7 +210,8 @@ sk_status sknet_get_pool_argmax(sknet_t *net, int32_t pool_idx, int32_t *idx_hos
 /* Number of device steps of the planned forward pass (pad, one per layer or fused group, softmax), a short
  * name for step i copied into name (HOST, at most cap bytes), and the average duration in
  * milliseconds of step i re-run iters times on hip_stream between two HIP events (the step
- * reads the activations the last forward left behind).  For benchmarking. */
+ * reads the activations the last forward left behind; padding, and 16-bit first layers that take the image
+ * themselves, read the image of that pass, which must still be there).  For benchmarking. */
 sk_status sknet_num_steps(const sknet_t *net, int32_t *count);
 sk_status sknet_step_name(const sknet_t *net, int32_t step, char *name, int32_t cap);
 sk_status sknet_time_step(sknet_t *net, int32_t step, int32_t iters, void *hip_stream, float *avg_ms);

@@ -145,7 +145,9 @@ hipError_t launch_k(const C1PoolF32Args &a, hipStream_t stream)
 {
     const long Ho = a.h_pad - KS, w4 = (a.w_pad - KS + 3) / 4;
     const long waves4 = ((Ho + 3) / 4 * w4 + 63) / 64;
-    // four rows a thread compute the fewest edge samples; a small image has too few of them for one wave a SIMD
+    // four rows a thread compute the fewest edge samples; a small image has too few of them for one wave a SIMD.  78 layers (k 3 and 4, 8 to 200
+    // maps, 32 x 40 to 8 x 700^2): two rows 0.76 to 1.0 of four's time below the line up to 48 maps (200 maps: up to 1.14), 0.99 to 1.6
+    // above it (200 maps at 200^2: 0.9); either at most 0.55 of padding, convolution and pool as launches
     if (Ho >= 4 && waves4 * a.n * ((a.c_out + 1) / 2) >= 1024) return launch_t<KS, 4>(a, waves4, stream);
     return launch_t<KS, 2>(a, ((Ho + 1) / 2 * w4 + 63) / 64, stream);
 }
