@@ -667,16 +667,17 @@ hipError_t launch_head1x1_f32(const HeadArgs &a, hipStream_t stream)
 }
 
 // One side at most 48 maps, the other at most 208: 13 of the 14 tiles that two halves of seven hold; beyond, other kernels were not compared.
-bool wgrad1x1_f32_supported(int c_in, int c_out, long plane)
+bool wgrad1x1_f32_supported(int c_in, int c_out, int n, long plane)
 {
     const int hi = std::max(c_in, c_out), lo = std::min(c_in, c_out);
-    return lo >= 1 && lo <= 48 && hi <= 208 && plane <= 0x3ffffffL;         // (offsets inside a tile of 16 maps are 32 bits)
+    return lo >= 1 && lo <= 48 && hi <= 208 && plane <= 0x3ffffffL &&       // (offsets inside a tile of 16 maps are 32 bits)
+           n * ((plane + W1_PX - 1) / W1_PX) <= 0x3fffffffL;
 }
 
 hipError_t launch_wgrad1x1_f32(const float *x, const float *dy, float *scratch, float *bias_part, int n, int c_in, long plane, int c_out,
                                int max_copies, int *copies, hipStream_t stream)
 {
-    if (!wgrad1x1_f32_supported(c_in, c_out, plane) || n < 1 || plane < 1 || max_copies < 1) return hipErrorInvalidValue;
+    if (!wgrad1x1_f32_supported(c_in, c_out, n, plane) || n < 1 || plane < 1 || max_copies < 1) return hipErrorInvalidValue;
     Wgrad1Args a;
     a.swap = c_in > c_out;
     a.r = a.swap ? x : dy;
@@ -687,7 +688,6 @@ hipError_t launch_wgrad1x1_f32(const float *x, const float *dy, float *scratch, 
     a.m_rows = (c_out + 15) / 16 * 16;
     a.ncols = (c_in + 15) / 16 * 16;
     a.per_image = (int)((plane + W1_PX - 1) / W1_PX);
-    if ((long)n * a.per_image > 0x3fffffffL) return hipErrorInvalidValue;
     a.total = n * a.per_image;
     const int rt = (a.cr + 15) / 16, ct = (a.cs + 15) / 16;
     // eight waves a CU (they have the next pixels on the way while they multiply; a second workgroup would double the copies)

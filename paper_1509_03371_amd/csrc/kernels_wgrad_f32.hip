@@ -1660,7 +1660,7 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     const bool rows_path = DT == 0 && x_bstride == 0 && grp_maps == 0 && wgrad_rows_f32_supported(c_in, c_out, k, d) &&
                            (c_in >= 16 || (a.total_segs >= 256 && a.Ho >= 4 * d));
     // 1x1 layers of few maps on one side: both operands straight from memory (84 layers, 12 x 60 to 8 x 512^2: 1.16 to 3.5 times as fast)
-    const bool w1_path = DT == 0 && k == 1 && x_bstride == 0 && grp_maps == 0 && wgrad1x1_f32_supported(c_in, c_out, (long)H * W);
+    const bool w1_path = DT == 0 && k == 1 && x_bstride == 0 && grp_maps == 0 && wgrad1x1_f32_supported(c_in, c_out, n, (long)H * W);
     const bool bias_in_kernel = db && ((h_path && MB <= 4) || rows_path || w1_path);
     if (bias_in_kernel) a.bias_part = bias_part;
     hipError_t e = hipErrorInvalidValue;

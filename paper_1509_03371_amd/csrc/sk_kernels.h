@@ -301,7 +301,7 @@ hipError_t launch_wgrad_rows_f32(const float *x, const float *dy, float *scratch
 
 // 1x1 kernels of at most 48 maps on one side and 208 on the other (kernels_1x1_f32.hip): private copies
 // [16 * ceil(c_out / 16)][16 * ceil(c_in / 16)], else as above
-bool wgrad1x1_f32_supported(int c_in, int c_out, long plane);
+bool wgrad1x1_f32_supported(int c_in, int c_out, int n, long plane);
 hipError_t launch_wgrad1x1_f32(const float *x, const float *dy, float *scratch, float *bias_part, int n, int c_in, long plane, int c_out,
                                int max_copies, int *copies, hipStream_t stream);
 
