@@ -78,7 +78,7 @@ typedef unsigned uint1u __attribute__((aligned(1)));
 // cost more than their bytes (48 maps at 527x527: 36.6 -> 26.4 us with codes = 4.5 TB/s, 32.3 -> 22.6 without).  The last
 // block of a row overlaps its neighbour.
 template <bool TAP, int U>
-__global__ void __launch_bounds__(256) maxpool2_chain_f32_kernel(const float *__restrict__ x, float *__restrict__ y,
+__global__ void __launch_bounds__(512) maxpool2_chain_f32_kernel(const float *__restrict__ x, float *__restrict__ y,
                                                                  uint8_t *__restrict__ tap, int H, int W, int Ho, int Wo,
                                                                  int d, int M, int nseg, int pblocks)
 {
@@ -158,7 +158,7 @@ hipError_t launch_maxpool_f32(const float *x, float *y, uint8_t *tap, int planes
 {
     if (Ho > 65535 || planes > 65535) return hipErrorInvalidValue;
     if (k == 2 && s == 1 && Ho == H - d && Wo == W - d && Wo >= 4) {
-        const PoolCut c = pool_cut(Ho, (Wo + 3) / 4, d, planes, tap ? POOL_WAVES : POOL_WAVES / 4);
+        const PoolCut c = pool_cut(Ho, (Wo + 3) / 4, d, planes, tap ? POOL_WAVES : POOL_WAVES / 4, 512);
         if (c.gy <= 65535) {
             const dim3 grid = c.grid((Wo + 3) / 4, planes);
             if (tap) launch_maxpool2_chain_f32<true>(c, grid, stream, x, y, tap, H, W, Ho, Wo, d);

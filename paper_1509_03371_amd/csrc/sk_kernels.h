@@ -14,8 +14,10 @@ namespace sk {
 // are there: the pools of 48 bf16 maps at 527x527, forward / backward in us, with 1024, 2048, 4096, 8192 waves asked for: 26.6 / 29.2, 16.9 /
 // 17.5, 16.2 / 15.7, 16.3 / 15.8.  Below four windows for fewer waves (short_waves): with winner codes and backward, where a window is some
 // hundred instructions, POOL_WAVES too, without codes a quarter.  A workgroup holds several classes or segments of rows that do not fill it.
+// `most`: threads of a workgroup for rows of 129 to 256 columns, one of which fills 256 badly: the fp32 forward kernel takes 512 (48 maps at
+// 527x527 20.9 -> 18.5 us); its gradient (23.9 -> 25.1) and the 16-bit kernels (128 maps at 332x332 11.6 -> 12.2) do not.
 // 128 pools (8 to 128 maps of 24x24 to 1066x1066, 1 to 8 images, d = 1 to 8, fp32 and bf16) against one window, or input sample, a thread:
-// without codes 0.39 to 1.06 of the time, with codes 0.42 to 1.08, backward 0.14 to 1.08; geometric means 0.79, 0.74, 0.76 (chains of
+// without codes 0.39 to 1.07 of the time, with codes 0.40 to 1.07, backward 0.14 to 1.06; geometric means 0.79, 0.74, 0.75 (chains of
 // four windows and more in workgroups of one segment: backward up to 1.49 on small maps, whose 2.4 us became 3.3).
 struct PoolCut {
     int bx, bp, bs;              // workgroup: columns x residue classes x segments
@@ -25,7 +27,7 @@ struct PoolCut {
     dim3 block() const { return dim3(bx, bp, bs); }
 };
 constexpr long POOL_WAVES = 4096;
-inline PoolCut pool_cut(int Ho, int cols, int d, long planes, long short_waves)
+inline PoolCut pool_cut(int Ho, int cols, int d, long planes, long short_waves, int most = 256)
 {
     PoolCut c{};
     const int links = (Ho + d - 1) / d;
@@ -35,15 +37,15 @@ inline PoolCut pool_cut(int Ho, int cols, int d, long planes, long short_waves)
         if (c.len == 1 || threads() >= 64 * (c.len > 4 ? POOL_WAVES : short_waves)) break;
     }
     // the workgroup whose waves have the fewest idle lanes: whole rows or parts of them, several classes or segments of narrow ones
-    const int wg = threads() >= 32 * POOL_WAVES ? 256 : 64;
+    const int wg = threads() < 32 * POOL_WAVES ? 64 : cols > 128 && cols <= 256 ? most : 256;
     auto up = [](int v, int m) { return (v + m - 1) / m; };
     double best = 0.;
-    for (int most = wg; most >= 64; most /= 2) {
-        const int parts = up(cols, most), bx = up(cols, parts);
+    for (int part = wg; part >= 64; part /= 2) {
+        const int parts = up(cols, part), bx = up(cols, parts);
         for (int classes : {wg / bx, 1}) {
             const int bp = up(d, up(d, std::max(1, std::min(d, classes)))), bs = std::min(c.nseg, std::max(1, wg / (bx * bp))), n = bx * bp * bs;
             const double fill = (double)cols / (parts * bx) * d / (up(d, bp) * bp) * c.nseg / (up(c.nseg, bs) * bs) * n / (up(n, 64) * 64);
-            if (fill > best * (most == wg ? 1.02 : 1.25)) {      // (wide rows in narrow parts: 48 maps of 8 x 1066^2 10 % slower)
+            if (fill > best * (part == wg ? 1.02 : 1.25)) {      // (wide rows in narrow parts: 48 maps of 8 x 1066^2 10 % slower)
                 best = fill;
                 c.bx = bx;
                 c.bp = bp;
