@@ -14,7 +14,8 @@ namespace sk {
 // hipMemcpy into pageable memory runs at 10 to 18 GB/s: one thread copies out of the runtime's staging buffer and takes the page
 // faults of memory that was never touched, while the link (56 GB/s into pinned memory) waits.  Here LANES threads, the caller among them,
 // each take the next piece: link -> own pinned piece -> destination.  An epoch of sixteen U-Net
-// steps that reads its 124 MB of weights at the end: 64.0 -> 53.5 ms, with the up-convolutions put in order on the device instead of here.
+// steps that reads its 124 MB of weights at the end: 64.0 -> 53.5 ms, with the up-convolutions put in order on the device instead of here (how fast
+// such copies are depends on the machine: the same epoch on the old path took 57 to 64 ms on five of them).
 // Owned by a plan (LANES * PIECE = 8 MB of pinned memory, given back with it); used like the rest of the plan by one thread at a time.
 struct HostReader {
     static constexpr int LANES = 4;
