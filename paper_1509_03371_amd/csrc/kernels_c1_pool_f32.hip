@@ -30,14 +30,18 @@ __global__ __launch_bounds__(64) void conv_c1_pool_f32_kernel(C1PoolF32Args a, i
     constexpr int WR = R + KS, WC = KS + 4;              // window: R + 1 rows and 5 columns of outputs
     const int H = a.h_pad, W = a.w_pad, Ho = H - KS, Wo = W - KS;
     const int w4 = (Wo + 3) / 4, rows = (Ho + R - 1) / R;
-    const int idx = blockIdx.x * 64 + threadIdx.x;
-    if (idx >= rows * w4) {
-        if ((int)blockIdx.x * 64 >= rows * w4 && blockIdx.y == 0 && blockIdx.z == 0) {       // the workgroup without samples
-            for (int q = threadIdx.x; q < KS * KS * a.n_pad; q += 64) a.used_w[q] = a.wp[q];
-            for (int q = threadIdx.x; q < a.n_pad; q += 64) a.used_b[q] = a.bias[q];
+    if (blockIdx.x == 0) {               // ahead of the samples: behind them its loads and stores would be the launch's tail
+        if (blockIdx.y == 0 && blockIdx.z == 0) {
+            auto copy = [](const float *from, float *to, int floats) {        // (a multiple of sixteen, at sixteen bytes)
+                for (int q = 4 * threadIdx.x; q < floats; q += 4 * 64) *reinterpret_cast<float4 *>(to + q) = *reinterpret_cast<const float4 *>(from + q);
+            };
+            copy(a.wp, a.used_w, KS * KS * a.n_pad);
+            copy(a.bias, a.used_b, a.n_pad);
         }
         return;
     }
+    const int idx = (blockIdx.x - 1) * 64 + threadIdx.x;
+    if (idx >= rows * w4) return;
     const int rg = idx / w4;
     // the last group of a row or column is moved back inside the map: its samples are written twice, with the same values
     const int x0 = min(4 * (idx - rg * w4), Wo - 4), y0 = min(R * rg, Ho - R), b = blockIdx.z;

@@ -68,7 +68,7 @@ struct sknet {
     int pending_head = 0;
     // fp32 inference plans: padding, first layer and its pool run as one launch (the layer's output is not stored)
     bool c1_pool = false;
-    float *c1_used = nullptr;         // ... and leaves its packed weights here, then its biases: get_activation runs the layer on those of the pass
+    float *c1_used = nullptr;         // ... and leaves its packed weights here (behind act[0]), then its biases: get_activation runs the layer on those of the pass
     int device = 0;                   // of the plan
     int head_pool = 0;                // fp32 inference plans: the fused head takes the maxima of the pool in front of it (its d), whose maps are not stored
     bool kept(int layer) const        // is the output of `layer` in memory in the form the layer defines?
@@ -98,10 +98,11 @@ struct sknet {
         }
         tap.clear();
         free_dev(gbuf[0]); free_dev(gbuf[1]); free_dev(loss_partial); free_dev(wgrad_scratch);
-        free_dev(logits_f32); free_dev(dz_f32); free_dev(head_w1p); free_dev(zero_page); free_dev(c1_used);
+        free_dev(logits_f32); free_dev(dz_f32); free_dev(head_w1p); free_dev(zero_page);
         steps.clear();
         vpool.clear(); pending.clear(); pending_head = 0;
         fuse_head = c1_pool = false;
+        c1_used = nullptr;
         head_pool = 0;
         for (auto &c : convs) release_conv(c);
         planned = forward_done = backward_done = false;
@@ -577,7 +578,15 @@ sk_status sknet_plan(sknet_t *net, int32_t n, int32_t h, int32_t w, int32_t pad,
         if (i >= 2 && net->vpool[i - 2]) continue;    // the output of a pool that runs inside its neighbours
         const bool f32 = (i == 0) ? !half : stored_f32(net, i - 1);
         const long count = f32 ? dims[i].count(n) : octet_floats(n, dims[i]);
-        st = alloc_f(&net->act[i], count);
+        if (i == 0 && net->c1_pool) {
+            // the packed weights and biases of the pass behind the padded image, in the form that alloc_conv gives them below
+            const ConvParams &c = net->convs[0];
+            const long at = (count + 63) / 64 * 64, rows = (long)round_up(c.c_in, 16) * c.k * c.k;
+            st = alloc_f(&net->act[0], at + (rows + 1) * round_up(c.c_out, 16));
+            if (st == SK_OK) net->c1_used = net->act[0] + at;
+        } else {
+            st = alloc_f(&net->act[i], count);
+        }
         if (count > max_count) max_count = count;
     }
     if (st == SK_OK && half && net->layers[L - 1].kind != SK_CONV) st = alloc_f(&net->logits_f32, dims[L].count(n));
@@ -611,15 +620,6 @@ sk_status sknet_plan(sknet_t *net, int32_t n, int32_t h, int32_t w, int32_t pad,
             hipError_t e = sk::launch_pack_head_w1(c1.w_dev, net->head_w1p, net->dtype, c1.c_out, c1.c_in, nullptr);
             if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
             if (e != hipSuccess) st = fail(SK_EDEVICE, "plan: packing the head weights failed: %s", hipGetErrorString(e));
-        }
-    }
-    if (st == SK_OK && net->c1_pool) {
-        const ConvParams &c = net->convs[0];
-        const long floats = (long)(c.rows_fwd + 1) * c.n_pad;       // (the rows of the maps that pad the one map stay zero)
-        st = alloc_f(&net->c1_used, floats);
-        if (st == SK_OK) {
-            hipError_t e = hipMemset(net->c1_used, 0, sizeof(float) * (size_t)floats);
-            if (e != hipSuccess) st = fail(SK_EDEVICE, "plan: clearing a buffer failed: %s", hipGetErrorString(e));
         }
     }
     if (st == SK_OK && training) {
@@ -931,12 +931,19 @@ sk_status sknet_get_activation(sknet_t *net, int32_t layer_idx, float *nchw_host
         SK_HIP(on.status);
         float *tmp = nullptr;
         SK_TRY(alloc_f(&tmp, dm.count(net->n)));
-        sk::ConvF32Args a = conv_args(net->convs[0], net->act[0], net->n, in, l.d, l.relu, tmp, dm);
-        a.wp = net->c1_used;
-        a.bias = net->c1_used + (long)net->convs[0].rows_fwd * net->convs[0].n_pad;
-        hipError_t e = l.kind == SK_CONV ? sk::launch_conv_f32(a, nullptr)
-                                         : sk::launch_maxpool_f32(net->act[layer_idx], tmp, nullptr, net->n * in.c, in.h, in.w, dm.h, dm.w, l.k, l.d, l.s,
-                                                                  nullptr);
+        hipError_t e = hipSuccess;
+        if (l.kind == SK_CONV) {
+            const ConvParams &c = net->convs[0];
+            sk::ConvF32Args a = conv_args(c, net->act[0], net->n, in, l.d, l.relu, tmp, dm);
+            a.wp = net->c1_used;
+            a.bias = net->c1_used + (long)c.rows_fwd * c.n_pad;
+            // the pass leaves the rows of the one map; those of the maps that pad it are zero
+            const long rows = (long)l.k * l.k;
+            if (c.rows_fwd > rows) e = hipMemsetAsync(net->c1_used + rows * c.n_pad, 0, sizeof(float) * (size_t)((c.rows_fwd - rows) * c.n_pad), nullptr);
+            if (e == hipSuccess) e = sk::launch_conv_f32(a, nullptr);
+        } else {
+            e = sk::launch_maxpool_f32(net->act[layer_idx], tmp, nullptr, net->n * in.c, in.h, in.w, dm.h, dm.w, l.k, l.d, l.s, nullptr);
+        }
         if (e == hipSuccess) e = hipMemcpy(nchw_host, tmp, sizeof(float) * dm.count(net->n), hipMemcpyDeviceToHost);
         (void)hipFree(tmp);
         if (e != hipSuccess) return fail(SK_EDEVICE, "get_activation: %s", hipGetErrorString(e));
