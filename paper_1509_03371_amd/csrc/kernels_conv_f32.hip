@@ -18,117 +18,14 @@
 // store instruction writes 64-byte runs of consecutive pixels of one map.
 #include <type_traits>
 
+#include "conv_f32_store.h"
 #include "sk_kernels.h"
+#include "split_f32.h"
 
 namespace sk {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
 constexpr int CONV_TX = 64;   // output columns per workgroup
 constexpr int CONV_CC = 4;    // input maps per K chunk
-
-// Epilogue shared by the kernels below: bias, ReLU, optional ReLU-derivative mask, predicated store.
-// acc[rw][xt][nt][r] belongs to output map o_first + 16*nt + r, row oy_first + rw*d, column
-// ox_first + 16*xt.  The vector memory counter is one in-order queue for loads and stores, so a
-// load awaited between stores makes that wait cover every store before it.  The bias is therefore
-// fetched in one batch and awaited once; the store loop without a mask then contains no load at
-// all, and the masked variant fetches the masks of a whole pixel tile before its first store.
-template <int NT, int RW, int XN = 4>
-__device__ __forceinline__ void store_outputs(const ConvF32Args &a, floatx4 (&acc)[RW][4][NT], int b, int o_first,
-                                              int oy_first, int d, int ox_first)
-{
-    float bia[NT][4];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) bia[nt][r4] = 0.f;
-    if (a.bias) {                                       // uniform branch; the vector holds n_pad entries
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int o = o_first + nt * 16 + r4;
-                bia[nt][r4] = a.bias[o < a.n_pad ? o : a.n_pad - 1];
-            }
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0): the bias is in registers from here on
-    __builtin_amdgcn_sched_barrier(0);
-    const long oplane = (long)a.OH * a.OW;
-    // mode 0: plain store; 1: ReLU-derivative mask; 2: the value already in y is added before bias and ReLU
-    auto store_tiles = [&](auto mode) {
-        constexpr int MODE = decltype(mode)::value;
-#pragma unroll
-        for (int rw = 0; rw < RW; ++rw) {
-            const int oy = oy_first + rw * d;
-            if (oy >= a.Ho) continue;
-            const long rowbase = (((long)b * a.out_maps + a.o_off + o_first) * a.OH + (long)oy * a.oy_mul + a.oy_off) * a.OW + a.ox_off;
-#pragma unroll
-            for (int xt = 0; xt < XN; ++xt) {
-                const int ox = ox_first + xt * 16;
-                if (ox >= a.Wo) continue;
-                const long pbase = rowbase + (long)ox * a.ox_mul;
-                float mk[NT][4];
-                if constexpr (MODE != 0) {
-                    const float *side = MODE == 1 ? a.mask : a.y;
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int r4 = 0; r4 < 4; ++r4) {
-                            // maps beyond c_out are never stored; their mask address is clamped to
-                            // map 0 of the same pixel so that the load stays inside the tensor
-                            const int oo = nt * 16 + r4;
-                            mk[nt][r4] = side[pbase + (o_first + oo < a.c_out ? oo : -o_first) * oplane];
-                        }
-                }
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        const int oo = nt * 16 + r4;
-                        if (o_first + oo >= a.c_out) continue;
-                        float v = acc[rw][xt][nt][r4] + bia[nt][r4];
-                        if constexpr (MODE == 2) v += mk[nt][r4];
-                        if (a.relu) v = v > 0.f ? v : 0.f;
-                        if constexpr (MODE == 1)
-                            if (!(mk[nt][r4] > 0.f)) v = 0.f;
-                        a.y[pbase + oo * oplane] = v;
-                    }
-            }
-        }
-    };
-    // the four taps of an up-convolution stacked as GEMM maps: each 16-map tile belongs to one tap, which
-    // moves its maps back by tap*tap_maps and its pixels to the tap's place in the 2x2 block (no mask here)
-    auto store_taps = [&]() {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int o0 = o_first + nt * 16;
-            const int tap = o0 / a.tap_maps, om = o0 - tap * a.tap_maps;
-#pragma unroll
-            for (int rw = 0; rw < RW; ++rw) {
-                const int oy = oy_first + rw * d;
-                if (oy >= a.Ho) continue;
-                const long rowbase = (((long)b * a.out_maps + a.o_off + om) * a.OH + (long)oy * a.oy_mul + (tap >> 1)) * a.OW + (tap & 1);
-#pragma unroll
-                for (int xt = 0; xt < XN; ++xt) {
-                    const int ox = ox_first + xt * 16;
-                    if (ox >= a.Wo) continue;
-                    const long pbase = rowbase + (long)ox * a.ox_mul;
-#pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) {
-                        if (o0 + r4 >= a.c_out) continue;
-                        float v = acc[rw][xt][nt][r4] + bia[nt][r4];
-                        if (a.relu) v = v > 0.f ? v : 0.f;
-                        a.y[pbase + r4 * oplane] = v;
-                    }
-                }
-            }
-        }
-    };
-    if (a.tap_maps > 0) store_taps();
-    else if (a.mask) store_tiles(std::integral_constant<int, 1>{});
-    else if (a.accumulate) store_tiles(std::integral_constant<int, 2>{});
-    else store_tiles(std::integral_constant<int, 0>{});
-}
 
 template <int NT, int RW>
 __global__ __launch_bounds__(256) void conv_f32_kernel(ConvF32Args a, int tiles_hi, int tiles_lo,
@@ -716,6 +613,7 @@ hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t stream)
         if (a.k == 3) return launch_conv_c1_f32<3>(a, stream);
         if (a.k == 4) return launch_conv_c1_f32<4>(a, stream);
     }
+    if (conv_split_f32_supported(a)) return launch_conv_split_f32(a, stream);
     const int tiles = a.n_pad / 16;
     if (tiles == 1) return launch_conv_f32_nt<1>(a, stream);
     if (tiles == 2) return launch_conv_f32_nt<2>(a, stream);
@@ -731,27 +629,80 @@ hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t stream)
 }
 
 // ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ void pack_weights_f32_body(const float *w, float *wp, int c_out, int c_in, int k,
-                                                      int flip_transpose, int rows, int n_pad)
+// Every layer that launch_conv_split_f32 may be asked to run (conv_split_f32_supported looks at the sizes of the maps too).  With fewer than
+// sixteen input maps the sums are short, and what splitting the operands costs in precision is more than what the fewer roundings of the
+// sums give back: error against 64 bits over that of fp32 operands, 3x3 / 4x4: 8 maps 1.53 / 1.51, 12 maps 1.24 / 1.20, 16 maps 1.00 / 0.96, 48
+// maps 0.93 / 0.92, 512 maps 0.86 / 0.87
+bool conv_split_f32_packed(int k, int gemm_c_in) { return (k == 3 || k == 4) && gemm_c_in >= 16; }
+
+long split_weights_at(int k, int gemm_c_in, int n_pad) { return (long)(gemm_c_in + 15) / 16 * 16 * k * k * n_pad; }
+
+long packed_f32_floats(int k, int gemm_c_in, int n_pad)
 {
+    const long plain = split_weights_at(k, gemm_c_in, n_pad);
+    return plain + (conv_split_f32_packed(k, gemm_c_in) ? (long)((gemm_c_in + 7) / 8) * k * (n_pad / 16) * 512 + SPLIT_TAIL_FLOATS : 0);
+}
+
+// Largest finite magnitude of count weights, in gridDim.x (at most 64) parts
+__device__ __forceinline__ void weight_max_body(const float *w, long count, float *part)
+{
+    __shared__ float wm[4];
+    float m = 0.f;
+    for (long q = blockIdx.x * 256L + threadIdx.x; q < count; q += gridDim.x * 256L) m = fmaxf(m, split_finite(fabsf(w[q])));
+    m = split_wave_max(m);
+    if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
+}
+__global__ __launch_bounds__(256) void weight_max_kernel(const float *w, long count, float *part) { weight_max_body(w, count, part); }
+
+// Both packed forms of a GEMM's weights, from value(m, i, j, o): input map m, tap (i, j), output map o; zero beyond the real extents.
+// First [rows][n_pad] floats, rows (m*k + i)*k + j.  Then, with a tail (see sk_kernels.h, its maxima in place), the fragments of the split
+// convolution: per chunk of eight maps, kernel row and tile of sixteen output maps two parts of [64 lanes][8] fp16, lane l = output map
+// l % 16 of the tile at tap (row, l / 16), the chunk's maps side by side.
+template <class V> __device__ __forceinline__ void pack_f32_forms(float *wp, int k, int gemm_c_in, int rows, int n_pad, float *tail, V value)
+{
+    const long first = blockIdx.x * (long)blockDim.x + threadIdx.x, step = (long)gridDim.x * blockDim.x;
     const long total = (long)rows * n_pad;
-    for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < total; q += (long)gridDim.x * blockDim.x) {
+    for (long q = first; q < total; q += step) {
         const int col = (int)(q % n_pad), row = (int)(q / n_pad);
-        const int j = row % k, i = (row / k) % k, m = row / (k * k);   // m = input map of this GEMM
-        float v = 0.f;
-        if (!flip_transpose) {
-            if (m < c_in && col < c_out) v = w[(((long)col * c_in + m) * k + i) * k + j];
-        } else {
-            if (m < c_out && col < c_in) v = w[(((long)m * c_in + col) * k + (k - 1 - i)) * k + (k - 1 - j)];
-        }
-        wp[q] = v;
+        wp[q] = value(row / (k * k), (row / k) % k, row % k, col);
+    }
+    if (!tail) return;
+    const int se = split_exponent(split_wave_max(tail[threadIdx.x & 63]), 14);
+    if (first == 0) reinterpret_cast<int *>(tail)[64] = se;
+    const float scale = split_pow2(se);
+    uint4v *frag = reinterpret_cast<uint4v *>(wp + total);
+    const int m_tiles = n_pad / 16;
+    const long lanes = (long)((gemm_c_in + 7) / 8) * k * m_tiles * 64;
+    for (long q = first; q < lanes; q += step) {
+        const int lane = (int)(q & 63), tile = (int)((q >> 6) % m_tiles), j = lane >> 4;
+        const long ci = (q >> 6) / m_tiles;
+        const int i = (int)(ci % k), c = (int)(ci / k) * 8, o = tile * 16 + (lane & 15);
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = j < k ? value(c + e, i, j, o) : 0.f;
+        uint4v p[2];
+        split2(v, scale, p);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) frag[((ci * m_tiles + tile) * 2 + s) * 64 + lane] = p[s];
     }
 }
 
-__global__ void pack_weights_f32_kernel(const float *w, float *wp, int c_out, int c_in, int k,
-                                        int flip_transpose, int rows, int n_pad)
+__device__ __forceinline__ void pack_weights_f32_body(const float *w, float *wp, int c_out, int c_in, int k,
+                                                      int flip_transpose, int rows, int n_pad, float *tail)
 {
-    pack_weights_f32_body(w, wp, c_out, c_in, k, flip_transpose, rows, n_pad);
+    const int gemm_c_in = flip_transpose ? c_out : c_in;
+    pack_f32_forms(wp, k, gemm_c_in, rows, n_pad, tail, [=](int m, int i, int j, int col) {
+        if (!flip_transpose) return m < c_in && col < c_out ? w[(((long)col * c_in + m) * k + i) * k + j] : 0.f;
+        return m < c_out && col < c_in ? w[(((long)m * c_in + col) * k + (k - 1 - i)) * k + (k - 1 - j)] : 0.f;
+    });
+}
+
+__global__ void pack_weights_f32_kernel(const float *w, float *wp, int c_out, int c_in, int k,
+                                        int flip_transpose, int rows, int n_pad, float *tail)
+{
+    pack_weights_f32_body(w, wp, c_out, c_in, k, flip_transpose, rows, n_pad, tail);
 }
 
 // Packings of a 3-D kernel W3[c_out][C][k][k][k] (depth, row, column taps) for the 2-D convolution that treats
@@ -761,22 +712,22 @@ __global__ void pack_weights_f32_kernel(const float *w, float *wp, int c_out, in
 //                                                   Wp[((al*c_out + o)*k + i)*k + j][c] = W3[o][c][k-1-a0-al][k-1-i][k-1-j]
 // Rows and columns beyond the real extents are zero.
 __global__ void pack_weights3d_f32_kernel(const float *w3, float *wp, int c_out, int C, int k, int a0, int len, int flip_transpose,
-                                          int rows, int n_pad)
+                                          int rows, int n_pad, float *tail)
 {
-    const long total = (long)rows * n_pad;
-    for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < total; q += (long)gridDim.x * blockDim.x) {
-        const int col = (int)(q % n_pad), row = (int)(q / n_pad);
-        const int j = row % k, i = (row / k) % k, m = row / (k * k);
-        float v = 0.f;
+    pack_f32_forms(wp, k, len * (flip_transpose ? c_out : C), rows, n_pad, tail, [=](int m, int i, int j, int col) {
         if (!flip_transpose) {
             const int al = m / C, c = m - al * C;
-            if (al < len && col < c_out) v = w3[((((long)col * C + c) * k + a0 + al) * k + i) * k + j];
-        } else {
-            const int al = m / c_out, o = m - al * c_out;
-            if (al < len && col < C) v = w3[((((long)o * C + col) * k + (k - 1 - a0 - al)) * k + (k - 1 - i)) * k + (k - 1 - j)];
+            return al < len && col < c_out ? w3[((((long)col * C + c) * k + a0 + al) * k + i) * k + j] : 0.f;
         }
-        wp[q] = v;
-    }
+        const int al = m / c_out, o = m - al * c_out;
+        return al < len && col < C ? w3[((((long)o * C + col) * k + (k - 1 - a0 - al)) * k + (k - 1 - i)) * k + (k - 1 - j)] : 0.f;
+    });
+}
+
+// the tail of packed weights that have the split form, else nullptr
+static float *split_tail(float *wp, int k, int gemm_c_in, int n_pad)
+{
+    return conv_split_f32_packed(k, gemm_c_in) ? wp + packed_f32_floats(k, gemm_c_in, n_pad) - SPLIT_TAIL_FLOATS : nullptr;
 }
 
 hipError_t launch_pack_weights3d_f32(const float *w3, float *wp, int c_out, int C, int k, int a0, int len, int flip_transpose, int rows,
@@ -784,16 +735,23 @@ hipError_t launch_pack_weights3d_f32(const float *w3, float *wp, int c_out, int 
 {
     const long total = (long)rows * n_pad;
     const int blocks = (int)((total + 255) / 256 < 1024 ? (total + 255) / 256 : 1024);
+    float *tail = split_tail(wp, k, len * (flip_transpose ? c_out : C), n_pad);
+    if (tail) hipLaunchKernelGGL(weight_max_kernel, dim3(64), dim3(256), 0, stream, w3, (long)c_out * C * k * k * k, tail);
     hipLaunchKernelGGL(pack_weights3d_f32_kernel, dim3(blocks), dim3(256), 0, stream, w3, wp, c_out, C, k, a0, len, flip_transpose, rows,
-                       n_pad);
+                       n_pad, tail);
     return hipGetLastError();
 }
 
-struct PackF32Jobs { PackF32Job job[BATCH_MAX]; };
+struct PackF32Jobs { PackF32Job job[BATCH_MAX]; float *tail[BATCH_MAX]; };
+__global__ __launch_bounds__(256) void weight_max_batch_kernel(PackF32Jobs b)
+{
+    const PackF32Job &j = b.job[blockIdx.y];
+    if (b.tail[blockIdx.y]) weight_max_body(j.w, (long)j.c_out * j.c_in * j.k * j.k, b.tail[blockIdx.y]);
+}
 __global__ void pack_weights_f32_batch_kernel(PackF32Jobs b)
 {
     const PackF32Job &j = b.job[blockIdx.y];
-    pack_weights_f32_body(j.w, j.wp, j.c_out, j.c_in, j.k, j.flip_transpose, j.rows, j.n_pad);
+    pack_weights_f32_body(j.w, j.wp, j.c_out, j.c_in, j.k, j.flip_transpose, j.rows, j.n_pad, b.tail[blockIdx.y]);
 }
 
 hipError_t launch_pack_weights_f32_batch(const PackF32Job *jobs, int n, hipStream_t stream)
@@ -801,12 +759,16 @@ hipError_t launch_pack_weights_f32_batch(const PackF32Job *jobs, int n, hipStrea
     if (n < 1 || n > BATCH_MAX) return hipErrorInvalidValue;
     PackF32Jobs b;
     long most = 1;
+    bool splits = false;
     for (int t = 0; t < n; ++t) {
         b.job[t] = jobs[t];
+        b.tail[t] = split_tail(jobs[t].wp, jobs[t].k, jobs[t].flip_transpose ? jobs[t].c_out : jobs[t].c_in, jobs[t].n_pad);
+        splits = splits || b.tail[t];
         const long total = (long)jobs[t].rows * jobs[t].n_pad;
         most = total > most ? total : most;
     }
     const int blocks = (int)((most + 255) / 256 < 256 ? (most + 255) / 256 : 256);
+    if (splits) hipLaunchKernelGGL(weight_max_batch_kernel, dim3(64, n), dim3(256), 0, stream, b);
     hipLaunchKernelGGL(pack_weights_f32_batch_kernel, dim3(blocks, n), dim3(256), 0, stream, b);
     return hipGetLastError();
 }
@@ -816,8 +778,10 @@ hipError_t launch_pack_weights_f32(const float *w_oihw, float *wp, int c_out, in
 {
     const long total = (long)rows * n_pad;
     const int blocks = (int)((total + 255) / 256 < 1024 ? (total + 255) / 256 : 1024);
+    float *tail = split_tail(wp, k, flip_transpose ? c_out : c_in, n_pad);
+    if (tail) hipLaunchKernelGGL(weight_max_kernel, dim3(64), dim3(256), 0, stream, w_oihw, (long)c_out * c_in * k * k, tail);
     hipLaunchKernelGGL(pack_weights_f32_kernel, dim3(blocks), dim3(256), 0, stream, w_oihw, wp, c_out,
-                       c_in, k, flip_transpose, rows, n_pad);
+                       c_in, k, flip_transpose, rows, n_pad, tail);
     return hipGetLastError();
 }
 

@@ -1,0 +1,338 @@
+// SK (dilated) convolution for fp32 activations on the 16-bit matrix unit of gfx950: 3x3 and 4x4 layers and their data gradients.
+//
+// The 16-bit unit is sixteen times as fast as its fp32 form.  Samples and weights are pairs of fp16 values (split_f32.h), a product is three
+// MFMAs, so the unit needs 3/16 of the time; memory holds fp32 as before.  A workgroup of four waves owns 16 WX columns of 4 R / WX rows
+// that lie d apart (as in kernels_conv_f32.hip, their kernel rows fall on few input rows).  Per chunk of eight input maps it
+//  - loads its samples into registers while it multiplies the chunk before,
+//  - finds their largest magnitude (one LDS exchange), from which the power of two that scales them follows; where that falls, the sums so
+//    far follow it (they rarely do: three bits of room),
+//  - writes the pairs to LDS as units of one pixel's eight maps: a B operand is 16 pixels x (4 kernel columns x 8 maps), one 16-byte read a
+//    lane, as in the 16-bit convolution; the fourth column of a 3x3 kernel has zero weights,
+//  - multiplies kernel rows in steps of G whose weights are in registers, so that a staged row is read once for G kernel rows.  Weight
+//    fragments come straight into LDS, a step ahead.
+// What bounds it: MFMAs at 0.55 to 0.6 of the matrix unit's time at the 1.9 GHz that the power limit leaves; the rest are the two barriers
+// a chunk and LDS reads.  Two or three workgroups share a CU and fill each other's waits.  48 -> 48 maps, 4x4, us (TFLOP/s) on the fp32
+// matrix unit and here: 537^2 d = 2 202 -> 65 (327), 8 x 1024^2 d = 8 4745 -> 1534 (403); 64 -> 64, 3x3, 566^2 236 -> 84.
+// Tried: three bf16 parts and six products (exact parts, no scale) 537^2 113 us, its sums rounded six times a step 1.2 times as far off as
+// fp32 operands; products of a step summed apart and added by the vector unit: half the error, 14 % more time; both staged chunks in LDS: no gain.
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+#include "conv_f32_store.h"
+#include "lds_dma.h"
+#include "sk_kernels.h"
+#include "split_f32.h"
+
+namespace sk {
+
+namespace {
+
+// KS x KS kernels; MT tiles of sixteen output maps; a wave owns R output rows of sixteen columns, WX waves lie side by side and 4 / WX one
+// above the other; PITCH: staged columns
+template <int KS, int MT, int R, int WX, int PITCH> struct SplitTile {
+    static constexpr int TX = 16 * WX, RT = R * (4 / WX);    // output columns and rows of a tile
+    static constexpr int RR = RT + KS - 1;                   // staged rows
+    static constexpr int G = KS == 4 ? 2 : KS;               // kernel rows of a step, whose weights are in registers together
+    static constexpr int STEPS = KS / G;
+    static constexpr int PLANE = RR * PITCH;                 // 16-byte units of one staged part
+    static constexpr int UPT = (PLANE + 255) / 256;          // units a thread stages
+    static constexpr int WSTEP = G * MT * 2 * 1024;          // bytes of a step's weight fragments
+    static constexpr size_t SMEM = (size_t)2 * PLANE * 16 + 2 * WSTEP + 64;
+    static_assert(KS % G == 0, "whole steps");
+};
+
+template <int KS, int MT, int R, int WX, int PITCH, bool PADZ>
+__global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, const unsigned char *wsp, const int *wexp, int m_tiles, int tiles_hi,
+                                                                int tiles_lo, int rem, int nblocks, int gx, int gy, int total, int per_xcd)
+{
+    using T = SplitTile<KS, MT, R, WX, PITCH>;
+    constexpr int RR = T::RR, G = T::G, STEPS = T::STEPS, UPT = T::UPT, PLANE = T::PLANE;
+    extern __shared__ unsigned char smem[];
+    unsigned char *xs = smem, *ws = smem + 2 * PLANE * 16;
+    float *most = reinterpret_cast<float *>(ws + 2 * T::WSTEP);      // [2][4]: largest magnitude that each wave stages, by chunk; [8..]: the rare path's
+    const int d = a.d, pw = T::TX + (KS - 1) * d, units = RR * pw;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wx = wave % WX, wy = wave / WX;
+
+    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (tile >= total) return;
+    const int bx = tile % gx, byz = tile / gx;
+    const int by = byz % gy, bz = byz / gy;
+    int py, ty;
+    if (by < rem * tiles_hi) {
+        py = by / tiles_hi;
+        ty = by - py * tiles_hi;
+    } else {
+        const int b2 = by - rem * tiles_hi;
+        py = rem + b2 / tiles_lo;
+        ty = b2 % tiles_lo;
+    }
+    const int b = bz / nblocks, nb = bz - b * nblocks;
+    const int x0 = bx * T::TX, tile0 = nb * MT;
+
+    floatx4 acc[R][1][MT];
+#pragma unroll
+    for (int y = 0; y < R; ++y)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[y][0][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const long plane = (long)a.H * a.W;
+    const float *xb = a.x + (long)b * (a.x_bstride ? a.x_bstride : (long)a.c_in * plane);
+    const int nchunks = (a.c_in + 7) / 8;
+
+    // the units (pixel, eight maps) that this thread stages: byte offset inside a map, LDS address, whether the pixel lies in the image
+    unsigned off[UPT];
+    int dst[UPT];
+    bool ok[UPT];
+#pragma unroll
+    for (int q = 0; q < UPT; ++q) {
+        const int u = min(tid + 256 * q, units - 1);
+        const int t = u / pw, c = u - t * pw;
+        int iy = py + d * (ty * T::RT + t) - a.in_off, ix = x0 + c - a.in_off;
+        ok[q] = iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
+        iy = min(max(iy, 0), a.H - 1);
+        ix = min(max(ix, 0), a.W - 1);
+        off[q] = 4u * (unsigned)(iy * a.W + ix);
+        dst[q] = (t * PITCH + c) * 16;
+    }
+    const int grp_chunks = a.grp_maps > 0 ? a.grp_maps / 8 : 0x7fffffff;
+    int pf_left = grp_chunks;
+    long pf_skip = 0;
+    float xr[UPT][8];
+    auto prefetch = [&](int chunk) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const char *src = reinterpret_cast<const char *>(xb + pf_skip + (long)min(chunk * 8 + e, a.c_in - 1) * plane);
+#pragma unroll
+            for (int q = 0; q < UPT; ++q) xr[q][e] = *reinterpret_cast<const float *>(src + off[q]);
+        }
+        if (--pf_left == 0) {
+            pf_left = grp_chunks;
+            pf_skip += a.grp_skip;
+        }
+    };
+    // the scale of the sums: 2^(se + the weights'); it falls where larger samples come
+    int se = SPLIT_MOST;
+    auto measure = [&](int chunk) {
+        float m = 0.f;
+#pragma unroll
+        for (int q = 0; q < UPT; ++q)
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) m = fmaxf(fmaxf(fabsf(xr[q][e]), fabsf(xr[q][e + 1])), m);
+        m = split_wave_max(m);
+        if (lane == 0) most[(chunk & 1) * 4 + wave] = m;
+    };
+    auto commit = [&](int chunk) {
+        const floatx4 m4 = *reinterpret_cast<const floatx4 *>(most + (chunk & 1) * 4);
+        float m = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
+        m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
+        if (__builtin_bit_cast(unsigned, m) == 0x7f800000u) {            // infinities don't decide the scale of the finite samples beside them
+            float f = 0.f;
+            for (int q = 0; q < UPT; ++q)
+                for (int e = 0; e < 8; ++e) f = fmaxf(f, split_finite(fabsf(xr[q][e])));
+            f = split_wave_max(f);
+            if (lane == 0) most[8 + wave] = f;
+            __syncthreads();
+            m = fmaxf(fmaxf(most[8], most[9]), fmaxf(most[10], most[11]));
+            m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
+            __syncthreads();
+        }
+        const int need = split_exponent(m, 15);
+        if (need < se) {
+            const int to = split_exponent(m, 12);                        // three bits of room: neighbouring chunks don't ask again
+            if (chunk > 0) {
+                const float f = to - se < -126 ? 0.f : split_pow2(to - se);
+#pragma unroll
+                for (int y = 0; y < R; ++y)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) acc[y][0][mt] *= f;
+            }
+            se = to;
+        }
+        const float scale = split_pow2(se);
+#pragma unroll
+        for (int q = 0; q < UPT; ++q) {
+            if (256 * q + 255 >= RR * (T::TX + KS - 1) && tid + 256 * q >= units) continue;
+            uint4v p[2];
+            split2(xr[q], scale, p);
+            if constexpr (PADZ)
+                if (!ok[q]) p[0] = p[1] = uint4v{0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < 2; ++s) *reinterpret_cast<uint4v *>(xs + s * PLANE * 16 + dst[q]) = p[s];
+        }
+    };
+    // fragments [chunk][kernel row][map tile][part] of 1 KB; a step's stand in LDS as [kernel row][MT][part]
+    auto load_weights = [&](int chunk, int step, int buf) {
+        const unsigned char *src = wsp + (long)(chunk * KS + step * G) * m_tiles * 2048 + lane * 16;
+#pragma unroll
+        for (int f = 0; f < G * MT * 2; f += 4) {
+            const int fw = f + wave;
+            if (G * MT * 2 % 4 == 0 || fw < G * MT * 2) {
+                const int i = fw / (MT * 2), m = min(tile0 + fw / 2 % MT, m_tiles - 1);
+                lds_dma16(src + ((i * m_tiles + m) * 2 + (fw & 1)) * 1024, ws + buf * T::WSTEP + fw * 1024);
+            }
+        }
+    };
+    const bool idle = x0 + wx * 16 >= a.Wo;                   // this wave's columns lie right of the image
+    const unsigned char *xp = xs + (wy * R * PITCH + wx * 16 + l16 + min(g, KS - 1) * d) * 16;     // the column behind a 3x3 kernel meets zero weights
+
+    load_weights(0, 0, 0);
+    prefetch(0);
+    measure(0);
+    for (int chunk = 0; chunk < nchunks; ++chunk) {
+        const bool more = chunk + 1 < nchunks;
+        wide_barrier();                                       // every wave is done with the staged maps and has measured its share of the next
+        commit(chunk);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            // the step's weights have arrived: behind them only the loads of the next chunk's maps may be under way
+            if (s == 1 && more) wide_wait<8 * UPT>();
+            else wide_wait<0>();
+            wide_barrier();
+            const int buf = (STEPS & 1) ? ((chunk + s) & 1) : (s & 1);
+            if (s + 1 < STEPS) load_weights(chunk, s + 1, buf ^ 1);
+            else if (more) load_weights(chunk + 1, 0, buf ^ 1);
+            if (s == 0 && more) prefetch(chunk + 1);
+            if (!idle) {
+                const unsigned char *wb = ws + buf * T::WSTEP + lane * 16, *xq = xp + s * G * PITCH * 16;
+                uint4v A[G][MT][2], B[2][2];
+                auto fetch = [&](int r) {
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) B[r & 1][p] = *reinterpret_cast<const uint4v *>(xq + (p * PLANE + r * PITCH) * 16);
+                };
+                fetch(0);
+#pragma unroll
+                for (int i = 0; i < G; ++i)
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) A[i][m][p] = *reinterpret_cast<const uint4v *>(wb + ((i * MT + m) * 2 + p) * 1024);
+#pragma unroll
+                for (int r = 0; r < R + G - 1; ++r) {             // staged row r is kernel row i of output row r - i
+                    if (r + 1 < R + G - 1) fetch(r + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};     // the small products first
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+#pragma unroll
+                        for (int i = 0; i < G; ++i) {
+                            const int y = r - i;
+                            if (y < 0 || y >= R) continue;
+#pragma unroll
+                            for (int m = 0; m < MT; ++m) acc[y][0][m] = split_mfma(A[i][m][PA[q]], B[r & 1][PB[q]], acc[y][0][m]);
+                        }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        if (more) measure(chunk + 1);
+    }
+    if (idle) return;
+    const int down = -(se + *wexp);
+#pragma unroll
+    for (int y = 0; y < R; ++y)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) acc[y][0][m][r4] = __builtin_ldexpf(acc[y][0][m][r4], down);
+    store_outputs<MT, R, 1, 1>(a, acc, b, tile0 * 16 + 4 * g, py + d * (ty * T::RT + wy * R), d, x0 + wx * 16 + l16);
+}
+
+template <int KS, int MT, int R, int WX, int PITCH, bool PADZ>
+hipError_t launch_split_t(const ConvF32Args &a, hipStream_t stream)
+{
+    using T = SplitTile<KS, MT, R, WX, PITCH>;
+    static_assert(T::SMEM <= 81920, "two workgroups share a CU");
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&conv_split_f32_kernel<KS, MT, R, WX, PITCH, PADZ>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::SMEM);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const int q = a.Ho / a.d, rem = a.Ho % a.d;
+    const int tiles_hi = (q + 1 + T::RT - 1) / T::RT, tiles_lo = (q + T::RT - 1) / T::RT;
+    const long gy = (long)rem * tiles_hi + (long)(a.d - rem) * tiles_lo;
+    const int m_tiles = a.n_pad / 16, nblocks = (m_tiles + MT - 1) / MT, gx = (a.Wo + T::TX - 1) / T::TX;
+    const long total = gx * gy * a.n * nblocks;
+    if (total <= 0 || total > 0x7ffffff0L) return hipErrorInvalidValue;
+    const int per_xcd = (int)((total + 7) / 8);
+    hipLaunchKernelGGL((conv_split_f32_kernel<KS, MT, R, WX, PITCH, PADZ>), dim3(per_xcd * 8), dim3(256), T::SMEM, stream, a,
+                       reinterpret_cast<const unsigned char *>(a.wp + split_weights_at(KS, a.c_in, a.n_pad)),
+                       reinterpret_cast<const int *>(a.wp + packed_f32_floats(KS, a.c_in, a.n_pad) - SPLIT_TAIL_FLOATS + 64), m_tiles, tiles_hi,
+                       tiles_lo > 0 ? tiles_lo : 1, rem, nblocks, gx, (int)gy, (int)total, per_xcd);
+    return hipGetLastError();
+}
+
+template <int KS, int MT, int R, int WX, bool PADZ> hipError_t launch_split_d(const ConvF32Args &a, hipStream_t stream)
+{
+    constexpr int TX = 16 * WX;
+    const int halo = (KS - 1) * a.d;
+    if (halo <= 8) return launch_split_t<KS, MT, R, WX, TX + 8, PADZ>(a, stream);
+    if (halo <= 16) return launch_split_t<KS, MT, R, WX, TX + 16, PADZ>(a, stream);
+    return launch_split_t<KS, MT, R, WX, TX + 24, PADZ>(a, stream);
+}
+
+template <int KS, int MT, int R, int WX> hipError_t launch_split_p(const ConvF32Args &a, hipStream_t stream)
+{
+    if (a.in_off != 0) return launch_split_d<KS, MT, R, WX, true>(a, stream);
+    return launch_split_d<KS, MT, R, WX, false>(a, stream);
+}
+
+// What a tile costs, in us: a launch takes about chunks * max(lat * rounds of resident workgroups, work * tiles per CU) + over * tiles per
+// CU (+ 4).  Fitted to 181 layers of 8 to 1024 -> 16 to 512 maps on 20 x 24 to 3 x 430 x 560, d = 1 to 8 (6 to 8 % rms); the tile it picks is on
+// average 0.9 % and at most 10 % slower than the fastest of these, and 1.2 to 4.9 times as fast as the fp32 matrix unit.
+struct SplitCost {
+    int mt, r, wx, slots;             // as SplitTile; workgroups resident on a CU
+    float lat, work, over;
+};
+constexpr SplitCost SPLIT_COST3[] = {{2, 8, 4, 4, 2.31f, 1.47f, 3.43f}, {2, 6, 4, 3, 1.99f, 1.20f, 2.22f}, {2, 4, 2, 3, 1.58f, 0.90f, 1.24f},
+                                     {1, 4, 4, 3, 1.31f, 0.55f, 1.12f}, {1, 4, 2, 4, 1.20f, 0.64f, 0.79f}, {3, 5, 4, 2, 2.28f, 1.43f, 3.66f},
+                                     {3, 4, 2, 3, 2.00f, 1.24f, 1.98f}};
+constexpr SplitCost SPLIT_COST4[] = {{2, 8, 4, 2, 2.87f, 2.04f, 3.12f}, {2, 6, 4, 3, 2.43f, 1.59f, 2.05f}, {2, 4, 2, 3, 1.92f, 1.20f, 1.10f},
+                                     {1, 4, 4, 2, 1.38f, 0.75f, 0.79f}, {1, 4, 2, 2, 1.38f, 0.80f, 0.66f}, {3, 5, 4, 3, 2.79f, 2.01f, 1.68f},
+                                     {3, 4, 2, 3, 2.40f, 1.65f, 1.79f}};
+
+double split_cost(const ConvF32Args &a, const SplitCost &c)
+{
+    const long tx = 16 * c.wx, rt = c.r * (4 / c.wx), q = a.Ho / a.d, rem = a.Ho % a.d;
+    const long gy = rem * ((q + rt) / rt) + (a.d - rem) * ((q + rt - 1) / rt);
+    const double tiles = (double)((a.Wo + tx - 1) / tx) * gy * a.n * ((a.n_pad / 16 + c.mt - 1) / c.mt);
+    const double per_cu = std::ceil(tiles / 256), rounds = std::ceil(tiles / (256 * c.slots));
+    return (a.c_in + 7) / 8 * std::max(c.lat * rounds, c.work * per_cu) + c.over * per_cu;
+}
+
+template <int KS> hipError_t launch_ks(const ConvF32Args &a, hipStream_t stream)
+{
+    const SplitCost *cost = KS == 3 ? SPLIT_COST3 : SPLIT_COST4;
+    int best = 0;
+    for (int t = 1; t < 7; ++t)
+        if (split_cost(a, cost[t]) < split_cost(a, cost[best])) best = t;
+    switch (best) {
+    case 0: return launch_split_p<KS, 2, 8, 4>(a, stream);
+    case 1: return launch_split_p<KS, 2, 6, 4>(a, stream);
+    case 2: return launch_split_p<KS, 2, 4, 2>(a, stream);
+    case 3: return launch_split_p<KS, 1, 4, 4>(a, stream);
+    case 4: return launch_split_p<KS, 1, 4, 2>(a, stream);
+    case 5: return launch_split_p<KS, 3, 5, 4>(a, stream);
+    default: return launch_split_p<KS, 3, 4, 2>(a, stream);
+    }
+}
+
+}  // namespace
+
+// 3x3 layers of so few pixels are faster on the fp32 matrix unit (64 -> 64 on 20 x 24 12.7 us against 13.9; on 40 x 36 17.3 against 14.3)
+bool conv_split_f32_supported(const ConvF32Args &a)
+{
+    return conv_split_f32_packed(a.k, a.c_in) && (a.k - 1) * a.d <= 24 && (long)a.H * a.W < (1L << 29) &&
+           (a.k == 4 || (long)a.n * a.Ho * a.Wo >= 1000) &&
+           (a.grp_maps == 0 || (a.grp_maps > 0 && a.grp_maps % 8 == 0 && a.c_in % a.grp_maps == 0 && a.grp_skip >= 0));
+}
+
+hipError_t launch_conv_split_f32(const ConvF32Args &a, hipStream_t stream)
+{
+    return a.k == 3 ? launch_ks<3>(a, stream) : launch_ks<4>(a, stream);
+}
+
+}  // namespace sk

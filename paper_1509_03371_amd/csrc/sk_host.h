@@ -120,8 +120,8 @@ inline sk_status alloc_conv(ConvParams &c, bool training, int dtype = SK_F32)
     SK_TRY(alloc_f(&c.w_dev, c.wcount()));
     SK_TRY(alloc_f(&c.b_dev, c.n_pad));
     if (dtype == SK_F32) {
-        SK_TRY(alloc_f(&c.wp_fwd, (long)c.rows_fwd * c.n_pad));
-        if (training) SK_TRY(alloc_f(&c.wp_bwd, (long)c.rows_bwd * c.n_pad_bwd));
+        SK_TRY(alloc_f(&c.wp_fwd, sk::packed_f32_floats(c.k, c.c_in, c.n_pad)));
+        if (training) SK_TRY(alloc_f(&c.wp_bwd, sk::packed_f32_floats(c.k, c.c_out, c.n_pad_bwd)));
     } else {   // 16-bit elements, allocated in floats
         SK_TRY(alloc_f(&c.wp16_fwd, (sk::packed_h_elems(c.c_out, (c.c_in + 7) / 8, c.k, c.mt16) + 1) / 2));
         if (training) SK_TRY(alloc_f(&c.wp16_bwd, (sk::packed_h_elems(c.c_in, (c.c_out + 7) / 8, c.k, c.mt16_bwd) + 1) / 2));

@@ -139,11 +139,11 @@ sk_status alloc_conv3(Conv3 &c, bool training, bool needs_dgrad, bool half)
     c.n_pad_bwd = round_up(c.c_in, 16);
     SK_TRY(alloc_f(&c.w_dev, c.wcount()));
     SK_TRY(alloc_f(&c.b_dev, c.n_pad));
-    for (auto &r : c.fwd) SK_TRY(alloc_f(&r.wp, (long)r.rows * c.n_pad));
+    for (auto &r : c.fwd) SK_TRY(alloc_f(&r.wp, sk::packed_f32_floats(c.k, r.len * c.c_in, c.n_pad)));
     if (training) {
         if (needs_dgrad) {
             c.bwd = make_runs(c.k, c.d, c.c_out);
-            for (auto &r : c.bwd) SK_TRY(alloc_f(&r.wp, (long)r.rows * c.n_pad_bwd));
+            for (auto &r : c.bwd) SK_TRY(alloc_f(&r.wp, sk::packed_f32_floats(c.k, r.len * c.c_out, c.n_pad_bwd)));
         }
         SK_TRY(alloc_f(&c.dw, c.wcount()));
         SK_TRY(alloc_f(&c.db, c.c_out));

@@ -1,0 +1,120 @@
+"""GPU parity of the fp32 3x3 and 4x4 convolutions on the 16-bit matrix unit: every tile shape, ragged tiles, maps and map groups, kernel
+strides up to the widest they take (a halo of 24; one more stays on the fp32 matrix unit), zero borders and ReLU masks of the data gradient,
+samples and weights of any magnitude.
+
+A value is a pair of fp16 values to 2^-23 of its magnitude, of three products the fourth partial one is below 2^-22, so a product is within
+2^-21 and the fp32 sum of K products within (K + 8) * 2^-24 of the sum of magnitudes; values far below the largest of their tile are within 2^-40
+of that."""
+import numpy as np
+import pytest
+import torch
+
+import sk_synth as S
+from oracle import layers as OL
+
+pytestmark = pytest.mark.gpu
+
+
+def forward(k, d, img, w0, b0, relu=True):
+    from paper_1509_03371_amd import binding as B
+    n, c_in, h, w = img.shape
+    c_out = w0.shape[0]
+    net = B.SKNet([S.conv(c_out, k, d, relu=relu), S.conv(2, 1, 1, relu=False)], c_in, 2)
+    net.set_weights(0, w0, b0)
+    net.set_weights(1, np.ones((2, c_out, 1, 1), np.float32), np.zeros(2, np.float32))
+    net.plan(n, h, w, pad=False, keep=True)
+    net.forward(torch.from_numpy(img).cuda())
+    out = net.get_activation(0)
+    net.close()
+    return out
+
+
+def check(k, d, img, w0, b0):
+    got = forward(k, d, img, w0, b0)
+    ref, size = OL.conv_sk(img, w0, b0, d, relu=True), OL.conv_sk(np.abs(img), np.abs(w0), np.abs(b0), d)
+    products = k * k * img.shape[1]
+    floor = products * 2.0 ** -40 * (np.abs(img).max() * np.abs(w0).max(axis=(1, 2, 3)) + np.abs(w0).max() * np.abs(img).max())
+    assert np.all(np.abs(got - ref) <= (products + 9) * 2.0 ** -24 * size + floor[None, :, None, None] + 1e-44)
+
+
+@pytest.mark.parametrize("k,d,c_in,c_out,n,h,w", [
+    (4, 1, 16, 16, 1, 4, 4), (4, 1, 17, 20, 2, 23, 70), (4, 2, 24, 48, 1, 150, 165), (4, 8, 48, 48, 1, 90, 97), (4, 9, 16, 48, 1, 60, 60),
+    (4, 4, 40, 96, 1, 140, 141), (4, 3, 16, 33, 4, 160, 150), (4, 1, 16, 130, 1, 67, 66), (4, 5, 31, 64, 1, 260, 270), (4, 1, 48, 48, 1, 515, 530),
+    (3, 1, 16, 16, 1, 34, 36), (3, 1, 16, 16, 1, 10, 12), (3, 2, 20, 50, 2, 45, 71), (3, 12, 16, 32, 1, 80, 77), (3, 13, 16, 32, 1, 80, 77),
+    (3, 4, 64, 96, 1, 100, 131), (3, 1, 64, 64, 1, 300, 290), (3, 1, 24, 144, 1, 142, 130), (3, 6, 33, 48, 3, 160, 170), (3, 1, 128, 128, 1, 68, 66),
+])
+def test_forward(k, d, c_in, c_out, n, h, w):
+    rng = np.random.default_rng(h * w + c_in)
+    img = rng.standard_normal((n, c_in, h, w)).astype(np.float32)
+    w0, b0 = rng.standard_normal((c_out, c_in, k, k)).astype(np.float32), rng.standard_normal(c_out).astype(np.float32)
+    check(k, d, img, w0, b0)
+
+
+@pytest.mark.parametrize("case", ["tiny", "huge", "rising", "falling", "zero chunk", "bright corner", "small weights", "large weights"])
+def test_magnitudes(case):
+    rng = np.random.default_rng(5)
+    img = rng.standard_normal((1, 40, 70, 130)).astype(np.float32)
+    w0 = rng.standard_normal((48, 40, 4, 4)).astype(np.float32)
+    steps = np.float32(2.0) ** np.repeat(np.arange(-16, 17, 8), 8).astype(np.float32)[None, :, None, None]
+    if case == "tiny":
+        img *= np.float32(1e-30)
+    elif case == "huge":
+        img *= np.float32(1e30)
+    elif case == "rising":                                  # the scale of the sums falls from chunk to chunk
+        img *= steps
+    elif case == "falling":
+        img *= steps[:, ::-1]
+    elif case == "zero chunk":
+        img[:, :8] = 0
+        img[:, 16:24] = 0
+    elif case == "bright corner":
+        img[:, 3, :9, :9] *= np.float32(1e6)
+    elif case == "small weights":
+        w0 *= np.float32(1e-25)
+    else:
+        w0 *= np.float32(1e20)
+    check(4, 2, img, w0, np.zeros(48, np.float32))
+
+
+def test_infinities_and_nan_stay_where_they_are():
+    rng = np.random.default_rng(6)
+    img = rng.standard_normal((1, 16, 60, 120)).astype(np.float32)
+    w0 = rng.standard_normal((48, 16, 4, 4)).astype(np.float32)
+    clean = forward(4, 1, img, w0, np.zeros(48, np.float32), relu=False)
+    bad = img.copy()
+    bad[0, 2, 20, 30] = np.inf
+    bad[0, 9, 40, 90] = np.nan
+    got = forward(4, 1, bad, w0, np.zeros(48, np.float32), relu=False)
+    hit = np.zeros(clean.shape, bool)
+    hit[:, :, 17:21, 27:31] = True
+    hit[:, :, 37:41, 87:91] = True
+    assert not np.isfinite(got[hit]).any()
+    size = OL.conv_sk(np.abs(img), np.abs(w0), np.zeros(48), 1)
+    assert np.all(np.abs(got - clean)[~hit] <= 2 * (256 + 9) * 2.0 ** -24 * size[~hit])
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("k,d,maps,classes,n,h,w", [
+    (4, 1, 8, 16, 2, 19, 71), (4, 2, 20, 17, 1, 47, 66), (4, 8, 48, 48, 1, 70, 131), (4, 9, 16, 16, 1, 70, 80), (3, 1, 40, 32, 1, 40, 131),
+    (3, 12, 48, 16, 1, 85, 90), (3, 4, 64, 20, 1, 60, 64), (3, 2, 130, 16, 1, 40, 70),
+])
+def test_data_gradient(k, d, maps, classes, n, h, w, relu):
+    from paper_1509_03371_amd import binding as B
+    rng = np.random.default_rng(h + w)
+    w1 = rng.standard_normal((classes, maps, k, k)).astype(np.float32) * np.float32(0.2)
+    net = B.SKNet([S.conv(maps, 1, 1, relu=relu), S.conv(classes, k, d, relu=False)], 2, classes)
+    net.set_weights(0, rng.standard_normal((maps, 2, 1, 1)).astype(np.float32), rng.standard_normal(maps).astype(np.float32))
+    net.set_weights(1, w1, np.zeros(classes, np.float32))
+    net.plan(n, h, w, pad=False, training=True)
+    prob = net.forward(torch.from_numpy(rng.standard_normal((n, 2, h, w)).astype(np.float32)).cuda()).cpu().numpy().astype(np.float64)
+    labels = rng.integers(-1, classes, (n,) + prob.shape[2:]).astype(np.int32)
+    got = net.get_activation_grad(0, torch.from_numpy(labels).cuda())
+    kept = labels >= 0
+    dz = (prob - np.eye(classes)[np.maximum(labels, 0)].transpose(0, 3, 1, 2)) * kept[:, None] / max(1, kept.sum())
+    ref, size = OL.conv_sk_bwd_data(dz, w1, d, (h, w)), OL.conv_sk_bwd_data(np.abs(dz), np.abs(w1), d, (h, w))
+    if relu:
+        ref = ref * (net.get_activation(0) > 0)
+    products = k * k * classes
+    bound = (products + 9) * 2.0 ** -24 * size + 1e-6 / max(1, kept.sum()) * np.abs(w1).sum(axis=(0, 2, 3))[None, :, None, None]
+    assert np.abs(ref).max() > 1e-6 and np.all(np.abs(got - ref) <= bound)
+    net.close()
