@@ -10,21 +10,25 @@
 //    lane, as in the 16-bit convolution; the fourth column of a 3x3 kernel has zero weights,
 //  - multiplies kernel rows in steps of G whose weights are in registers, so that a staged row is read once for G kernel rows.  Weight
 //    fragments come straight into LDS, a step ahead.
-// What bounds it: MFMAs at 0.55 to 0.6 of the matrix unit's time at the 1.9 GHz that the power limit leaves; the rest are the two barriers
-// a chunk and LDS reads.  Two or three workgroups share a CU and fill each other's waits.  48 -> 48 maps, 4x4, us (TFLOP/s) on the fp32
-// matrix unit and here: 537^2 d = 2 202 -> 65 (327), 8 x 1024^2 d = 8 4745 -> 1534 (403); 64 -> 64, 3x3, 566^2 236 -> 84.
+// What bounds it: power.  MFMAs take 0.7 of the matrix unit's time at the 1.7 GHz that is left of 2.4 (8 x 1024^2); the rest are the two
+// barriers a chunk, LDS reads and 0.7 other vector instructions an MFMA.  Two or three workgroups share a CU and fill each other's waits.
+// 48 -> 48 maps, 4x4, us (TFLOP/s) on the fp32 matrix unit and here: 537^2 d = 2 202 -> 59 (360), 8 x 1024^2 d = 8 4745 -> 1421 (435); 64 -> 64, 3x3,
+// 566^2 236 -> 76.
 // Tried: three bf16 parts and six products (exact parts, no scale) 537^2 113 us, its sums rounded six times a step 1.2 times as far off as
-// fp32 operands; products of a step summed apart and added by the vector unit: half the error, 14 % more time; both staged chunks in LDS: no gain.
+// fp32 operands; products of a step summed apart and added by the vector unit: half the error, 14 % more time; both staged chunks in LDS: no
+// gain; four pixels a load: a tenth slower (bank conflicts of the writes); 64-bit addresses in loads and stores, which were as many vector
+// instructions as all others: 65 us.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
 
-#include "conv_f32_store.h"
 #include "lds_dma.h"
 #include "sk_kernels.h"
 #include "split_f32.h"
 
 namespace sk {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -41,6 +45,67 @@ template <int KS, int MT, int R, int WX, int PITCH> struct SplitTile {
     static constexpr size_t SMEM = (size_t)2 * PLANE * 16 + 2 * WSTEP + 64;
     static_assert(KS % G == 0, "whole steps");
 };
+
+// base + a 32-bit offset of the lane + one of the wave: no vector arithmetic, where a pointer costs a 64-bit addition per access.  What lies at
+// SPLIT_NOWHERE is not read or written
+constexpr unsigned SPLIT_NOWHERE = 0xfffffff0u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t split_rsrc(const void *base)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, SPLIT_NOWHERE, 0x00027000);
+}
+
+// acc * 2^down, bias, ReLU and stores of R rows d apart from oy on, lane column ox, maps o_first + 4 g ..  MODE 1: where the mask is positive;
+// 2: added to what y holds.  Masks and old values are read ahead of the first store (one queue holds loads and stores).
+template <int MT, int R, int MODE>
+__device__ __forceinline__ void split_store(const ConvF32Args &a, const floatx4 (&acc)[R][MT], int down, int b, int o_first, int oy, int ox, int g)
+{
+    const long oplane = (long)a.OH * a.OW;                         // below 2^26: offsets inside sixteen maps are 32-bit
+    const long first = ((long)b * a.out_maps + a.o_off + o_first) * oplane;
+    unsigned at[MT][4];
+    float bia[MT][4];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const int o = o_first + 16 * m + 4 * g + r4;
+            at[m][r4] = ox < a.Wo && o < a.c_out ? 4u * ((unsigned)(4 * g + r4) * (unsigned)oplane + (unsigned)(ox * a.ox_mul + a.ox_off)) : SPLIT_NOWHERE;
+            bia[m][r4] = a.bias ? a.bias[min(o, a.n_pad - 1)] : 0.f;
+        }
+    const auto row = [&](int y) { return 4u * (unsigned)(((oy + y * a.d) * a.oy_mul + a.oy_off) * a.OW); };
+    float old[R][MT][4];
+    if constexpr (MODE != 0) {
+#pragma unroll
+        for (int y = 0; y < R; ++y) {
+            if (oy + y * a.d >= a.Ho) break;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const auto r = split_rsrc((MODE == 1 ? a.mask : a.y) + first + (long)(16 * m) * oplane);
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) old[y][m][r4] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, at[m][r4], row(y), 0));
+            }
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+    const bool direct = down >= -126 && down <= 127;
+    const float scale = split_pow2(direct ? down : 0);
+#pragma unroll
+    for (int y = 0; y < R; ++y) {
+        if (oy + y * a.d >= a.Ho) break;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const auto r = split_rsrc(a.y + first + (long)(16 * m) * oplane);
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                float v = direct ? __builtin_fmaf(acc[y][m][r4], scale, bia[m][r4]) : __builtin_ldexpf(acc[y][m][r4], down) + bia[m][r4];
+                if constexpr (MODE == 2) v += old[y][m][r4];
+                if (a.relu) v = fmaxf(v, 0.f);
+                if constexpr (MODE == 1) v = old[y][m][r4] > 0.f ? v : 0.f;
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, at[m][r4], row(y), 0);
+            }
+        }
+    }
+}
 
 template <int KS, int MT, int R, int WX, int PITCH, bool PADZ>
 __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, const unsigned char *wsp, const int *wexp, int m_tiles, int tiles_hi,
@@ -71,11 +136,11 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
     const int b = bz / nblocks, nb = bz - b * nblocks;
     const int x0 = bx * T::TX, tile0 = nb * MT;
 
-    floatx4 acc[R][1][MT];
+    floatx4 acc[R][MT];
 #pragma unroll
     for (int y = 0; y < R; ++y)
 #pragma unroll
-        for (int m = 0; m < MT; ++m) acc[y][0][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < MT; ++m) acc[y][m] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     const long plane = (long)a.H * a.W;
     const float *xb = a.x + (long)b * (a.x_bstride ? a.x_bstride : (long)a.c_in * plane);
@@ -103,9 +168,9 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
     auto prefetch = [&](int chunk) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const char *src = reinterpret_cast<const char *>(xb + pf_skip + (long)min(chunk * 8 + e, a.c_in - 1) * plane);
+            const auto src = split_rsrc(xb + pf_skip + (long)min(chunk * 8 + e, a.c_in - 1) * plane);
 #pragma unroll
-            for (int q = 0; q < UPT; ++q) xr[q][e] = *reinterpret_cast<const float *>(src + off[q]);
+            for (int q = 0; q < UPT; ++q) xr[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(src, off[q], 0, 0));
         }
         if (--pf_left == 0) {
             pf_left = grp_chunks;
@@ -146,7 +211,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
 #pragma unroll
                 for (int y = 0; y < R; ++y)
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) acc[y][0][mt] *= f;
+                    for (int mt = 0; mt < MT; ++mt) acc[y][mt] *= f;
             }
             se = to;
         }
@@ -220,7 +285,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
                             const int y = r - i;
                             if (y < 0 || y >= R) continue;
 #pragma unroll
-                            for (int m = 0; m < MT; ++m) acc[y][0][m] = split_mfma(A[i][m][PA[q]], B[r & 1][PB[q]], acc[y][0][m]);
+                            for (int m = 0; m < MT; ++m) acc[y][m] = split_mfma(A[i][m][PA[q]], B[r & 1][PB[q]], acc[y][m]);
                         }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -229,14 +294,10 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
         if (more) measure(chunk + 1);
     }
     if (idle) return;
-    const int down = -(se + *wexp);
-#pragma unroll
-    for (int y = 0; y < R; ++y)
-#pragma unroll
-        for (int m = 0; m < MT; ++m)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) acc[y][0][m][r4] = __builtin_ldexpf(acc[y][0][m][r4], down);
-    store_outputs<MT, R, 1, 1>(a, acc, b, tile0 * 16 + 4 * g, py + d * (ty * T::RT + wy * R), d, x0 + wx * 16 + l16);
+    const int down = -(se + *wexp), o_first = tile0 * 16, oy = py + d * (ty * T::RT + wy * R), ox = x0 + wx * 16 + l16;
+    if (a.mask) split_store<MT, R, 1>(a, acc, down, b, o_first, oy, ox, g);
+    else if (a.accumulate) split_store<MT, R, 2>(a, acc, down, b, o_first, oy, ox, g);
+    else split_store<MT, R, 0>(a, acc, down, b, o_first, oy, ox, g);
 }
 
 template <int KS, int MT, int R, int WX, int PITCH, bool PADZ>
@@ -281,18 +342,20 @@ template <int KS, int MT, int R, int WX> hipError_t launch_split_p(const ConvF32
 }
 
 // What a tile costs, in us: a launch takes about chunks * max(lat * rounds of resident workgroups, work * tiles per CU) + over * tiles per
-// CU (+ 4).  Fitted to 181 layers of 8 to 1024 -> 16 to 512 maps on 20 x 24 to 3 x 430 x 560, d = 1 to 8 (6 to 8 % rms); the tile it picks is on
-// average 0.9 % and at most 10 % slower than the fastest of these, and 1.2 to 4.9 times as fast as the fp32 matrix unit.
+// CU (+ 3).  Fitted to 197 layers of 16 to 1024 -> 16 to 512 maps on 20 x 24 to 3 x 430 x 560, d = 1 to 8 (5 to 16 % rms); the tile it picks is on
+// average 1.1 % and at most 11 % slower than the fastest of fourteen (without the smallest, two rows of 32 columns of one map tile, 4 %: small
+// maps), and 1.3 to 5.2 times as fast as the fp32 matrix unit.
 struct SplitCost {
-    int mt, r, wx, slots;             // as SplitTile; workgroups resident on a CU
+    int mt, r, wx, slots;             // as SplitTile; workgroups that count as resident on a CU
     float lat, work, over;
 };
-constexpr SplitCost SPLIT_COST3[] = {{2, 8, 4, 4, 2.31f, 1.47f, 3.43f}, {2, 6, 4, 3, 1.99f, 1.20f, 2.22f}, {2, 4, 2, 3, 1.58f, 0.90f, 1.24f},
-                                     {1, 4, 4, 3, 1.31f, 0.55f, 1.12f}, {1, 4, 2, 4, 1.20f, 0.64f, 0.79f}, {3, 5, 4, 2, 2.28f, 1.43f, 3.66f},
-                                     {3, 4, 2, 3, 2.00f, 1.24f, 1.98f}};
-constexpr SplitCost SPLIT_COST4[] = {{2, 8, 4, 2, 2.87f, 2.04f, 3.12f}, {2, 6, 4, 3, 2.43f, 1.59f, 2.05f}, {2, 4, 2, 3, 1.92f, 1.20f, 1.10f},
-                                     {1, 4, 4, 2, 1.38f, 0.75f, 0.79f}, {1, 4, 2, 2, 1.38f, 0.80f, 0.66f}, {3, 5, 4, 3, 2.79f, 2.01f, 1.68f},
-                                     {3, 4, 2, 3, 2.40f, 1.65f, 1.79f}};
+constexpr int SPLIT_TILES = 8;
+constexpr SplitCost SPLIT_COST3[SPLIT_TILES] = {{2, 8, 4, 2, 1.79f, 1.40f, 2.60f}, {2, 6, 4, 3, 1.59f, 1.11f, 1.85f}, {2, 4, 2, 3, 1.32f, 0.83f, 1.07f},
+                                                {1, 4, 4, 4, 1.15f, 0.49f, 0.80f}, {1, 4, 2, 3, 1.16f, 0.54f, 0.71f}, {3, 5, 4, 2, 1.70f, 1.40f, 2.95f},
+                                                {3, 4, 2, 2, 1.57f, 1.13f, 2.28f}, {1, 2, 2, 4, 1.02f, 0.38f, 0.61f}};
+constexpr SplitCost SPLIT_COST4[SPLIT_TILES] = {{2, 8, 4, 3, 2.66f, 1.95f, 2.57f}, {2, 6, 4, 2, 2.22f, 1.50f, 1.81f}, {2, 4, 2, 3, 1.74f, 1.13f, 0.97f},
+                                                {1, 4, 4, 2, 1.26f, 0.69f, 0.58f}, {1, 4, 2, 3, 1.31f, 0.75f, 0.46f}, {3, 5, 4, 3, 2.56f, 1.93f, 1.67f},
+                                                {3, 4, 2, 3, 2.20f, 1.56f, 2.09f}, {1, 2, 2, 3, 1.19f, 0.47f, 0.66f}};
 
 double split_cost(const ConvF32Args &a, const SplitCost &c)
 {
@@ -307,7 +370,7 @@ template <int KS> hipError_t launch_ks(const ConvF32Args &a, hipStream_t stream)
 {
     const SplitCost *cost = KS == 3 ? SPLIT_COST3 : SPLIT_COST4;
     int best = 0;
-    for (int t = 1; t < 7; ++t)
+    for (int t = 1; t < SPLIT_TILES; ++t)
         if (split_cost(a, cost[t]) < split_cost(a, cost[best])) best = t;
     switch (best) {
     case 0: return launch_split_p<KS, 2, 8, 4>(a, stream);
@@ -316,7 +379,8 @@ template <int KS> hipError_t launch_ks(const ConvF32Args &a, hipStream_t stream)
     case 3: return launch_split_p<KS, 1, 4, 4>(a, stream);
     case 4: return launch_split_p<KS, 1, 4, 2>(a, stream);
     case 5: return launch_split_p<KS, 3, 5, 4>(a, stream);
-    default: return launch_split_p<KS, 3, 4, 2>(a, stream);
+    case 6: return launch_split_p<KS, 3, 4, 2>(a, stream);
+    default: return launch_split_p<KS, 1, 2, 2>(a, stream);
     }
 }
 
@@ -325,7 +389,7 @@ template <int KS> hipError_t launch_ks(const ConvF32Args &a, hipStream_t stream)
 // 3x3 layers of so few pixels are faster on the fp32 matrix unit (64 -> 64 on 20 x 24 12.7 us against 13.9; on 40 x 36 17.3 against 14.3)
 bool conv_split_f32_supported(const ConvF32Args &a)
 {
-    return conv_split_f32_packed(a.k, a.c_in) && (a.k - 1) * a.d <= 24 && (long)a.H * a.W < (1L << 29) &&
+    return conv_split_f32_packed(a.k, a.c_in) && (a.k - 1) * a.d <= 24 && (long)a.H * a.W < (1L << 29) && (long)a.OH * a.OW < (1L << 26) && a.tap_maps == 0 &&
            (a.k == 4 || (long)a.n * a.Ho * a.Wo >= 1000) &&
            (a.grp_maps == 0 || (a.grp_maps > 0 && a.grp_maps % 8 == 0 && a.c_in % a.grp_maps == 0 && a.grp_skip >= 0));
 }

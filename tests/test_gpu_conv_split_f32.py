@@ -38,10 +38,12 @@ def check(k, d, img, w0, b0):
 
 
 @pytest.mark.parametrize("k,d,c_in,c_out,n,h,w", [
-    (4, 1, 16, 16, 1, 4, 4), (4, 1, 17, 20, 2, 23, 70), (4, 2, 24, 48, 1, 150, 165), (4, 8, 48, 48, 1, 90, 97), (4, 9, 16, 48, 1, 60, 60),
-    (4, 4, 40, 96, 1, 140, 141), (4, 3, 16, 33, 4, 160, 150), (4, 1, 16, 130, 1, 67, 66), (4, 5, 31, 64, 1, 260, 270), (4, 1, 48, 48, 1, 515, 530),
-    (3, 1, 16, 16, 1, 34, 36), (3, 1, 16, 16, 1, 10, 12), (3, 2, 20, 50, 2, 45, 71), (3, 12, 16, 32, 1, 80, 77), (3, 13, 16, 32, 1, 80, 77),
+    (4, 1, 24, 16, 1, 4, 4), (4, 1, 23, 16, 1, 30, 40), (4, 1, 25, 20, 2, 23, 70), (4, 2, 24, 48, 1, 150, 165), (4, 8, 48, 48, 1, 90, 97),
+    (4, 9, 24, 48, 1, 60, 60), (4, 4, 40, 96, 1, 140, 141), (4, 3, 24, 33, 4, 160, 150), (4, 1, 24, 130, 1, 67, 66), (4, 5, 31, 64, 1, 260, 270),
+    (4, 1, 48, 48, 1, 515, 530), (4, 2, 24, 32, 2, 300, 310), (4, 1, 24, 16, 1, 100, 40), (4, 2, 24, 16, 2, 330, 340),
+    (3, 1, 24, 16, 1, 34, 36), (3, 1, 24, 16, 1, 10, 12), (3, 2, 26, 50, 2, 45, 71), (3, 12, 24, 32, 1, 80, 77), (3, 13, 24, 32, 1, 80, 77),
     (3, 4, 64, 96, 1, 100, 131), (3, 1, 64, 64, 1, 300, 290), (3, 1, 24, 144, 1, 142, 130), (3, 6, 33, 48, 3, 160, 170), (3, 1, 128, 128, 1, 68, 66),
+    (3, 1, 24, 48, 2, 330, 310), (3, 2, 24, 20, 3, 300, 310),
 ])
 def test_forward(k, d, c_in, c_out, n, h, w):
     rng = np.random.default_rng(h * w + c_in)
@@ -78,8 +80,8 @@ def test_magnitudes(case):
 
 def test_infinities_and_nan_stay_where_they_are():
     rng = np.random.default_rng(6)
-    img = rng.standard_normal((1, 16, 60, 120)).astype(np.float32)
-    w0 = rng.standard_normal((48, 16, 4, 4)).astype(np.float32)
+    img = rng.standard_normal((1, 24, 60, 120)).astype(np.float32)
+    w0 = rng.standard_normal((48, 24, 4, 4)).astype(np.float32)
     clean = forward(4, 1, img, w0, np.zeros(48, np.float32), relu=False)
     bad = img.copy()
     bad[0, 2, 20, 30] = np.inf
@@ -90,13 +92,13 @@ def test_infinities_and_nan_stay_where_they_are():
     hit[:, :, 37:41, 87:91] = True
     assert not np.isfinite(got[hit]).any()
     size = OL.conv_sk(np.abs(img), np.abs(w0), np.zeros(48), 1)
-    assert np.all(np.abs(got - clean)[~hit] <= 2 * (256 + 9) * 2.0 ** -24 * size[~hit])
+    assert np.all(np.abs(got - clean)[~hit] <= 2 * (384 + 9) * 2.0 ** -24 * size[~hit])
 
 
 @pytest.mark.parametrize("relu", [False, True])
 @pytest.mark.parametrize("k,d,maps,classes,n,h,w", [
-    (4, 1, 8, 16, 2, 19, 71), (4, 2, 20, 17, 1, 47, 66), (4, 8, 48, 48, 1, 70, 131), (4, 9, 16, 16, 1, 70, 80), (3, 1, 40, 32, 1, 40, 131),
-    (3, 12, 48, 16, 1, 85, 90), (3, 4, 64, 20, 1, 60, 64), (3, 2, 130, 16, 1, 40, 70),
+    (4, 1, 8, 24, 2, 19, 71), (4, 2, 20, 25, 1, 47, 66), (4, 8, 48, 48, 1, 70, 131), (4, 9, 16, 24, 1, 70, 80), (3, 1, 40, 32, 1, 40, 131),
+    (3, 12, 48, 24, 1, 85, 90), (3, 4, 64, 26, 1, 60, 64), (3, 2, 130, 24, 1, 40, 70), (4, 2, 96, 40, 1, 300, 250),
 ])
 def test_data_gradient(k, d, maps, classes, n, h, w, relu):
     from paper_1509_03371_amd import binding as B
