@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
     };
     auto commit = [&](int chunk) {
         const floatx4 m4 = *reinterpret_cast<const floatx4 *>(most + (chunk & 1) * 4);
-        float m = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
+        float m = split_max(split_max(m4[0], m4[1]), split_max(m4[2], m4[3]));
         m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
         if (__builtin_bit_cast(unsigned, m) == 0x7f800000u) {            // infinities don't decide the scale of the finite samples beside them
             float f = 0.f;

@@ -62,7 +62,7 @@ struct WgradRowsArgs {
     float *scratch, *bias_part;
     int n, c_in, c_out, c8i, c8o, H, W, Ho, Wo, d;
     int slot_bytes;               // bytes of a ring slot
-    int xstrips, nseg, rs, total_walks;
+    int xstrips, nseg, rs, total_walks, total_rows;      // nseg = 0: equal shares of rows
     int copy_floats;              // floats of one private copy
 };
 
@@ -102,10 +102,12 @@ __device__ __forceinline__ uint4v read_frag(const char *lds_base, unsigned off_l
 }
 
 struct Walk {
-    int b, x0, py, r0, rows;      // rows: gradient rows of this walk (it has rows + 3 steps), 0 = empty
+    int b, x0, py, r0, rows;      // rows: gradient rows of this walk (it has rows + 3 steps)
 };
 
-template <int DT, int MT, int NCT>
+// WALKS: whole walks of rs rows, a contiguous range of their list; else an equal share of all (image, strip, phase, row in the phase), in
+// walks that end with their phase or the share
+template <int DT, int MT, int NCT, bool WALKS>
 __global__ __launch_bounds__(64 * WR_WAVES) void wgrad_rows_h_kernel(WgradRowsArgs a)
 {
     extern __shared__ uint4v smem16[];
@@ -142,27 +144,47 @@ __global__ __launch_bounds__(64 * WR_WAVES) void wgrad_rows_h_kernel(WgradRowsAr
         }
     }
 
-    // this workgroup's walks: a contiguous range of the list (segments of one strip and phase are neighbours)
-    const int w_begin = (int)((long)a.total_walks * blockIdx.x / gridDim.x), w_end = (int)((long)a.total_walks * (blockIdx.x + 1) / gridDim.x);
-    auto decode = [&](int t) {
-        Walk w;
-        const int seg = t % a.nseg;
-        int rest = t / a.nseg;
-        w.py = rest % d;
-        rest /= d;
-        w.x0 = (rest % a.xstrips) * WR_TX;
-        w.b = rest / a.xstrips;
-        const int rows_p = a.Ho > w.py ? (a.Ho - w.py + d - 1) / d : 0;
-        w.r0 = seg * a.rs;
-        int rows = rows_p - w.r0;
-        rows = rows < 0 ? 0 : (rows > a.rs ? a.rs : rows);
-        w.rows = rows;
+    // this workgroup's walks (see WALKS)
+    const long units = WALKS ? a.total_walks : a.total_rows;
+    const int w_begin = (int)(units * blockIdx.x / gridDim.x), w_end = (int)(units * (blockIdx.x + 1) / gridDim.x);
+    auto decode = [&](int t) {                                   // walk t, or the one that starts at row t; none beyond the last
+        Walk w{};
+        if (t >= w_end) return w;
+        if constexpr (WALKS) {
+            const int seg = t % a.nseg;
+            int rest = t / a.nseg;
+            w.py = rest % d;
+            rest /= d;
+            w.x0 = (rest % a.xstrips) * WR_TX;
+            w.b = rest / a.xstrips;
+            const int rows_p = a.Ho > w.py ? (a.Ho - w.py + d - 1) / d : 0;
+            w.r0 = seg * a.rs;
+            const int rows = rows_p - w.r0;
+            w.rows = rows < 0 ? 0 : (rows > a.rs ? a.rs : rows);
+        } else {
+            const int strip = t / a.Ho, yy = t - strip * a.Ho, long_phases = a.Ho % d;
+            w.b = strip / a.xstrips;
+            w.x0 = (strip - w.b * a.xstrips) * WR_TX;
+            int rows = a.Ho / d + 1;                             // of a phase: one more in the first ones
+            if (yy < long_phases * rows) {
+                w.py = yy / rows;
+                w.r0 = yy - w.py * rows;
+            } else {
+                const int y2 = yy - long_phases * rows;
+                --rows;
+                w.py = y2 / rows;
+                w.r0 = y2 - w.py * rows;
+                w.py += long_phases;
+            }
+            w.rows = min(rows - w.r0, w_end - t);
+        }
         return w;
     };
     int total_steps = 0;
-    for (int t = w_begin; t < w_end; ++t) {
-        const Walk w = decode(t);
-        total_steps += w.rows > 0 ? w.rows + 3 : 0;
+    for (int t = w_begin; t < w_end;) {
+        const int rows = decode(t).rows;
+        total_steps += rows > 0 ? rows + 3 : 0;
+        t += WALKS ? 1 : rows;
     }
 
     // Loads of a step, 1 KB each: one per input octet (first 64 pixels), one per gradient octet, and the packed
@@ -197,13 +219,9 @@ __global__ __launch_bounds__(64 * WR_WAVES) void wgrad_rows_h_kernel(WgradRowsAr
     const char *zsrc = zg + lane * 16;
     bool yok[2] = {false, false};                               // gradient loads: this lane's column lies inside the gradient
     auto start_walk = [&]() {
-        Walk w;
-        w.rows = 0;
-        while (it < w_end) {
-            w = decode(it);
-            if (w.rows > 0) break;
-            ++it;
-        }
+        Walk w = decode(it);
+        if constexpr (WALKS)
+            while (w.rows == 0 && it < w_end) w = decode(++it);
         irows = w.rows;
         is = 0;
         if (irows == 0) return;
@@ -240,7 +258,7 @@ __global__ __launch_bounds__(64 * WR_WAVES) void wgrad_rows_h_kernel(WgradRowsAr
                 lds_dma16(p, dst + ldst[u]);
         }
         if (++is == irows + 3) {
-            ++it;
+            it += WALKS ? 1 : irows;
             start_walk();
         }
     };
@@ -380,24 +398,24 @@ __global__ void __launch_bounds__(256) wgrad_rows_reduce_kernel(const float *__r
     }
 }
 
-template <int DT, int MT, int NCT>
+template <int DT, int MT, int NCT, bool WALKS>
 hipError_t launch_t(const WgradRowsArgs &a, size_t smem, int blocks, hipStream_t stream)
 {
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&wgrad_rows_h_kernel<DT, MT, NCT>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&wgrad_rows_h_kernel<DT, MT, NCT, WALKS>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((wgrad_rows_h_kernel<DT, MT, NCT>), dim3(blocks), dim3(64 * WR_WAVES), smem, stream, a);
+    hipLaunchKernelGGL((wgrad_rows_h_kernel<DT, MT, NCT, WALKS>), dim3(blocks), dim3(64 * WR_WAVES), smem, stream, a);
     return hipGetLastError();
 }
 
 template <int DT>
 hipError_t launch_dt(const WgradRowsArgs &a, int MT, int NCT, size_t smem, int blocks, hipStream_t stream)
 {
-#define SK_WR_CASE(mt, nct) if (MT == mt && NCT == nct) return launch_t<DT, mt, nct>(a, smem, blocks, stream);
+#define SK_WR_CASE(mt, nct) if (MT == mt && NCT == nct) return a.nseg > 0 ? launch_t<DT, mt, nct, true>(a, smem, blocks, stream) : launch_t<DT, mt, nct, false>(a, smem, blocks, stream);
     SK_WR_CASE(1, 1) SK_WR_CASE(2, 1) SK_WR_CASE(3, 1)
     SK_WR_CASE(1, 2) SK_WR_CASE(2, 2) SK_WR_CASE(3, 2)
     SK_WR_CASE(1, 3) SK_WR_CASE(2, 3) SK_WR_CASE(3, 3)
@@ -430,6 +448,15 @@ size_t wgrad_rows_h_scratch_floats(int c_in, int c_out)
     return 512 * (16 * NCT * MT * 256 + MT * 16);
 }
 
+hipError_t launch_wgrad_rows_reduce(const float *scratch, float *dw, int copies, int copy_floats, int c_out, int c_in, int MT, int NCT, const float *bias_part,
+                                    float *db, hipStream_t stream)
+{
+    const int dw_blocks = (copy_floats + 63) / 64, db_blocks = db ? (c_out + 63) / 64 : 0;
+    hipLaunchKernelGGL(wgrad_rows_reduce_kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, stream, scratch, dw, copies, copy_floats, c_out, c_in, MT, NCT,
+                       dw_blocks, bias_part, db);
+    return hipGetLastError();
+}
+
 // scratch: scratch_floats floats (private copies, then the bias partials).  zeros: at least 1 KB of zeros.
 hipError_t launch_wgrad_rows_h(const void *x, const void *dy, const void *zeros, float *dw, float *db, float *scratch, size_t scratch_floats,
                                int dtype, int n, int c_in, int H, int W, int c_out, int d, hipStream_t stream)
@@ -450,18 +477,23 @@ hipError_t launch_wgrad_rows_h(const void *x, const void *dy, const void *zeros,
     const long fit = (long)(scratch_floats / ((size_t)a.copy_floats + bias_floats));
     if (fit < 1) return hipErrorInvalidValue;
     if (blocks > fit) blocks = fit;
-    // rows per walk: about one workgroup's share of all rows, so that the three extra steps of a walk stay a small part
     a.xstrips = (a.Wo + WR_TX - 1) / WR_TX;
     const long total_rows = (long)n * a.xstrips * a.Ho;
+    // Steps of the longest share (a walk has three more than rows), with the rows dealt out in walks of equal length and in equal shares.
+    // Equal walks are 270 on 256 workgroups at 562^2, d = 2: two for some, 53 us a layer, 41 with equal shares; 252 at 544^2, d = 4: 39 us, 41.
     long rs = (total_rows + blocks - 1) / blocks;
     rs = rs < 8 ? 8 : (rs > 128 ? 128 : rs);
     const int rows_p = (a.Ho + d - 1) / d;                      // rows of the longest phase
     a.nseg = (int)((rows_p + rs - 1) / rs);
     a.rs = (rows_p + a.nseg - 1) / a.nseg;                      // equal segments
     const long walks = (long)n * a.xstrips * d * a.nseg;
-    if (walks > 0x7fffffffL) return hipErrorInvalidValue;
+    if (walks > 0x7fffffffL || total_rows > 0x7fffffffL) return hipErrorInvalidValue;
     a.total_walks = (int)walks;
-    if (blocks > walks) blocks = walks;
+    a.total_rows = (int)total_rows;
+    const long walk_blocks = std::min(blocks, walks), share_blocks = std::min(blocks, (total_rows + 7) / 8), share = (total_rows + share_blocks - 1) / share_blocks;
+    const long walk_steps = (walks + walk_blocks - 1) / walk_blocks * (a.rs + 3), share_steps = share + 3 * ((share + rows_p - 2) / rows_p + 1);
+    blocks = walk_steps <= share_steps ? walk_blocks : share_blocks;
+    if (walk_steps > share_steps) a.nseg = 0;
     a.bias_part = db ? scratch + (size_t)blocks * a.copy_floats : nullptr;
     size_t smem = (size_t)a.slot_bytes * WR_SLOTS;
     const size_t red = (size_t)16 * MT * 64 * 16 + 4096;        // the hand-over of one input-map tile, the bias sums
@@ -469,10 +501,7 @@ hipError_t launch_wgrad_rows_h(const void *x, const void *dy, const void *zeros,
     if (smem > 160 * 1024) return hipErrorInvalidValue;
     hipError_t e = dtype == 1 ? launch_dt<1>(a, MT, NCT, smem, (int)blocks, stream) : launch_dt<2>(a, MT, NCT, smem, (int)blocks, stream);
     if (e != hipSuccess) return e;
-    const int dw_blocks = (a.copy_floats + 63) / 64, db_blocks = db ? (c_out + 63) / 64 : 0;
-    hipLaunchKernelGGL(wgrad_rows_reduce_kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, stream, scratch, dw, (int)blocks, a.copy_floats, c_out,
-                       c_in, MT, NCT, dw_blocks, a.bias_part, db);
-    return hipGetLastError();
+    return launch_wgrad_rows_reduce(scratch, dw, (int)blocks, a.copy_floats, c_out, c_in, MT, NCT, a.bias_part, db, stream);
 }
 
 }  // namespace sk

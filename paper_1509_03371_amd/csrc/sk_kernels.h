@@ -311,6 +311,14 @@ bool wgrad_rows_f32_supported(int c_in, int c_out, int k, int d);
 hipError_t launch_wgrad_rows_f32(const float *x, const float *dy, float *scratch, float *bias_part, int n, int c_in, int H, int W, int c_out, int d,
                                  int max_copies, int *copies, hipStream_t stream);
 
+// 4x4 kernels of 16 to 48 maps on either side, large images, on the 16-bit matrix unit (kernels_wgrad_split_f32.hip)
+bool wgrad_split_f32_supported(int c_in, int c_out, int k, int d, int n, int H, int W);
+hipError_t launch_wgrad_split_f32(const float *x, const float *dy, float *dw, float *db, float *scratch, size_t scratch_floats, int n, int c_in, int H,
+                                  int W, int c_out, int d, hipStream_t stream);
+// sums of private copies in accumulator order (kernels_wgrad_rows_h.hip) and of bias_part[copy][16 MT]
+hipError_t launch_wgrad_rows_reduce(const float *scratch, float *dw, int copies, int copy_floats, int c_out, int c_in, int MT, int NCT, const float *bias_part,
+                                    float *db, hipStream_t stream);
+
 // 1x1 kernels of at most 48 maps on one side and 208 on the other (kernels_1x1_f32.hip): private copies
 // [16 * ceil(c_out / 16)][16 * ceil(c_in / 16)], else as above
 bool wgrad1x1_f32_supported(int c_in, int c_out, int n, long plane);

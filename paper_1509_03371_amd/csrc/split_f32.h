@@ -38,21 +38,25 @@ __device__ __forceinline__ void split2(const float (&v)[8], float scale, uint4v 
     }
 }
 
-// largest of non-negative values over the wave, in every lane
+// Largest of non-negative values; their bits are in the values' order, and comparing those needs no quieting of NaNs
+__device__ __forceinline__ float split_max(float a, float b)
+{
+    return __builtin_bit_cast(float, max(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b)));
+}
+
+// ... over the wave, in every lane
 __device__ __forceinline__ float split_wave_max(float m)
 {
     const auto step = [&](auto ctrl) {
-        const int o = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), decltype(ctrl)::value, 0xf, 0xf, true);
-        m = fmaxf(m, __builtin_bit_cast(float, o));
+        m = split_max(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), decltype(ctrl)::value, 0xf, 0xf, true)));
     };
     step(std::integral_constant<int, 0x111>{});      // row_shr 1, 2, 4, 8: lane 15 of a row has the row's
     step(std::integral_constant<int, 0x112>{});
     step(std::integral_constant<int, 0x114>{});
     step(std::integral_constant<int, 0x118>{});
     const int v = __builtin_bit_cast(int, m);
-    const float a = fmaxf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(v, 15)), __builtin_bit_cast(float, __builtin_amdgcn_readlane(v, 31)));
-    const float b = fmaxf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(v, 47)), __builtin_bit_cast(float, __builtin_amdgcn_readlane(v, 63)));
-    return fmaxf(a, b);
+    const int a = max(__builtin_amdgcn_readlane(v, 15), __builtin_amdgcn_readlane(v, 31)), b = max(__builtin_amdgcn_readlane(v, 47), __builtin_amdgcn_readlane(v, 63));
+    return __builtin_bit_cast(float, max(a, b));
 }
 
 // the power of two that takes m to 2^top .. 2^(top + 1)

@@ -1,0 +1,81 @@
+"""GPU parity of the fp32 4x4 weight gradient on the 16-bit matrix unit, and of how the row-streaming gradients deal out their rows: phases that
+are no equal share, strips with one half beyond the image, several images, operands whose magnitudes rise and fall from row to row.
+
+Both operands are pairs of fp16 values, a product is within 2^-21 of its magnitude, and a sum of K products within (K + 8) * 2^-24 of the sum
+of magnitudes; the reference takes the maps and error maps of the pass itself."""
+import numpy as np
+import pytest
+import torch
+
+import sk_synth as S
+
+pytestmark = pytest.mark.gpu
+
+
+def gradient(c_in, c_out, d, n, h, w, dtype="f32", scale=None):
+    """(gradient of a 4x4 layer, its bias gradient, the layer's input, its error map)"""
+    from paper_1509_03371_amd import binding as B
+    rng = np.random.default_rng(h + w)
+    net = B.SKNet([S.conv(c_in, 1, 1, relu=True), S.conv(c_out, 4, d, relu=False), S.conv(2, 1, 1, relu=False)], 3, 2, dtype=dtype)
+    for i in range(3):
+        s = net.conv_shape(i)
+        net.set_weights(i, (rng.standard_normal(s) / np.sqrt(np.prod(s[1:]))).astype(np.float32), rng.standard_normal(s[0]).astype(np.float32) * np.float32(i != 0))
+    net.plan(n, h, w, pad=False, training=True)
+    img = rng.standard_normal((n, 3, h, w)).astype(np.float32)
+    if scale is not None:
+        img *= scale
+    net.forward(torch.from_numpy(img).cuda())
+    lab = torch.from_numpy(rng.integers(-1, 2, (n, h - 3 * d, w - 3 * d)).astype(np.int32)).cuda()
+    net.backward(lab)
+    dw, db = net.get_grad(1)
+    x, dy = net.get_activation(0), net.get_activation_grad(1, lab)
+    net.close()
+    return dw, db, x, dy
+
+
+def sums(x, dy, d):
+    x, dy = torch.from_numpy(x).double(), torch.from_numpy(dy).double()
+    n, c_out, ho, wo = dy.shape
+    out = torch.zeros(c_out, x.shape[1], 4, 4, dtype=torch.double)
+    for i in range(4):
+        for j in range(4):
+            win = x[:, :, i * d:i * d + ho, j * d:j * d + wo]
+            for b in range(n):
+                out[:, :, i, j] += dy[b].reshape(c_out, -1) @ win[b].reshape(win.shape[1], -1).T.contiguous()
+    return out.numpy(), dy.sum(dim=(0, 2, 3)).numpy()
+
+
+@pytest.mark.parametrize("c_in,c_out,d,n,h,w", [
+    (48, 48, 2, 1, 180, 300), (48, 48, 8, 1, 207, 217), (32, 16, 1, 3, 103, 99), (40, 24, 3, 2, 209, 140), (48, 40, 7, 1, 721, 50), (16, 48, 1, 2, 303, 310),
+    (32, 32, 4, 12, 100, 40),
+])
+def test_gradient(c_in, c_out, d, n, h, w):
+    dw, db, x, dy = gradient(c_in, c_out, d, n, h, w)
+    ref, rb = sums(x, dy, d)
+    size, sb = sums(np.abs(x), np.abs(dy), d)
+    products = dy.size // c_out
+    assert np.abs(ref).max() > 1e-4
+    assert np.all(np.abs(dw - ref) <= (products + 9) * 2.0 ** -24 * size) and np.all(np.abs(db - rb) <= (products + 9) * 2.0 ** -24 * sb)
+    # sums of random signs: what the bound allows all of them at once, a right kernel shows a hundredth of
+    assert np.linalg.norm(dw - ref) <= 3e-7 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("way", ["rising", "falling", "dark half"])
+def test_magnitudes(way):
+    h, w, d = 180, 300, 2
+    ramp = np.float32(2.0) ** np.linspace(-12, 12, h).astype(np.float32)[:, None]
+    scale = {"rising": ramp, "falling": ramp[::-1], "dark half": np.where(np.arange(w) < 150, np.float32(1e-7), np.float32(1))[None, :]}[way]
+    dw, db, x, dy = gradient(48, 48, d, 1, h, w, scale=scale.astype(np.float32))
+    ref, _ = sums(x, dy, d)
+    assert np.linalg.norm(dw - ref) <= 1e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("c_in,c_out,d,n,h,w", [(48, 48, 2, 1, 568, 568), (16, 24, 8, 1, 100, 300), (24, 8, 5, 2, 61, 81), (48, 48, 21, 1, 90, 130), (8, 16, 3, 1, 700, 70)])
+def test_rows_of_16_bit_gradients(c_in, c_out, d, n, h, w):
+    dw, db, x, dy = gradient(c_in, c_out, d, n, h, w, dtype="bf16")
+    ref, rb = sums(x, dy, d)
+    size, sb = sums(np.abs(x), np.abs(dy), d)
+    products = dy.size // c_out
+    # operands are the stored bf16 values themselves; only the fp32 sums are rounded
+    assert np.all(np.abs(dw - ref) <= (products + 2) * 2.0 ** -24 * size) and np.all(np.abs(db - rb) <= (products + 2) * 2.0 ** -24 * sb)
+    assert np.linalg.norm(dw - ref) <= 2e-6 * np.linalg.norm(ref)
