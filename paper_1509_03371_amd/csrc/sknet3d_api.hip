@@ -85,9 +85,10 @@ void release_conv3(Conv3 &c)
     free_dev(c.dw); free_dev(c.db); free_dev(c.vw); free_dev(c.vb); free_dev(c.dw_tap);
 }
 
-// rebuild the packed forms from the device master (asynchronous)
+// rebuild the packed fp32 forms from the device master (asynchronous); 16-bit nets have none (repack_conv3_h)
 sk_status repack_conv3(Conv3 &c, hipStream_t stream)
 {
+    if (c.fwd.empty() || !c.fwd[0].wp) return SK_OK;
     for (auto &r : c.fwd)
         SK_HIP(sk::launch_pack_weights3d_f32(c.w_dev, r.wp, c.c_out, c.c_in, c.k, r.a0, r.len, 0, r.rows, c.n_pad, stream));
     for (auto &r : c.bwd)
@@ -139,9 +140,10 @@ sk_status alloc_conv3(Conv3 &c, bool training, bool needs_dgrad, bool half)
     c.n_pad_bwd = round_up(c.c_in, 16);
     SK_TRY(alloc_f(&c.w_dev, c.wcount()));
     SK_TRY(alloc_f(&c.b_dev, c.n_pad));
-    for (auto &r : c.fwd) SK_TRY(alloc_f(&r.wp, sk::packed_f32_floats(c.k, r.len * c.c_in, c.n_pad)));
+    if (!half)
+        for (auto &r : c.fwd) SK_TRY(alloc_f(&r.wp, sk::packed_f32_floats(c.k, r.len * c.c_in, c.n_pad)));
     if (training) {
-        if (needs_dgrad) {
+        if (needs_dgrad && !half) {
             c.bwd = make_runs(c.k, c.d, c.c_out);
             for (auto &r : c.bwd) SK_TRY(alloc_f(&r.wp, sk::packed_f32_floats(c.k, r.len * c.c_out, c.n_pad_bwd)));
         }
@@ -732,9 +734,7 @@ sk_status sknet3d_sgd_step(sknet3d_t *net, float lr, float momentum, float weigh
         sb.w[sb.n] = c.b_dev; sb.dw[sb.n] = c.db; sb.v[sb.n] = momentum != 0.f ? c.vb : nullptr; sb.count[sb.n] = c.c_out; ++sb.n;
     }
     if (sb.n > 0) SK_HIP(sk::launch_sgd_batch_f32(sb, lr, momentum, weight_decay, stream));
-    for (auto &c : net->convs) SK_TRY(repack_conv3(c, stream));
-    if (net->half())
-        for (auto &c : net->convs) SK_TRY(repack_conv3_h(c, net->dtype, c.wp16_bwd != nullptr, stream));
+    for (auto &c : net->convs) SK_TRY(net->half() ? repack_conv3_h(c, net->dtype, c.wp16_bwd != nullptr, stream) : repack_conv3(c, stream));
     return SK_OK;
 }
 
