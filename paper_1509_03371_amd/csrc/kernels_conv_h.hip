@@ -26,6 +26,8 @@
 // the grid is persistent (one workgroup per CU), walks tiles in an XCD-aware order and keeps a
 // two-stage LDS pipeline running across tile boundaries: while chunk q is multiplied, chunk q+1
 // (next octets, or the first octets of the next tile) is in flight from HBM/L2 into registers.
+#include <algorithm>
+
 #include "sk_kernels.h"
 
 namespace sk {
@@ -1283,6 +1285,36 @@ static hipError_t launch_conv_h_ring_mask(const ConvHArgs &a, hipStream_t stream
     return launch_conv_h_ring_m<DT, KS, MT, MAP4, R, false, S, RESW>(a, stream);
 }
 
+template <int DT, int MT, int R> static hipError_t launch_conv_h_ring_producers(const ConvHArgs &a, hipStream_t stream)
+{
+    if (a.vpool) return launch_conv_h_ring_m<DT, 4, MT, true, R, false, 3, true, 4, true>(a, stream);
+    return launch_conv_h_ring_m<DT, 4, MT, true, R, false, 3, true, 4>(a, stream);
+}
+
+// Rows of a tile of the 4x4 layers with producer waves.  One workgroup runs on a CU, so a launch lasts as many rounds as the CU with the most
+// tiles, and a round costs about the tile's rows + 2; one 512^2 image is 1.4 rounds of 8 rows, which are two, 1.8 of 6 rows or 2.8 of 4.  With a
+// pooled output 8 rows cost a tenth more (four registers spill), and overlapping tiles or the tile in front of a run count.
+// us with 8, 6, 4 rows, bf16, 48 -> 48: 562^2 d = 2 34.4, 31.0, 32.7; 5 x 253^2 34.5, 30.7, 33.0; 117 x 137 17.3, 15.6, 12.9; 2 x 294 x 327 22.2, 29.5, 24.2;
+// 8 x 1032^2 561, 567, 611; pooled 3 x 397 x 525 62.9, 58.5, 65.6, 8 x 1074^2 667, 643, 699.  Over 70 plain layers of 16 to 48 maps, 64^2 to 8 x 1000^2,
+// d = 1 to 16, 0.86 of the time of 8 rows (1.003 of the best of the three), over 99 pooled ones 0.89 (1.002; one of 1.05).
+template <int MT> static int ring_rows(const ConvHArgs &a)
+{
+    const long cus = device_cus() / 8 * 8, q = a.Ho / a.d, rem = a.Ho % a.d, xtiles = (a.Wo + CH_TX - 1) / CH_TX;
+    const auto cost = [&](long r) {
+        const long tiles = xtiles * (rem * ((q + r) / r) + (a.d - rem) * ((q + r - 1) / r)) * a.n;
+        const double row = r + 2;
+        if (!a.vpool) return row * ((tiles + cus - 1) / cus);
+        const double spill = r == 8 ? 1.1 : 1.0;
+        if (tiles / cus >= 8) return spill * row * ((tiles + cus - 1) / cus + 1);
+        const long overlapping = xtiles * (rem * std::max(1L, (q + r - 2) / (r - 1)) + (a.d - rem) * std::max(1L, (q + r - 3) / (r - 1))) * a.n;
+        return spill * row * ((overlapping + cus - 1) / cus);
+    };
+    int rows = 8;
+    if (cost(6) < cost(rows) && ring_smem<4, MT, true, 6, 3, true>(a.d, a.c_out, a.c8_in, a.Ho, a.hd, 5) <= 160 * 1024) rows = 6;
+    if (cost(4) < cost(rows) && ring_smem<4, MT, true, 4, 3, true>(a.d, a.c_out, a.c8_in, a.Ho, a.hd, 3) <= 160 * 1024) rows = 4;
+    return rows;
+}
+
 // Preference: weights resident in LDS with a 3-stage ring of input tiles (one map group, all chunk
 // slabs fit), else a 4-stage ring that streams the weight slab with each chunk, else the
 // register-staged two-stage kernel.
@@ -1294,8 +1326,10 @@ static hipError_t launch_conv_h_ring_or_staged(const ConvHArgs &a, hipStream_t s
         // the forward 4x4 convolution of the benchmark nets: loads on four waves of their own (three waves per SIMD)
         if constexpr (KS == 4 && MAP4 && R == 8)
             if (!a.mask) {
-                if (a.vpool) return launch_conv_h_ring_m<DT, KS, MT, MAP4, R, false, 3, true, 4, true>(a, stream);
-                return launch_conv_h_ring_m<DT, KS, MT, MAP4, R, false, 3, true, 4>(a, stream);
+                const int rows = ring_rows<MT>(a);
+                if (rows == 4) return launch_conv_h_ring_producers<DT, MT, 4>(a, stream);
+                if (rows == 6) return launch_conv_h_ring_producers<DT, MT, 6>(a, stream);
+                return launch_conv_h_ring_producers<DT, MT, 8>(a, stream);
             }
         if (a.vpool || a.hd) return hipErrorInvalidValue;
         return launch_conv_h_ring_mask<DT, KS, MT, MAP4, R, 3, true>(a, stream);
