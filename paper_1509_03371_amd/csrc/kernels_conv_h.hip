@@ -1690,23 +1690,41 @@ hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream)
 
 // ------------------------------------------------------------------------------------------------
 // Weight packing for the 16-bit convolutions.  The packed array is a sequence of 1 KB MFMA A fragments,
-//   [mgroup][chunk][column step cs][kernel row i][m-tile mt][lane group g][l16][e = 0..7]
+//   [mgroup][chunk][fragment: column step cs, kernel row i][m-tile mt][lane group g][l16][e = 0..7]
 // with element = W[o][c][i][j] (forward) where o = (mgroup*MT + mt)*16 + l16 and
 //   map4 = 0: c = (chunk*4 + g)*8 + e,   j = cs
 //   map4 = 1: c = chunk*8 + e,           j = 4*cs + g (zero for j >= k): k >= 4, and 3x3 with CONV_H_TAPCOLS
 //   map4 = 2: c = chunk*8 + e,           j = 4*cs + (0, 2, 1, 3)[g]: kernels_conv_wide_big_h.hip, whose LDS reads serve
-//                                        groups 0 and 1 together and want their columns two kernel strides apart
+//                                        groups 0 and 1 together and want their columns two kernel strides apart; the one or
+//                                        two columns left behind the last four are fragments of four or two kernel rows
 // flip_transpose = 1 builds the data-gradient operator instead: the roles of input and output maps
 // are swapped and both taps are mirrored (element = W[c][o][k-1-i][k-1-j]).
 // Entries whose o or c lie beyond the real extents are zero.
-// kernel column, within its column step, that lane group g carries
-__device__ __forceinline__ int pack_col(int map4, int g) { return map4 == 2 ? (g >> 1) | ((g & 1) << 1) : g; }
+// fragments of a chunk
+__host__ __device__ constexpr int pack_frags(int map4, int k)
+{
+    return map4 == 0 ? k * k : map4 == 1 ? (k + 3) / 4 * k : k / 4 * k + (k % 4 * k + 3) / 4;
+}
+// kernel row and column that lane group g carries in fragment f of a chunk; false: none, zero weights
+__device__ __forceinline__ bool pack_tap(int map4, int k, int f, int g, int &i, int &j)
+{
+    const int cs = f / k, left = f - (k >> 2) * k;
+    i = f - cs * k;
+    if (map4 == 0) j = cs;
+    else if (map4 == 1) j = 4 * cs + g;
+    else if (left < 0) j = 4 * cs + ((g >> 1) | ((g & 1) << 1));
+    else {
+        j = (k & ~3) + ((k & 3) == 2 ? g >> 1 : 0);
+        i = (k & 3) == 2 ? 2 * left + (g & 1) : 4 * left + g;
+    }
+    return i < k && j < k;
+}
 
 template <int DT>
 __device__ __forceinline__ void pack_weights_h_body(const float *w, unsigned short *wp, int c_out, int c_in, int k, int flip_transpose,
                                                     int mt_per_group, int map4, int gemm_m, int gemm_c8, long total)
 {
-    const int OC = map4 ? 1 : 4, CS = map4 ? (k + 3) / 4 : k;
+    const int OC = map4 ? 1 : 4, NF = pack_frags(map4, k);
     const int nchunks = (gemm_c8 + OC - 1) / OC;
     for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < total; q += (long)gridDim.x * blockDim.x) {
         long r = q;
@@ -1714,15 +1732,14 @@ __device__ __forceinline__ void pack_weights_h_body(const float *w, unsigned sho
         const int l16 = (int)(r % 16); r /= 16;
         const int g = (int)(r % 4); r /= 4;
         const int mt = (int)(r % mt_per_group); r /= mt_per_group;
-        const int i = (int)(r % k); r /= k;
-        const int cs = (int)(r % CS); r /= CS;
+        const int f = (int)(r % NF); r /= NF;
         const int ch = (int)(r % nchunks); r /= nchunks;
         const int mg = (int)r;
         const int m = (mg * mt_per_group + mt) * 16 + l16;          // GEMM output map
         const int c = map4 ? ch * 8 + e : (ch * 4 + g) * 8 + e;     // GEMM input map
-        const int j = map4 ? 4 * cs + pack_col(map4, g) : cs;
+        int i, j;
         float v = 0.f;
-        if (m < gemm_m && c < gemm_c8 * 8 && j < k) {
+        if (pack_tap(map4, k, f, g, i, j) && m < gemm_m && c < gemm_c8 * 8) {
             if (!flip_transpose) {
                 if (m < c_out && c < c_in) v = w[(((long)m * c_in + c) * k + i) * k + j];
             } else {
@@ -1756,7 +1773,7 @@ __global__ void __launch_bounds__(256) pack_weights_h_batch_kernel(PackHJobs b)
     while (t + 1 < b.n && (int)blockIdx.x >= b.start[t + 1]) ++t;
     const PackHJobDev &jb = b.job[t];
     const int k = jb.k, k2 = k * k, MT = jb.mt, map4 = jb.map4, flip = jb.flip_transpose;
-    const int OC = map4 ? 1 : 4, CS = map4 ? (k + 3) / 4 : k, nchunks = (jb.gemm_c8 + OC - 1) / OC, Cc = 8 * OC;
+    const int OC = map4 ? 1 : 4, NF = pack_frags(map4, k), nchunks = (jb.gemm_c8 + OC - 1) / OC, Cc = 8 * OC;
     const int lb = (int)blockIdx.x - b.start[t], mtile = lb / nchunks, ch = lb - mtile * nchunks;
     const int m0 = mtile * 16, c0 = ch * Cc;                  // first GEMM output map / GEMM input map of the slab
     // forward: slab[ml][cl*k2 + tap] = W[m0+ml][c0+cl][tap]; data-gradient operator: slab[cl][ml*k2 + tap] =
@@ -1771,22 +1788,23 @@ __global__ void __launch_bounds__(256) pack_weights_h_batch_kernel(PackHJobs b)
         pack_slab[r * (run + 1) + rem] = v;
     }
     __syncthreads();
-    const int units = CS * k * 64;
-    const long frag0 = (((long)(mtile / MT) * nchunks + ch) * CS * k) * MT + mtile % MT;
+    const int units = NF * 64;
+    const long frag0 = (((long)(mtile / MT) * nchunks + ch) * NF) * MT + mtile % MT;
     for (int u = threadIdx.x; u < units; u += 256) {
-        const int l16 = u & 15, g = (u >> 4) & 3, ci = u >> 6, cs = ci / k, i = ci - cs * k;
-        const int j = map4 ? 4 * cs + pack_col(map4, g) : cs;
+        const int l16 = u & 15, g = (u >> 4) & 3, f = u >> 6;
+        int i, j;
+        const bool tap = pack_tap(map4, k, f, g, i, j);
         unsigned short h[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int cl = map4 ? e : g * 8 + e;
             float v = 0.f;
-            if (j < k) v = flip ? pack_slab[cl * (run + 1) + l16 * k2 + (k - 1 - i) * k + (k - 1 - j)] : pack_slab[l16 * (run + 1) + cl * k2 + i * k + j];
+            if (tap) v = flip ? pack_slab[cl * (run + 1) + l16 * k2 + (k - 1 - i) * k + (k - 1 - j)] : pack_slab[l16 * (run + 1) + cl * k2 + i * k + j];
             h[e] = H<DT>::cvt(v);
         }
         uint4v out = {(unsigned)h[0] | ((unsigned)h[1] << 16), (unsigned)h[2] | ((unsigned)h[3] << 16),
                       (unsigned)h[4] | ((unsigned)h[5] << 16), (unsigned)h[6] | ((unsigned)h[7] << 16)};
-        *reinterpret_cast<uint4v *>(jb.wp + (frag0 + (long)ci * MT) * 512 + (g * 16 + l16) * 8) = out;
+        *reinterpret_cast<uint4v *>(jb.wp + (frag0 + (long)f * MT) * 512 + (g * 16 + l16) * 8) = out;
     }
 }
 
@@ -1796,10 +1814,11 @@ __global__ void __launch_bounds__(256) pack_weights_h_batch_kernel(PackHJobs b)
 //
 // 1x1: never.  Of 156 layers and data gradients (32 -> 64 to 1024 -> 512 maps, 48 -> 200 among them, 32^2 to 8 x 512^2, bf16) none is
 // faster here than there beyond half a percent.
-// k > 4: by rounds of tiles per CU, here and there.  A tile of the kernel for many maps costs 1.25 (5x5, 6x6), 1.6 (8x8) and
-// 2.5 (10x10) of conv_h_kernel's: over 928 layers (32 to 128 -> 64 to 1024 maps, 8^2 to 3 x 300^2, d = 1 to 8, bf16) the kernel
+// k > 4: by rounds of tiles per CU, here and there.  A tile of the kernel for many maps costs 1.04 (5x5, 6x6), 1.6 (8x8) and
+// 2.2 (10x10) of conv_h_kernel's; with the columns left padded to four it was 1.25, 1.6 and 2.5: over 928 layers (32 to 128 -> 64 to 1024 maps, 8^2 to 3 x 300^2, d = 1 to 8, bf16) the kernel
 // for many maps took 0.95 to 2.74 of the time below these lines (10x10 64 -> 64 at 32^2: 79 us of 37, 8x8 at 250^2: 66 of 55)
-// and 0.53 to 1.07 above (10x10 64 -> 256 at 250^2: 184 us of 259).
+// and 0.53 to 1.07 above (10x10 64 -> 256 at 250^2: 184 us of 259).  Nineteen layers between the two lines (5x5, 6x6 and 10x10, 32 to 192
+// -> 192 to 1024 maps): there 0.70 to 0.99 of the time here.
 // 3x3 to 64 maps, `once` = no CU has more than one of the smallest tiles there.  A launch then lasts as long as one tile: here
 // 4.9 us + 2.65 a chunk of 32 input maps (2.0 up to 64 columns, where half of the waves idle), there 5.3 + 1.65 forward and
 // 6.4 + 1.8 in a data gradient, which reads zeros around the image and a mask (982 and 990 layers of 32 to 256 maps, 12^2 to
@@ -1833,7 +1852,7 @@ int conv_h_size_mt(int gemm_m, int gemm_c8, int k, int d, int n, int Ho, int Wo,
     }
     const long here = conv_h_big_square(k, mt, d, gemm_m) ? std::min(rounds(mt, 128, 4), rounds(mt, 64, 8)) : rounds(mt, 128, 4);
     const long there = conv_wide_big_path(a).shape == 2 ? rounds(4, 32, 16) : rounds(4, 64, 8);
-    return 100 * here < (k == 10 ? 250 : k == 8 ? 160 : 125) * there ? mt : 0;
+    return 100 * here < (k == 10 ? 220 : k == 8 ? 160 : 104) * there ? mt : 0;
 }
 
 // ... for the forward layers of the U-Net and the USK-Net.  Many maps on a small image: with one persistent workgroup per CU
@@ -1863,14 +1882,12 @@ static int packed_map4(int gemm_m, int gemm_c8, int k, int mt)
 // size in 16-bit elements of the packing of a GEMM with gemm_m output maps and gemm_c8 input octets
 long packed_h_elems(int gemm_m, int gemm_c8, int k, int mt)
 {
-    const bool tapcols = mt > 0 && (mt & CONV_H_TAPCOLS) != 0;
+    const int map4 = packed_map4(gemm_m, gemm_c8, k, mt);
     if (mt > 0) mt &= ~CONV_H_TAPCOLS;
     if (mt <= 0) mt = packed_mt(gemm_m, gemm_c8, k);
     const int m_tiles = (gemm_m + 15) / 16, mgroups = (m_tiles + mt - 1) / mt;
-    const bool map4 = k >= 4 || tapcols;
-    const int OC = map4 ? 1 : 4, CS = map4 ? (k + 3) / 4 : k;
-    const int nchunks = (gemm_c8 + OC - 1) / OC;
-    return (long)mgroups * nchunks * CS * k * mt * 512;
+    const int OC = map4 ? 1 : 4, nchunks = (gemm_c8 + OC - 1) / OC;
+    return (long)mgroups * nchunks * pack_frags(map4, k) * mt * 512;
 }
 
 hipError_t launch_pack_weights_h(const float *w_oihw, void *wp, int dtype, int c_out, int c_in, int k,
@@ -1909,8 +1926,8 @@ hipError_t launch_pack_weights_h_batch(const PackHJob *jobs, int n, int dtype, h
         o.total = packed_h_elems(o.gemm_m, o.gemm_c8, j.k, j.mt);
         o.mt = j.mt > 0 ? (j.mt & ~CONV_H_TAPCOLS) : 0;
         if (o.mt <= 0) o.mt = packed_mt(o.gemm_m, o.gemm_c8, j.k);
-        const int OC = o.map4 ? 1 : 4, CS = o.map4 ? (j.k + 3) / 4 : j.k, nchunks = (o.gemm_c8 + OC - 1) / OC;
-        const long tiles = o.total / ((long)CS * j.k * 512);                 // (map tiles of all groups) x chunks
+        const int OC = o.map4 ? 1 : 4, nchunks = (o.gemm_c8 + OC - 1) / OC;
+        const long tiles = o.total / ((long)pack_frags(o.map4, j.k) * 512);                 // (map tiles of all groups) x chunks
         if (tiles % nchunks != 0) return hipErrorInvalidValue;
         smem = std::max(smem, sizeof(float) * (16 * 8 * OC * j.k * j.k + 32));
         b.start[t] = (int)blocks;

@@ -1,9 +1,10 @@
 // 16-bit convolution with many output maps and a large kernel (5x5, 6x6, 8x8, 10x10; 64 maps and more, forward and data
 // gradient): the scheme of kernels_conv_wide_h.hip with the four lane groups of the MFMA on four kernel columns of one input octet.
 //
-// A chunk is one input octet; its kernel is walked in steps of four columns x KR rows (KR = 4 or 5; 3 for 6x6), columns beyond
-// the kernel have zero weights.  A step's weights (64 maps: 4 KR fragments of 1 KB) lie in a ring of three slots, two steps
-// ahead; the input tile of the next octet (a row is 4 ceil(k/4) - 1 kernel strides wider than the output) loads meanwhile.
+// A chunk is one input octet; its kernel is walked in steps of four columns x KR rows (KR = 4 or 5; 3 for 6x6), and the one or two
+// columns left behind the last four in one step more, whose fragments hold four or two kernel rows of them (as a column step of
+// their own, padded with zero weights, they were a sixth of the MFMAs at 10x10, a quarter at 6x6 and three tenths at 5x5).  A step's
+// weights (64 maps: 4 KR fragments of 1 KB) lie in a ring of three slots, two steps ahead; the input tile of the next octet loads meanwhile.
 // What bounded conv_h_kernel here is LDS: 16 maps x 64 pixels a wave at 10x10 are 23 fragments read per 40 MFMAs, more than the
 // 128 bytes a CU moves per cycle while the matrix unit keeps up.  A wave of this kernel multiplies 32 maps x 128 pixels: 22
 // fragments per 80 MFMAs.
@@ -11,9 +12,10 @@
 // The lane groups take the columns in the order 0, 2, 1, 3 (the packing does the same): ds_read_b128 serves lanes of groups 0
 // and 1 (2 and 3) together, and columns two kernel strides apart fall on different banks at stride 8, one apart on the same.
 //
-// Measured (bf16, us, conv_h_kernel -> here): 10x10 d = 8 192 -> 1024 at 200^2 756 -> 496 (1.30 PFLOP/s; the zero columns are a
-// sixth of the MFMAs), 8x8 d = 8 128 -> 512 at 314^2 640 -> 544 (1.03: 1296 tiles are 5.06 rounds of 256), 6x6 64 -> 128 at 344^2
-// 107 -> 86, 5x5 d = 2 48 -> 128 at 169^2 45 -> 28.  4x4 layers stay on the ring kernel: a step would be 32 MFMAs a wave.
+// Measured (bf16, us, conv_h_kernel -> here with the columns left padded to four -> here): 10x10 d = 8 192 -> 1024 at 200^2 756 -> 457 -> 411
+// (1.57 PFLOP/s, where the clock falls with the power), 64 -> 256 at 322^2 - -> 173 -> 151; 8x8 d = 8 128 -> 512 at 314^2 640 -> 490 (1.14:
+// 1296 tiles are 5.06 rounds of 256); 6x6 64 -> 128 at 344^2 107 -> 81 -> 64, d = 8 128 -> 128 at 300^2 - -> 137 -> 105; 5x5 64 -> 128 at
+// 2 x 300^2 - -> 95 -> 79.  4x4 layers stay on the ring kernel: a step would be 32 MFMAs a wave.
 #include "conv_wide.h"
 
 namespace sk {
@@ -30,7 +32,10 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
     using T = WideTile<8, KS, MG, R, XW>;
     extern __shared__ uint4v lds[];
     constexpr int RR = T::RT + KS - 1;
-    constexpr int KR = big_rows<KS>(), RP = KS / KR, CS = (KS + 3) / 4, NS = CS * RP;    // rows of a step, steps of a chunk
+    constexpr int KR = big_rows<KS>(), RP = KS / KR, CF = KS / 4;             // rows of a step, steps of four columns: of one column step, all
+    constexpr int TC = KS % 4, TR = TC ? 4 / TC : 1, TF = TC ? (KS + TR - 1) / TR : 0;   // columns left; kernel rows of their fragments, fragments
+    constexpr int NS = CF * RP + (TC ? 1 : 0), CHUNK_BYTES = (CF * KS + TF) * 4096;
+    static_assert(TC != 3 && TF <= KR, "the columns left are one step");
     constexpr int SLAB = KR * 4;                               // 1 KB weight fragments of a step
     constexpr int NW = (SLAB + 7) / 8;                         // weight loads of a wave per step
 
@@ -62,13 +67,13 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
         c.ch = 0;
         c.o_in = 0;
         c.x = reinterpret_cast<const char *>(q.a.x) + (long)c.p.b * (q.a.xb8 > 0 ? q.a.xb8 : q.a.c8_in) * plane;
-        c.w = reinterpret_cast<const char *>(q.a.wp) + (long)c.p.mg * q.w.nchunks * (CS * KS * 4 * 1024);
+        c.w = reinterpret_cast<const char *>(q.a.wp) + (long)c.p.mg * q.w.nchunks * CHUNK_BYTES;
     };
     // the chunk after c; false at the end of this workgroup's list
     auto step_chunk = [&](Cursor &c) {
         if (++c.ch < nchunks) {
             c.x += plane;
-            c.w += CS * KS * 4 * 1024;
+            c.w += CHUNK_BYTES;
             if (grp8 > 0 && ++c.o_in == grp8) {
                 c.o_in = 0;
                 c.x += skip_bytes;
@@ -109,9 +114,10 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
         if constexpr (PAD) wide_load_lds(xoff[u] != ~0u ? c.x + xoff[u] : zeros + lane16, dst);
         else wide_load_lds(c.x + xoff[u], dst);
     };
-    // step s of a chunk: column step s / RP, kernel rows from (s % RP) * KR on
+    // step s of a chunk: column step s / RP, kernel rows from (s % RP) * KR on; the last one: the columns left
     auto load_w = [&](const Cursor &c, int s, int sl, int u) {
-        wide_load_lds(c.w + ((s / RP) * KS + (s % RP) * KR) * 4096 + wblk[u] * 1024 + lane16, wbuf + (sl * SLAB + wblk[u]) * 64);
+        const int blk = TF < KR && TC && s == NS - 1 ? min(wblk[u], TF * 4 - 1) : wblk[u];
+        wide_load_lds(c.w + s * (KR * 4096) + blk * 1024 + lane16, wbuf + (sl * SLAB + blk) * 64);
     };
 
     floatx4 acc[R][WM];
@@ -121,11 +127,18 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
         for (int mt = 0; mt < WM; ++mt) acc[y][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     const int dil = k.a.d, col = (g >> 1) | ((g & 1) << 1);    // this lane group's kernel column within a column step
-    const uint4v *const xfrag = xbuf + (pwv / XW) * R * pw + (pwv % XW) * 16 + l16 + col * dil;
+    const int pixel = (pwv / XW) * R * pw + (pwv % XW) * 16 + l16;
+    const uint4v *const xfrag = xbuf + pixel + col * dil;
+    // its tap of a fragment of the columns left: two columns of two rows, or four rows of one (where the last fragment of 5x5 has one row)
+    const uint4v *const xtail = xbuf + pixel + (4 * CF + (TC == 2 ? g >> 1 : 0)) * dil + (TC == 2 ? g & 1 : g) * pw;
+    const uint4v *const xend = xbuf + pixel + 4 * CF * dil + (KS - 1) * pw;
     const uint4v *const wfrag = wbuf + wm * WM * 64 + lane;
     // One step; its N loads for later steps go between the MFMAs.
-    auto step = [&](bool act, int buf, int s, int sl, auto loads, auto &&load) {
-        constexpr int N = decltype(loads)::value, GROUPS = KR * R, SPREAD = N > 0 ? GROUPS / std::max(N, 1) : 1;
+    auto step = [&](bool act, int buf, auto si, int sl, auto loads, auto &&load) {
+        constexpr int s = decltype(si)::value, N = decltype(loads)::value;
+        constexpr bool TAIL = TC && s == NS - 1;
+        // fragments of weights; input rows that a fragment reads and the one before it does not
+        constexpr int FR = TAIL ? TF : KR, PR = TAIL ? (TC == 1 ? R : TR) : 1, GROUPS = FR * R, SPREAD = N > 0 ? GROUPS / std::max(N, 1) : 1;
         static_assert(N <= GROUPS, "one load per group of MFMAs at most");
         if (!act) {
 #pragma unroll
@@ -133,17 +146,18 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
             return;
         }
         const uint4v *wl = wfrag + sl * SLAB * 64;
-        const uint4v *xl = xfrag + buf * oct_units + (s / RP) * 4 * dil + (s % RP) * KR * pw;
-        constexpr int NREAD = KR * WM + R + KR - 1, HEAD = WM + 3;
-        uint4v af[KR][WM], bf[R + KR - 1];
-        // fragments in the order of their use: row 0's maps and the input rows, then maps and one more input row per kernel row
+        const uint4v *xl = (TAIL ? xtail : xfrag + (s / RP) * 4 * dil + (s % RP) * KR * pw) + buf * oct_units, *xe = xend + buf * oct_units;
+        constexpr int NB = R + (FR - 1) * PR, NREAD = FR * WM + NB, HEAD = WM + 3;
+        uint4v af[FR][WM], bf[NB];
+        // fragments in the order of their use: the first's maps and input rows, then maps and the input rows that come on
+        auto row = [&](int q) { bf[q] = TAIL && TC == 1 && q >= R ? xe[(q - R) * pw] : xl[q * pw]; };
         auto read = [&](int q) {
             if (q < WM) af[0][q] = wl[q * 64];
-            else if (q < WM + R) bf[q - WM] = xl[(q - WM) * pw];
+            else if (q < WM + R) row(q - WM);
             else {
-                const int i = 1 + (q - WM - R) / (WM + 1), m = (q - WM - R) % (WM + 1);
+                const int i = 1 + (q - WM - R) / (WM + PR), m = (q - WM - R) % (WM + PR);
                 if (m < WM) af[i][m] = wl[(i * 4 + m) * 64];
-                else bf[R + i - 1] = xl[(R + i - 1) * pw];
+                else row(R + (i - 1) * PR + m - WM);
             }
         };
 #pragma unroll
@@ -154,7 +168,7 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
             const int i = q / R, y = q % R;
             if (HEAD + q < NREAD) read(HEAD + q);
 #pragma unroll
-            for (int mt = 0; mt < WM; ++mt) acc[y][mt] = wide_mfma<DT>(af[i][mt], bf[y + i], acc[y][mt]);
+            for (int mt = 0; mt < WM; ++mt) acc[y][mt] = wide_mfma<DT>(af[i][mt], bf[y + PR * i], acc[y][mt]);
             if (q % SPREAD == SPREAD - 1 && q / SPREAD < N) load(q / SPREAD);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -213,7 +227,7 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
             wide_barrier();
             // the cursor moves on while the other wave of the SIMD multiplies (its input loads are all under way)
             if (s == NS - 1 && wave < 4) move();
-            step(act, buf, s, sl, std::integral_constant<int, NW + XN>{}, [&](int q) {
+            step(act, buf, si, sl, std::integral_constant<int, NW + XN>{}, [&](int q) {
                 if (q < NW) {
                     if (s + 2 < NS) load_w(cur, s + 2, ahead, q);
                     else load_w(nxt, s + 2 - NS, ahead, q);
@@ -240,12 +254,30 @@ __global__ __launch_bounds__(512, 2) void conv_wide_big_h_kernel(WideArgs k)
         constexpr int s = decltype(si)::value, N = s + 2 < NS ? NW : 0;
         const int ahead = sl == 0 ? 2 : sl - 1;
         wide_barrier();
-        step(act, buf, s, sl, std::integral_constant<int, N>{}, [&](int q) { load_w(cur, s + 2, ahead, q); });
+        step(act, buf, si, sl, std::integral_constant<int, N>{}, [&](int q) { load_w(cur, s + 2, ahead, q); });
         wide_wait<N>();
         sl = sl == 2 ? 0 : sl + 1;
     });
     if (act) epilogue(cur);
 }
+
+int tile_units(int pw, int rows) { return (rows * pw + 63) / 64 * 64; }
+
+template <int KS>
+size_t big_smem(const WideGeom &w)
+{
+    return (size_t)2 * w.oct_units * 16 + (size_t)3 * big_rows<KS>() * 4096 + (size_t)w.pgroups * 64 * sizeof(float);
+}
+
+// (the biases of all maps share the LDS with the tile: see conv_h_wide)
+template <int KS>
+bool big_fits(const WideGeom &w)
+{
+    return w.oct_units / 64 <= 48 && big_smem<KS>(w) <= 160 * 1024;
+}
+
+// input loads of a wave per chunk
+int big_loads(int units) { return units / 64 <= 16 ? 2 : units / 64 <= 32 ? 4 : 6; }
 
 template <int KS, int XW>
 WideGeom big_geom(const ConvHArgs &a)
@@ -262,28 +294,21 @@ WideGeom big_geom(const ConvHArgs &a)
     w.tiles_lo = (q + T::RT - 1) / T::RT;
     w.ytiles = w.rem * w.tiles_hi + (a.d - w.rem) * w.tiles_lo;
     if (w.tiles_lo < 1) w.tiles_lo = 1;
+    // Which tiles are taken stays with rows of whole column steps, for which it was measured (`fits`).  The two columns left of 6x6 and 10x10
+    // need fewer, and neighbouring lane groups read them from neighbouring rows, which fall on different banks 16 units apart modulo 16
+    // (see above)
     w.pw = T::TX + (4 * ((KS + 3) / 4) - 1) * a.d;
-    w.oct_units = ((T::RT + KS - 1) * w.pw + 63) / 64 * 64;
+    w.oct_units = tile_units(w.pw, T::RT + KS - 1);
+    const bool fits = big_fits<KS>(w);
+    const int even = (T::TX + (KS - 1) * a.d + 15) / 16 * 16;
+    if (KS % 4 == 2 && even <= w.pw) {
+        w.pw = even;
+        w.oct_units = tile_units(w.pw, T::RT + KS - 1);
+    }
     const long tiles = (long)w.xtiles * w.ytiles * w.mgroups * a.n;
-    w.tiles = w.total = tiles > 0x3fffffffL ? 0 : (int)tiles;
+    w.tiles = w.total = !fits || tiles > 0x3fffffffL ? 0 : (int)tiles;
     return w;
 }
-
-template <int KS>
-size_t big_smem(const WideGeom &w)
-{
-    return (size_t)2 * w.oct_units * 16 + (size_t)3 * big_rows<KS>() * 4096 + (size_t)w.pgroups * 64 * sizeof(float);
-}
-
-// (the biases of all maps share the LDS with the tile: see conv_h_wide)
-template <int KS>
-bool big_fits(const WideGeom &w)
-{
-    return w.tiles >= 1 && w.oct_units / 64 <= 48 && big_smem<KS>(w) <= 160 * 1024;
-}
-
-// input loads of a wave per chunk
-int big_loads(const WideGeom &w) { return w.oct_units / 64 <= 16 ? 2 : w.oct_units / 64 <= 32 ? 4 : 6; }
 
 template <int DT, int KS, int XW, int NX, bool PAD, int OUT>
 hipError_t launch_big_n(const WideArgs &k, size_t smem, hipStream_t stream)
@@ -308,9 +333,9 @@ hipError_t launch_big_x(const ConvHArgs &a, hipStream_t stream)
     k.a = a;
     k.w = big_geom<KS, XW>(a);
     const size_t smem = big_smem<KS>(k.w);
-    if (!big_fits<KS>(k.w) || !a.zeros) return hipErrorInvalidValue;
+    if (k.w.tiles < 1 || !a.zeros) return hipErrorInvalidValue;
     if ((long)a.H * a.W * 16 >= 0xffffffffL || (long)(a.out_f32 ? a.c_out * 4L : a.c8_out_total * 16L) * a.OH * a.OW >= 0x7fffffffL) return hipErrorInvalidValue;
-    switch (big_loads(k.w)) {
+    switch (big_loads(k.w.oct_units)) {
     case 2: return launch_big_n<DT, KS, XW, 2, PAD, OUT>(k, smem, stream);
     case 4: return launch_big_n<DT, KS, XW, 4, PAD, OUT>(k, smem, stream);
     default: return launch_big_n<DT, KS, XW, 6, PAD, OUT>(k, smem, stream);
@@ -325,7 +350,7 @@ int big_columns(const ConvHArgs &a)
     if (a.out_f32) return 4;
     const WideGeom sq = big_geom<KS, 2>(a), flat = big_geom<KS, 4>(a);
     const int cus = wide_cus();
-    return big_fits<KS>(sq) && (sq.tiles + cus - 1) / cus <= (flat.tiles + cus - 1) / cus ? 2 : 4;
+    return sq.tiles >= 1 && (sq.tiles + cus - 1) / cus <= (flat.tiles + cus - 1) / cus ? 2 : 4;
 }
 
 template <int DT, int KS>
@@ -342,7 +367,7 @@ ConvHPath big_path(const ConvHArgs &a)
 {
     const int columns = big_columns<KS>(a);
     const WideGeom w = columns == 2 ? big_geom<KS, 2>(a) : big_geom<KS, 4>(a);
-    return {big_fits<KS>(w) ? 2 : -1, columns, 1, big_loads(w)};
+    return {w.tiles >= 1 ? 2 : -1, columns, 1, big_loads(w.oct_units)};
 }
 
 template <int DT>
