@@ -684,6 +684,7 @@ template <class V> __device__ __forceinline__ void pack_f32_forms(float *wp, int
         for (int e = 0; e < 8; ++e) v[e] = j < k ? value(c + e, i, j, o) : 0.f;
         uint4v p[2];
         split2(v, scale, p);
+        split_infinite(v, p);
 #pragma unroll
         for (int s = 0; s < 2; ++s) frag[((ci * m_tiles + tile) * 2 + s) * 64 + lane] = p[s];
     }

@@ -192,7 +192,8 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
         const floatx4 m4 = *reinterpret_cast<const floatx4 *>(most + (chunk & 1) * 4);
         float m = split_max(split_max(m4[0], m4[1]), split_max(m4[2], m4[3]));
         m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
-        if (__builtin_bit_cast(unsigned, m) == 0x7f800000u) {            // infinities don't decide the scale of the finite samples beside them
+        const bool infinite = __builtin_bit_cast(unsigned, m) == 0x7f800000u;
+        if (infinite) {                                                  // infinities don't decide the scale of the finite samples beside them
             float f = 0.f;
             for (int q = 0; q < UPT; ++q)
                 for (int e = 0; e < 8; ++e) f = fmaxf(f, split_finite(fabsf(xr[q][e])));
@@ -203,9 +204,9 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
             m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
             __syncthreads();
         }
-        const int need = split_exponent(m, 15);
+        const int need = split_exponent(m, 14);
         if (need < se) {
-            const int to = split_exponent(m, 12);                        // three bits of room: neighbouring chunks don't ask again
+            const int to = split_exponent(m, 12);                        // two bits of room: neighbouring chunks don't ask again
             if (chunk > 0) {
                 const float f = to - se < -126 ? 0.f : split_pow2(to - se);
 #pragma unroll
@@ -221,6 +222,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
             if (256 * q + 255 >= RR * (T::TX + KS - 1) && tid + 256 * q >= units) continue;
             uint4v p[2];
             split2(xr[q], scale, p);
+            if (infinite) split_infinite(xr[q], p);
             if constexpr (PADZ)
                 if (!ok[q]) p[0] = p[1] = uint4v{0, 0, 0, 0};
 #pragma unroll

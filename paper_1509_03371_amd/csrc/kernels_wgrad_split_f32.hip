@@ -196,8 +196,8 @@ __global__ __launch_bounds__(64 * WS_WAVES) void wgrad_split_f32_kernel(Args a)
             wide_barrier();
             read();
         }
-        nx = split_exponent(mx, 15) < sx ? split_exponent(mx, 12) : sx;
-        ny = split_exponent(my, 15) < sy ? split_exponent(my, 12) : sy;
+        nx = split_exponent(mx, 14) < sx ? split_exponent(mx, 12) : sx;
+        ny = split_exponent(my, 14) < sy ? split_exponent(my, 12) : sy;
     };
     float bsum[8] = {};
     auto commit = [&](int step, int slot, auto set) {

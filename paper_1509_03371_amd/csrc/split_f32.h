@@ -1,6 +1,7 @@
 // fp32 values as pairs of fp16 values, for products on the 16-bit matrix unit.
 //
-// A value times a power of two that takes the largest of its kind to 2^12 .. 2^16 is the sum of an fp16 value and the fp16-rounded rest:
+// A value times a power of two that takes the largest of its kind to 2^12 .. 2^15 (where fp16 ends, 2^16, values round up to infinity) is
+// the sum of an fp16 value and the fp16-rounded rest:
 // exactly or (a quarter of the values) to one bit of 24, as long as it is above 2^-17 of the largest, and to 2^-40 of the largest below.  A
 // product takes three of the four partial products; the fourth is below 2^-22 of it, on average 2^-24 and of either sign.  The matrix unit
 // adds 32 products to an fp32 sum at a time, where its fp32 form adds four, so long sums are rounded less often and come out closer to 64
@@ -35,6 +36,20 @@ __device__ __forceinline__ void split2(const float (&v)[8], float scale, uint4v 
         const split_halfx2 l = {(_Float16)__builtin_fmaf(v[e], scale, -(float)h[0]), (_Float16)__builtin_fmaf(v[e + 1], scale, -(float)h[1])};
         p[0][e / 2] = __builtin_bit_cast(unsigned, h);
         p[1][e / 2] = __builtin_bit_cast(unsigned, l);
+    }
+}
+
+// Infinities among v stand in the second part alone: there they meet the first part of the other operand, whose sign is the value's, and no
+// other product (inf - inf of two of them would come out as NaN, which ReLU drops)
+__device__ __forceinline__ void split_infinite(const float (&v)[8], uint4v (&p)[2])
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const unsigned bits = __builtin_bit_cast(unsigned, v[e]);
+        if ((bits & 0x7fffffffu) != 0x7f800000u) continue;
+        const unsigned at = 16 * (e & 1), keep = ~(0xffffu << at);
+        p[0][e / 2] &= keep;
+        p[1][e / 2] = (p[1][e / 2] & keep) | ((bits >> 16 & 0x8000u) | 0x7c00u) << at;
     }
 }
 

@@ -95,6 +95,37 @@ def test_infinities_and_nan_stay_where_they_are():
     assert np.all(np.abs(got - clean)[~hit] <= 2 * (384 + 9) * 2.0 ** -24 * size[~hit])
 
 
+@pytest.mark.parametrize("k", [3, 4])
+def test_samples_just_below_a_power_of_two(k):
+    # the maps behind the first eight are eight times as large and end an ulp below 16: as far as the scale of the first ones reaches
+    rng = np.random.default_rng(7)
+    img = rng.uniform(-1.5, 1.5, (1, 40, 70, 130)).astype(np.float32)
+    img[:, 8:] *= 8
+    img[:, 8:, ::3, ::5] = np.nextafter(np.float32(16), np.float32(0))
+    w0 = rng.standard_normal((48, 40, k, k)).astype(np.float32)
+    w0[::5] = np.nextafter(np.float32(4), np.float32(0))
+    check(k, 2, img, w0, np.zeros(48, np.float32))
+
+
+@pytest.mark.parametrize("which", ["samples", "weights"])
+def test_infinities_keep_their_sign(which):
+    # as on the fp32 matrix unit: ReLU drops minus infinity and keeps plus infinity
+    rng = np.random.default_rng(8)
+    img = rng.uniform(0.5, 1.5, (1, 24, 60, 120)).astype(np.float32)
+    w0 = rng.standard_normal((48, 24, 4, 4)).astype(np.float32)
+    w0 += np.sign(w0) * np.float32(0.01)
+    if which == "samples":
+        img[0, 2, 20, 30], img[0, 13, 40, 90] = np.inf, -np.inf
+    else:
+        w0[3, 5, 1, 2], w0[17, 20, 0, 3] = np.inf, -np.inf
+    got = forward(4, 1, img, w0, np.zeros(48, np.float32))
+    ref = OL.conv_sk(img, w0, np.zeros(48), 1, relu=True)
+    assert np.isinf(ref).any() and np.array_equal(np.isinf(got), np.isinf(ref))
+    clean = OL.conv_sk(np.where(np.isinf(img), 0, img), np.where(np.isinf(w0), 0, w0), np.zeros(48), 1, relu=False)
+    dropped = (ref == 0) & (clean > 1)                       # minus infinity
+    assert dropped.any() and not got[dropped].any()
+
+
 @pytest.mark.parametrize("relu", [False, True])
 @pytest.mark.parametrize("k,d,maps,classes,n,h,w", [
     (4, 1, 8, 24, 2, 19, 71), (4, 2, 20, 25, 1, 47, 66), (4, 8, 48, 48, 1, 70, 131), (4, 9, 16, 24, 1, 70, 80), (3, 1, 40, 32, 1, 40, 131),

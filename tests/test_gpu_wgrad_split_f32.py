@@ -12,7 +12,7 @@ import sk_synth as S
 pytestmark = pytest.mark.gpu
 
 
-def gradient(c_in, c_out, d, n, h, w, dtype="f32", scale=None):
+def gradient(c_in, c_out, d, n, h, w, dtype="f32", scale=None, maps=None):
     """(gradient of a 4x4 layer, its bias gradient, the layer's input, its error map)"""
     from paper_1509_03371_amd import binding as B
     rng = np.random.default_rng(h + w)
@@ -20,8 +20,14 @@ def gradient(c_in, c_out, d, n, h, w, dtype="f32", scale=None):
     for i in range(3):
         s = net.conv_shape(i)
         net.set_weights(i, (rng.standard_normal(s) / np.sqrt(np.prod(s[1:]))).astype(np.float32), rng.standard_normal(s[0]).astype(np.float32) * np.float32(i != 0))
+    if maps is not None:                                    # every map of the layer's input is this image
+        w0 = np.zeros(net.conv_shape(0), np.float32)
+        w0[:, 0] = 1
+        net.set_weights(0, w0, np.zeros(c_in, np.float32))
     net.plan(n, h, w, pad=False, training=True)
     img = rng.standard_normal((n, 3, h, w)).astype(np.float32)
+    if maps is not None:
+        img[:, 0] = maps
     if scale is not None:
         img *= scale
     net.forward(torch.from_numpy(img).cuda())
@@ -66,6 +72,18 @@ def test_magnitudes(way):
     ramp = np.float32(2.0) ** np.linspace(-12, 12, h).astype(np.float32)[:, None]
     scale = {"rising": ramp, "falling": ramp[::-1], "dark half": np.where(np.arange(w) < 150, np.float32(1e-7), np.float32(1))[None, :]}[way]
     dw, db, x, dy = gradient(48, 48, d, 1, h, w, scale=scale.astype(np.float32))
+    ref, _ = sums(x, dy, d)
+    assert np.linalg.norm(dw - ref) <= 1e-6 * np.linalg.norm(ref)
+
+
+def test_samples_just_below_a_power_of_two():
+    # rows behind the first four are eight times as large and end an ulp below 16: as far as the scale of the first ones reaches
+    h, w, d = 180, 300, 1
+    maps = np.random.default_rng(9).uniform(0.1, 1.5, (1, h, w)).astype(np.float32)
+    maps[:, 4:] *= 8
+    maps[:, 4::3, ::5] = np.nextafter(np.float32(16), np.float32(0))
+    dw, db, x, dy = gradient(48, 48, d, 1, h, w, maps=maps)
+    assert x.max() == maps.max()
     ref, _ = sums(x, dy, d)
     assert np.linalg.norm(dw - ref) <= 1e-6 * np.linalg.norm(ref)
 
