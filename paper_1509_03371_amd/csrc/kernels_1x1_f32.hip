@@ -395,7 +395,7 @@ __global__ __launch_bounds__(P1_THREADS, 2) void head1x1_kernel(HeadArgs a, int 
 // (at most three): of dY and X.  Both operands come from global memory as they are: lane (g, l16) loads pixels 4 g .. 4 g + 3 of map l16 of a
 // tile, the operand of four K steps.  Eight waves, each with sums of its own, stride over blocks of 16 pixels and meet in LDS at the end; a
 // workgroup writes one private copy, which wgrad_reduce_kernel adds up.  The sums of dY come along in registers.
-// 48 -> 200 maps at 512^2, sums of dY and reduction included: 267 -> 142 us; 200 -> 2: 146 -> 45 (260 and 212 MB read; 8 x 512^2 2.2 ms -> 1.0,
+// 48 -> 200 maps at 512^2, sums of dY and reduction included: 267 -> 142 us, 104 with a workgroup on every CU; 200 -> 2: 146 -> 45 (260 and 212 MB read; 8 x 512^2 2.2 ms -> 1.0,
 // 1.04 -> 0.36).
 constexpr int W1_WAVES = 8, W1_THREADS = 64 * W1_WAVES, W1_PX = 16, W1_ROUND = 4;
 

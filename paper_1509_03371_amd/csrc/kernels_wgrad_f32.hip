@@ -1376,6 +1376,10 @@ static int wgrad_max_copies(int groups)
     return c < 1 ? 1 : c;
 }
 
+// ... but one a CU for the 1x1 kernel of few maps on one side, whose workgroups own the whole gradient (48 -> 200 maps at 512^2: 151 us with the
+// 128 copies that the groups of the other kernel's tiling leave, 93 with 256)
+constexpr int WG_1X1_COPIES = 256;
+
 // floats of the bias partials: one per map and per slice (the slices of bias_grad_kernel, or one per workgroup
 // of the 16-bit kernel, which sums dY itself)
 static size_t wgrad_bias_floats(int c_out) { return (size_t)(c_out + 15) / 16 * 16 * (WG_MAX_BLOCKS > BG_SLICES ? WG_MAX_BLOCKS : BG_SLICES); }
@@ -1397,6 +1401,7 @@ size_t wgrad_f32_scratch_floats(int c_out, int c_in, int k)
         copies = std::max(copies, wgrad_max_copies(wgrad_tile_groups(MT2, NT2, MB2, NB2)));
         NTk = std::max(NTk, NT2);
     }
+    if (k == 1 && wgrad1x1_f32_supported(c_in, c_out, 1, 1)) copies = std::max(copies, WG_1X1_COPIES);
     const size_t segs = (size_t)copies * MTo * 16 * NTk * 16 + wgrad_bias_floats(c_out);
     return std::max(segs, wgrad_rows_h_supported(c_in, c_out, k, 1) ? wgrad_rows_h_scratch_floats(c_in, c_out) : (size_t)0);
 }
@@ -1639,7 +1644,9 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     // once by the reduction -- cost more than a second workgroup per CU hides (measured 96 + 12 -> 87 + 7 us per layer)
     if (h_path && wgrad_tile_groups(a.MTo, a.NTk, MB, NB) == 1 && a.NTk >= 48 && a.total_segs < 24L * 2 * cus && resident > cus) resident = cus;
     if (resident > WG_MAX_BLOCKS) resident = WG_MAX_BLOCKS;
-    int max_copies = wgrad_max_copies(groups);
+    // 1x1 layers of few maps on one side: both operands straight from memory (84 layers, 12 x 60 to 8 x 512^2: 1.16 to 3.5 times as fast)
+    const bool w1_path = DT == 0 && k == 1 && x_bstride == 0 && grp_maps == 0 && wgrad1x1_f32_supported(c_in, c_out, n, (long)H * W);
+    int max_copies = w1_path ? std::max(wgrad_max_copies(groups), WG_1X1_COPIES) : wgrad_max_copies(groups);
     if (scratch_cap > 0) {
         // a scratch buffer of a given size: as many private copies as it holds (fewer workgroups, same sums)
         const size_t per = wgrad_copy_floats(c_out, c_in, k), bias = wgrad_bias_floats(c_out);
@@ -1661,8 +1668,6 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     // at d = 16: 25.0 us here, 29.2 there) and 1.24 to 1.55 above this line
     const bool rows_path = DT == 0 && x_bstride == 0 && grp_maps == 0 && wgrad_rows_f32_supported(c_in, c_out, k, d) &&
                            (c_in >= 16 || (a.total_segs >= 256 && a.Ho >= 4 * d));
-    // 1x1 layers of few maps on one side: both operands straight from memory (84 layers, 12 x 60 to 8 x 512^2: 1.16 to 3.5 times as fast)
-    const bool w1_path = DT == 0 && k == 1 && x_bstride == 0 && grp_maps == 0 && wgrad1x1_f32_supported(c_in, c_out, n, (long)H * W);
     const bool bias_in_kernel = db && ((h_path && MB <= 4) || rows_path || w1_path);
     if (bias_in_kernel) a.bias_part = bias_part;
     hipError_t e = hipErrorInvalidValue;
