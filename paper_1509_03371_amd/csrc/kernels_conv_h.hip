@@ -1661,6 +1661,7 @@ hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream)
     if (conv_h_wide32(a)) return launch_conv_wide32_h(a, stream);
     // the packed weights were laid out for this many map tiles per group (0 = the default choice)
     const int mt = a.mt > 0 ? a.mt : conv_h_mt(a.c_out, a.k);
+    if (conv1x1_few_h_applies(a)) return launch_conv1x1_few_h(a, mt, stream);
     if (a.img && (!conv_c1_h_applies(a, mt) || a.img_h < 1 || a.img_w < 1 || a.pad_top < 0 || a.pad_left < 0 || (a.pad_mode != 0 && a.pad_mode != 1)))
         return hipErrorInvalidValue;                                // only that kernel reads the image
     if (conv_c1_h_applies(a, mt)) {

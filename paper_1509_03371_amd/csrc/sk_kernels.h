@@ -184,6 +184,9 @@ bool conv_h_supported(int k, int d, int gemm_m);
 // does this launch (single_map set, img left null) run on the kernel that can read the fp32 image itself?
 bool conv_h_reads_image(const ConvHArgs &a);
 hipError_t launch_conv_h(const ConvHArgs &a, hipStream_t stream);
+// 1x1 layers of at most sixteen maps to fp32 sums (kernels_1x1_h.hip); mt: map tiles a group of the packed weights
+bool conv1x1_few_h_applies(const ConvHArgs &a);
+hipError_t launch_conv1x1_few_h(const ConvHArgs &a, int mt, hipStream_t stream);
 // Layers with many maps (1x1, 3x3: kernels_conv_wide_h.hip; 5x5, 6x6, 8x8, 10x10: kernels_conv_wide_big_h.hip).  Decided by
 // what the weight packing knows too, so that weights packed with mt = 0 are always packed for the kernel that reads them
 // (four map tiles per group there); where the size of the maps speaks against it conv_h_size_mt gives another mt
