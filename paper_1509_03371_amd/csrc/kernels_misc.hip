@@ -2,6 +2,8 @@
 // kernel stride (forward with tap codes, gather-form backward), per-pixel softmax and softmax
 // loss, SGD, crop-and-place copy.  One element per thread, x fastest, so that a 64-lane
 // wavefront reads and writes consecutive addresses.
+#include <type_traits>
+
 #include "mirror_index.h"
 #include "sk_kernels.h"
 
@@ -77,7 +79,7 @@ typedef unsigned uint1u __attribute__((aligned(1)));
 // Bound by HBM, but only with four columns a thread: with one, the 32 memory instructions of eight windows of 64 threads
 // cost more than their bytes (48 maps at 527x527: 36.6 -> 26.4 us with codes = 4.5 TB/s, 32.3 -> 22.6 without).  The last
 // block of a row overlaps its neighbour.
-template <bool TAP, int U>
+template <bool TAP, int U, bool NT>
 __global__ void __launch_bounds__(512) maxpool2_chain_f32_kernel(const float *__restrict__ x, float *__restrict__ y,
                                                                  uint8_t *__restrict__ tap, int H, int W, int Ho, int Wo,
                                                                  int d, int M, int nseg, int pblocks)
@@ -129,8 +131,10 @@ __global__ void __launch_bounds__(512) maxpool2_chain_f32_kernel(const float *__
                 best[c] = lower ? h2[c] : h[c];
                 if (TAP) code |= (((lower ? hc2 : hc) >> (8 * c) & 1u) | (lower ? 2u : 0u) | (best[c] > 0.f ? POOL_POSITIVE : 0u)) << (8 * c);
             }
-            *reinterpret_cast<float4u *>(dst + (long)u * ostep) = best;
-            if (TAP) *reinterpret_cast<uint1u *>(tdst + (long)u * ostep) = code;
+            if constexpr (NT) __builtin_nontemporal_store(best, reinterpret_cast<float4u *>(dst + (long)u * ostep));
+            else *reinterpret_cast<float4u *>(dst + (long)u * ostep) = best;
+            if constexpr (TAP && NT) __builtin_nontemporal_store(code, reinterpret_cast<uint1u *>(tdst + (long)u * ostep));
+            else if constexpr (TAP) *reinterpret_cast<uint1u *>(tdst + (long)u * ostep) = code;
             h = h2;
             hc = hc2;
         }
@@ -148,9 +152,14 @@ static void launch_maxpool2_chain_f32(const PoolCut &c, dim3 grid, hipStream_t s
                                       int d)
 {
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, c.block(), 0, stream, x, y, tap, H, W, Ho, Wo, d, c.len, c.nseg, c.pblocks); };
-    if (c.len >= 4) go(&maxpool2_chain_f32_kernel<TAP, 4>);
-    else if (c.len >= 2) go(&maxpool2_chain_f32_kernel<TAP, 2>);
-    else go(&maxpool2_chain_f32_kernel<TAP, 1>);
+    const auto with = [&](auto around) {
+        constexpr bool NT = decltype(around)::value;
+        if (c.len >= 4) go(&maxpool2_chain_f32_kernel<TAP, 4, NT>);
+        else if (c.len >= 2) go(&maxpool2_chain_f32_kernel<TAP, 2, NT>);
+        else go(&maxpool2_chain_f32_kernel<TAP, 1, NT>);
+    };
+    if (TAP && pool_stores_around(4L * grid.z * Ho * Wo)) with(std::integral_constant<bool, TAP>{});
+    else with(std::false_type{});
 }
 
 hipError_t launch_maxpool_f32(const float *x, float *y, uint8_t *tap, int planes, int H, int W,

@@ -4,6 +4,8 @@
 // bias gradient.  One 16-byte unit (8 maps of one pixel) per thread, pixels fastest, so a wavefront
 // moves 1 KB of consecutive addresses per access.  Comparisons are done on the exactly widened
 // fp32 values, so pooling is bit-exact in both formats.
+#include <type_traits>
+
 #include "sk_kernels.h"
 
 namespace sk {
@@ -221,8 +223,8 @@ __device__ __forceinline__ unsigned bit_planes_h(unsigned a, unsigned b)
     return (both | (both >> 15)) & 0xffffu;
 }
 
-// U: windows whose loads are in flight together
-template <int DT, bool TAP, int U>
+// U: windows whose loads are in flight together; NT: see pool_stores_around
+template <int DT, bool TAP, int U, bool NT>
 __global__ void __launch_bounds__(256) maxpool2_chain_h_kernel(const uint4v *__restrict__ x, uint4v *__restrict__ y,
                                                                unsigned *__restrict__ tap, int H, int W, int Ho, int Wo,
                                                                int d, int M, int nseg, int pblocks)
@@ -263,8 +265,13 @@ __global__ void __launch_bounds__(256) maxpool2_chain_h_kernel(const uint4v *__r
             uint4v o;
             unsigned lower;                               // whose winner lies in row y + d
             row_first_max<DT>(h, h2, o, lower);
-            dst[(long)u * ostep] = o;
-            if (TAP) tdst[(long)u * ostep] = bit_planes_h((hc & ~lower) | (hc2 & lower), lower) | (bit_planes_h(positive_h<DT>(o), 0u) << 16);
+            if constexpr (NT) __builtin_nontemporal_store(o, dst + (long)u * ostep);
+            else dst[(long)u * ostep] = o;
+            if constexpr (TAP) {
+                const unsigned code = bit_planes_h((hc & ~lower) | (hc2 & lower), lower) | (bit_planes_h(positive_h<DT>(o), 0u) << 16);
+                if constexpr (NT) __builtin_nontemporal_store(code, tdst + (long)u * ostep);
+                else tdst[(long)u * ostep] = code;
+            }
             h = h2;
             hc = hc2;
         }
@@ -284,9 +291,14 @@ static void launch_maxpool2_chain_h(const PoolCut &c, dim3 grid, hipStream_t str
         hipLaunchKernelGGL(kernel, grid, c.block(), 0, stream, static_cast<const uint4v *>(x), static_cast<uint4v *>(y),
                            static_cast<unsigned *>(tap), H, W, Ho, Wo, d, c.len, c.nseg, c.pblocks);
     };
-    if (c.len >= 4) go(&maxpool2_chain_h_kernel<DT, TAP, 4>);
-    else if (c.len >= 2) go(&maxpool2_chain_h_kernel<DT, TAP, 2>);
-    else go(&maxpool2_chain_h_kernel<DT, TAP, 1>);
+    const auto with = [&](auto around) {
+        constexpr bool NT = decltype(around)::value;
+        if (c.len >= 4) go(&maxpool2_chain_h_kernel<DT, TAP, 4, NT>);
+        else if (c.len >= 2) go(&maxpool2_chain_h_kernel<DT, TAP, 2, NT>);
+        else go(&maxpool2_chain_h_kernel<DT, TAP, 1, NT>);
+    };
+    if (TAP && pool_stores_around(16L * grid.z * Ho * Wo)) with(std::integral_constant<bool, TAP>{});
+    else with(std::false_type{});
 }
 
 hipError_t launch_maxpool_h(const void *x, void *y, void *tap, int dtype, long planes8, int H, int W, int Ho, int Wo,

@@ -58,6 +58,12 @@ inline PoolCut pool_cut(int Ho, int cols, int d, long planes, long short_waves, 
     return c;
 }
 
+// Pools with winner codes: results and codes past the L2 (nontemporal stores) where the results are too many to stay there and few enough for the 256 MB of
+// the cache behind it, so that what they push out is not the rows that neighbours still read.  Training steps of the SK-Net with and without, us: bf16
+// 400 x 300 (12 MB) 400 and 397, 512^2 (28) 583 and 589, 3 x 512^2 1268 and 1292, 2 x 1024^2 (210) 2701 and 2733, 3 x 1024^2 (320) 3990 and 3969; fp32
+// 256^2 (16) 634 and 630, 512^2 (55) 1355 and 1361, 4 x 512^2 (220) 4613 and 4651, 2 x 1024^2 (420) 9271 and 9226.  The gradients gain nothing.
+constexpr bool pool_stores_around(long result_bytes) { return result_bytes >= 20L << 20 && result_bytes <= 256L << 20; }
+
 // ---- implicit-GEMM SK convolution, fp32 activations, fp32 MFMA --------------------------------
 // Computes, for every image b, output map o and output position (y, x) in [0,Ho) x [0,Wo):
 //   acc = bias[o] + sum_{c,i,j} Wp[(c*k+i)*k+j][o] * X[b, c, y + i*d - in_off, x + j*d - in_off]
