@@ -1668,7 +1668,8 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     // at d = 16: 25.0 us here, 29.2 there) and 1.24 to 1.55 above this line
     const bool rows_path = DT == 0 && x_bstride == 0 && grp_maps == 0 && wgrad_rows_f32_supported(c_in, c_out, k, d) &&
                            (c_in >= 16 || (a.total_segs >= 256 && a.Ho >= 4 * d));
-    const bool bias_in_kernel = db && ((h_path && MB <= 4) || rows_path || w1_path);
+    const bool c1_path = DT == 0 && x_bstride == 0 && grp_maps == 0 && wgrad_c1_f32_supported(c_in, c_out, k, n, a.Ho, a.Wo);
+    const bool bias_in_kernel = db && ((h_path && MB <= 4) || rows_path || w1_path || c1_path);
     if (bias_in_kernel) a.bias_part = bias_part;
     hipError_t e = hipErrorInvalidValue;
     if constexpr (DT != 0) {
@@ -1684,6 +1685,9 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     if (w1_path) {
         e = launch_wgrad1x1_f32(static_cast<const float *>(x), static_cast<const float *>(dy), scratch, db ? bias_part : nullptr, n, c_in, (long)H * W,
                                 c_out, max_copies, &blocks, stream);
+    } else if (c1_path) {
+        e = launch_wgrad_c1_f32(static_cast<const float *>(x), static_cast<const float *>(dy), scratch, db ? bias_part : nullptr, n, H, W, c_out, k, d,
+                                max_copies, &blocks, stream);
     } else if (rows_path) {
         e = launch_wgrad_rows_f32(static_cast<const float *>(x), static_cast<const float *>(dy), scratch, db ? bias_part : nullptr, n, c_in, H, W,
                                   c_out, d, max_copies, &blocks, stream);

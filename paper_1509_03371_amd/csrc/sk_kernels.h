@@ -333,6 +333,10 @@ hipError_t launch_wgrad_rows_reduce(const float *scratch, float *dw, int copies,
 bool wgrad1x1_f32_supported(int c_in, int c_out, int n, long plane);
 hipError_t launch_wgrad1x1_f32(const float *x, const float *dy, float *scratch, float *bias_part, int n, int c_in, long plane, int c_out,
                                int max_copies, int *copies, hipStream_t stream);
+// one input map, kernels of 2x2 to 4x4, at most 64 output maps (kernels_wgrad_c1_f32.hip): as above
+bool wgrad_c1_f32_supported(int c_in, int c_out, int k, int n, int Ho, int Wo);
+hipError_t launch_wgrad_c1_f32(const float *x, const float *dy, float *scratch, float *bias_part, int n, int H, int W, int c_out, int k, int d,
+                               int max_copies, int *copies, hipStream_t stream);
 
 // the same with the input addressed as launch_conv_f32 addresses it: images x_bstride floats apart (0 = c_in*H*W),
 // the c_in maps in groups of grp_maps (a power of two, or 0 = none) with grp_skip more floats between groups
