@@ -1153,11 +1153,21 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float *__restri
         // bias: 64 maps per workgroup, wave w adds slices w, w+4, ... in four running sums; then the waves in order
         const int o = ((int)blockIdx.x - dw_blocks) * RED_ELEMS + e;
         float v[4] = {0.f, 0.f, 0.f, 0.f};              // (short chains: hundreds of partial sums of one sign round in step)
-        if (o < c_out)
-            for (int sl = w; sl < slices; sl += 16)
+        if (o < c_out) {
+            const float *src = bias_part + (long)o * slices;
+            int sl = w;
+            for (; sl + 60 < slices; sl += 64) {
+                float t[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) t[u] = src[sl + 4 * u];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) v[u & 3] += t[u];
+            }
+            for (; sl < slices; sl += 16)
 #pragma unroll
                 for (int u = 0; u < 4; ++u)
-                    if (sl + 4 * u < slices) v[u] += bias_part[(long)o * slices + sl + 4 * u];
+                    if (sl + 4 * u < slices) v[u] += src[sl + 4 * u];
+        }
         sh[w][e] = (v[0] + v[1]) + (v[2] + v[3]);
         __syncthreads();
         if (w == 0 && o < c_out) db[o] = (sh[0][e] + sh[1][e]) + (sh[2][e] + sh[3][e]);
@@ -1187,12 +1197,24 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float *__restri
     if (q >= 0) {
         const float *src = scratch + (long)o * ncols + col;
         int cpy = w;
-        for (; cpy + 12 < copies; cpy += 16) {
-            s0 += src[(cpy + 0) * stride];
-            s1 += src[(cpy + 4) * stride];
-            s2 += src[(cpy + 8) * stride];
-            s3 += src[(cpy + 12) * stride];
-        }
+        auto rounds = [&](auto count) {                 // of four loads, `count` of them in flight together
+            constexpr int N = decltype(count)::value;
+            for (; cpy + 16 * N - 4 < copies; cpy += 16 * N) {
+                float v[4 * N];
+#pragma unroll
+                for (int i = 0; i < 4 * N; ++i) v[i] = src[(cpy + 4 * i) * stride];
+#pragma unroll
+                for (int i = 0; i < 4 * N; i += 4) {
+                    s0 += v[i];
+                    s1 += v[i + 1];
+                    s2 += v[i + 2];
+                    s3 += v[i + 3];
+                }
+            }
+        };
+        rounds(std::integral_constant<int, 8>{});
+        rounds(std::integral_constant<int, 2>{});
+        rounds(std::integral_constant<int, 1>{});
         for (; cpy < copies; cpy += 4) s0 += src[cpy * stride];
     }
     sh[w][e] = (s0 + s1) + (s2 + s3);
@@ -1207,6 +1229,9 @@ __global__ void __launch_bounds__(256) wgrad_reduce_kernel(const float *__restri
 // span leaves in the gradient's own order, again as float4 per thread.  Fixed summation order.
 constexpr int TRR_SPAN = 1024;     // floats of one row per workgroup at most
 
+// DEEP: loads in flight in fours: four where a thread has sixteen copies or more (64 -> 64 3x3 maps, 256 copies: 14.2 -> 8.7 us), one where not, whose
+// workgroups are many and would be fewer at a time with the registers of the other (two copies of 512 -> 512: 10.1 us, 11.3 so).
+template <int DEEP>
 __global__ void __launch_bounds__(256) wgrad_tr_reduce_kernel(const float *__restrict__ scratch, float *__restrict__ dw, int copies, int c_out, int K,
                                                               int m_rows, int ncols, int k2, int rpb, int parts, int dw_blocks,
                                                               const float *__restrict__ bias_part, float *__restrict__ db, int slices)
@@ -1219,7 +1244,25 @@ __global__ void __launch_bounds__(256) wgrad_tr_reduce_kernel(const float *__res
         const int o = ((int)blockIdx.x - dw_blocks) * 64 + e;
         float v = 0.f;
         if (o < c_out)
-            for (int sl = w; sl < slices; sl += 4) v += bias_part[(long)o * slices + sl];
+        {
+            const float *src = bias_part + (long)o * slices;
+            int sl = w;
+            for (; sl + 60 < slices; sl += 64) {
+                float u[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) u[i] = src[sl + 4 * i];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v += u[i];
+            }
+            for (; sl + 12 < slices; sl += 16) {
+                float u[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = src[sl + 4 * i];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v += u[i];
+            }
+            for (; sl < slices; sl += 4) v += src[sl];
+        }
         sh[w * 64 + e] = v;
         __syncthreads();
         if (w == 0 && o < c_out) db[o] = (sh[e] + sh[64 + e]) + (sh[128 + e] + sh[192 + e]);
@@ -1237,16 +1280,23 @@ __global__ void __launch_bounds__(256) wgrad_tr_reduce_kernel(const float *__res
         const float *src = scratch + (long)o * ncols + col0 + 4 * tt;
         floatx4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0, s3 = s0;
         int c = cw;
-        for (; c + 3 * nsplit < copies; c += 4 * nsplit) {
-            const floatx4 v0 = *reinterpret_cast<const floatx4 *>(src + (long)c * stride);
-            const floatx4 v1 = *reinterpret_cast<const floatx4 *>(src + (long)(c + nsplit) * stride);
-            const floatx4 v2 = *reinterpret_cast<const floatx4 *>(src + (long)(c + 2 * nsplit) * stride);
-            const floatx4 v3 = *reinterpret_cast<const floatx4 *>(src + (long)(c + 3 * nsplit) * stride);
-            s0 += v0;
-            s1 += v1;
-            s2 += v2;
-            s3 += v3;
-        }
+        auto rounds = [&](auto count) {                           // of four copies, `count` of them in flight together
+            constexpr int N = decltype(count)::value;
+            for (; c + (4 * N - 1) * nsplit < copies; c += 4 * N * nsplit) {
+                floatx4 v[4 * N];
+#pragma unroll
+                for (int i = 0; i < 4 * N; ++i) v[i] = *reinterpret_cast<const floatx4 *>(src + (long)(c + i * nsplit) * stride);
+#pragma unroll
+                for (int i = 0; i < 4 * N; i += 4) {
+                    s0 += v[i];
+                    s1 += v[i + 1];
+                    s2 += v[i + 2];
+                    s3 += v[i + 3];
+                }
+            }
+        };
+        if constexpr (DEEP > 1) rounds(std::integral_constant<int, DEEP>{});
+        rounds(std::integral_constant<int, 1>{});
         for (; c < copies; c += nsplit) s0 += *reinterpret_cast<const floatx4 *>(src + (long)c * stride);
         *reinterpret_cast<floatx4 *>(sh + cw * span + 4 * tt) = (s0 + s1) + (s2 + s3);
     }
@@ -1731,8 +1781,9 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
         int rpb = (256 / want_split) * 4 / run_len;
         rpb = rpb < 1 ? 1 : (rpb > nruns ? nruns : rpb);
         const int parts = (nruns + rpb - 1) / rpb, tr_blocks = c_out * parts;
-        hipLaunchKernelGGL(wgrad_tr_reduce_kernel, dim3(tr_blocks + db_blocks), dim3(256), 0, stream, scratch, dw, blocks, c_out, K, a.MTo * 16,
-                           a.NTk * 16, k2, rpb, parts, tr_blocks, bias_part, db, bias_in_kernel ? blocks : BG_SLICES);
+        const bool deep = blocks >= 16 * (256 / (rpb * run_len / 4));
+        hipLaunchKernelGGL(deep ? wgrad_tr_reduce_kernel<4> : wgrad_tr_reduce_kernel<1>, dim3(tr_blocks + db_blocks), dim3(256), 0, stream, scratch, dw,
+                           blocks, c_out, K, a.MTo * 16, a.NTk * 16, k2, rpb, parts, tr_blocks, bias_part, db, bias_in_kernel ? blocks : BG_SLICES);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(dw_blocks + db_blocks), dim3(256), 0, stream, scratch, dw, blocks, c_out, K,
