@@ -643,9 +643,16 @@ hipError_t launch_tap3d_to_index_h(const void *tap, int32_t *idx, int C, int Do,
 // octet layout.  Forward (bwd = 0): out[o][a * C8*8 + c][i][j] = w[o][c][a][i][j] (c_out x k*C8*8 maps; the maps an octet pads
 // stay zero).  Data gradient (bwd = 1): out[a' * O8*8 + o][c][i][j] = w[o][c][k-1-a'][i][j] (k*O8*8 x c_in maps), which the
 // 2-D data-gradient packing then flips in the plane and transposes.
-__global__ void expand_taps3d_kernel(const float *__restrict__ w, float *__restrict__ out, int c_out, int c_in, int k, int bwd, long total)
+struct ExpandJobs { ExpandTaps3d job[BATCH_MAX]; };
+
+// blockIdx.y: job
+__global__ void expand_taps3d_kernel(ExpandJobs jobs)
 {
+    const ExpandTaps3d &jb = jobs.job[blockIdx.y];
+    const float *__restrict__ w = jb.w;
+    const int c_out = jb.c_out, c_in = jb.c_in, k = jb.k, bwd = jb.bwd;
     const int kk = k * k, C8 = (c_in + 7) / 8 * 8, O8 = (c_out + 7) / 8 * 8;
+    const long total = jb.floats();
     for (long q = blockIdx.x * (long)blockDim.x + threadIdx.x; q < total; q += (long)gridDim.x * blockDim.x) {
         const int r = (int)(q % kk);
         long t = q / kk;
@@ -659,15 +666,21 @@ __global__ void expand_taps3d_kernel(const float *__restrict__ w, float *__restr
             const int a = m / O8, o = m - a * O8;
             if (o < c_out) v = w[(((long)o * c_in + c) * k + (k - 1 - a)) * kk + r];
         }
-        out[q] = v;
+        jb.out[q] = v;
     }
 }
 
-hipError_t launch_expand_taps3d(const float *w, float *out, int c_out, int c_in, int k, int bwd, hipStream_t stream)
+hipError_t launch_expand_taps3d(const ExpandTaps3d *jobs, int n, hipStream_t stream)
 {
-    if (c_out < 1 || c_in < 1 || k < 1) return hipErrorInvalidValue;
-    const long total = bwd ? (long)k * ((c_out + 7) / 8 * 8) * c_in * k * k : (long)c_out * k * ((c_in + 7) / 8 * 8) * k * k;
-    hipLaunchKernelGGL(expand_taps3d_kernel, dim3(grid_for(total)), dim3(256), 0, stream, w, out, c_out, c_in, k, bwd, total);
+    if (n < 1 || n > BATCH_MAX) return hipErrorInvalidValue;
+    ExpandJobs b{};
+    long most = 0;
+    for (int t = 0; t < n; ++t) {
+        if (jobs[t].c_out < 1 || jobs[t].c_in < 1 || jobs[t].k < 1) return hipErrorInvalidValue;
+        b.job[t] = jobs[t];
+        most = std::max(most, jobs[t].floats());
+    }
+    hipLaunchKernelGGL(expand_taps3d_kernel, dim3(grid_for(most), n), dim3(256), 0, stream, b);
     return hipGetLastError();
 }
 

@@ -384,8 +384,18 @@ hipError_t launch_maxpool3d_bwd_h(const void *dy, const void *tap, const void *r
                                   int Do, int Ho, int Wo, int k, int d, hipStream_t stream);
 hipError_t launch_tap3d_to_index_h(const void *tap, int32_t *idx, int C, int Do, int Ho, int Wo, int H, int W, int k, int d, int s,
                                    hipStream_t stream);
-// a 3-D kernel's fp32 master as the OIHW master of the 2-D convolution over (depth tap, map) pairs; bwd = 1: of its data gradient
-hipError_t launch_expand_taps3d(const float *w, float *out, int c_out, int c_in, int k, int bwd, hipStream_t stream);
+// a 3-D kernel's fp32 master as the OIHW master of the 2-D convolution over (depth tap, map) pairs; bwd = 1: of its data gradient.  Up to
+// BATCH_MAX in one launch
+struct ExpandTaps3d {
+    const float *w;
+    float *out;
+    int c_out, c_in, k, bwd;
+    __host__ __device__ long floats() const
+    {
+        return bwd ? (long)k * ((c_out + 7) / 8 * 8) * c_in * k * k : (long)c_out * k * ((c_in + 7) / 8 * 8) * k * k;
+    }
+};
+hipError_t launch_expand_taps3d(const ExpandTaps3d *jobs, int n, hipStream_t stream);
 hipError_t launch_maxpool3d_f32(const float *x, float *y, uint8_t *tap, int C, int D, int H, int W, int Do, int Ho, int Wo, int k,
                                 int d, int s, hipStream_t stream);
 // gradient of the s = 1 pool from its winner codes; relu_src (optional, like dx) zeroes the result where it is <= 0

@@ -49,7 +49,7 @@ struct Conv3 {
     void *wp16 = nullptr;              // 16-bit nets: the kernel as a 2-D convolution over k * 8*ceil(c_in/8) input maps, packed MFMA fragments
     void *wp16_bwd = nullptr;          // ... and its data gradient: a 2-D convolution over k * 8*ceil(c_out/8) maps of the zero-padded gradient
     int mt16 = 0, mt16_bwd = 0;        // map tiles per workgroup that wp16 and wp16_bwd are packed for (0 = default)
-    float *exp2d = nullptr;            // fp32 staging of the two 2-D masters these are packed from
+    float *exp2d = nullptr;            // fp32 staging of the two 2-D masters that these are packed from, one behind the other
     float *dw = nullptr, *db = nullptr, *vw = nullptr, *vb = nullptr, *dw_tap = nullptr;
     // weight gradient of all depth taps in one launch: k > 1 and (d = 1, the tapped slices adjacent, or a power-of-two
     // map count, which the kernel's grouped addressing needs); 16-bit storage: whole octets per tap, where the grouped
@@ -85,7 +85,7 @@ void release_conv3(Conv3 &c)
     free_dev(c.dw); free_dev(c.db); free_dev(c.vw); free_dev(c.vb); free_dev(c.dw_tap);
 }
 
-// rebuild the packed fp32 forms from the device master (asynchronous); 16-bit nets have none (repack_conv3_h)
+// rebuild the packed fp32 forms from the device master (asynchronous); 16-bit nets have none (repack_convs3_h)
 sk_status repack_conv3(Conv3 &c, hipStream_t stream)
 {
     if (c.fwd.empty() || !c.fwd[0].wp) return SK_OK;
@@ -110,25 +110,42 @@ sk_status upload_conv3(Conv3 &c, hipStream_t stream)
 // 16-bit storage: depth tap a of input map c becomes input map a * 8*ceil(c_in/8) + c of a 2-D convolution (the maps an
 // octet pads are zero), packed as the 2-D 16-bit kernels want it; with_bwd: also the data gradient's 2-D convolution
 // over the (flipped depth tap, output map) pairs.  Built on the device from the device master (asynchronous).
-sk_status repack_conv3_h(Conv3 &c, int dtype, bool with_bwd, hipStream_t stream)
+// All layers' masters in one launch and all packed forms in another: by two launches a form, the ten forms of a net of five layers were a twenty-fifth
+// of a training step on 81 x 145^2.
+// (with_bwd: makes the data gradients' forms where there are none)
+sk_status repack_convs3_h(Conv3 *convs, int count, int dtype, bool with_bwd, hipStream_t stream)
 {
-    const int c8 = (c.c_in + 7) / 8, o8 = (c.c_out + 7) / 8, kk = c.k * c.k;
-    const long fwd_floats = (long)c.c_out * c.k * c8 * 8 * kk, bwd_floats = (long)c.k * o8 * 8 * c.c_in * kk;
-    if (!c.exp2d) SK_TRY(alloc_f(&c.exp2d, std::max(fwd_floats, bwd_floats)));
-    if (!c.wp16) SK_HIP(hipMalloc(&c.wp16, sizeof(unsigned short) * (size_t)sk::packed_h_elems(c.c_out, c.k * c8, c.k, c.mt16)));
-    SK_HIP(sk::launch_expand_taps3d(c.w_dev, c.exp2d, c.c_out, c.c_in, c.k, 0, stream));
-    SK_HIP(sk::launch_pack_weights_h(c.exp2d, c.wp16, dtype, c.c_out, c.k * c8 * 8, c.k, 0, c.mt16, stream));
-    if (with_bwd) {
-        if (!c.wp16_bwd) SK_HIP(hipMalloc(&c.wp16_bwd, sizeof(unsigned short) * (size_t)sk::packed_h_elems(c.c_in, c.k * o8, c.k, c.mt16_bwd)));
-        SK_HIP(sk::launch_expand_taps3d(c.w_dev, c.exp2d, c.c_out, c.c_in, c.k, 1, stream));
-        SK_HIP(sk::launch_pack_weights_h(c.exp2d, c.wp16_bwd, dtype, c.k * o8 * 8, c.c_in, c.k, 1, c.mt16_bwd, stream));
+    sk::ExpandTaps3d ex[sk::BATCH_MAX];
+    sk::PackHJob pk[sk::BATCH_MAX];
+    int n = 0;
+    for (int i = 0; i < count; ++i) {
+        Conv3 &c = convs[i];
+        const int c8 = (c.c_in + 7) / 8, o8 = (c.c_out + 7) / 8;
+        ex[n] = {c.w_dev, nullptr, c.c_out, c.c_in, c.k, 0};
+        const sk::ExpandTaps3d grad{c.w_dev, nullptr, c.c_out, c.c_in, c.k, 1};
+        const long fwd_floats = ex[n].floats();
+        if (!c.exp2d) SK_TRY(alloc_f(&c.exp2d, fwd_floats + grad.floats()));
+        if (!c.wp16) SK_HIP(hipMalloc(&c.wp16, sizeof(unsigned short) * (size_t)sk::packed_h_elems(c.c_out, c.k * c8, c.k, c.mt16)));
+        ex[n].out = c.exp2d;
+        pk[n++] = {c.exp2d, c.wp16, c.c_out, c.k * c8 * 8, c.k, 0, c.mt16};
+        if (with_bwd || c.wp16_bwd) {
+            if (!c.wp16_bwd) SK_HIP(hipMalloc(&c.wp16_bwd, sizeof(unsigned short) * (size_t)sk::packed_h_elems(c.c_in, c.k * o8, c.k, c.mt16_bwd)));
+            ex[n] = grad;
+            ex[n].out = c.exp2d + fwd_floats;
+            pk[n++] = {c.exp2d + fwd_floats, c.wp16_bwd, c.k * o8 * 8, c.c_in, c.k, 1, c.mt16_bwd};
+        }
+        if (i + 1 == count || n + 2 > sk::BATCH_MAX) {
+            SK_HIP(sk::launch_expand_taps3d(ex, n, stream));
+            SK_HIP(sk::launch_pack_weights_h_batch(pk, n, dtype, stream));
+            n = 0;
+        }
     }
     return SK_OK;
 }
 
 sk_status upload_conv3_h(Conv3 &c, int dtype, bool with_bwd = false)
 {
-    SK_TRY(repack_conv3_h(c, dtype, with_bwd, nullptr));
+    SK_TRY(repack_convs3_h(&c, 1, dtype, with_bwd, nullptr));
     SK_HIP(hipStreamSynchronize(nullptr));
     return SK_OK;
 }
@@ -423,7 +440,7 @@ sk_status sknet3d_set_weights(sknet3d_t *net, int32_t conv_idx, const float *w_h
     if (!b_host)   // keep the device's current biases (an SGD step may have changed them)
         SK_HIP(hipMemcpy(c.b.data(), c.b_dev, sizeof(float) * c.c_out, hipMemcpyDeviceToHost));
     SK_TRY(upload_conv3(c, nullptr));
-    if (net->half()) SK_TRY(upload_conv3_h(c, net->dtype, c.wp16_bwd != nullptr));
+    if (net->half()) SK_TRY(upload_conv3_h(c, net->dtype));
     if (net->fuse_head && conv_idx == (int)net->convs.size() - 2) {
         SK_HIP(sk::launch_pack_head_w1(c.w_dev, net->head_w1p, net->dtype, c.c_out, c.c_in, nullptr));
         SK_HIP(hipStreamSynchronize(nullptr));
@@ -734,7 +751,9 @@ sk_status sknet3d_sgd_step(sknet3d_t *net, float lr, float momentum, float weigh
         sb.w[sb.n] = c.b_dev; sb.dw[sb.n] = c.db; sb.v[sb.n] = momentum != 0.f ? c.vb : nullptr; sb.count[sb.n] = c.c_out; ++sb.n;
     }
     if (sb.n > 0) SK_HIP(sk::launch_sgd_batch_f32(sb, lr, momentum, weight_decay, stream));
-    for (auto &c : net->convs) SK_TRY(net->half() ? repack_conv3_h(c, net->dtype, c.wp16_bwd != nullptr, stream) : repack_conv3(c, stream));
+    if (net->half()) SK_TRY(repack_convs3_h(net->convs.data(), (int)net->convs.size(), net->dtype, false, stream));
+    else
+        for (auto &c : net->convs) SK_TRY(repack_conv3(c, stream));
     return SK_OK;
 }
 
