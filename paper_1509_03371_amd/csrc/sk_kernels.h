@@ -390,7 +390,7 @@ struct ExpandTaps3d {
     const float *w;
     float *out;
     int c_out, c_in, k, bwd;
-    __host__ __device__ long floats() const
+    constexpr long floats() const
     {
         return bwd ? (long)k * ((c_out + 7) / 8 * 8) * c_in * k * k : (long)c_out * k * ((c_in + 7) / 8 * 8) * k * k;
     }
