@@ -1820,11 +1820,19 @@ __global__ void __launch_bounds__(256) pack_weights_h_batch_kernel(PackHJobs b)
     // the bank count
     const int run = (flip ? 16 : Cc) * k2, rows = flip ? Cc : 16, row_lim = jb.c_out, col0 = flip ? m0 : c0;
     const int row0 = flip ? c0 : m0;
-    for (int s = threadIdx.x; s < rows * run; s += 256) {
-        const int r = s / run, rem = s - r * run, cc = rem / k2;
-        float v = 0.f;
-        if (row0 + r < row_lim && col0 + cc < jb.c_in) v = jb.w[((long)(row0 + r) * jb.c_in + col0) * k2 + rem];
-        pack_slab[r * (run + 1) + rem] = v;
+    for (int s0 = threadIdx.x; s0 < rows * run; s0 += 8 * 256) {      // eight loads on the way together
+        float v[8];
+        int at[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int s = s0 + 256 * u, r = s / run, rem = s - r * run, cc = rem / k2;
+            const bool real = s < rows * run && row0 + r < row_lim && col0 + cc < jb.c_in;
+            at[u] = r * (run + 1) + rem;
+            v[u] = real ? jb.w[((long)(row0 + r) * jb.c_in + col0) * k2 + rem] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (s0 + 256 * u < rows * run) pack_slab[at[u]] = v[u];
     }
     __syncthreads();
     const int units = NF * 64;

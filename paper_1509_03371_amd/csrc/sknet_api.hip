@@ -865,12 +865,14 @@ sk_status sknet_sgd_step(sknet_t *net, float lr, float momentum, float weight_de
     // one launch updates every weight and bias tensor, a second rebuilds every packed form
     // (a net is a dozen small tensors: one launch each would cost more than the work)
     const int nc = (int)net->convs.size();
+    const ConvParams *head = net->fuse_head ? &net->convs[net->conv_of_layer[(int)net->layers.size() - 2]] : nullptr;
     if (2 * nc > sk::BATCH_MAX) {
         for (auto &c : net->convs) {
             SK_HIP(sk::launch_sgd_f32(c.w_dev, c.dw, momentum != 0.f ? c.vw : nullptr, c.wcount(), lr, momentum, weight_decay, stream));
             SK_HIP(sk::launch_sgd_f32(c.b_dev, c.db, momentum != 0.f ? c.vb : nullptr, c.c_out, lr, momentum, weight_decay, stream));
             SK_TRY(repack_conv(c, true, net->dtype, stream));
         }
+        if (head) SK_HIP(sk::launch_pack_head_w1(head->w_dev, net->head_w1p, net->dtype, head->c_out, head->c_in, stream));
         return SK_OK;
     }
     sk::SgdBatch sb{};
@@ -888,13 +890,14 @@ sk_status sknet_sgd_step(sknet_t *net, float lr, float momentum, float weight_de
             if (c.wp16_bwd) ph[np++] = {c.w_dev, c.wp16_bwd, c.c_out, c.c_in, c.k, 1, c.mt16_bwd};
         }
     }
+    if (head && np < sk::BATCH_MAX) {      // (16-bit storage) the fragments of a 1x1 layer in groups of one tile; the tiles behind its last stay zero
+        ph[np++] = {head->w_dev, net->head_w1p, head->c_out, head->c_in, 1, 0, 1};
+        head = nullptr;
+    }
     SK_HIP(sk::launch_sgd_batch_f32(sb, lr, momentum, weight_decay, stream));
     if (net->dtype == SK_F32) SK_HIP(sk::launch_pack_weights_f32_batch(pf, np, stream));
     else SK_HIP(sk::launch_pack_weights_h_batch(ph, np, net->dtype, stream));
-    if (net->fuse_head) {
-        const ConvParams &c1 = net->convs[net->conv_of_layer[(int)net->layers.size() - 2]];
-        SK_HIP(sk::launch_pack_head_w1(c1.w_dev, net->head_w1p, net->dtype, c1.c_out, c1.c_in, stream));
-    }
+    if (head) SK_HIP(sk::launch_pack_head_w1(head->w_dev, net->head_w1p, net->dtype, head->c_out, head->c_in, stream));
     return SK_OK;
 }
 
