@@ -1697,7 +1697,7 @@ static hipError_t launch_wgrad_dt(const void *x, const void *dy, float *dw, floa
     // 1x1 layers of few maps on one side: both operands straight from memory (84 layers, 12 x 60 to 8 x 512^2: 1.16 to 3.5 times as fast)
     const bool w1_path = DT == 0 && k == 1 && x_bstride == 0 && grp_maps == 0 && wgrad1x1_f32_supported(c_in, c_out, n, (long)H * W);
     // (with less than two blocks of sixteen pixels a wave, more copies cost more than they spread: 8 -> 200 maps at 128^2 14.7 us with 128, 16.1 with 256;
-    // 64 gradients of 8 and 48 -> 16 to 200 maps, 24 x 30 to 4 x 400^2: 0.63 to 1.02 of the time without the line above)
+    // 64 gradients of 8 and 48 -> 16 to 200 maps, 24 x 30 to 4 x 400^2: 0.63 to 1.02 of the time with the other kernel's count)
     const bool w1_spread = w1_path && (long)n * (((long)H * W + 15) / 16) >= 8L * WG_1X1_COPIES;
     int max_copies = w1_spread ? std::max(wgrad_max_copies(groups), WG_1X1_COPIES) : wgrad_max_copies(groups);
     if (scratch_cap > 0) {
