@@ -643,12 +643,12 @@ long packed_f32_floats(int k, int gemm_c_in, int n_pad)
     return plain + (conv_split_f32_packed(k, gemm_c_in) ? (long)((gemm_c_in + 7) / 8) * k * (n_pad / 16) * 512 + SPLIT_TAIL_FLOATS : 0);
 }
 
-// Largest finite magnitude of count weights, in gridDim.x (at most 64) parts
+// Largest magnitude of count weights, in gridDim.x (at most 64) parts
 __device__ __forceinline__ void weight_max_body(const float *w, long count, float *part)
 {
     __shared__ float wm[4];
     float m = 0.f;
-    for (long q = blockIdx.x * 256L + threadIdx.x; q < count; q += gridDim.x * 256L) m = fmaxf(m, split_finite(fabsf(w[q])));
+    for (long q = blockIdx.x * 256L + threadIdx.x; q < count; q += gridDim.x * 256L) m = fmaxf(m, fabsf(w[q]));
     m = split_wave_max(m);
     if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
     __syncthreads();
@@ -669,8 +669,11 @@ template <class V> __device__ __forceinline__ void pack_f32_forms(float *wp, int
         wp[q] = value(row / (k * k), (row / k) % k, row % k, col);
     }
     if (!tail) return;
-    const int se = split_exponent(split_wave_max(tail[threadIdx.x & 63]), 14);
-    if (first == 0) reinterpret_cast<int *>(tail)[64] = se;
+    const float most = split_wave_max(tail[threadIdx.x & 63]);
+    const bool infinite = most == __builtin_huge_valf();
+    const int se = split_exponent(most, 14);
+    if (first == 0) reinterpret_cast<int *>(tail)[64] = infinite ? SPLIT_WIDE : se;
+    if (infinite) return;                                            // nobody reads the fragments
     const float scale = split_pow2(se);
     uint4v *frag = reinterpret_cast<uint4v *>(wp + total);
     const int m_tiles = n_pad / 16;
@@ -684,7 +687,6 @@ template <class V> __device__ __forceinline__ void pack_f32_forms(float *wp, int
         for (int e = 0; e < 8; ++e) v[e] = j < k ? value(c + e, i, j, o) : 0.f;
         uint4v p[2];
         split2(v, scale, p);
-        split_infinite(v, p);
 #pragma unroll
         for (int s = 0; s < 2; ++s) frag[((ci * m_tiles + tile) * 2 + s) * 64 + lane] = p[s];
     }

@@ -10,6 +10,8 @@
 //    lane, as in the 16-bit convolution; the fourth column of a 3x3 kernel has zero weights,
 //  - multiplies kernel rows in steps of G whose weights are in registers, so that a staged row is read once for G kernel rows.  Weight
 //    fragments come straight into LDS, a step ahead.
+// From a chunk with an infinite sample on, and where a weight is infinite, the tile is multiplied on the fp32 matrix unit (inf - inf of two parts
+// is NaN, which ReLU drops, and so is a part of 0 times infinity).
 // What bounds it: power.  MFMAs take 0.7 of the matrix unit's time at the 1.7 GHz that is left of 2.4 (8 x 1024^2); the rest are the two
 // barriers a chunk, LDS reads and 0.7 other vector instructions an MFMA.  Two or three workgroups share a CU and fill each other's waits.
 // 48 -> 48 maps, 4x4, us (TFLOP/s) on the fp32 matrix unit and here: 537^2 d = 2 202 -> 59 (360), 8 x 1024^2 d = 8 4745 -> 1421 (435); 64 -> 64, 3x3,
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
     constexpr int RR = T::RR, G = T::G, STEPS = T::STEPS, UPT = T::UPT, PLANE = T::PLANE;
     extern __shared__ unsigned char smem[];
     unsigned char *xs = smem, *ws = smem + 2 * PLANE * 16;
-    float *most = reinterpret_cast<float *>(ws + 2 * T::WSTEP);      // [2][4]: largest magnitude that each wave stages, by chunk; [8..]: the rare path's
+    float *most = reinterpret_cast<float *>(ws + 2 * T::WSTEP);      // [2][4]: largest magnitude that each wave stages, by chunk
     const int d = a.d, pw = T::TX + (KS - 1) * d, units = RR * pw;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wx = wave % WX, wy = wave / WX;
@@ -188,22 +190,11 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
         m = split_wave_max(m);
         if (lane == 0) most[(chunk & 1) * 4 + wave] = m;
     };
-    auto commit = [&](int chunk) {
+    auto commit = [&](int chunk) {                            // false: infinite samples, nothing is staged
         const floatx4 m4 = *reinterpret_cast<const floatx4 *>(most + (chunk & 1) * 4);
         float m = split_max(split_max(m4[0], m4[1]), split_max(m4[2], m4[3]));
         m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
-        const bool infinite = __builtin_bit_cast(unsigned, m) == 0x7f800000u;
-        if (infinite) {                                                  // infinities don't decide the scale of the finite samples beside them
-            float f = 0.f;
-            for (int q = 0; q < UPT; ++q)
-                for (int e = 0; e < 8; ++e) f = fmaxf(f, split_finite(fabsf(xr[q][e])));
-            f = split_wave_max(f);
-            if (lane == 0) most[8 + wave] = f;
-            __syncthreads();
-            m = fmaxf(fmaxf(most[8], most[9]), fmaxf(most[10], most[11]));
-            m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
-            __syncthreads();
-        }
+        if (__builtin_bit_cast(unsigned, m) == 0x7f800000u) return false;
         const int need = split_exponent(m, 14);
         if (need < se) {
             const int to = split_exponent(m, 12);                        // two bits of room: neighbouring chunks don't ask again
@@ -222,12 +213,12 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
             if (256 * q + 255 >= RR * (T::TX + KS - 1) && tid + 256 * q >= units) continue;
             uint4v p[2];
             split2(xr[q], scale, p);
-            if (infinite) split_infinite(xr[q], p);
             if constexpr (PADZ)
                 if (!ok[q]) p[0] = p[1] = uint4v{0, 0, 0, 0};
 #pragma unroll
             for (int s = 0; s < 2; ++s) *reinterpret_cast<uint4v *>(xs + s * PLANE * 16 + dst[q]) = p[s];
         }
+        return true;
     };
     // fragments [chunk][kernel row][map tile][part] of 1 KB; a step's stand in LDS as [kernel row][MT][part]
     auto load_weights = [&](int chunk, int step, int buf) {
@@ -244,13 +235,60 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
     const bool idle = x0 + wx * 16 >= a.Wo;                   // this wave's columns lie right of the image
     const unsigned char *xp = xs + (wy * R * PITCH + wx * 16 + l16 + min(g, KS - 1) * d) * 16;     // the column behind a 3x3 kernel meets zero weights
 
-    load_weights(0, 0, 0);
-    prefetch(0);
-    measure(0);
-    for (int chunk = 0; chunk < nchunks; ++chunk) {
+    // A chunk on the fp32 matrix unit: the LDS of a unit's two parts holds its eight samples as they are, weights come from their fp32 form.  Only taps
+    // and maps that exist are multiplied: 0 * inf is NaN
+    auto multiply_f32 = [&](int chunk) {
+        const long skip = (long)(chunk / grp_chunks) * a.grp_skip;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const auto src = split_rsrc(xb + skip + (long)min(chunk * 8 + e, a.c_in - 1) * plane);
+#pragma unroll
+            for (int q = 0; q < UPT; ++q) xr[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(src, off[q], 0, 0));
+        }
+        wide_barrier();                                       // every wave is done with the staged maps
+#pragma unroll
+        for (int q = 0; q < UPT; ++q) {
+            if (256 * q + 255 >= RR * (T::TX + KS - 1) && tid + 256 * q >= units) continue;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                floatx4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = chunk * 8 + 4 * h + e < a.c_in && (!PADZ || ok[q]) ? xr[q][4 * h + e] : 0.f;
+                *reinterpret_cast<floatx4 *>(xs + h * PLANE * 16 + dst[q]) = v;
+            }
+        }
+        wide_barrier();
+        if (idle) return;
+        const float *wf = a.wp + (long)(chunk * 8 + g) * (KS * KS) * a.n_pad + l16;
+#pragma unroll 1
+        for (int t = 0; t < 2 * KS * KS; ++t) {
+            const int h = t >= KS * KS, tap = t - h * KS * KS, i = tap / KS, j = tap - i * KS;
+            const float *xq = reinterpret_cast<const float *>(xs + (h * PLANE + (wy * R + i) * PITCH + wx * 16 + l16 + j * d) * 16) + g;
+            float A[MT];
+#pragma unroll
+            for (int m = 0; m < MT; ++m) A[m] = wf[(long)(h * 4 * KS * KS + tap) * a.n_pad + min(tile0 + m, m_tiles - 1) * 16];
+#pragma unroll
+            for (int y = 0; y < R; ++y) {
+                const float B = xq[y * PITCH * 4];
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[y][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[m], B, acc[y][m], 0, 0, 0);
+            }
+        }
+    };
+
+    const int we = *wexp;
+    bool pairs = we != SPLIT_WIDE;                            // false from the first chunk on that pairs cannot hold
+    int chunk = 0;
+    if (pairs) {
+        load_weights(0, 0, 0);
+        prefetch(0);
+        measure(0);
+    }
+    for (; pairs && chunk < nchunks; ++chunk) {
         const bool more = chunk + 1 < nchunks;
         wide_barrier();                                       // every wave is done with the staged maps and has measured its share of the next
-        commit(chunk);
+        pairs = commit(chunk);
+        if (!pairs) break;
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             // the step's weights have arrived: behind them only the loads of the next chunk's maps may be under way
@@ -295,8 +333,19 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
         }
         if (more) measure(chunk + 1);
     }
+    if (!pairs) {
+        wide_wait<0>();                                       // weights on their way to LDS
+        if (chunk > 0)
+#pragma unroll
+            for (int y = 0; y < R; ++y)
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int r4 = 0; r4 < 4; ++r4) acc[y][m][r4] = __builtin_ldexpf(acc[y][m][r4], -(se + we));
+        for (; chunk < nchunks; ++chunk) multiply_f32(chunk);
+    }
     if (idle) return;
-    const int down = -(se + *wexp), o_first = tile0 * 16, oy = py + d * (ty * T::RT + wy * R), ox = x0 + wx * 16 + l16;
+    const int down = pairs ? -(se + we) : 0, o_first = tile0 * 16, oy = py + d * (ty * T::RT + wy * R), ox = x0 + wx * 16 + l16;
     if (a.mask) split_store<MT, R, 1>(a, acc, down, b, o_first, oy, ox, g);
     else if (a.accumulate) split_store<MT, R, 2>(a, acc, down, b, o_first, oy, ox, g);
     else split_store<MT, R, 0>(a, acc, down, b, o_first, oy, ox, g);

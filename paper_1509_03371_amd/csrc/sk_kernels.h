@@ -104,7 +104,7 @@ hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t stream);
 
 // Layers of enough input maps on the 16-bit matrix unit, fp32 values as pairs of fp16 (kernels_conv_split_f32.hip); launch_conv_f32 hands them
 // over.  Behind the packed fp32 weights stand theirs, at split_weights_at floats, as fragments in two parts, and a tail: 64 partial
-// maxima, then the power of two by which the parts are scaled (int)
+// maxima, then the power of two by which the parts are scaled (int), or SPLIT_WIDE
 bool conv_split_f32_packed(int k, int gemm_c_in);                     // do weights of this GEMM have that form too?
 long split_weights_at(int k, int gemm_c_in, int n_pad);
 long packed_f32_floats(int k, int gemm_c_in, int n_pad);              // of the packed weights, all forms

@@ -20,6 +20,7 @@ typedef _Float16 split_halfx8 __attribute__((ext_vector_type(8)));
 typedef _Float16 split_halfx2 __attribute__((ext_vector_type(2)));
 typedef unsigned int uint4v __attribute__((ext_vector_type(4)));
 
+constexpr int SPLIT_WIDE = 1000;      // in the place of a weights' power of two: pairs cannot hold them
 constexpr int SPLIT_MOST = 110;       // largest power of two that values are scaled by (values below 2^-98 lose bits)
 
 __device__ __forceinline__ split_floatx4 split_mfma(uint4v a, uint4v b, split_floatx4 c)
@@ -36,20 +37,6 @@ __device__ __forceinline__ void split2(const float (&v)[8], float scale, uint4v 
         const split_halfx2 l = {(_Float16)__builtin_fmaf(v[e], scale, -(float)h[0]), (_Float16)__builtin_fmaf(v[e + 1], scale, -(float)h[1])};
         p[0][e / 2] = __builtin_bit_cast(unsigned, h);
         p[1][e / 2] = __builtin_bit_cast(unsigned, l);
-    }
-}
-
-// Infinities among v stand in the second part alone: there they meet the first part of the other operand, whose sign is the value's, and no
-// other product (inf - inf of two of them would come out as NaN, which ReLU drops)
-__device__ __forceinline__ void split_infinite(const float (&v)[8], uint4v (&p)[2])
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const unsigned bits = __builtin_bit_cast(unsigned, v[e]);
-        if ((bits & 0x7fffffffu) != 0x7f800000u) continue;
-        const unsigned at = 16 * (e & 1), keep = ~(0xffffu << at);
-        p[0][e / 2] &= keep;
-        p[1][e / 2] = (p[1][e / 2] & keep) | ((bits >> 16 & 0x8000u) | 0x7c00u) << at;
     }
 }
 

@@ -126,6 +126,27 @@ def test_infinities_keep_their_sign(which):
     assert dropped.any() and not got[dropped].any()
 
 
+@pytest.mark.parametrize("which", ["samples", "weights", "both"])
+@pytest.mark.parametrize("k,d,c_in", [(3, 1, 24), (3, 4, 26), (3, 1, 31), (4, 1, 24), (4, 3, 29), (4, 2, 31)])
+def test_infinities_meet_real_taps_and_maps_alone(k, d, c_in, which):
+    # every kernel column meets one, the last map among them; an infinite sample meets an infinite weight; later chunks add finite products
+    rng = np.random.default_rng(9 * k + c_in)
+    img = rng.uniform(0.5, 1.5, (1, c_in, 50, 110)).astype(np.float32)
+    w0 = rng.standard_normal((40, c_in, k, k)).astype(np.float32)
+    w0 += np.sign(w0) * np.float32(0.01)
+    if which != "weights":
+        img[0, 2, 20, 30], img[0, c_in - 1, 33, 90], img[0, 12, 40, 5] = np.inf, -np.inf, np.inf
+    if which != "samples":
+        w0[3, 2, 1, 2], w0[17, c_in - 1, 0, k - 1], w0[39, 5, k - 1, 0] = np.inf, -np.inf, np.inf
+    got = forward(k, d, img, w0, np.zeros(40, np.float32), relu=False)
+    with np.errstate(invalid="ignore"):
+        ref, size = OL.conv_sk(img, w0, np.zeros(40), d, relu=False), OL.conv_sk(np.abs(img), np.abs(w0), np.zeros(40), d)
+    assert np.isposinf(ref).any() and np.isneginf(ref).any()
+    assert np.array_equal(np.isposinf(got), np.isposinf(ref)) and np.array_equal(np.isneginf(got), np.isneginf(ref)) and np.array_equal(np.isnan(got), np.isnan(ref))
+    finite = np.isfinite(ref)
+    assert np.all(np.abs(got[finite] - ref[finite]) <= (k * k * c_in + 9) * 2.0 ** -24 * size[finite])
+
+
 @pytest.mark.parametrize("relu", [False, True])
 @pytest.mark.parametrize("k,d,maps,classes,n,h,w", [
     (4, 1, 8, 24, 2, 19, 71), (4, 2, 20, 25, 1, 47, 66), (4, 8, 48, 48, 1, 70, 131), (4, 9, 16, 24, 1, 70, 80), (3, 1, 40, 32, 1, 40, 131),
