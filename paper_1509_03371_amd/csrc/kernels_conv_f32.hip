@@ -637,76 +637,95 @@ bool conv_split_f32_packed(int k, int gemm_c_in) { return (k == 3 || k == 4) && 
 
 long split_weights_at(int k, int gemm_c_in, int n_pad) { return (long)(gemm_c_in + 15) / 16 * 16 * k * k * n_pad; }
 
+long split_tail_at(int k, int gemm_c_in, int n_pad) { return split_weights_at(k, gemm_c_in, n_pad) + (long)((gemm_c_in + 7) / 8) * k * (n_pad / 16) * 512; }
+
 long packed_f32_floats(int k, int gemm_c_in, int n_pad)
 {
-    const long plain = split_weights_at(k, gemm_c_in, n_pad);
-    return plain + (conv_split_f32_packed(k, gemm_c_in) ? (long)((gemm_c_in + 7) / 8) * k * (n_pad / 16) * 512 + SPLIT_TAIL_FLOATS : 0);
+    if (!conv_split_f32_packed(k, gemm_c_in)) return split_weights_at(k, gemm_c_in, n_pad);
+    return split_tail_at(k, gemm_c_in, n_pad) + (SPLIT_PARTS + 1) * n_pad + (long)((gemm_c_in + 7) / 8) * (n_pad / 16);
 }
 
-// Largest magnitude of count weights, in gridDim.x (at most 64) parts
-__device__ __forceinline__ void weight_max_body(const float *w, long count, float *part)
+// A GEMM's weights as value(m, i, j, o): input map m, tap (i, j), output map o, and the packed forms they go to; zero beyond the real extents
+struct PackedF32 {
+    float *wp;
+    int k, gemm_c_in, rows, n_pad;
+    float *tail;                                                     // nullptr: no split form
+};
+
+// Each output map's largest finite magnitude, in SPLIT_PARTS parts of the input maps.  Blocks (of 256 threads): part * map tiles + tile
+template <class V> __device__ __forceinline__ void weight_max_body(const PackedF32 &f, int blk, V value)
 {
-    __shared__ float wm[4];
+    const int m_tiles = f.n_pad / 16, part = blk / m_tiles, o = (blk - part * m_tiles) * 16 + (threadIdx.x >> 4), kk = f.k * f.k;
+    const int begin = f.gemm_c_in * part / SPLIT_PARTS * kk, end = f.gemm_c_in * (part + 1) / SPLIT_PARTS * kk;
     float m = 0.f;
-    for (long q = blockIdx.x * 256L + threadIdx.x; q < count; q += gridDim.x * 256L) m = fmaxf(m, fabsf(w[q]));
-    m = split_wave_max(m);
-    if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]));
+    for (int q = begin + (threadIdx.x & 15); q < end; q += 16) {
+        const int c = q / kk, t = q - c * kk, i = t / f.k;
+        const float v = fabsf(value(c, i, t - i * f.k, o));
+        m = __builtin_bit_cast(unsigned, v) == SPLIT_INFINITE ? m : fmaxf(m, v);
+    }
+#pragma unroll
+    for (int s = 8; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
+    if ((threadIdx.x & 15) == 0) f.tail[part * f.n_pad + o] = m;
 }
-__global__ __launch_bounds__(256) void weight_max_kernel(const float *w, long count, float *part) { weight_max_body(w, count, part); }
 
-// Both packed forms of a GEMM's weights, from value(m, i, j, o): input map m, tap (i, j), output map o; zero beyond the real extents.
-// First [rows][n_pad] floats, rows (m*k + i)*k + j.  Then, with a tail (see sk_kernels.h, its maxima in place), the fragments of the split
-// convolution: per chunk of eight maps, kernel row and tile of sixteen output maps two parts of [64 lanes][8] fp16, lane l = output map
+// Both packed forms.  First [rows][n_pad] floats, rows (m*k + i)*k + j.  Then, with a tail (see sk_kernels.h, its maxima in place), the fragments of the
+// split convolution: per chunk of eight maps, kernel row and tile of sixteen output maps two parts of [64 lanes][8] fp16, lane l = output map
 // l % 16 of the tile at tap (row, l / 16), the chunk's maps side by side.
-template <class V> __device__ __forceinline__ void pack_f32_forms(float *wp, int k, int gemm_c_in, int rows, int n_pad, float *tail, V value)
+template <class V> __device__ __forceinline__ void pack_f32_forms(const PackedF32 &f, V value)
 {
+    const int k = f.k, n_pad = f.n_pad;
     const long first = blockIdx.x * (long)blockDim.x + threadIdx.x, step = (long)gridDim.x * blockDim.x;
-    const long total = (long)rows * n_pad;
+    const long total = (long)f.rows * n_pad;
     for (long q = first; q < total; q += step) {
         const int col = (int)(q % n_pad), row = (int)(q / n_pad);
-        wp[q] = value(row / (k * k), (row / k) % k, row % k, col);
+        f.wp[q] = value(row / (k * k), (row / k) % k, row % k, col);
     }
-    if (!tail) return;
-    const float most = split_wave_max(tail[threadIdx.x & 63]);
-    const bool infinite = most == __builtin_huge_valf();
-    const int se = split_exponent(most, 14);
-    if (first == 0) reinterpret_cast<int *>(tail)[64] = infinite ? SPLIT_WIDE : se;
-    if (infinite) return;                                            // nobody reads the fragments
-    const float scale = split_pow2(se);
-    uint4v *frag = reinterpret_cast<uint4v *>(wp + total);
-    const int m_tiles = n_pad / 16;
-    const long lanes = (long)((gemm_c_in + 7) / 8) * k * m_tiles * 64;
-    for (long q = first; q < lanes; q += step) {
-        const int lane = (int)(q & 63), tile = (int)((q >> 6) % m_tiles), j = lane >> 4;
-        const long ci = (q >> 6) / m_tiles;
-        const int i = (int)(ci % k), c = (int)(ci / k) * 8, o = tile * 16 + (lane & 15);
-        float v[8];
+    if (!f.tail) return;
+    uint4v *frag = reinterpret_cast<uint4v *>(f.wp + total);
+    const int m_tiles = n_pad / 16, lane = threadIdx.x & 63, g = lane >> 4, chunks = (f.gemm_c_in + 7) / 8;
+    int *const wexp = reinterpret_cast<int *>(f.tail + SPLIT_PARTS * n_pad), *const wide = wexp + n_pad;
+    for (long q = first >> 6; q < (long)chunks * m_tiles; q += step >> 6) {        // a wave: a chunk's fragments of a map tile
+        const int tile = (int)(q % m_tiles), chunk = (int)(q / m_tiles), o = tile * 16 + (lane & 15);
+        float most = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = j < k ? value(c + e, i, j, o) : 0.f;
-        uint4v p[2];
-        split2(v, scale, p);
+        for (int p = 0; p < SPLIT_PARTS; p += 4) most = fmaxf(most, f.tail[(p + g) * n_pad + o]);
+        most = fmaxf(most, __shfl_xor(most, 16, 64));
+        most = fmaxf(most, __shfl_xor(most, 32, 64));
+        const int we = split_exponent(__builtin_bit_cast(unsigned, most), 14);
+        if (chunk == 0 && g == 0) wexp[o] = we;
+        const float scale = split_pow2(we);
+        SplitRange range;
+        float v[4][8];                                               // (k is 3 or 4)
 #pragma unroll
-        for (int s = 0; s < 2; ++s) frag[((ci * m_tiles + tile) * 2 + s) * 64 + lane] = p[s];
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[i][e] = i < k && g < k ? value(chunk * 8 + e, i, g, o) : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (i == k) break;
+            range = split_range(range, split_range(v[i]));
+            uint4v p[2];
+            split2(v[i], scale, p);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) frag[(((long)(chunk * k + i) * m_tiles + tile) * 2 + s) * 64 + lane] = p[s];
+        }
+        const bool any = __ballot(split_wide(range, we)) != 0;
+        if (lane == 0) wide[q] = any;
     }
 }
 
-__device__ __forceinline__ void pack_weights_f32_body(const float *w, float *wp, int c_out, int c_in, int k,
-                                                      int flip_transpose, int rows, int n_pad, float *tail)
-{
-    const int gemm_c_in = flip_transpose ? c_out : c_in;
-    pack_f32_forms(wp, k, gemm_c_in, rows, n_pad, tail, [=](int m, int i, int j, int col) {
+struct WeightsF32 {                                                  // OIHW; flip_transpose: of the data gradient
+    const float *w;
+    int c_out, c_in, k, flip_transpose;
+    __device__ __forceinline__ float operator()(int m, int i, int j, int col) const
+    {
         if (!flip_transpose) return m < c_in && col < c_out ? w[(((long)col * c_in + m) * k + i) * k + j] : 0.f;
         return m < c_out && col < c_in ? w[(((long)m * c_in + col) * k + (k - 1 - i)) * k + (k - 1 - j)] : 0.f;
-    });
-}
+    }
+};
 
-__global__ void pack_weights_f32_kernel(const float *w, float *wp, int c_out, int c_in, int k,
-                                        int flip_transpose, int rows, int n_pad, float *tail)
-{
-    pack_weights_f32_body(w, wp, c_out, c_in, k, flip_transpose, rows, n_pad, tail);
-}
+__global__ __launch_bounds__(256) void weight_max_kernel(WeightsF32 w, PackedF32 f) { weight_max_body(f, blockIdx.x, w); }
+__global__ __launch_bounds__(256) void pack_weights_f32_kernel(WeightsF32 w, PackedF32 f) { pack_f32_forms(f, w); }
 
 // Packings of a 3-D kernel W3[c_out][C][k][k][k] (depth, row, column taps) for the 2-D convolution that treats
 // depth taps as input maps; al runs over the len taps of the launch:
@@ -714,23 +733,26 @@ __global__ void pack_weights_f32_kernel(const float *w, float *wp, int c_out, in
 // flip_transpose = 1 (data gradient: every axis flipped, map roles swapped; taps k-1-(a0 + al)):
 //                                                   Wp[((al*c_out + o)*k + i)*k + j][c] = W3[o][c][k-1-a0-al][k-1-i][k-1-j]
 // Rows and columns beyond the real extents are zero.
-__global__ void pack_weights3d_f32_kernel(const float *w3, float *wp, int c_out, int C, int k, int a0, int len, int flip_transpose,
-                                          int rows, int n_pad, float *tail)
-{
-    pack_f32_forms(wp, k, len * (flip_transpose ? c_out : C), rows, n_pad, tail, [=](int m, int i, int j, int col) {
+struct Weights3dF32 {
+    const float *w3;
+    int c_out, C, k, a0, len, flip_transpose;
+    __device__ __forceinline__ float operator()(int m, int i, int j, int col) const
+    {
         if (!flip_transpose) {
             const int al = m / C, c = m - al * C;
             return al < len && col < c_out ? w3[((((long)col * C + c) * k + a0 + al) * k + i) * k + j] : 0.f;
         }
         const int al = m / c_out, o = m - al * c_out;
         return al < len && col < C ? w3[((((long)o * C + col) * k + (k - 1 - a0 - al)) * k + (k - 1 - i)) * k + (k - 1 - j)] : 0.f;
-    });
-}
+    }
+};
 
-// the tail of packed weights that have the split form, else nullptr
-static float *split_tail(float *wp, int k, int gemm_c_in, int n_pad)
+__global__ __launch_bounds__(256) void weight_max3d_kernel(Weights3dF32 w, PackedF32 f) { weight_max_body(f, blockIdx.x, w); }
+__global__ __launch_bounds__(256) void pack_weights3d_f32_kernel(Weights3dF32 w, PackedF32 f) { pack_f32_forms(f, w); }
+
+static PackedF32 packed_f32(float *wp, int k, int gemm_c_in, int rows, int n_pad)
 {
-    return conv_split_f32_packed(k, gemm_c_in) ? wp + packed_f32_floats(k, gemm_c_in, n_pad) - SPLIT_TAIL_FLOATS : nullptr;
+    return {wp, k, gemm_c_in, rows, n_pad, conv_split_f32_packed(k, gemm_c_in) ? wp + split_tail_at(k, gemm_c_in, n_pad) : nullptr};
 }
 
 hipError_t launch_pack_weights3d_f32(const float *w3, float *wp, int c_out, int C, int k, int a0, int len, int flip_transpose, int rows,
@@ -738,53 +760,50 @@ hipError_t launch_pack_weights3d_f32(const float *w3, float *wp, int c_out, int 
 {
     const long total = (long)rows * n_pad;
     const int blocks = (int)((total + 255) / 256 < 1024 ? (total + 255) / 256 : 1024);
-    float *tail = split_tail(wp, k, len * (flip_transpose ? c_out : C), n_pad);
-    if (tail) hipLaunchKernelGGL(weight_max_kernel, dim3(64), dim3(256), 0, stream, w3, (long)c_out * C * k * k * k, tail);
-    hipLaunchKernelGGL(pack_weights3d_f32_kernel, dim3(blocks), dim3(256), 0, stream, w3, wp, c_out, C, k, a0, len, flip_transpose, rows,
-                       n_pad, tail);
+    const PackedF32 f = packed_f32(wp, k, len * (flip_transpose ? c_out : C), rows, n_pad);
+    const Weights3dF32 w{w3, c_out, C, k, a0, len, flip_transpose};
+    if (f.tail) hipLaunchKernelGGL(weight_max3d_kernel, dim3(SPLIT_PARTS * (n_pad / 16)), dim3(256), 0, stream, w, f);
+    hipLaunchKernelGGL(pack_weights3d_f32_kernel, dim3(blocks), dim3(256), 0, stream, w, f);
     return hipGetLastError();
 }
 
-struct PackF32Jobs { PackF32Job job[BATCH_MAX]; float *tail[BATCH_MAX]; };
+struct PackF32Jobs { WeightsF32 w[BATCH_MAX]; PackedF32 f[BATCH_MAX]; };
 __global__ __launch_bounds__(256) void weight_max_batch_kernel(PackF32Jobs b)
 {
-    const PackF32Job &j = b.job[blockIdx.y];
-    if (b.tail[blockIdx.y]) weight_max_body(j.w, (long)j.c_out * j.c_in * j.k * j.k, b.tail[blockIdx.y]);
+    const PackedF32 &f = b.f[blockIdx.y];
+    if (f.tail && (int)blockIdx.x < SPLIT_PARTS * (f.n_pad / 16)) weight_max_body(f, blockIdx.x, b.w[blockIdx.y]);
 }
-__global__ void pack_weights_f32_batch_kernel(PackF32Jobs b)
-{
-    const PackF32Job &j = b.job[blockIdx.y];
-    pack_weights_f32_body(j.w, j.wp, j.c_out, j.c_in, j.k, j.flip_transpose, j.rows, j.n_pad, b.tail[blockIdx.y]);
-}
+__global__ __launch_bounds__(256) void pack_weights_f32_batch_kernel(PackF32Jobs b) { pack_f32_forms(b.f[blockIdx.y], b.w[blockIdx.y]); }
 
 hipError_t launch_pack_weights_f32_batch(const PackF32Job *jobs, int n, hipStream_t stream)
 {
     if (n < 1 || n > BATCH_MAX) return hipErrorInvalidValue;
     PackF32Jobs b;
     long most = 1;
-    bool splits = false;
+    int max_blocks = 0;
     for (int t = 0; t < n; ++t) {
-        b.job[t] = jobs[t];
-        b.tail[t] = split_tail(jobs[t].wp, jobs[t].k, jobs[t].flip_transpose ? jobs[t].c_out : jobs[t].c_in, jobs[t].n_pad);
-        splits = splits || b.tail[t];
-        const long total = (long)jobs[t].rows * jobs[t].n_pad;
+        const PackF32Job &j = jobs[t];
+        b.w[t] = {j.w, j.c_out, j.c_in, j.k, j.flip_transpose};
+        b.f[t] = packed_f32(j.wp, j.k, j.flip_transpose ? j.c_out : j.c_in, j.rows, j.n_pad);
+        if (b.f[t].tail) max_blocks = max_blocks > SPLIT_PARTS * (j.n_pad / 16) ? max_blocks : SPLIT_PARTS * (j.n_pad / 16);
+        const long total = (long)j.rows * j.n_pad;
         most = total > most ? total : most;
     }
     const int blocks = (int)((most + 255) / 256 < 256 ? (most + 255) / 256 : 256);
-    if (splits) hipLaunchKernelGGL(weight_max_batch_kernel, dim3(64, n), dim3(256), 0, stream, b);
+    if (max_blocks) hipLaunchKernelGGL(weight_max_batch_kernel, dim3(max_blocks, n), dim3(256), 0, stream, b);
     hipLaunchKernelGGL(pack_weights_f32_batch_kernel, dim3(blocks, n), dim3(256), 0, stream, b);
     return hipGetLastError();
 }
 
-hipError_t launch_pack_weights_f32(const float *w_oihw, float *wp, int c_out, int c_in, int k,
-                                   int flip_transpose, int rows, int n_pad, hipStream_t stream)
+hipError_t launch_pack_weights_f32(const float *w_oihw, float *wp, int c_out, int c_in, int k, int flip_transpose, int rows, int n_pad,
+                                   hipStream_t stream)
 {
     const long total = (long)rows * n_pad;
     const int blocks = (int)((total + 255) / 256 < 1024 ? (total + 255) / 256 : 1024);
-    float *tail = split_tail(wp, k, flip_transpose ? c_out : c_in, n_pad);
-    if (tail) hipLaunchKernelGGL(weight_max_kernel, dim3(64), dim3(256), 0, stream, w_oihw, (long)c_out * c_in * k * k, tail);
-    hipLaunchKernelGGL(pack_weights_f32_kernel, dim3(blocks), dim3(256), 0, stream, w_oihw, wp, c_out,
-                       c_in, k, flip_transpose, rows, n_pad, tail);
+    const PackedF32 f = packed_f32(wp, k, flip_transpose ? c_out : c_in, rows, n_pad);
+    const WeightsF32 w{w_oihw, c_out, c_in, k, flip_transpose};
+    if (f.tail) hipLaunchKernelGGL(weight_max_kernel, dim3(SPLIT_PARTS * (n_pad / 16)), dim3(256), 0, stream, w, f);
+    hipLaunchKernelGGL(pack_weights_f32_kernel, dim3(blocks), dim3(256), 0, stream, w, f);
     return hipGetLastError();
 }
 

@@ -4,14 +4,14 @@
 // MFMAs, so the unit needs 3/16 of the time; memory holds fp32 as before.  A workgroup of four waves owns 16 WX columns of 4 R / WX rows
 // that lie d apart (as in kernels_conv_f32.hip, their kernel rows fall on few input rows).  Per chunk of eight input maps it
 //  - loads its samples into registers while it multiplies the chunk before,
-//  - finds their largest magnitude (one LDS exchange), from which the power of two that scales them follows; where that falls, the sums so
-//    far follow it (they rarely do: three bits of room),
+//  - finds their largest and least magnitude (one LDS exchange).  The power of two that scales them follows from the largest; where it has to move
+//    (there are three bits of room), the sums so far follow it.  Weights have one for each output map,
 //  - writes the pairs to LDS as units of one pixel's eight maps: a B operand is 16 pixels x (4 kernel columns x 8 maps), one 16-byte read a
 //    lane, as in the 16-bit convolution; the fourth column of a 3x3 kernel has zero weights,
 //  - multiplies kernel rows in steps of G whose weights are in registers, so that a staged row is read once for G kernel rows.  Weight
 //    fragments come straight into LDS, a step ahead.
-// From a chunk with an infinite sample on, and where a weight is infinite, the tile is multiplied on the fp32 matrix unit (inf - inf of two parts
-// is NaN, which ReLU drops, and so is a part of 0 times infinity).
+// A tile that meets a sample or a weight that pairs would hold in fewer bits (infinite, or not zero and more than 2^28 to 2^31 below the chunk's or the
+// output map's largest: one chunk in thirty thousand of normal samples) starts again on the fp32 matrix unit, unscaled.
 // What bounds it: power.  MFMAs take 0.7 of the matrix unit's time at the 1.7 GHz that is left of 2.4 (8 x 1024^2); the rest are the two
 // barriers a chunk, LDS reads and 0.7 other vector instructions an MFMA.  Two or three workgroups share a CU and fill each other's waits.
 // 48 -> 48 maps, 4x4, us (TFLOP/s) on the fp32 matrix unit and here: 537^2 d = 2 202 -> 59 (360), 8 x 1024^2 d = 8 4745 -> 1421 (435); 64 -> 64, 3x3,
@@ -44,7 +44,7 @@ template <int KS, int MT, int R, int WX, int PITCH> struct SplitTile {
     static constexpr int PLANE = RR * PITCH;                 // 16-byte units of one staged part
     static constexpr int UPT = (PLANE + 255) / 256;          // units a thread stages
     static constexpr int WSTEP = G * MT * 2 * 1024;          // bytes of a step's weight fragments
-    static constexpr size_t SMEM = (size_t)2 * PLANE * 16 + 2 * WSTEP + 64;
+    static constexpr size_t SMEM = (size_t)2 * PLANE * 16 + 2 * WSTEP + 64;       // (64: ranges)
     static_assert(KS % G == 0, "whole steps");
 };
 
@@ -56,15 +56,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t split_rsrc(const void *base)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, SPLIT_NOWHERE, 0x00027000);
 }
 
-// acc * 2^down, bias, ReLU and stores of R rows d apart from oy on, lane column ox, maps o_first + 4 g ..  MODE 1: where the mask is positive;
+// (acc + low / 2^12) * 2^-(se + the output map's power of two), bias, ReLU and stores of R rows d apart from oy on, lane column ox, maps o_first + 4 g ..  MODE 1: where the mask is positive;
 // 2: added to what y holds.  Masks and old values are read ahead of the first store (one queue holds loads and stores).
 template <int MT, int R, int MODE>
-__device__ __forceinline__ void split_store(const ConvF32Args &a, const floatx4 (&acc)[R][MT], int down, int b, int o_first, int oy, int ox, int g)
+__device__ __forceinline__ void split_store(const ConvF32Args &a, const floatx4 (&acc)[R][MT], const floatx4 (&low)[R][MT], int se, const int *wexp,
+                                            int b, int o_first, int oy, int ox, int g)
 {
     const long oplane = (long)a.OH * a.OW;                         // below 2^26: offsets inside sixteen maps are 32-bit
     const long first = ((long)b * a.out_maps + a.o_off + o_first) * oplane;
     unsigned at[MT][4];
     float bia[MT][4];
+    int down[MT][4];
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -72,6 +74,7 @@ __device__ __forceinline__ void split_store(const ConvF32Args &a, const floatx4 
             const int o = o_first + 16 * m + 4 * g + r4;
             at[m][r4] = ox < a.Wo && o < a.c_out ? 4u * ((unsigned)(4 * g + r4) * (unsigned)oplane + (unsigned)(ox * a.ox_mul + a.ox_off)) : SPLIT_NOWHERE;
             bia[m][r4] = a.bias ? a.bias[min(o, a.n_pad - 1)] : 0.f;
+            down[m][r4] = wexp ? -(se + wexp[min(o, a.n_pad - 1)]) : 0;          // (none: sums as they are)
         }
     const auto row = [&](int y) { return 4u * (unsigned)(((oy + y * a.d) * a.oy_mul + a.oy_off) * a.OW); };
     float old[R][MT][4];
@@ -89,8 +92,6 @@ __device__ __forceinline__ void split_store(const ConvF32Args &a, const floatx4 
     }
     __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt(0)
     __builtin_amdgcn_sched_barrier(0);
-    const bool direct = down >= -126 && down <= 127;
-    const float scale = split_pow2(direct ? down : 0);
 #pragma unroll
     for (int y = 0; y < R; ++y) {
         if (oy + y * a.d >= a.Ho) break;
@@ -99,7 +100,7 @@ __device__ __forceinline__ void split_store(const ConvF32Args &a, const floatx4 
             const auto r = split_rsrc(a.y + first + (long)(16 * m) * oplane);
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
-                float v = direct ? __builtin_fmaf(acc[y][m][r4], scale, bia[m][r4]) : __builtin_ldexpf(acc[y][m][r4], down) + bia[m][r4];
+                float v = __builtin_ldexpf(split_sum(acc[y][m][r4], low[y][m][r4]), down[m][r4]) + bia[m][r4];
                 if constexpr (MODE == 2) v += old[y][m][r4];
                 if (a.relu) v = fmaxf(v, 0.f);
                 if constexpr (MODE == 1) v = old[y][m][r4] > 0.f ? v : 0.f;
@@ -110,14 +111,14 @@ __device__ __forceinline__ void split_store(const ConvF32Args &a, const floatx4 
 }
 
 template <int KS, int MT, int R, int WX, int PITCH, bool PADZ>
-__global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, const unsigned char *wsp, const int *wexp, int m_tiles, int tiles_hi,
-                                                                int tiles_lo, int rem, int nblocks, int gx, int gy, int total, int per_xcd)
+__global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, const unsigned char *wsp, const int *wexp, const int *wwide, int m_tiles,
+                                                                int tiles_hi, int tiles_lo, int rem, int nblocks, int gx, int gy, int total, int per_xcd)
 {
     using T = SplitTile<KS, MT, R, WX, PITCH>;
     constexpr int RR = T::RR, G = T::G, STEPS = T::STEPS, UPT = T::UPT, PLANE = T::PLANE;
     extern __shared__ unsigned char smem[];
     unsigned char *xs = smem, *ws = smem + 2 * PLANE * 16;
-    float *most = reinterpret_cast<float *>(ws + 2 * T::WSTEP);      // [2][4]: largest magnitude that each wave stages, by chunk
+    unsigned *ranges = reinterpret_cast<unsigned *>(ws + 2 * T::WSTEP);      // [2][most, least][4]: of what each wave stages, by chunk
     const int d = a.d, pw = T::TX + (KS - 1) * d, units = RR * pw;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wx = wave % WX, wy = wave / WX;
@@ -138,11 +139,11 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
     const int b = bz / nblocks, nb = bz - b * nblocks;
     const int x0 = bx * T::TX, tile0 = nb * MT;
 
-    floatx4 acc[R][MT];
+    floatx4 acc[R][MT], low[R][MT];                           // sums of h h' and of h l' + l h'
 #pragma unroll
     for (int y = 0; y < R; ++y)
 #pragma unroll
-        for (int m = 0; m < MT; ++m) acc[y][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < MT; ++m) acc[y][m] = low[y][m] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     const long plane = (long)a.H * a.W;
     const float *xb = a.x + (long)b * (a.x_bstride ? a.x_bstride : (long)a.c_in * plane);
@@ -168,9 +169,14 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
     long pf_skip = 0;
     float xr[UPT][8];
     auto prefetch = [&](int chunk) {
+        // (the compiler does not see that these are the same in every lane)
+        const unsigned long at = (unsigned long)(xb + pf_skip + (long)chunk * 8 * plane);
+        const unsigned at_lo = __builtin_amdgcn_readfirstlane((unsigned)at), at_hi = __builtin_amdgcn_readfirstlane((unsigned)(at >> 32));
+        const float *const maps = reinterpret_cast<const float *>((unsigned long)at_hi << 32 | at_lo);
+        const int last = __builtin_amdgcn_readfirstlane(a.c_in - 1 - chunk * 8);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const auto src = split_rsrc(xb + pf_skip + (long)min(chunk * 8 + e, a.c_in - 1) * plane);
+            const auto src = split_rsrc(maps + (long)min(e, last) * plane);
 #pragma unroll
             for (int q = 0; q < UPT; ++q) xr[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(src, off[q], 0, 0));
         }
@@ -179,34 +185,49 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
             pf_skip += a.grp_skip;
         }
     };
-    // the scale of the sums: 2^(se + the weights'); it falls where larger samples come
-    int se = SPLIT_MOST;
+    // the scale of the samples: 2^se; it moves where they are larger or much smaller than those before.  `first` is the first one
+    int se = SPLIT_MOST, first = 2 * SPLIT_MOST, wide_weights = 0;
+    bool pairs = true;                                        // false from the first chunk on that pairs cannot hold
+    const auto *const flags = reinterpret_cast<const __attribute__((address_space(4))) int *>(reinterpret_cast<size_t>(wwide));     // (scalar loads)
     auto measure = [&](int chunk) {
-        float m = 0.f;
+        wide_weights = 0;
 #pragma unroll
-        for (int q = 0; q < UPT; ++q)
+        for (int m = 0; m < MT; ++m) wide_weights |= flags[chunk * m_tiles + min(tile0 + m, m_tiles - 1)];
+        SplitRange r;
 #pragma unroll
-            for (int e = 0; e < 8; e += 2) m = fmaxf(fmaxf(fabsf(xr[q][e]), fabsf(xr[q][e + 1])), m);
-        m = split_wave_max(m);
-        if (lane == 0) most[(chunk & 1) * 4 + wave] = m;
-    };
-    auto commit = [&](int chunk) {                            // false: infinite samples, nothing is staged
-        const floatx4 m4 = *reinterpret_cast<const floatx4 *>(most + (chunk & 1) * 4);
-        float m = split_max(split_max(m4[0], m4[1]), split_max(m4[2], m4[3]));
-        m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
-        if (__builtin_bit_cast(unsigned, m) == 0x7f800000u) return false;
-        const int need = split_exponent(m, 14);
-        if (need < se) {
-            const int to = split_exponent(m, 12);                        // two bits of room: neighbouring chunks don't ask again
-            if (chunk > 0) {
-                const float f = to - se < -126 ? 0.f : split_pow2(to - se);
-#pragma unroll
-                for (int y = 0; y < R; ++y)
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) acc[y][mt] *= f;
-            }
-            se = to;
+        for (int q = 0; q < UPT; ++q) r = split_range(r, split_range(xr[q]));
+        r = split_wave_range(r);
+        if (lane == SPLIT_LAST_LANE) {
+            ranges[(chunk & 1) * 8 + wave] = r.most;
+            ranges[(chunk & 1) * 8 + 4 + wave] = r.least;
         }
+    };
+    // The scale for a chunk's samples, or SPLIT_WIDE: pairs don't hold them, or the scaled sums would leave fp32's range
+    auto scale_chunk = [&](int chunk) {
+        const uint4v m4 = *reinterpret_cast<const uint4v *>(ranges + (chunk & 1) * 8), l4 = *reinterpret_cast<const uint4v *>(ranges + (chunk & 1) * 8 + 4);
+        const SplitRange r{(unsigned)__builtin_amdgcn_readfirstlane((int)max(max(m4[0], m4[1]), max(m4[2], m4[3]))),
+                           (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(l4[0], l4[1]), max(l4[2], l4[3])))};
+        const int need = split_exponent(r.most, 14), to = split_exponent(r.most, 13);      // a bit of room: neighbouring chunks don't ask again
+        const bool move = r.most > 0 && (need < se || need > se + 2);
+        const int next = move ? to : se;
+        first = first > SPLIT_MOST && r.most > 0 ? next : first;
+        const bool wide = wide_weights || split_wide(r, next) || (move && (to - first > 60 || first - to > 60));
+        return __builtin_amdgcn_readfirstlane(wide ? SPLIT_WIDE : next);      // (the compiler does not see that it is uniform)
+    };
+    auto move_scale = [&](int to) {
+        if (to != se) {
+            const float f = to - se < -126 ? 0.f : split_pow2(to - se);      // (less: from the start, where sums are zero)
+#pragma unroll
+            for (int y = 0; y < R; ++y)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    acc[y][mt] *= f;
+                    low[y][mt] *= f;
+                }
+        }
+        se = to;
+    };
+    auto commit = [&]() {
         const float scale = split_pow2(se);
 #pragma unroll
         for (int q = 0; q < UPT; ++q) {
@@ -218,7 +239,6 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
 #pragma unroll
             for (int s = 0; s < 2; ++s) *reinterpret_cast<uint4v *>(xs + s * PLANE * 16 + dst[q]) = p[s];
         }
-        return true;
     };
     // fragments [chunk][kernel row][map tile][part] of 1 KB; a step's stand in LDS as [kernel row][MT][part]
     auto load_weights = [&](int chunk, int step, int buf) {
@@ -235,60 +255,18 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
     const bool idle = x0 + wx * 16 >= a.Wo;                   // this wave's columns lie right of the image
     const unsigned char *xp = xs + (wy * R * PITCH + wx * 16 + l16 + min(g, KS - 1) * d) * 16;     // the column behind a 3x3 kernel meets zero weights
 
-    // A chunk on the fp32 matrix unit: the LDS of a unit's two parts holds its eight samples as they are, weights come from their fp32 form.  Only taps
-    // and maps that exist are multiplied: 0 * inf is NaN
-    auto multiply_f32 = [&](int chunk) {
-        const long skip = (long)(chunk / grp_chunks) * a.grp_skip;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const auto src = split_rsrc(xb + skip + (long)min(chunk * 8 + e, a.c_in - 1) * plane);
-#pragma unroll
-            for (int q = 0; q < UPT; ++q) xr[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(src, off[q], 0, 0));
-        }
-        wide_barrier();                                       // every wave is done with the staged maps
-#pragma unroll
-        for (int q = 0; q < UPT; ++q) {
-            if (256 * q + 255 >= RR * (T::TX + KS - 1) && tid + 256 * q >= units) continue;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                floatx4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = chunk * 8 + 4 * h + e < a.c_in && (!PADZ || ok[q]) ? xr[q][4 * h + e] : 0.f;
-                *reinterpret_cast<floatx4 *>(xs + h * PLANE * 16 + dst[q]) = v;
-            }
-        }
-        wide_barrier();
-        if (idle) return;
-        const float *wf = a.wp + (long)(chunk * 8 + g) * (KS * KS) * a.n_pad + l16;
-#pragma unroll 1
-        for (int t = 0; t < 2 * KS * KS; ++t) {
-            const int h = t >= KS * KS, tap = t - h * KS * KS, i = tap / KS, j = tap - i * KS;
-            const float *xq = reinterpret_cast<const float *>(xs + (h * PLANE + (wy * R + i) * PITCH + wx * 16 + l16 + j * d) * 16) + g;
-            float A[MT];
-#pragma unroll
-            for (int m = 0; m < MT; ++m) A[m] = wf[(long)(h * 4 * KS * KS + tap) * a.n_pad + min(tile0 + m, m_tiles - 1) * 16];
-#pragma unroll
-            for (int y = 0; y < R; ++y) {
-                const float B = xq[y * PITCH * 4];
-#pragma unroll
-                for (int m = 0; m < MT; ++m) acc[y][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[m], B, acc[y][m], 0, 0, 0);
-            }
-        }
-    };
-
-    const int we = *wexp;
-    bool pairs = we != SPLIT_WIDE;                            // false from the first chunk on that pairs cannot hold
     int chunk = 0;
-    if (pairs) {
-        load_weights(0, 0, 0);
-        prefetch(0);
-        measure(0);
-    }
-    for (; pairs && chunk < nchunks; ++chunk) {
+    load_weights(0, 0, 0);
+    prefetch(0);
+    measure(0);
+    for (; chunk < nchunks; ++chunk) {
         const bool more = chunk + 1 < nchunks;
         wide_barrier();                                       // every wave is done with the staged maps and has measured its share of the next
-        pairs = commit(chunk);
+        const int scale = scale_chunk(chunk);
+        pairs = scale != SPLIT_WIDE;
         if (!pairs) break;
+        move_scale(scale);
+        commit();
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             // the step's weights have arrived: behind them only the loads of the next chunk's maps may be under way
@@ -317,7 +295,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
                 for (int r = 0; r < R + G - 1; ++r) {             // staged row r is kernel row i of output row r - i
                     if (r + 1 < R + G - 1) fetch(r + 1);
                     __builtin_amdgcn_sched_barrier(0);
-                    constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};     // the small products first
+                    constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 0, 1};
 #pragma unroll
                     for (int q = 0; q < 3; ++q)
 #pragma unroll
@@ -325,7 +303,10 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
                             const int y = r - i;
                             if (y < 0 || y >= R) continue;
 #pragma unroll
-                            for (int m = 0; m < MT; ++m) acc[y][m] = split_mfma(A[i][m][PA[q]], B[r & 1][PB[q]], acc[y][m]);
+                            for (int m = 0; m < MT; ++m) {
+                                floatx4 &sum = q == 1 ? acc[y][m] : low[y][m];
+                                sum = split_mfma(A[i][m][PA[q]], B[r & 1][PB[q]], sum);
+                            }
                         }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -334,21 +315,62 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
         if (more) measure(chunk + 1);
     }
     if (!pairs) {
+        // All of it on the fp32 matrix unit: the LDS of a unit's two parts holds its eight samples as they are, weights come from their fp32 form.  Only
+        // taps and maps that exist are multiplied: 0 * inf is NaN
         wide_wait<0>();                                       // weights on their way to LDS
-        if (chunk > 0)
 #pragma unroll
-            for (int y = 0; y < R; ++y)
+        for (int y = 0; y < R; ++y)
 #pragma unroll
-                for (int m = 0; m < MT; ++m)
+            for (int m = 0; m < MT; ++m) acc[y][m] = low[y][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        pf_left = grp_chunks;
+        pf_skip = 0;
+        chunk = 0;
+        prefetch(0);
+        while (true) {
 #pragma unroll
-                    for (int r4 = 0; r4 < 4; ++r4) acc[y][m][r4] = __builtin_ldexpf(acc[y][m][r4], -(se + we));
-        for (; chunk < nchunks; ++chunk) multiply_f32(chunk);
+            for (int q = 0; q < UPT; ++q) {
+                if (256 * q + 255 >= RR * (T::TX + KS - 1) && tid + 256 * q >= units) continue;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    floatx4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = chunk * 8 + 4 * h + e < a.c_in && (!PADZ || ok[q]) ? xr[q][4 * h + e] : 0.f;
+                    *reinterpret_cast<floatx4 *>(xs + h * PLANE * 16 + dst[q]) = v;
+                }
+            }
+            wide_barrier();
+            if (chunk + 1 < nchunks) prefetch(chunk + 1);
+            if (!idle) {
+                const float *wf = a.wp + (long)(chunk * 8 + g) * (KS * KS) * a.n_pad + l16;
+#pragma unroll 1
+                for (int t = 0; t < 2 * KS; ++t) {
+                    const int h = t >= KS, i = t - h * KS;
+                    const float *xq = reinterpret_cast<const float *>(xs + (h * PLANE + (wy * R + i) * PITCH + wx * 16 + l16) * 16) + g;
+                    float A[KS][MT];
+#pragma unroll
+                    for (int j = 0; j < KS; ++j)
+#pragma unroll
+                        for (int m = 0; m < MT; ++m) A[j][m] = wf[(long)((h * 4 * KS + i) * KS + j) * a.n_pad + min(tile0 + m, m_tiles - 1) * 16];
+#pragma unroll
+                    for (int j = 0; j < KS; ++j)
+#pragma unroll
+                        for (int y = 0; y < R; ++y) {
+                            const float B = xq[(y * PITCH + j * d) * 4];
+#pragma unroll
+                            for (int m = 0; m < MT; ++m) acc[y][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[j][m], B, acc[y][m], 0, 0, 0);
+                        }
+                }
+            }
+            if (++chunk == nchunks) break;
+            wide_barrier();                                   // every wave is done with the staged maps
+        }
     }
     if (idle) return;
-    const int down = pairs ? -(se + we) : 0, o_first = tile0 * 16, oy = py + d * (ty * T::RT + wy * R), ox = x0 + wx * 16 + l16;
-    if (a.mask) split_store<MT, R, 1>(a, acc, down, b, o_first, oy, ox, g);
-    else if (a.accumulate) split_store<MT, R, 2>(a, acc, down, b, o_first, oy, ox, g);
-    else split_store<MT, R, 0>(a, acc, down, b, o_first, oy, ox, g);
+    const int o_first = tile0 * 16, oy = py + d * (ty * T::RT + wy * R), ox = x0 + wx * 16 + l16;
+    const int *we = pairs ? wexp : nullptr;
+    if (a.mask) split_store<MT, R, 1>(a, acc, low, se, we, b, o_first, oy, ox, g);
+    else if (a.accumulate) split_store<MT, R, 2>(a, acc, low, se, we, b, o_first, oy, ox, g);
+    else split_store<MT, R, 0>(a, acc, low, se, we, b, o_first, oy, ox, g);
 }
 
 template <int KS, int MT, int R, int WX, int PITCH, bool PADZ>
@@ -370,10 +392,11 @@ hipError_t launch_split_t(const ConvF32Args &a, hipStream_t stream)
     const long total = gx * gy * a.n * nblocks;
     if (total <= 0 || total > 0x7ffffff0L) return hipErrorInvalidValue;
     const int per_xcd = (int)((total + 7) / 8);
+    const float *tail = a.wp + split_tail_at(KS, a.c_in, a.n_pad);
     hipLaunchKernelGGL((conv_split_f32_kernel<KS, MT, R, WX, PITCH, PADZ>), dim3(per_xcd * 8), dim3(256), T::SMEM, stream, a,
                        reinterpret_cast<const unsigned char *>(a.wp + split_weights_at(KS, a.c_in, a.n_pad)),
-                       reinterpret_cast<const int *>(a.wp + packed_f32_floats(KS, a.c_in, a.n_pad) - SPLIT_TAIL_FLOATS + 64), m_tiles, tiles_hi,
-                       tiles_lo > 0 ? tiles_lo : 1, rem, nblocks, gx, (int)gy, (int)total, per_xcd);
+                       reinterpret_cast<const int *>(tail + SPLIT_PARTS * a.n_pad), reinterpret_cast<const int *>(tail + (SPLIT_PARTS + 1) * a.n_pad), m_tiles,
+                       tiles_hi, tiles_lo > 0 ? tiles_lo : 1, rem, nblocks, gx, (int)gy, (int)total, per_xcd);
     return hipGetLastError();
 }
 
@@ -393,20 +416,19 @@ template <int KS, int MT, int R, int WX> hipError_t launch_split_p(const ConvF32
 }
 
 // What a tile costs, in us: a launch takes about chunks * max(lat * rounds of resident workgroups, work * tiles per CU) + over * tiles per
-// CU (+ 3).  Fitted to 197 layers of 16 to 1024 -> 16 to 512 maps on 20 x 24 to 3 x 430 x 560, d = 1 to 8 (5 to 16 % rms); the tile it picks is on
-// average 1.1 % and at most 11 % slower than the fastest of fourteen (without the smallest, two rows of 32 columns of one map tile, 4 %: small
-// maps), and 1.3 to 5.2 times as fast as the fp32 matrix unit.
+// CU (+ 3).  Fitted to 211 layers of 24 to 512 -> 16 to 512 maps on 8 x 8 to 940 x 900, d = 1 to 8; with the tile it picks a pass of the layer and two
+// 1x1 layers is on average 0.6 % and at most 6 % longer than with the fastest of the eight.
 struct SplitCost {
     int mt, r, wx, slots;             // as SplitTile; workgroups that count as resident on a CU
     float lat, work, over;
 };
 constexpr int SPLIT_TILES = 8;
-constexpr SplitCost SPLIT_COST3[SPLIT_TILES] = {{2, 8, 4, 2, 1.79f, 1.40f, 2.60f}, {2, 6, 4, 3, 1.59f, 1.11f, 1.85f}, {2, 4, 2, 3, 1.32f, 0.83f, 1.07f},
-                                                {1, 4, 4, 4, 1.15f, 0.49f, 0.80f}, {1, 4, 2, 3, 1.16f, 0.54f, 0.71f}, {3, 5, 4, 2, 1.70f, 1.40f, 2.95f},
-                                                {3, 4, 2, 2, 1.57f, 1.13f, 2.28f}, {1, 2, 2, 4, 1.02f, 0.38f, 0.61f}};
-constexpr SplitCost SPLIT_COST4[SPLIT_TILES] = {{2, 8, 4, 3, 2.66f, 1.95f, 2.57f}, {2, 6, 4, 2, 2.22f, 1.50f, 1.81f}, {2, 4, 2, 3, 1.74f, 1.13f, 0.97f},
-                                                {1, 4, 4, 2, 1.26f, 0.69f, 0.58f}, {1, 4, 2, 3, 1.31f, 0.75f, 0.46f}, {3, 5, 4, 3, 2.56f, 1.93f, 1.67f},
-                                                {3, 4, 2, 3, 2.20f, 1.56f, 2.09f}, {1, 2, 2, 3, 1.19f, 0.47f, 0.66f}};
+constexpr SplitCost SPLIT_COST3[SPLIT_TILES] = {{2, 8, 4, 2, 1.63f, 1.19f, 3.72f}, {2, 6, 4, 2, 1.51f, 0.97f, 2.95f}, {2, 4, 2, 4, 1.31f, 0.66f, 1.75f},
+                                                {1, 4, 4, 4, 1.10f, 0.47f, 0.98f}, {1, 4, 2, 4, 1.09f, 0.47f, 0.93f}, {3, 5, 4, 2, 1.68f, 1.05f, 4.04f},
+                                                {3, 4, 2, 2, 1.60f, 0.96f, 3.26f}, {1, 2, 2, 4, 0.95f, 0.34f, 0.72f}};
+constexpr SplitCost SPLIT_COST4[SPLIT_TILES] = {{2, 8, 4, 3, 2.16f, 1.84f, 2.42f}, {2, 6, 4, 2, 1.70f, 1.41f, 2.08f}, {2, 4, 2, 3, 1.31f, 0.96f, 1.25f},
+                                                {1, 4, 4, 2, 0.88f, 0.64f, 0.49f}, {1, 4, 2, 3, 0.88f, 0.65f, 0.45f}, {3, 5, 4, 3, 1.97f, 1.59f, 2.52f},
+                                                {3, 4, 2, 3, 1.69f, 1.35f, 2.07f}, {1, 2, 2, 3, 0.63f, 0.44f, 0.43f}};
 
 double split_cost(const ConvF32Args &a, const SplitCost &c)
 {

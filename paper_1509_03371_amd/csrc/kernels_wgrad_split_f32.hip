@@ -25,6 +25,48 @@ namespace sk {
 
 namespace {
 
+// p[0][e] + p[1][e] = v[e] * scale
+__device__ __forceinline__ void split2_plain(const float (&v)[8], float scale, uint4v (&p)[2])
+{
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const split_halfx2 h = {(_Float16)__builtin_fmaf(v[e], scale, 0.f), (_Float16)__builtin_fmaf(v[e + 1], scale, 0.f)};
+        const split_halfx2 l = {(_Float16)__builtin_fmaf(v[e], scale, -(float)h[0]), (_Float16)__builtin_fmaf(v[e + 1], scale, -(float)h[1])};
+        p[0][e / 2] = __builtin_bit_cast(unsigned, h);
+        p[1][e / 2] = __builtin_bit_cast(unsigned, l);
+    }
+}
+
+// Largest of non-negative values; their bits are in the values' order, and comparing those needs no quieting of NaNs
+__device__ __forceinline__ float split_max(float a, float b)
+{
+    return __builtin_bit_cast(float, max(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b)));
+}
+
+// ... over the wave, in every lane
+__device__ __forceinline__ float split_wave_max_f32(float m)
+{
+    const auto step = [&](auto ctrl) {
+        m = split_max(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), decltype(ctrl)::value, 0xf, 0xf, true)));
+    };
+    step(std::integral_constant<int, 0x111>{});      // row_shr 1, 2, 4, 8: lane 15 of a row has the row's
+    step(std::integral_constant<int, 0x112>{});
+    step(std::integral_constant<int, 0x114>{});
+    step(std::integral_constant<int, 0x118>{});
+    const int v = __builtin_bit_cast(int, m);
+    const int a = max(__builtin_amdgcn_readlane(v, 15), __builtin_amdgcn_readlane(v, 31)), b = max(__builtin_amdgcn_readlane(v, 47), __builtin_amdgcn_readlane(v, 63));
+    return __builtin_bit_cast(float, max(a, b));
+}
+
+// the power of two that takes m to 2^top .. 2^(top + 1)
+__device__ __forceinline__ int split_exponent_f32(float m, int top)
+{
+    const int e = (int)((__builtin_bit_cast(unsigned, m) >> 23) & 0xff) - 127;
+    const int s = top - e;
+    return s < SPLIT_MOST ? s : SPLIT_MOST;
+}
+__device__ __forceinline__ float split_finite(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7f800000u) == 0x7f800000u ? 0.f : v; }
+
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
 typedef short short4v __attribute__((ext_vector_type(4)));
@@ -170,7 +212,7 @@ __global__ __launch_bounds__(64 * WS_WAVES) void wgrad_split_f32_kernel(Args a)
             for (int e = 0; e < 8; e += 2) m[u] = fmaxf(fmaxf(value(xr[S][u][e]), value(xr[S][u][e + 1])), m[u]);
         }
         if (!grad) m[1] = split_max(m[0], m[1]);                     // uniform
-        const float my = grad ? split_wave_max(m[0]) : 0.f, mx = split_wave_max(m[1]);
+        const float my = grad ? split_wave_max_f32(m[0]) : 0.f, mx = split_wave_max_f32(m[1]);
         if (lane == 0) {
             most[(step & 1) * 16 + wave] = mx;
             most[(step & 1) * 16 + 8 + wave] = my;
@@ -196,21 +238,21 @@ __global__ __launch_bounds__(64 * WS_WAVES) void wgrad_split_f32_kernel(Args a)
             wide_barrier();
             read();
         }
-        nx = split_exponent(mx, 14) < sx ? split_exponent(mx, 12) : sx;
-        ny = split_exponent(my, 14) < sy ? split_exponent(my, 12) : sy;
+        nx = split_exponent_f32(mx, 14) < sx ? split_exponent_f32(mx, 12) : sx;
+        ny = split_exponent_f32(my, 14) < sy ? split_exponent_f32(my, 12) : sy;
     };
     float bsum[8] = {};
     auto commit = [&](int step, int slot, auto set) {
         constexpr int S = decltype(set)::value;
         char *xb = lds + (step & 1) * x_buf;
         uint4v p[2];
-        split2(xr[S][0], split_pow2(grad ? ny : nx), p);
+        split2_plain(xr[S][0], split_pow2(grad ? ny : nx), p);
         if (mine[0]) {
             char *to = (grad ? lds + y_base + slot * y_slot : xb) + dst[0];
             *reinterpret_cast<uint4v *>(to) = p[0];
             *reinterpret_cast<uint4v *>(to + (grad ? y_part : x_part)) = p[1];
         }
-        split2(xr[S][1], split_pow2(nx), p);
+        split2_plain(xr[S][1], split_pow2(nx), p);
         if (mine[1]) {
             *reinterpret_cast<uint4v *>(xb + dst[1]) = p[0];
             *reinterpret_cast<uint4v *>(xb + dst[1] + x_part) = p[1];

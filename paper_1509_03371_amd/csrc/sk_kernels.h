@@ -103,12 +103,14 @@ bool conv_f32_groups_supported(int k, int d, int grp_maps);
 hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t stream);
 
 // Layers of enough input maps on the 16-bit matrix unit, fp32 values as pairs of fp16 (kernels_conv_split_f32.hip); launch_conv_f32 hands them
-// over.  Behind the packed fp32 weights stand theirs, at split_weights_at floats, as fragments in two parts, and a tail: 64 partial
-// maxima, then the power of two by which the parts are scaled (int), or SPLIT_WIDE
+// over.  Behind the packed fp32 weights, which it takes where pairs would hold samples or weights in fewer bits, stand the parts' fragments, at
+// split_weights_at floats, and, at split_tail_at, each output map's largest finite magnitude in SPLIT_PARTS parts [part][n_pad], the powers of two that the
+// maps' weights are scaled by (int [n_pad]) and whether pairs hold a chunk's (int [chunk of eight input maps][tile of sixteen output maps], see split_wide)
 bool conv_split_f32_packed(int k, int gemm_c_in);                     // do weights of this GEMM have that form too?
 long split_weights_at(int k, int gemm_c_in, int n_pad);
 long packed_f32_floats(int k, int gemm_c_in, int n_pad);              // of the packed weights, all forms
-constexpr int SPLIT_TAIL_FLOATS = 128;
+long split_tail_at(int k, int gemm_c_in, int n_pad);
+constexpr int SPLIT_PARTS = 8;
 bool conv_split_f32_supported(const ConvF32Args &a);
 hipError_t launch_conv_split_f32(const ConvF32Args &a, hipStream_t stream);
 
