@@ -6,10 +6,10 @@
 // the transposing LDS read; wave w takes tap column w % 4 and half w / 4 of the strip) on pairs of fp16 values (split_f32.h): a step loads
 // one input row and one gradient row into registers, a unit (pixel, eight maps) at a time, while the rows before are multiplied, and writes
 // the pairs to LDS.  Input rows alternate between two buffers; gradient rows stand in a ring of five, where a step reads the four that
-// meet its input row.  A product is three MFMAs.  Both operands have a scale of their own, from the largest finite magnitude of each row; it
-// falls where larger ones come, then sums and the gradient rows that are still needed follow.  The products of a step are summed apart and
-// added to the gradient by the vector unit, which rounds to nearest: sums left in the matrix unit over hundreds of steps came out 1.1 times
-// as far off as fp32 operands' (4 x 676^2), so they are half as far.
+// meet its input row.  A product is three MFMAs.  Every row has a scale of its own, from its largest magnitude; the products of a step are summed apart
+// and added to the gradient by the vector unit, which undoes the scales of the two rows and rounds to nearest (sums left in the matrix unit over hundreds
+// of steps came out 1.1 times as far off as fp32 operands', 4 x 676^2; so they are half as far).  Where a sample of either row is infinite or would be
+// held in fewer bits as a pair (split_f32.h), the fp32 matrix unit multiplies the two rows, from memory.
 //
 // What bounds it: a step of 64 pixels is 108 MFMAs a wave, 3456 cycles a SIMD, 2300 cycles of LDS reads and as many of vector instructions, in
 // two waves a SIMD that meet at a barrier a step: 7000 cycles, MFMAs in 0.45 of them.  48 -> 48 maps, on the fp32 matrix unit and here, with the
@@ -25,55 +25,15 @@ namespace sk {
 
 namespace {
 
-// p[0][e] + p[1][e] = v[e] * scale
-__device__ __forceinline__ void split2_plain(const float (&v)[8], float scale, uint4v (&p)[2])
-{
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-        const split_halfx2 h = {(_Float16)__builtin_fmaf(v[e], scale, 0.f), (_Float16)__builtin_fmaf(v[e + 1], scale, 0.f)};
-        const split_halfx2 l = {(_Float16)__builtin_fmaf(v[e], scale, -(float)h[0]), (_Float16)__builtin_fmaf(v[e + 1], scale, -(float)h[1])};
-        p[0][e / 2] = __builtin_bit_cast(unsigned, h);
-        p[1][e / 2] = __builtin_bit_cast(unsigned, l);
-    }
-}
-
-// Largest of non-negative values; their bits are in the values' order, and comparing those needs no quieting of NaNs
-__device__ __forceinline__ float split_max(float a, float b)
-{
-    return __builtin_bit_cast(float, max(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b)));
-}
-
-// ... over the wave, in every lane
-__device__ __forceinline__ float split_wave_max_f32(float m)
-{
-    const auto step = [&](auto ctrl) {
-        m = split_max(m, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, m), decltype(ctrl)::value, 0xf, 0xf, true)));
-    };
-    step(std::integral_constant<int, 0x111>{});      // row_shr 1, 2, 4, 8: lane 15 of a row has the row's
-    step(std::integral_constant<int, 0x112>{});
-    step(std::integral_constant<int, 0x114>{});
-    step(std::integral_constant<int, 0x118>{});
-    const int v = __builtin_bit_cast(int, m);
-    const int a = max(__builtin_amdgcn_readlane(v, 15), __builtin_amdgcn_readlane(v, 31)), b = max(__builtin_amdgcn_readlane(v, 47), __builtin_amdgcn_readlane(v, 63));
-    return __builtin_bit_cast(float, max(a, b));
-}
-
-// the power of two that takes m to 2^top .. 2^(top + 1)
-__device__ __forceinline__ int split_exponent_f32(float m, int top)
-{
-    const int e = (int)((__builtin_bit_cast(unsigned, m) >> 23) & 0xff) - 127;
-    const int s = top - e;
-    return s < SPLIT_MOST ? s : SPLIT_MOST;
-}
-__device__ __forceinline__ float split_finite(float v) { return (__builtin_bit_cast(unsigned, v) & 0x7f800000u) == 0x7f800000u ? 0.f : v; }
-
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));      // sixteen bytes at any float
 typedef unsigned int uint2v __attribute__((ext_vector_type(2)));
 typedef short short4v __attribute__((ext_vector_type(4)));
 
 constexpr int WS_TX = 64, WS_WAVES = 8, WS_RING = 5;
 constexpr int WS_DP = 68;            // LDS pitch (units) between the octets of a row: octet o + 1 lands 16 banks further
 constexpr unsigned WS_NOWHERE = 0xfffffff0u;
+constexpr int WS_MOST = 63;           // rows' powers of two are in +-63, so that the sum of two is one of fp32's
 
 struct Args {
     const float *x, *dy;
@@ -105,9 +65,9 @@ __global__ __launch_bounds__(64 * WS_WAVES) void wgrad_split_f32_kernel(Args a)
     const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, jl = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tapj = wave & 3, ip = wave >> 2, d = a.d;
-    // [buffer][part][octet][xp] input rows, [slot][part][octet][WS_DP] gradient rows, then maxima [2][input, gradient][wave]
+    // [buffer][part][octet][xp] input rows, [slot][part][octet][WS_DP] gradient rows, then ranges [2][input, gradient][most, least][wave]
     const int x_part = a.c8i * a.xp * 16, x_buf = 2 * x_part, y_part = a.c8o * WS_DP * 16, y_slot = 2 * y_part, y_base = 2 * x_buf;
-    float *most = reinterpret_cast<float *>(lds + y_base + WS_RING * y_slot);
+    unsigned *ranges = reinterpret_cast<unsigned *>(lds + y_base + WS_RING * y_slot);
 
     // this lane's read offsets inside a part (lane 4r + q of a 16-lane group names pixel r, map quad q)
     const int rr = jl >> 2, q = jl & 3, pix = 8 * g + rr;
@@ -202,57 +162,50 @@ __global__ __launch_bounds__(64 * WS_WAVES) void wgrad_split_f32_kernel(Args a)
             start_walk();
         }
     };
-    auto measure = [&](int step, auto set, auto value) {         // the largest value(sample) of this wave's rows
+    auto measure = [&](int step, auto set) {                     // the range of this wave's rows
         constexpr int S = decltype(set)::value;
-        float m[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            m[u] = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) m[u] = fmaxf(fmaxf(value(xr[S][u][e]), value(xr[S][u][e + 1])), m[u]);
-        }
-        if (!grad) m[1] = split_max(m[0], m[1]);                     // uniform
-        const float my = grad ? split_wave_max_f32(m[0]) : 0.f, mx = split_wave_max_f32(m[1]);
-        if (lane == 0) {
-            most[(step & 1) * 16 + wave] = mx;
-            most[(step & 1) * 16 + 8 + wave] = my;
+        SplitRange y = split_range(xr[S][0]), x = split_range(xr[S][1]);
+        if (!grad) {                                             // uniform
+            x = split_range(x, y);
+            y = SplitRange{};
+        } else y = split_wave_range(y);
+        x = split_wave_range(x);
+        if (lane == SPLIT_LAST_LANE) {
+            unsigned *to = ranges + (step & 1) * 32 + wave;
+            to[0] = x.most;
+            to[8] = x.least;
+            to[16] = y.most;
+            to[24] = y.least;
         }
     };
-    const auto magnitude = [](float v) { return fabsf(v); };
-    int sx = SPLIT_MOST, sy = SPLIT_MOST, nx = SPLIT_MOST, ny = SPLIT_MOST;       // scales of the staged rows and sums; of the row that follows
-    auto scales = [&](int step, auto set) {
-        float mx, my;
-        const auto read = [&]() {
-            const floatx4 *m4 = reinterpret_cast<const floatx4 *>(most + (step & 1) * 16);
-            const auto most8 = [](floatx4 v, floatx4 w) {
-                const float m = split_max(split_max(split_max(v[0], v[1]), split_max(v[2], v[3])), split_max(split_max(w[0], w[1]), split_max(w[2], w[3])));
-                return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
-            };
-            mx = most8(m4[0], m4[1]);
-            my = most8(m4[2], m4[3]);
+    // powers of two, or SPLIT_WIDE: of the input row that is multiplied and of the gradient rows that it meets; of the rows that follow
+    int sx = 0, sy[4] = {}, nx = 0, ny = 0;
+    auto scales = [&](int step) {
+        const uint4v *r4 = reinterpret_cast<const uint4v *>(ranges + (step & 1) * 32);
+        const auto most8 = [&](int at) {
+            const uint4v v = r4[at], w = r4[at + 1];
+            return (unsigned)__builtin_amdgcn_readfirstlane((int)max(max(max(v[0], v[1]), max(v[2], v[3])), max(max(w[0], w[1]), max(w[2], w[3]))));
         };
-        read();
-        if (split_max(mx, my) == __builtin_huge_valf()) {            // infinities don't decide the scale of the finite samples beside them
-            wide_barrier();
-            measure(step, set, [](float v) { return split_finite(fabsf(v)); });
-            wide_barrier();
-            read();
-        }
-        nx = split_exponent_f32(mx, 14) < sx ? split_exponent_f32(mx, 12) : sx;
-        ny = split_exponent_f32(my, 14) < sy ? split_exponent_f32(my, 12) : sy;
+        const auto scale = [](SplitRange r) {
+            const int s = min(split_exponent(r.most, 14), WS_MOST);
+            return s < -WS_MOST || split_wide(r, s) ? SPLIT_WIDE : s;
+        };
+        nx = scale({most8(0), most8(2)});
+        ny = scale({most8(4), most8(6)});
     };
     float bsum[8] = {};
     auto commit = [&](int step, int slot, auto set) {
         constexpr int S = decltype(set)::value;
         char *xb = lds + (step & 1) * x_buf;
         uint4v p[2];
-        split2_plain(xr[S][0], split_pow2(grad ? ny : nx), p);
+        const float scale_x = nx == SPLIT_WIDE ? 1.f : split_pow2(nx), scale_y = ny == SPLIT_WIDE ? 1.f : split_pow2(ny);      // (wide: nobody reads the pairs)
+        split2(xr[S][0], grad ? scale_y : scale_x, p);
         if (mine[0]) {
             char *to = (grad ? lds + y_base + slot * y_slot : xb) + dst[0];
             *reinterpret_cast<uint4v *>(to) = p[0];
             *reinterpret_cast<uint4v *>(to + (grad ? y_part : x_part)) = p[1];
         }
-        split2_plain(xr[S][1], split_pow2(nx), p);
+        split2(xr[S][1], scale_x, p);
         if (mine[1]) {
             *reinterpret_cast<uint4v *>(xb + dst[1]) = p[0];
             *reinterpret_cast<uint4v *>(xb + dst[1] + x_part) = p[1];
@@ -271,24 +224,52 @@ __global__ __launch_bounds__(64 * WS_WAVES) void wgrad_split_f32_kernel(Args a)
 
     using Even = std::integral_constant<int, 0>;
     using Odd = std::integral_constant<int, 1>;
-    const int first_rows = lw.rows;
-    int halves = lw.x0 + 32 < a.Wo ? 2 : 1;                      // of the strip that hold gradient pixels
+    Walk cw = lw;                                                // the walk that is multiplied: the loads are three steps on, less than a walk
     load(Even{});
     load(Odd{});
-    measure(0, Even{}, magnitude);
+    measure(0, Even{});
     wide_barrier();
-    scales(0, Even{});
+    scales(0);
     commit(0, 0, Even{});
     sx = nx;
-    sy = ny;
+    sy[0] = ny;
     load(Even{});
-    measure(1, Odd{}, magnitude);
+    measure(1, Odd{});
     wide_barrier();
-    int rows = first_rows, s = 0, slot = 0;                      // of the walk that is multiplied: the loads are three steps on, less than a walk
+    int s = 0, slot = 0;
+    // The input row of step s and the gradient row of step s - i on the fp32 matrix unit, from memory: lane (g, jl) loads pixels 4 g .. 4 g + 3 of map jl of
+    // a tile, the operand of four K steps.  (Maps that do not exist read the last one: nobody reads their sums)
+    auto multiply_f32 = [&](int ii, int i) {
+        const float *xs = a.x + (long)cw.b * a.c_in * xplane + (long)(cw.py + (cw.r0 + s) * d) * a.W + cw.x0 + tapj * d;
+        const float *ys = a.dy + (long)cw.b * a.c_out * yplane + (long)(cw.py + (cw.r0 + s - i) * d) * a.Wo + cw.x0;
+        const int last = a.Wo - 4 - cw.x0;                       // (rows have four gradient pixels at least)
+        // sixteen bytes from pixel px of the strip on, zeros behind the row's end: from where they end at it, moved down
+        const auto load4 = [&](const float *row, int px) {
+            const int at = min(px, last), down = px - at;
+            floatx4 v = *reinterpret_cast<const float4u *>(row + at);
+            if (down & 1) v = floatx4{v[1], v[2], v[3], 0.f};
+            if (down & 2) v = floatx4{v[2], v[3], 0.f, 0.f};
+            return down & ~3 ? floatx4{0.f, 0.f, 0.f, 0.f} : v;
+        };
+#pragma unroll 1
+        for (int p0 = 0; p0 < WS_TX && cw.x0 + p0 < a.Wo; p0 += 16) {
+            floatx4 A[MT], B[NCT];
+#pragma unroll
+            for (int m = 0; m < MT; ++m) A[m] = load4(ys + (long)min(16 * m + jl, a.c_out - 1) * yplane, p0 + 4 * g);
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) B[ct] = load4(xs + (long)min(16 * ct + jl, a.c_in - 1) * xplane, p0 + 4 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int ct = 0; ct < NCT; ++ct)
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) acc[ct][ii][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[m][e], B[ct][e], acc[ct][ii][m], 0, 0, 0);
+        }
+    };
     // Step `step` multiplies its rows, which stand in LDS, writes those of the next (scaled by what everybody measured before the last barrier),
     // sets out for those three steps on and measures those of the step after the next, which have had two steps to arrive
     auto body = [&](int step, auto even, auto odd) {
-        scales(step + 1, odd);
+        scales(step + 1);
         const char *xrow = lds + (step & 1) * x_buf;
         uint4v bf[2][NCT][2];
 #pragma unroll
@@ -302,83 +283,69 @@ __global__ __launch_bounds__(64 * WS_WAVES) void wgrad_split_f32_kernel(Args a)
 #pragma unroll
         for (int ii = 0; ii < 2; ++ii) {
             const int i = 2 * ip + ii;
-            if (s < i || s - i >= rows) continue;                // uniform
+            if (s < i || s - i >= cw.rows) continue;             // uniform
+            const int syi = ip ? sy[2 + ii] : sy[ii];
+            if (sx == SPLIT_WIDE || syi == SPLIT_WIDE) {
+                multiply_f32(ii, i);
+                continue;
+            }
             int sl = slot - i;
             sl = sl < 0 ? sl + WS_RING : sl;
             const char *yrow = lds + y_base + sl * y_slot;
-            floatx4 part[NCT][MT];
+            const float scale = split_pow2(-(sx + syi));
+            auto multiply = [&](auto halves) {                   // of the strip that hold gradient pixels
+                constexpr int HALVES = decltype(halves)::value;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h >= halves) break;                          // uniform
-                uint4v af[MT][2];
+                for (int m = 0; m < MT; ++m) {
+                    uint4v af[HALVES][2];
 #pragma unroll
-                for (int m = 0; m < MT; ++m)
+                    for (int h = 0; h < HALVES; ++h)
 #pragma unroll
-                    for (int p = 0; p < 2; ++p) af[m][p] = read_frag(yrow, p * y_part + a_off[m] + h * 512);
-                constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};
+                        for (int p = 0; p < 2; ++p) af[h][p] = read_frag(yrow, p * y_part + a_off[m] + h * 512);
 #pragma unroll
-                for (int pr = 0; pr < 3; ++pr)
+                    for (int ct = 0; ct < NCT; ++ct) {           // (a tile at a time: registers)
+                        floatx4 hi = {0.f, 0.f, 0.f, 0.f}, lo = hi;
 #pragma unroll
-                    for (int ct = 0; ct < NCT; ++ct)
+                        for (int h = 0; h < HALVES; ++h) {
+                            lo = split_mfma(af[h][1], bf[h][ct][0], lo);
+                            hi = split_mfma(af[h][0], bf[h][ct][0], hi);
+                            lo = split_mfma(af[h][0], bf[h][ct][1], lo);
+                        }
 #pragma unroll
-                        for (int m = 0; m < MT; ++m)
-                            part[ct][m] = split_mfma(af[m][PA[pr]], bf[h][ct][PB[pr]], h == 0 && pr == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : part[ct][m]);
-            }
-#pragma unroll
-            for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-                for (int m = 0; m < MT; ++m) acc[ct][ii][m] += part[ct][m];
-        }
-        measure(step + 2, even, magnitude);
-        wide_barrier();
-        if (nx != sx || ny != sy) {                              // rare: what is there follows the scales of the row that came in
-            const int down = nx + ny - sx - sy;
-            const float f = down < -126 ? 0.f : split_pow2(down);
-#pragma unroll
-            for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int m = 0; m < MT; ++m) acc[ct][i][m] *= f;
-            if (ny != sy) {
-                const _Float16 h = ny - sy < -24 ? (_Float16)0.f : (_Float16)split_pow2(ny - sy);
-                for (int r = 0; r < 3; ++r) {                    // the last three rows' slots, before the one that was just filled
-                    int sl = slot - r;
-                    sl = sl < 0 ? sl + WS_RING : sl;
-                    split_halfx8 *yrow = reinterpret_cast<split_halfx8 *>(lds + y_base + sl * y_slot);
-                    for (int e = tid; e < y_slot / 16; e += 64 * WS_WAVES) yrow[e] *= h;
+                        for (int r4 = 0; r4 < 4; ++r4) acc[ct][ii][m][r4] = __builtin_fmaf(split_sum(hi[r4], lo[r4]), scale, acc[ct][ii][m][r4]);
+                    }
                 }
-                wide_barrier();
-            }
-            sx = nx;
-            sy = ny;
+            };
+            if (cw.x0 + 32 < a.Wo) multiply(std::integral_constant<int, 2>{});
+            else multiply(std::integral_constant<int, 1>{});
         }
+        measure(step + 2, even);
+        wide_barrier();
+        sx = nx;
+        sy[3] = sy[2];
+        sy[2] = sy[1];
+        sy[1] = sy[0];
+        sy[0] = ny;
         slot = slot == WS_RING - 1 ? 0 : slot + 1;
-        if (++s == rows + 3) {
-            rows = lw.rows;
-            halves = lw.x0 + 32 < a.Wo ? 2 : 1;
+        if (++s == cw.rows + 3) {
+            cw = lw;
             s = 0;
         }
     };
-    for (int step = 0; rows > 0; step += 2) {
+    for (int step = 0; cw.rows > 0; step += 2) {
         body(step, Even{}, Odd{});
-        if (rows == 0) break;
+        if (cw.rows == 0) break;
         body(step + 1, Odd{}, Even{});
     }
 
     // the private copy, in accumulator order: [tap column][ct][tap row][map tile][lane][4]
-    const int down = -(sx + sy);
     float *copy = a.scratch + (long)blockIdx.x * a.copy_floats;
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int m = 0; m < MT; ++m) {
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) acc[ct][i][m][r4] = __builtin_ldexpf(acc[ct][i][m][r4], down);
-                *reinterpret_cast<floatx4 *>(copy + ((((tapj * NCT + ct) * 4 + 2 * ip + i) * MT + m) * 64 + lane) * 4) = acc[ct][i][m];
-            }
+            for (int m = 0; m < MT; ++m) *reinterpret_cast<floatx4 *>(copy + ((((tapj * NCT + ct) * 4 + 2 * ip + i) * MT + m) * 64 + lane) * 4) = acc[ct][i][m];
     if (a.bias_part != nullptr && grad) {                     // uniform: wave o8 < c8o has the sums of octet o8
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -393,7 +360,7 @@ __global__ __launch_bounds__(64 * WS_WAVES) void wgrad_split_f32_kernel(Args a)
 // octet o + 1 lands 16 or 48 banks further
 int ws_xp(int d) { return (WS_TX + 3 * d + 3) / 8 * 8 + 4; }
 
-size_t ws_smem(int c8i, int c8o, int d) { return ((size_t)4 * c8i * ws_xp(d) + (size_t)2 * WS_RING * c8o * WS_DP) * 16 + 128; }
+size_t ws_smem(int c8i, int c8o, int d) { return ((size_t)4 * c8i * ws_xp(d) + (size_t)2 * WS_RING * c8o * WS_DP) * 16 + 256; }
 
 template <int MT, int NCT> hipError_t launch_t(const Args &a, size_t smem, int blocks, hipStream_t stream)
 {
@@ -414,7 +381,7 @@ template <int MT, int NCT> hipError_t launch_t(const Args &a, size_t smem, int b
 bool wgrad_split_f32_supported(int c_in, int c_out, int k, int d, int n, int H, int W)
 {
     if (k != 4 || d < 1 || c_in < 16 || c_in > 48 || c_in % 8 != 0 || c_out < 16 || c_out > 48 || c_out % 8 != 0 || (long)H * W >= 1L << 24) return false;
-    if ((long)n * ((W - 3 * d + WS_TX - 1) / WS_TX) * (H - 3 * d) < (c_in >= 32 ? 700 : 3000)) return false;
+    if (W - 3 * d < 4 || (long)n * ((W - 3 * d + WS_TX - 1) / WS_TX) * (H - 3 * d) < (c_in >= 32 ? 700 : 3000)) return false;
     const int c8i = (c_in + 7) / 8, c8o = (c_out + 7) / 8, groups = c8o + (c8i * (WS_TX + 3 * d) + 63) / 64;
     return groups <= 2 * WS_WAVES && ws_smem(c8i, c8o, d) <= 160 * 1024;
 }
