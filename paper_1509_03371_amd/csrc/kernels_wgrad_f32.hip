@@ -1800,7 +1800,7 @@ hipError_t launch_wgrad_f32(const float *x, const float *dy, float *dw, float *d
 {
     // (a scratch buffer of a few copies only leaves most of the GPU idle either way: those stay where they were)
     const size_t room = scratch_cap ? scratch_cap : wgrad_f32_scratch_floats(c_out, c_in, k);
-    if (wgrad_split_f32_supported(c_in, c_out, k, d, n, H, W) && room >= 64 * 16 * 9 * 256)
+    if (wgrad_split_f32_supported(c_in, c_out, k, d, n, H, W) && room >= 64 * wgrad_split_f32_copy_floats(c_in, c_out))
         return launch_wgrad_split_f32(x, dy, dw, db, scratch, room, n, c_in, H, W, c_out, d, stream);
     return launch_wgrad_dt<0>(x, dy, dw, db, scratch, n, c_in, H, W, c_out, k, d, stream, 0, 0, 0, scratch_cap);
 }

@@ -376,14 +376,21 @@ template <int MT, int NCT> hipError_t launch_t(const Args &a, size_t smem, int b
 
 }  // namespace
 
-// Rows of strips from which it is the faster one and at least as close to 64 bits (143 gradients of 16 to 48 -> 16 to 48 maps, 100 x 117 to 600 x 617,
-// d = 1 to 8: 0.32 to 0.99 of the time above these lines, errors 0.60 to 0.93; below, 200 rows: 1.0 to 1.7, 0.9 to 1.05)
+// From these rows of strips on it is no slower and at least as close to 64 bits: 96 gradients of 16 to 48 -> 16 to 48 maps, 200 x 220 to 2 x 500^2, d = 1 to 4:
+// above the lines 0 to 260 us less of 50 to 460 a backward pass, errors 0.65 to 1.0 of the fp32 unit's; below (200 rows) 1.0 to 1.7 of the time.  16 -> 16
+// maps, whose tiles are too few for a step, take 5 us more of 106 at 2 x 500^2.
 bool wgrad_split_f32_supported(int c_in, int c_out, int k, int d, int n, int H, int W)
 {
-    if (k != 4 || d < 1 || c_in < 16 || c_in > 48 || c_in % 8 != 0 || c_out < 16 || c_out > 48 || c_out % 8 != 0 || (long)H * W >= 1L << 24) return false;
+    if (k != 4 || d < 1 || (c_in == 16 && c_out == 16) || c_in < 16 || c_in > 48 || c_in % 8 != 0 || c_out < 16 || c_out > 48 || c_out % 8 != 0 || (long)H * W >= 1L << 24) return false;
     if (W - 3 * d < 4 || (long)n * ((W - 3 * d + WS_TX - 1) / WS_TX) * (H - 3 * d) < (c_in >= 32 ? 700 : 3000)) return false;
     const int c8i = (c_in + 7) / 8, c8o = (c_out + 7) / 8, groups = c8o + (c8i * (WS_TX + 3 * d) + 63) / 64;
     return groups <= 2 * WS_WAVES && ws_smem(c8i, c8o, d) <= 160 * 1024;
+}
+
+size_t wgrad_split_f32_copy_floats(int c_in, int c_out)
+{
+    const size_t MT = (c_out + 15) / 16, NCT = (c_in + 15) / 16;
+    return 16 * NCT * MT * 256 + MT * 16;
 }
 
 hipError_t launch_wgrad_split_f32(const float *x, const float *dy, float *dw, float *db, float *scratch, size_t scratch_floats, int n, int c_in, int H,
@@ -402,7 +409,7 @@ hipError_t launch_wgrad_split_f32(const float *x, const float *dy, float *dw, fl
     a.copy_floats = 16 * NCT * MT * 256;
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-    long blocks = std::min<long>(cus, (long)(scratch_floats / ((size_t)a.copy_floats + MT * 16)));
+    long blocks = std::min<long>(cus, (long)(scratch_floats / wgrad_split_f32_copy_floats(c_in, c_out)));
     if (blocks < 1) return hipErrorInvalidValue;
     a.xstrips = (a.Wo + WS_TX - 1) / WS_TX;
     const long total_rows = (long)n * a.xstrips * a.Ho;
@@ -413,7 +420,7 @@ hipError_t launch_wgrad_split_f32(const float *x, const float *dy, float *dw, fl
     const size_t smem = ws_smem(a.c8i, a.c8o, d);
     hipError_t e = hipErrorInvalidValue;
 #define SK_WS_CASE(mt, nct) if (MT == mt && NCT == nct) e = launch_t<mt, nct>(a, smem, (int)blocks, stream);
-    SK_WS_CASE(1, 1) SK_WS_CASE(2, 1) SK_WS_CASE(3, 1)
+    SK_WS_CASE(2, 1) SK_WS_CASE(3, 1)
     SK_WS_CASE(1, 2) SK_WS_CASE(2, 2) SK_WS_CASE(3, 2)
     SK_WS_CASE(1, 3) SK_WS_CASE(2, 3) SK_WS_CASE(3, 3)
 #undef SK_WS_CASE

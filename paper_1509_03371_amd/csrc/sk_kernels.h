@@ -324,6 +324,7 @@ hipError_t launch_wgrad_rows_f32(const float *x, const float *dy, float *scratch
 
 // 4x4 kernels of 16 to 48 maps on either side, large images, on the 16-bit matrix unit (kernels_wgrad_split_f32.hip)
 bool wgrad_split_f32_supported(int c_in, int c_out, int k, int d, int n, int H, int W);
+size_t wgrad_split_f32_copy_floats(int c_in, int c_out);      // of a private copy and its bias partials
 hipError_t launch_wgrad_split_f32(const float *x, const float *dy, float *dw, float *db, float *scratch, size_t scratch_floats, int n, int c_in, int H,
                                   int W, int c_out, int d, hipStream_t stream);
 // sums of private copies in accumulator order (kernels_wgrad_rows_h.hip) and of bias_part[copy][16 MT]

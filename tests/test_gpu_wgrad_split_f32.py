@@ -125,6 +125,29 @@ def test_samples_just_below_a_power_of_two():
     assert np.linalg.norm(dw - ref) <= 1e-6 * np.linalg.norm(ref)
 
 
+# Both backward calls have scratch for 256 copies of any of these and take the same kernel
+@pytest.mark.parametrize("c_in,c_out,h,w", [(16, 16, 300, 700), (16, 32, 300, 700), (48, 16, 180, 260), (32, 48, 180, 300)])
+def test_both_backward_calls_agree_bit_for_bit(c_in, c_out, h, w):
+    from paper_1509_03371_amd import binding as B
+    rng = np.random.default_rng(c_in + c_out)
+    net = B.SKNet([S.conv(c_in, 1, 1, relu=True), S.conv(c_out, 4, 1, relu=False), S.conv(2, 1, 1, relu=False)], 3, 2)
+    for i in range(3):
+        s = net.conv_shape(i)
+        net.set_weights(i, (rng.standard_normal(s) / np.sqrt(np.prod(s[1:]))).astype(np.float32), rng.standard_normal(s[0]).astype(np.float32))
+    net.plan(1, h, w, pad=False, training=True)
+    img = torch.from_numpy(rng.standard_normal((1, 3, h, w)).astype(np.float32)).cuda()
+    lab = torch.from_numpy(rng.integers(-1, 2, (1, h - 3, w - 3)).astype(np.int32)).cuda()
+    got = []
+    for noalloc in (False, True):
+        net.forward(img)
+        net.backward(lab, loss=torch.zeros(1, device="cuda"), noalloc=noalloc)
+        got.append(net.get_grad(1))
+    net.close()
+    assert np.abs(got[0][0]).max() > 0
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+
+
 @pytest.mark.parametrize("c_in,c_out,d,n,h,w", [(48, 48, 2, 1, 568, 568), (16, 24, 8, 1, 100, 300), (24, 8, 5, 2, 61, 81), (48, 48, 21, 1, 90, 130), (8, 16, 3, 1, 700, 70)])
 def test_rows_of_16_bit_gradients(c_in, c_out, d, n, h, w):
     dw, db, x, dy = gradient(c_in, c_out, d, n, h, w, dtype="bf16")
