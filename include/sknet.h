@@ -394,6 +394,12 @@ sk_status sk_probe_copy(const void *src_dev, void *dst_dev, uint64_t bytes, int3
  *   at 1x1 / 3x3, 2 = many maps at 5x5 to 10x10; the others are 0, 1, 0 for kernel 0.  SK_EUNSUPPORTED: no kernel takes it. */
 sk_status sk_probe_conv_path(int32_t k, int32_t d, int32_t maps_in, int32_t maps_out, int32_t n, int32_t h_out, int32_t w_out,
                              int32_t flags, int32_t *path4);
+/* sk_probe_pairs_path: whether an fp32 layer of these sizes runs on the 16-bit matrix unit, its values as pairs of fp16, and on which tile; host arithmetic
+ *   only.  what: 0 = the convolution, 1 = a data gradient (maps_in = the gradient's maps, the samples around the map are zeros), 2 = the weight
+ *   gradient of a layer of maps_in to maps_out maps with h_out x w_out outputs.  tile3 (HOST) receives map tiles, rows and waves side by side of a
+ *   convolution's tile, or output and input map tiles and 0 of a weight gradient; zeros: the layer stays on the fp32 matrix unit. */
+sk_status sk_probe_pairs_path(int32_t k, int32_t d, int32_t maps_in, int32_t maps_out, int32_t n, int32_t h_out, int32_t w_out,
+                              int32_t what, int32_t *tile3);
 
 #ifdef __cplusplus
 }

@@ -96,6 +96,7 @@ _SIGS = {
     "sk_probe_mfma": [_i32, _i32, _i32, _vp, C.POINTER(C.c_double)],
     "sk_probe_copy": [_vp, _vp, C.c_uint64, _i32, _vp, C.POINTER(C.c_double)],
     "sk_probe_conv_path": [_i32] * 8 + [_ip],
+    "sk_probe_pairs_path": [_i32] * 8 + [_ip],
 }
 for _name, _args in _SIGS.items():
     _f = getattr(lib, _name)
@@ -174,6 +175,13 @@ def sk_probe_conv_path(k, d, maps_in, maps_out, n, h_out, w_out, data_gradient=F
     out = (C.c_int32 * 4)()
     flags = (1 if data_gradient else 0) | (2 if planes else 0) | (4 if scratch else 0)
     _check(lib.sk_probe_conv_path(k, d, maps_in, maps_out, n, h_out, w_out, flags, out))
+    return tuple(out)
+
+
+def sk_probe_pairs_path(k, d, maps_in, maps_out, n, h_out, w_out, what=0):
+    """Tile of an fp32 layer on pairs of fp16 (what: 0 convolution, 1 data gradient, 2 weight gradient), zeros if it is on the fp32 unit."""
+    out = (C.c_int32 * 3)()
+    _check(lib.sk_probe_pairs_path(k, d, maps_in, maps_out, n, h_out, w_out, what, out))
     return tuple(out)
 
 

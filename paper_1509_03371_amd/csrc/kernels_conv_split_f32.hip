@@ -439,13 +439,17 @@ double split_cost(const ConvF32Args &a, const SplitCost &c)
     return (a.c_in + 7) / 8 * std::max(c.lat * rounds, c.work * per_cu) + c.over * per_cu;
 }
 
-template <int KS> hipError_t launch_ks(const ConvF32Args &a, hipStream_t stream)
+int best_tile(const ConvF32Args &a, const SplitCost *cost)
 {
-    const SplitCost *cost = KS == 3 ? SPLIT_COST3 : SPLIT_COST4;
     int best = 0;
     for (int t = 1; t < SPLIT_TILES; ++t)
         if (split_cost(a, cost[t]) < split_cost(a, cost[best])) best = t;
-    switch (best) {
+    return best;
+}
+
+template <int KS> hipError_t launch_ks(const ConvF32Args &a, hipStream_t stream)
+{
+    switch (best_tile(a, KS == 3 ? SPLIT_COST3 : SPLIT_COST4)) {
     case 0: return launch_split_p<KS, 2, 8, 4>(a, stream);
     case 1: return launch_split_p<KS, 2, 6, 4>(a, stream);
     case 2: return launch_split_p<KS, 2, 4, 2>(a, stream);
@@ -465,6 +469,13 @@ bool conv_split_f32_supported(const ConvF32Args &a)
     return conv_split_f32_packed(a.k, a.c_in) && (a.k - 1) * a.d <= 24 && (long)a.H * a.W < (1L << 29) && (long)a.OH * a.OW < (1L << 26) && a.tap_maps == 0 &&
            (a.k == 4 || (long)a.n * a.Ho * a.Wo >= 1000) &&
            (a.grp_maps == 0 || (a.grp_maps > 0 && a.grp_maps % 8 == 0 && a.c_in % a.grp_maps == 0 && a.grp_skip >= 0));
+}
+
+SplitPath conv_split_f32_path(const ConvF32Args &a)
+{
+    if (!conv_split_f32_supported(a)) return {0, 0, 0};
+    const SplitCost &c = a.k == 3 ? SPLIT_COST3[best_tile(a, SPLIT_COST3)] : SPLIT_COST4[best_tile(a, SPLIT_COST4)];
+    return {c.mt, c.r, c.wx};
 }
 
 hipError_t launch_conv_split_f32(const ConvF32Args &a, hipStream_t stream)

@@ -194,4 +194,24 @@ sk_status sk_probe_conv_path(int32_t k, int32_t d, int32_t maps_in, int32_t maps
     return SK_OK;
 }
 
+sk_status sk_probe_pairs_path(int32_t k, int32_t d, int32_t maps_in, int32_t maps_out, int32_t n, int32_t h_out, int32_t w_out,
+                              int32_t what, int32_t *tile3)
+{
+    if (!tile3 || k < 1 || d < 1 || maps_in < 1 || maps_out < 1 || n < 1 || h_out < 1 || w_out < 1 || what < 0 || what > 2)
+        return fail(SK_EINVAL, "probe_pairs_path: bad arguments");
+    const int halo = (k - 1) * d;
+    if (what == 2) {
+        const bool pairs = sk::wgrad_split_f32_supported(maps_in, maps_out, k, d, n, h_out + halo, w_out + halo);
+        tile3[0] = pairs ? (maps_out + 15) / 16 : 0; tile3[1] = pairs ? (maps_in + 15) / 16 : 0; tile3[2] = 0;
+        return SK_OK;
+    }
+    sk::ConvF32Args a{};
+    a.n = n; a.c_in = maps_in; a.c_out = maps_out; a.n_pad = (maps_out + 15) / 16 * 16; a.k = k; a.d = d;
+    a.Ho = a.OH = h_out; a.Wo = a.OW = w_out;
+    a.in_off = what == 1 ? halo : 0; a.H = what == 1 ? h_out - halo : h_out + halo; a.W = what == 1 ? w_out - halo : w_out + halo;
+    const sk::SplitPath p = sk::conv_split_f32_path(a);
+    tile3[0] = p.map_tiles; tile3[1] = p.rows; tile3[2] = p.waves;
+    return SK_OK;
+}
+
 }  // extern "C"

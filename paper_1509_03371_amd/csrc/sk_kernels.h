@@ -113,6 +113,8 @@ long split_tail_at(int k, int gemm_c_in, int n_pad);
 constexpr int SPLIT_PARTS = 8;
 bool conv_split_f32_supported(const ConvF32Args &a);
 hipError_t launch_conv_split_f32(const ConvF32Args &a, hipStream_t stream);
+struct SplitPath { int map_tiles, rows, waves; };      // of a tile, waves side by side; zeros: the layer stays on the fp32 matrix unit
+SplitPath conv_split_f32_path(const ConvF32Args &a);
 
 // 1x1 layers of at most 48 maps on one side (kernels_1x1_f32.hip); launch_conv_f32 hands them over
 bool conv1x1_f32_supported(const ConvF32Args &a);

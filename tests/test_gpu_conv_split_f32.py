@@ -1,4 +1,4 @@
-"""GPU parity of the fp32 3x3 and 4x4 convolutions on the 16-bit matrix unit: every tile shape, ragged tiles, maps and map groups, kernel
+"""GPU parity of the fp32 3x3 and 4x4 convolutions on the 16-bit matrix unit: every tile, ragged tiles, maps and map groups, kernel
 strides up to the widest they take (a halo of 24; one more stays on the fp32 matrix unit), zero borders and ReLU masks of the data gradient,
 samples and weights of any magnitude.
 
@@ -50,6 +50,34 @@ def test_forward(k, d, c_in, c_out, n, h, w):
     img = rng.standard_normal((n, c_in, h, w)).astype(np.float32)
     w0, b0 = rng.standard_normal((c_out, c_in, k, k)).astype(np.float32), rng.standard_normal(c_out).astype(np.float32)
     check(k, d, img, w0, b0)
+
+
+# (kernel, d, output maps, output height: of 24 maps, ten columns more) and the tile it picks (map tiles, rows, waves side by side): every tile at every
+# pitch of the staged rows that kernel strides lead to
+TILES = [
+    (3, 1, 16, 36, (1, 2, 2)), (3, 8, 16, 36, (1, 2, 2)), (3, 1, 96, 60, (1, 4, 2)), (3, 8, 64, 72, (1, 4, 2)), (3, 2, 32, 168, (1, 4, 4)),
+    (3, 8, 32, 156, (1, 4, 4)), (3, 4, 64, 200, (2, 4, 2)), (3, 8, 64, 200, (2, 4, 2)), (3, 1, 64, 350, (2, 6, 4)), (3, 8, 32, 410, (2, 6, 4)),
+    (3, 1, 32, 440, (2, 8, 4)), (3, 8, 32, 440, (2, 8, 4)), (3, 1, 48, 320, (3, 4, 2)), (3, 8, 48, 320, (3, 4, 2)), (3, 1, 48, 350, (3, 5, 4)),
+    (3, 8, 48, 350, (3, 5, 4)),
+    (4, 1, 16, 24, (1, 2, 2)), (4, 4, 16, 24, (1, 2, 2)), (4, 8, 16, 30, (1, 2, 2)), (4, 1, 96, 60, (1, 4, 2)), (4, 4, 96, 60, (1, 4, 2)),
+    (4, 8, 64, 72, (1, 4, 2)), (4, 2, 32, 168, (1, 4, 4)), (4, 4, 16, 560, (1, 4, 4)), (4, 8, 32, 156, (1, 4, 4)), (4, 1, 96, 180, (2, 4, 2)),
+    (4, 4, 64, 200, (2, 4, 2)), (4, 8, 64, 200, (2, 4, 2)), (4, 1, 64, 180, (2, 6, 4)), (4, 4, 64, 168, (2, 6, 4)), (4, 8, 64, 168, (2, 6, 4)),
+    (4, 1, 32, 440, (2, 8, 4)), (4, 4, 32, 440, (2, 8, 4)), (4, 8, 32, 440, (2, 8, 4)), (4, 1, 48, 200, (3, 4, 2)), (4, 4, 96, 132, (3, 4, 2)),
+    (4, 8, 96, 132, (3, 4, 2)), (4, 1, 48, 350, (3, 5, 4)), (4, 4, 48, 350, (3, 5, 4)), (4, 8, 48, 350, (3, 5, 4)),
+]
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("k,d,c_out,ho,tile", TILES)
+def test_every_tile(k, d, c_out, ho, tile, wide):
+    from paper_1509_03371_amd import binding as B
+    wo, halo = ho + 10, (k - 1) * d
+    assert B.sk_probe_pairs_path(k, d, 24, c_out, 1, ho, wo) == tile
+    rng = np.random.default_rng(ho)
+    img = rng.standard_normal((1, 24, ho + halo, wo + halo)).astype(np.float32)
+    if wide:                                                 # half of the tiles, all of them where there are few, on the fp32 matrix unit
+        img[0, rng.integers(24, size=40), rng.integers(ho + halo, size=40), rng.integers(wo + halo, size=40)] = np.float32(1e-20)
+    check(k, d, img, rng.standard_normal((c_out, 24, k, k)).astype(np.float32), rng.standard_normal(c_out).astype(np.float32))
 
 
 @pytest.mark.parametrize("case", ["tiny", "huge", "rising", "falling", "zero chunk", "bright corner", "small weights", "large weights"])
@@ -215,12 +243,7 @@ def test_infinities_meet_real_taps_and_maps_alone(k, d, c_in, which):
     assert np.all(np.abs(got[finite] - ref[finite]) <= (k * k * c_in + 9) * 2.0 ** -24 * size[finite])
 
 
-@pytest.mark.parametrize("relu", [False, True])
-@pytest.mark.parametrize("k,d,maps,classes,n,h,w", [
-    (4, 1, 8, 24, 2, 19, 71), (4, 2, 20, 25, 1, 47, 66), (4, 8, 48, 48, 1, 70, 131), (4, 9, 16, 24, 1, 70, 80), (3, 1, 40, 32, 1, 40, 131),
-    (3, 12, 48, 24, 1, 85, 90), (3, 4, 64, 26, 1, 60, 64), (3, 2, 130, 24, 1, 40, 70), (4, 2, 96, 40, 1, 300, 250),
-])
-def test_data_gradient(k, d, maps, classes, n, h, w, relu):
+def check_data_gradient(k, d, maps, classes, n, h, w, relu):
     from paper_1509_03371_amd import binding as B
     rng = np.random.default_rng(h + w)
     w1 = rng.standard_normal((classes, maps, k, k)).astype(np.float32) * np.float32(0.2)
@@ -240,3 +263,19 @@ def test_data_gradient(k, d, maps, classes, n, h, w, relu):
     bound = (products + 9) * 2.0 ** -24 * size + 1e-6 / max(1, kept.sum()) * np.abs(w1).sum(axis=(0, 2, 3))[None, :, None, None]
     assert np.abs(ref).max() > 1e-6 and np.all(np.abs(got - ref) <= bound)
     net.close()
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("k,d,maps,classes,n,h,w", [
+    (4, 1, 8, 24, 2, 19, 71), (4, 2, 20, 25, 1, 47, 66), (4, 8, 48, 48, 1, 70, 131), (4, 9, 16, 24, 1, 70, 80), (3, 1, 40, 32, 1, 40, 131),
+    (3, 12, 48, 24, 1, 85, 90), (3, 4, 64, 26, 1, 60, 64), (3, 2, 130, 24, 1, 40, 70), (4, 2, 96, 40, 1, 300, 250),
+])
+def test_data_gradient(k, d, maps, classes, n, h, w, relu):
+    check_data_gradient(k, d, maps, classes, n, h, w, relu)
+
+
+@pytest.mark.parametrize("k,d,maps,h,tile", TILES)
+def test_every_tile_of_data_gradients(k, d, maps, h, tile):
+    from paper_1509_03371_amd import binding as B
+    assert B.sk_probe_pairs_path(k, d, 24, maps, 1, h, h + 10, 1) == tile
+    check_data_gradient(k, d, maps, 24, 1, h, h + 10, True)

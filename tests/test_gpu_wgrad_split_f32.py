@@ -65,7 +65,11 @@ def sums(x, dy, d):
     (32, 32, 4, 12, 100, 40),
 ])
 def test_gradient(c_in, c_out, d, n, h, w):
-    dw, db, x, dy = gradient(c_in, c_out, d, n, h, w)
+    check_gradient(c_in, c_out, d, n, h, w)
+
+
+def check_gradient(c_in, c_out, d, n, h, w, **scales):
+    dw, db, x, dy = gradient(c_in, c_out, d, n, h, w, **scales)
     ref, rb = sums(x, dy, d)
     size, sb = sums(np.abs(x), np.abs(dy), d)
     products = dy.size // c_out
@@ -73,6 +77,19 @@ def test_gradient(c_in, c_out, d, n, h, w):
     assert np.all(np.abs(dw - ref) <= (products + 9) * 2.0 ** -24 * size) and np.all(np.abs(db - rb) <= (products + 9) * 2.0 ** -24 * sb)
     # sums of random signs: what the bound allows all of them at once, a right kernel shows a hundredth of
     assert np.linalg.norm(dw - ref) <= 3e-7 * np.linalg.norm(ref)
+
+
+# every kernel: (output map tiles, input map tiles); the last two stay on the fp32 matrix unit
+@pytest.mark.parametrize("c_in,c_out,d,n,h,w,tiles", [
+    (16, 24, 1, 1, 303, 700, (2, 1)), (16, 48, 2, 1, 306, 650, (3, 1)), (32, 16, 1, 1, 203, 230, (1, 2)), (24, 32, 2, 2, 260, 390, (2, 2)),
+    (32, 40, 3, 1, 250, 200, (3, 2)), (48, 16, 4, 1, 200, 270, (1, 3)), (40, 24, 1, 1, 180, 260, (2, 3)), (48, 40, 8, 1, 250, 230, (3, 3)),
+    (48, 48, 1, 1, 703, 7, (3, 3)), (48, 48, 1, 1, 710, 6, (0, 0)), (16, 16, 1, 1, 303, 700, (0, 0)),
+])
+@pytest.mark.parametrize("wide", [False, True])
+def test_every_kernel(c_in, c_out, d, n, h, w, tiles, wide):
+    from paper_1509_03371_amd import binding as B
+    assert B.sk_probe_pairs_path(4, d, c_in, c_out, n, h - 3 * d, w - 3 * d, 2)[:2] == tiles
+    check_gradient(c_in, c_out, d, n, h, w, map_scale=np.float32(10.0) ** -np.linspace(0, 20, c_in).astype(np.float32) if wide else None)
 
 
 @pytest.mark.parametrize("way", ["rising", "falling", "dark half"])

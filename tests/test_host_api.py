@@ -222,3 +222,15 @@ def test_small_data_gradients_keep_the_kernel_of_small_tiles(d, c_in, c_out, sma
     assert B.sk_probe_conv_path(3, d, c_in, c_out, 1, small, small)[0] == 1
     assert B.sk_probe_conv_path(3, d, c_in, c_out, 1, small, small, data_gradient=True)[0] == 0
     assert B.sk_probe_conv_path(3, d, c_in, c_out, 1, large, large, data_gradient=True)[0] == 1
+
+
+def test_pairs_path_probe():
+    from paper_1509_03371_amd import binding as B
+    assert all(B.sk_probe_pairs_path(4, 2, 48, 48, 1, 531, 531, what)[0] > 0 for what in (0, 1, 2))
+    assert B.sk_probe_pairs_path(4, 2, 23, 48, 1, 531, 531) == (0, 0, 0)          # too few input maps
+    assert B.sk_probe_pairs_path(4, 9, 48, 48, 1, 531, 531) == (0, 0, 0)          # a halo of 27
+    assert B.sk_probe_pairs_path(5, 1, 48, 48, 1, 531, 531) == (0, 0, 0)
+    assert B.sk_probe_pairs_path(3, 1, 48, 48, 1, 531, 531, 2) == (0, 0, 0)       # weight gradients: 4x4 alone
+    for bad in ((0, 1, 48, 48, 1, 9, 9, 0), (4, 1, 48, 48, 1, 9, 9, 3), (4, 1, 48, 48, 1, 0, 9, 0)):
+        with pytest.raises(B.SknetError):
+            B.sk_probe_pairs_path(*bad)
