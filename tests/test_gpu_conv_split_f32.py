@@ -279,3 +279,33 @@ def test_every_tile_of_data_gradients(k, d, maps, h, tile):
     from paper_1509_03371_amd import binding as B
     assert B.sk_probe_pairs_path(k, d, 24, maps, 1, h, h + 10, 1) == tile
     check_data_gradient(k, d, maps, 24, 1, h, h + 10, True)
+
+
+# Layers of volumes: the depth taps' maps in one launch (d = 1) or a launch each, whose sums are added to what is there (d = 2)
+@pytest.mark.parametrize("d", [1, 2])
+@pytest.mark.parametrize("case", ["plain", "weights far apart", "samples far apart", "infinity"])
+def test_volumes(case, d):
+    from oracle import nd as OND
+    from paper_1509_03371_amd import binding as B
+    rng = np.random.default_rng(d)
+    vol = rng.standard_normal((32, 7, 45, 83)).astype(np.float32)
+    w0 = rng.standard_normal((40, 32, 3, 3, 3)).astype(np.float32)
+    if case == "weights far apart":
+        w0 *= np.exp2(-np.linspace(0, 60, 40)).astype(np.float32)[:, None, None, None, None]
+        w0[::3, :16] *= np.float32(1e-15)
+    if case == "samples far apart":
+        vol[5, 3, 20, 40] = np.float32(1e20)
+    if case == "infinity":
+        vol[5, 3, 20, 40] = np.float32(np.inf)
+    net = B.SKNet3D([S.conv(40, 3, d, relu=False), S.conv(2, 1, 1, relu=False)], 32, 2)
+    net.set_weights(0, w0, np.zeros(40, np.float32))
+    net.set_weights(1, np.zeros((2, 40, 1, 1, 1), np.float32), np.zeros(2, np.float32))
+    net.plan(7, 45, 83, keep=True)
+    net.forward(torch.from_numpy(np.ascontiguousarray(vol.transpose(1, 0, 2, 3))).cuda())
+    got = net.get_activation(0).transpose(1, 0, 2, 3)
+    net.close()
+    with np.errstate(invalid="ignore"):
+        ref, size = OND.conv_sk3d(vol, w0, np.zeros(40), d), OND.conv_sk3d(np.abs(vol), np.abs(w0), np.zeros(40), d)
+    finite = np.isfinite(ref)
+    assert np.array_equal(got[~finite], ref[~finite].astype(np.float32)) and (case == "infinity") == (not finite.all())
+    assert np.all(np.abs(got[finite] - ref[finite]) <= (27 * 32 + 9) * 2.0 ** -24 * size[finite])
