@@ -34,7 +34,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "f16": 2500.0}   # MI355X dense MFMA peaks
-# fp32 layers on pairs of fp16 values (48 -> 48 k4: three products of the 16-bit unit each, results as accurate as the fp32 unit's)
+# fp32 layers on pairs of fp16 values (48 -> 48 k4: three products of the 16-bit unit each; their sums are closer to 64 bits
+# than the fp32 unit's, and values that a pair would hold in fewer bits go to that unit)
 PEAK_PAIRS_TFLOPS = round(2500.0 / 3, 1)
 HBM_PEAK_GBS = 8000.0
 METRIC = "labelled pixels/sec SK-Net fwd (and fwd+bwd) 1 GPU; conv % MFMA peak"

@@ -734,9 +734,9 @@ hipError_t launch_conv_f32(const ConvF32Args &a, hipStream_t stream)
 
 // ------------------------------------------------------------------------------------------------
 // Every layer that launch_conv_split_f32 may be asked to run (conv_split_f32_supported looks at the sizes of the maps too).  With fewer input
-// maps the sums are short, and what splitting the operands costs in precision is more than what the fewer roundings of the sums give back:
-// error against 64 bits over that of fp32 operands, 3x3 / 4x4: 8 maps 1.53 / 1.51, 12 maps 1.24 / 1.20, 16 maps 1.00 / 0.96, 20 maps 1.05 / 1.01, 24
-// maps 0.88 / 0.92, 48 maps 0.93 / 0.92, 512 maps 0.86 / 0.87
+// maps the sums are short, and what splitting the operands costs in precision is no longer less than what the fewer roundings of the sums give back:
+// error against 64 bits over that of fp32 operands, 3x3 / 4x4: 24 maps 0.68 / 0.61, 32 maps 0.63 / 0.58, 48 maps 0.59 / 0.55, 128 maps 0.54 / 0.52, 512 maps
+// 0.51 / 0.50 (with one sum of all partial products 24 maps 0.88 / 0.92, 20 maps 1.05 / 1.01, 8 maps 1.53 / 1.51)
 bool conv_split_f32_packed(int k, int gemm_c_in) { return (k == 3 || k == 4) && gemm_c_in >= 24; }
 
 long split_weights_at(int k, int gemm_c_in, int n_pad) { return (long)(gemm_c_in + 15) / 16 * 16 * k * k * n_pad; }

@@ -12,14 +12,15 @@
 //    fragments come straight into LDS, a step ahead.
 // A tile that meets a sample or a weight that pairs would hold in fewer bits (infinite, or not zero and more than 2^28 to 2^31 below the chunk's or the
 // output map's largest: one chunk in thirty thousand of normal samples) starts again on the fp32 matrix unit, unscaled.
-// What bounds it: power.  MFMAs take 0.7 of the matrix unit's time at the 1.7 GHz that is left of 2.4 (8 x 1024^2); the rest are the two
-// barriers a chunk, LDS reads and 0.7 other vector instructions an MFMA.  Two or three workgroups share a CU and fill each other's waits.
-// 48 -> 48 maps, 4x4, us (TFLOP/s) on the fp32 matrix unit and here: 537^2 d = 2 202 -> 59 (360), 8 x 1024^2 d = 8 4745 -> 1421 (435); 64 -> 64, 3x3,
-// 566^2 236 -> 76.
+// What bounds it: MFMAs take 0.42 of the time at 2.4 GHz (8 x 1024^2; such load lowers the clock); the rest are the two barriers a chunk, LDS reads and
+// one other vector instruction an MFMA.  Two workgroups share a CU and fill each other's waits (three did with one sum instead of two, which held
+// 2^-37 of the tile's largest: 59 us at 537^2).
+// 48 -> 48 maps, 4x4, us (TFLOP/s) on the fp32 matrix unit and here: 537^2 d = 2 216 -> 69 (301), 8 x 1024^2 d = 8 4775 -> 1676 (352); 64 -> 64, 3x3,
+// 566^2 234 -> 92.  With every tile sent to the fp32 unit 537^2 takes 242; seven such layers 0.95 to 1.25 of conv_f32_pf_kernel.
 // Tried: three bf16 parts and six products (exact parts, no scale) 537^2 113 us, its sums rounded six times a step 1.2 times as far off as
-// fp32 operands; products of a step summed apart and added by the vector unit: half the error, 14 % more time; both staged chunks in LDS: no
-// gain; four pixels a load: a tenth slower (bank conflicts of the writes); 64-bit addresses in loads and stores, which were as many vector
-// instructions as all others: 65 us.
+// fp32 operands; the second sum added to the first by the vector unit after each step: 72 us; a wide chunk alone on the fp32 unit and the next as pairs
+// again: the compiler keeps two copies of the sums, 15 % slower; both staged chunks in LDS: no gain; four pixels a load: a tenth slower (bank
+// conflicts of the writes); 64-bit addresses in loads and stores, which were as many vector instructions as all others: a tenth slower.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -342,7 +343,7 @@ __global__ __launch_bounds__(256, 2) void conv_split_f32_kernel(ConvF32Args a, c
             if (chunk + 1 < nchunks) prefetch(chunk + 1);
             if (!idle) {
                 const float *wf = a.wp + (long)(chunk * 8 + g) * (KS * KS) * a.n_pad + l16;
-#pragma unroll 1
+#pragma unroll 2
                 for (int t = 0; t < 2 * KS; ++t) {
                     const int h = t >= KS, i = t - h * KS;
                     const float *xq = reinterpret_cast<const float *>(xs + (h * PLANE + (wy * R + i) * PITCH + wx * 16 + l16) * 16) + g;
@@ -463,7 +464,7 @@ template <int KS> hipError_t launch_ks(const ConvF32Args &a, hipStream_t stream)
 
 }  // namespace
 
-// 3x3 layers of so few pixels are faster on the fp32 matrix unit (64 -> 64 on 20 x 24 12.7 us against 13.9; on 40 x 36 17.3 against 14.3)
+// 3x3 layers of so few pixels are no slower on the fp32 matrix unit (64 -> 64 on 20 x 24 13.5 us; on 40 x 36 17.8 against 13.2)
 bool conv_split_f32_supported(const ConvF32Args &a)
 {
     return conv_split_f32_packed(a.k, a.c_in) && (a.k - 1) * a.d <= 24 && (long)a.H * a.W < (1L << 29) && (long)a.OH * a.OW < (1L << 26) && a.tap_maps == 0 &&
