@@ -14,7 +14,7 @@
 // What bounds it: a step of 64 pixels is 108 MFMAs a wave, 3456 cycles a SIMD, 2300 cycles of LDS reads and 2600 of vector instructions, in
 // two waves a SIMD that meet at a barrier a step: 7000 cycles, MFMAs in 0.45 of them.  48 -> 48 maps, on the fp32 matrix unit and here, with the
 // reduction: 537^2 d = 2 217 -> 105 to 112 us, 4 x 676^2 d = 8 1139 -> 492; with every row on the fp32 unit 0.9 to 1.1 times the former.
-// Tried: the loads of a row one step ahead instead of two (a fifth slower); half of the waves staging while the others multiply: no difference; the fp32
+// Tried: the loads of a row one step ahead instead of two (a quarter slower); half of the waves staging while the others multiply: no difference; the fp32
 // unit's sums in the private copy, in memory (131 us for 97, spills); all input map tiles' sums of a step at once (116, spills drain the loads under way).
 #include <algorithm>
 
